@@ -2,32 +2,29 @@
 // block-scaled FP4 matrix cores.  All three products of the layer (Eqs. 3-5, Sec. 3.3) have
 // this form because every operand is stored along its own contraction dimension.
 //
-// Three kernels, chosen by the launcher at the end of the file:
+// Two kernels, chosen by plan_gemm at the end of the file:
 //   mx_gemm_pingpong_kernel  the main path (K a multiple of 128, at least 4 K steps per K split;
-//       every ViT-B/L product): V_MFMA_SCALE_F32_32X32X64_F8F6F4, one persistent workgroup of
-//       8 waves per compute unit, tile 256 x 256, operands global -> LDS by DMA loads, two wave
-//       groups alternating between their MFMA burst and their LDS/DMA work.  Described in full
-//       above the kernel.
-//   mx_gemm_dma_kernel       K a multiple of 128 but fewer than 4 K steps per split: same MFMA and
-//       LDS layout, 4 waves, tile 256 x 128, one tile per workgroup.
-//   mx_gemm_kernel           any K that is a multiple of 32 (e.g. 192): V_MFMA_SCALE_F32_16X16X128_F8F6F4,
-//       register-staged loads, zero-filled K tail.
+//       every ViT-B/L product): one persistent workgroup of 8 waves per compute unit, tile 256 x 256,
+//       operands global -> LDS by DMA loads, two wave groups alternating between their MFMA burst and
+//       their LDS/DMA work.  Described in full above the kernel.
+//   mx_gemm_tile_kernel      any K that is a multiple of 32, any size: one tile (128 x 128, 128 x 64 or 64 x 64)
+//       per workgroup of 4 waves, register-staged loads, zero-filled K tail.  Smaller products, short or ragged K.
 // A K-split product (dW: K = tokens, small output) writes FP32 partials to the caller's workspace
 // and splitk_reduce*_kernel adds them in a fixed order.
 //
-// Common to all three:
-//   - K step 128 = 64 bytes of codes and 4 scale bytes per row;
-//   - an MFMA consumes, per lane, 32 consecutive K elements (16 bytes, exactly one MX group) of
-//     one row and that group's E8M0 scale byte (16x16x128: row lane % 16, K block lane / 16;
-//     32x32x64: row lane % 32, K block lane / 32);
-//   - code tiles sit in LDS row-major with the 16-byte chunk index XOR-swizzled by (row >> 2) & 3,
-//     so that both the 16-byte writes (4 lanes per row) and the MFMA operand reads (one chunk of
-//     16 or 32 rows) are bank-conflict free;
+// Common to both:
+//   - V_MFMA_SCALE_F32_32X32X64_F8F6F4: it consumes, per lane, 32 consecutive K elements (16 bytes, exactly one
+//     MX group) of one row and that group's E8M0 scale byte (row lane % 32, K block lane / 32);
+//   - code tiles sit in LDS row-major with the 16-byte chunk index XOR-swizzled by the row (by (row >> 2) & 3
+//     at 64 bytes per row), so that both the 16-byte writes and the MFMA operand reads (one chunk of 32 rows)
+//     are bank-conflict free;
 //   - the MFMA's first operand is the B (n) side, so that a lane ends up with runs of four
 //     consecutive n of one m and stores 8 or 16 contiguous bytes.
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 // Timing hooks for instrumented builds of this file (a build that defines them before including it);
@@ -72,20 +69,6 @@ struct GemmArgs {
     int q_floor;             //   its scale rule: 0 truncation-free, 1 Eq. 2
 };
 
-constexpr int KSTEP_BYTES = 64;     // 128 FP4 elements
-
-__device__ __forceinline__ uint32_t lds_code_offset(uint32_t row, uint32_t chunk)
-{
-    return row * KSTEP_BYTES + ((chunk ^ ((row >> 2) & 3u)) << 4);
-}
-
-__device__ __forceinline__ uint32_t lds_scale_offset(uint32_t row, uint32_t kb, uint32_t tile_rows)
-{
-    // [kb][row tile / 4][row % 16][row tile % 4]
-    uint32_t tile = row >> 4;
-    return kb * tile_rows + (tile >> 2) * 64 + (row & 15u) * 4 + (tile & 3u);
-}
-
 // FP32 -> bf16, round to nearest even, with gfx950's packed convert instruction.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -102,203 +85,299 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
     return (uint16_t)f32x2_to_bf16x2(f, 0.f);
 }
 
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
-void mx_gemm_kernel(GemmArgs g)
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// 16-byte store.  A final output is written with the nontemporal hint: it is not read again
+// here, and without the hint an output larger than the last-level cache slows the whole kernel
+// down while it drains (split-K partials keep the default policy, the reduction reads them).
+template <bool STREAM>
+__device__ __forceinline__ void store16(void* dst, v4i v)
 {
-    constexpr int WAVES_N = BN / WN;
-    constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    constexpr int TM = WM / 16, TN = WN / 16;
-    constexpr int A_CHUNKS = BM * 4 / NT, B_CHUNKS = BN * 4 / NT;
-    static_assert(BM * 4 % NT == 0 && BN * 4 % NT == 0, "tile/thread mismatch");
-    static_assert(TM % 4 == 0 && TN % 4 == 0, "scale packing needs 4 tiles per dword");
-    static_assert(BM + BN <= NT * 2, "scale loader covers at most 2 rows per thread");
+    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(dst));
+    else        *reinterpret_cast<v4i*>(dst) = v;
+}
 
-    __shared__ __attribute__((aligned(16))) uint8_t lds_a[2][BM * KSTEP_BYTES];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_b[2][BN * KSTEP_BYTES];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_sa[2][BM * 4];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_sb[2][BN * 4];
-
-    // ---- which tile: give each XCD (workgroup id % 8) a contiguous range of tiles,
-    //      consecutive tiles sharing the same A row panel ----
-    const uint32_t nblk = g.tiles_m * g.tiles_n;
+// Workgroup -> (K split, tile).  The grid is one-dimensional over split * tiles.  Workgroup
+// ids go round-robin over the 8 XCDs, each with its own L2, so id % 8 = XCD gets a
+// contiguous range of the logical order (split, m tile, n tile): the workgroups that share
+// an A row panel or a B panel of one K range run on the same XCD at about the same time.
+__device__ __forceinline__ void decode_tile(const GemmArgs& g, uint32_t& zsplit, uint32_t& tm, uint32_t& tn)
+{
+    const uint32_t tiles = g.tiles_m * g.tiles_n, nblk = tiles * (uint32_t)g.split_k;
     uint32_t bid = blockIdx.x;
+    uint32_t per = nblk / 8, rem = nblk % 8;
+    uint32_t xcd = bid % 8, idx = bid / 8;
+    bid = xcd * per + (xcd < rem ? xcd : rem) + idx;       // bijection on [0, nblk)
+    zsplit = bid / tiles;
+    uint32_t t = bid - zsplit * tiles;
+    tm = t / g.tiles_n;
+    tn = t - tm * g.tiles_n;
+}
+
+// Four consecutive scale bytes [off, off + 4) of a row that starts `left` bytes before the end of the
+// scale array; the address has no alignment.  Bytes past the end of the array are not read (they belong
+// to K groups whose codes are zero; any other byte there is some row's scale, never the NaN code 255).
+__device__ __forceinline__ uint32_t load_scales4(const uint8_t* row, uint32_t off, uint32_t left)
+{
+    uint32_t v = 0u;
+    if (off + 4u <= left) {
+        __builtin_memcpy(&v, row + off, 4);
+    } else {
+        for (uint32_t b = 0; b < 4; ++b)
+            if (off + b < left) v |= (uint32_t)row[off + b] << (8 * b);
+    }
+    return v;
+}
+
+// ---------------------------------------------------------------------------
+// Products that the main kernel does not take: any K that is a multiple of 32, any m and n.
+//
+//   workgroup 4 waves (2 x 2), tile BM x BN, wave tile BM/2 x BN/2 of 32 x 32 x 64 MFMA tiles; K step KS.
+//   Operands go global -> registers -> LDS, the next step's loads in flight during the current step's
+//   MFMAs; chunks past the end of K are zero-filled in registers, so K needs no alignment beyond a group.
+//   (No DMA loads: they cannot zero-fill a ragged K tail, and scale rows of K/32 bytes have no alignment.)
+// Three shapes (chosen in plan_gemm, which gives the times):
+//   128 x 128, KS 128: 35 KB of LDS, three workgroups per compute unit, so that one stores its tile or waits for
+//     its first loads while the others multiply; at four, the 128 registers allowed spill (25216 x 1536 x 384:
+//     41 us against 27).
+//   128 x 64, KS 256: half the tile and twice the K step, for products with fewer tiles, where the latency of a
+//     K step counts (12608 x 192 x 768: 6.3 us against 7.4).
+//   64 x 64, KS 512: for products too small to fill the chip otherwise.  What such a launch costs is the chain
+//     launch -> first load -> multiply -> store; a K step of 512 puts all operand loads of a K <= 512 product in
+//     flight at once instead of one latency per 128.  A second K step in flight (two register sets) gained
+//     nothing: the step is a chain of LDS writes, barrier, LDS reads and eight dependent MFMAs, 0.9 us.
+// ---------------------------------------------------------------------------
+constexpr int T_NT = 256;
+
+template <int BM, int BN, int KS>
+struct TileShape {
+    static constexpr int ROWB = KS / 2;                         // code bytes of a row and K step
+    static constexpr int PITCH = ROWB;
+    static constexpr int SCALEB = KS / 32;
+    static constexpr int SPITCH = SCALEB + (KS > 128 ? 4 : 0);  // KS 128: one dword per row, conflict-free as it is
+    static constexpr int STAGE = (BM + BN) * (PITCH + SPITCH);
+    static constexpr int EP_PITCH = BN / 2 * 4 + 16;            // output strip: 32 rows of BN/2 FP32 values
+    static constexpr int LDS = 2 * STAGE > 4 * 32 * EP_PITCH ? 2 * STAGE : 4 * 32 * EP_PITCH;
+    // 16-byte column of a chunk: XOR-swizzled, so that the 16 lanes of an access phase (16 rows of one chunk, or
+    // 4 to 16 chunks of a row) spread over all banks
+    static __device__ __forceinline__ uint32_t column(uint32_t row, uint32_t chunk)
     {
-        uint32_t per = nblk / 8, rem = nblk % 8;
-        uint32_t xcd = bid % 8, idx = bid / 8;
-        bid = xcd * per + (xcd < rem ? xcd : rem) + idx;   // bijection on [0, nblk)
+        return (KS == 128 ? chunk ^ ((row >> 2) & 3u) : KS == 256 ? chunk ^ ((row >> 1) & 7u) : chunk ^ (row & 15u)) << 4;
     }
-    const uint32_t tm = bid / g.tiles_n, tn = bid % g.tiles_n;
-    const uint32_t m0 = tm * BM, n0 = tn * BN;
-    const uint32_t kbeg = blockIdx.z * g.k_per_split;
-    const uint32_t kend = min(g.k, kbeg + g.k_per_split);
-    const uint32_t nk = (kend - kbeg + 127) / 128;
-    const uint32_t kbytes = g.k >> 1, kgroups = g.k >> 5;
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-
-    // ---- global -> register staging ----
-    v4i ra[A_CHUNKS], rb[B_CHUNKS];
-    uint32_t rs[2];                         // scale dwords (rows tid and tid + NT)
-
-    auto gload = [&](uint32_t kt) {
-        const uint32_t k0 = kbeg + kt * 128;
-#pragma unroll
-        for (int u = 0; u < A_CHUNKS; ++u) {
-            uint32_t q = tid + u * NT, row = q >> 2, ch = q & 3;
-            bool ok = (m0 + row < g.m) && (k0 + ch * 32 < kend);
-            ra[u] = ok ? *reinterpret_cast<const v4i*>(g.a_codes + (size_t)(m0 + row) * kbytes + (k0 >> 1) + ch * 16)
-                       : v4i{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int u = 0; u < B_CHUNKS; ++u) {
-            uint32_t q = tid + u * NT, row = q >> 2, ch = q & 3;
-            bool ok = (n0 + row < g.n) && (k0 + ch * 32 < kend);
-            rb[u] = ok ? *reinterpret_cast<const v4i*>(g.b_codes + (size_t)(n0 + row) * kbytes + (k0 >> 1) + ch * 16)
-                       : v4i{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            int row = tid + u * NT;
-            rs[u] = 0x7F7F7F7Fu;            // scale 2^0 for rows / groups outside the matrix (their codes are 0)
-            if (row < BM + BN) {
-                bool is_a = row < BM;
-                uint32_t r = is_a ? m0 + row : n0 + (row - BM);
-                uint32_t lim = is_a ? g.m : g.n;
-                const uint8_t* sp = (is_a ? g.a_scales : g.b_scales) + (size_t)r * kgroups + (k0 >> 5);
-                if (r < lim) {
-                    if (k0 + 128 <= kend && (kgroups & 3u) == 0) {
-                        rs[u] = *reinterpret_cast<const uint32_t*>(sp);
-                    } else {
-                        uint32_t v = 0;
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            uint32_t s = (k0 + b * 32 < kend) ? sp[b] : 0x7Fu;
-                            v |= s << (8 * b);
-                        }
-                        rs[u] = v;
-                    }
-                }
-            }
-        }
-    };
-
-    auto lstore = [&](int buf) {
-#pragma unroll
-        for (int u = 0; u < A_CHUNKS; ++u) {
-            uint32_t q = tid + u * NT;
-            *reinterpret_cast<v4i*>(&lds_a[buf][lds_code_offset(q >> 2, q & 3)]) = ra[u];
-        }
-#pragma unroll
-        for (int u = 0; u < B_CHUNKS; ++u) {
-            uint32_t q = tid + u * NT;
-            *reinterpret_cast<v4i*>(&lds_b[buf][lds_code_offset(q >> 2, q & 3)]) = rb[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            int row = tid + u * NT;
-            if (row < BM + BN) {
-                bool is_a = row < BM;
-                uint32_t r = is_a ? row : row - BM;
-                uint8_t* dst = is_a ? lds_sa[buf] : lds_sb[buf];
-                uint32_t tr = is_a ? BM : BN;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) dst[lds_scale_offset(r, b, tr)] = (uint8_t)(rs[u] >> (8 * b));
-            }
-        }
-    };
-
-    v4f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    const uint32_t lrow = lane & 15, lkb = lane >> 4;
-
-    auto compute = [&](int buf) {
-        v4i fa[TM], fb[TN];
-        uint32_t sa[TM / 4], sb[TN / 4];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-            fa[i] = *reinterpret_cast<const v4i*>(&lds_a[buf][lds_code_offset(wm * WM + i * 16 + lrow, lkb)]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-            fb[j] = *reinterpret_cast<const v4i*>(&lds_b[buf][lds_code_offset(wn * WN + j * 16 + lrow, lkb)]);
-#pragma unroll
-        for (int i = 0; i < TM / 4; ++i)
-            sa[i] = *reinterpret_cast<const uint32_t*>(&lds_sa[buf][lkb * BM + ((wm * WM) / 64 + i) * 64 + lrow * 4]);
-#pragma unroll
-        for (int j = 0; j < TN / 4; ++j)
-            sb[j] = *reinterpret_cast<const uint32_t*>(&lds_sb[buf][lkb * BN + ((wn * WN) / 64 + j) * 64 + lrow * 4]);
-        static_for<0, TM>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            v8i xa = v8i{fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0};
-            static_for<0, TN>([&](auto jc) {
-                constexpr int j = decltype(jc)::value;
-                v8i xb = v8i{fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0};
-                // first operand = n side (B rows), second = m side (A rows)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                    xb, xa, acc[i][j], 4, 4, j & 3, (int)sb[j >> 2], i & 3, (int)sa[i >> 2]);
-            });
-        });
-    };
-
-    if (nk > 0) {
-        gload(0);
-        lstore(0);
-    }
-    __syncthreads();
-    for (uint32_t kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) gload(kt + 1);
-        compute(cur);
-        if (more) lstore(cur ^ 1);
-        __syncthreads();
-    }
-
-    // ---- epilogue: lane holds C[m = .. + lane%16][n = .. + 4*(lane/16) + 0..3] ----
+// Accumulators of one wave (TI x TJ tiles of 32 x 32; first row mrow0, first column nbase) through a per-wave
+// LDS strip of 32 rows, so that a store instruction writes 16 bytes per lane and whole row segments.
+template <int TI, int TJ, bool STREAM>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, uint8_t* ep, v16f (&acc)[TI][TJ], uint32_t mrow0,
+                                              uint32_t nbase, uint32_t zsplit)
+{
+    constexpr int COLS = 32 * TJ, PITCH = COLS * 4 + 16;
+    const uint32_t lane = threadIdx.x & 63, lrow = lane & 31, lhalf = lane >> 5;
     float* cf = static_cast<float*>(g.c);
     uint16_t* ch = static_cast<uint16_t*>(g.c);
     int64_t ldc = g.ldc;
     if (g.split_k > 1) {
-        cf += (size_t)blockIdx.z * g.m * g.n;
+        cf += (size_t)zsplit * g.m * g.n;
         ldc = g.n;
     }
     const bool as_bf16 = g.c_bf16 && g.split_k == 1;
-    const bool vec_ok = (ldc & 3) == 0;
+    const bool vec_ok = as_bf16 ? (ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(ch) & 15) == 0
+                                : (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(cf) & 15) == 0;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const uint32_t mm = m0 + wm * WM + i * 16 + lrow;
-        if (mm >= g.m) continue;
+    for (int i = 0; i < TI; ++i) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const uint32_t nn = n0 + wn * WN + j * 16 + lkb * 4;
-            if (nn >= g.n) continue;
-            v4f v = acc[i][j];
-            if (g.bias) v += *reinterpret_cast<const v4f*>(g.bias + nn);      // nn + 3 < n: n is a multiple of 4
-            size_t off = (size_t)mm * ldc + nn;
-            if (nn + 3 < g.n && vec_ok) {
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t col = 32 * j + 8 * q + 4 * lhalf;
+                v4f v = v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                if (g.bias != nullptr && nbase + col < g.n) v += *reinterpret_cast<const v4f*>(g.bias + nbase + col);   // n % 4 == 0
                 if (as_bf16) {
                     uint2 pk;
                     pk.x = f32x2_to_bf16x2(v.x, v.y);
                     pk.y = f32x2_to_bf16x2(v.z, v.w);
-                    *reinterpret_cast<uint2*>(ch + off) = pk;
+                    *reinterpret_cast<uint2*>(ep + lrow * PITCH + col * 2) = pk;
                 } else {
-                    *reinterpret_cast<float4*>(cf + off) = make_float4(v.x, v.y, v.z, v.w);
+                    *reinterpret_cast<v4f*>(ep + lrow * PITCH + col * 4) = v;
                 }
-            } else {
-                float e[4] = {v.x, v.y, v.z, v.w};
-                for (int r = 0; r < 4; ++r)
-                    if (nn + r < g.n) {
-                        if (as_bf16) ch[off + r] = f32_to_bf16_rne(e[r]);
-                        else         cf[off + r] = e[r];
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (as_bf16) {
+            constexpr int LPR = COLS / 8, RPI = 64 / LPR;          // lanes per row, rows per instruction
+#pragma unroll
+            for (int it = 0; it < 32 / RPI; ++it) {
+                const uint32_t row = it * RPI + lane / LPR, col = (lane % LPR) * 8;
+                const uint32_t mm = mrow0 + i * 32 + row, nn = nbase + col;
+                const v4i v = *reinterpret_cast<const v4i*>(ep + row * PITCH + col * 2);
+                if (mm < g.m && nn < g.n) {
+                    uint16_t* dst = ch + (size_t)mm * ldc + nn;
+                    if (nn + 8 <= g.n && vec_ok) {
+                        store16<STREAM>(dst, v);
+                    } else {
+                        for (int e = 0; e < 8; ++e)
+                            if (nn + e < g.n) dst[e] = (uint16_t)((uint32_t)v[e >> 1] >> (16 * (e & 1)));
                     }
+                }
+            }
+        } else {
+            constexpr int LPR = COLS / 4, RPI = 64 / LPR;
+#pragma unroll
+            for (int it = 0; it < 32 / RPI; ++it) {
+                const uint32_t row = it * RPI + lane / LPR, col = (lane % LPR) * 4;
+                const uint32_t mm = mrow0 + i * 32 + row, nn = nbase + col;
+                const v4i v = *reinterpret_cast<const v4i*>(ep + row * PITCH + col * 4);
+                if (mm < g.m && nn < g.n) {
+                    float* dst = cf + (size_t)mm * ldc + nn;
+                    if (nn + 4 <= g.n && vec_ok) {
+                        store16<STREAM>(dst, v);
+                    } else {
+                        for (int e = 0; e < 4; ++e)
+                            if (nn + e < g.n) dst[e] = __int_as_float(v[e]);
+                    }
+                }
             }
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
+}
+
+template <int BM, int BN, int KS, int OCC>
+__global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
+{
+    using S = TileShape<BM, BN, KS>;
+    constexpr int CPR = S::ROWB / 16;                              // 16-byte chunks per row and step
+    constexpr int A_CHUNKS = BM * CPR / T_NT, B_CHUNKS = BN * CPR / T_NT;
+    constexpr int DPR = KS / 128;                                  // scale dwords per row and step
+    constexpr int SDW = (BM + BN) * DPR, SC = (SDW + T_NT - 1) / T_NT;
+    constexpr int TI = BM / 64, TJ = BN / 64;                      // MFMA tiles of a wave
+    static_assert(BM * CPR % T_NT == 0 && BN * CPR % T_NT == 0, "tile/thread mismatch");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[S::LDS];
+
+    uint32_t zsplit, tm, tn;
+    decode_tile(g, zsplit, tm, tn);
+    const uint32_t m0 = tm * BM, n0 = tn * BN;
+    const uint32_t kbeg = zsplit * g.k_per_split;
+    const uint32_t kend = min(g.k, kbeg + g.k_per_split);
+    const uint32_t kbytes = g.k >> 1, kgroups = g.k >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const uint32_t lrow = lane & 31, lhalf = lane >> 5;
+
+    // Rows past the matrix edge read the last valid row (their products are never stored).  Offsets fit 32 bits:
+    // k <= 2^24, at most 128 rows.
+    const uint8_t* a_base = g.a_codes + (size_t)m0 * kbytes;
+    const uint8_t* b_base = g.b_codes + (size_t)n0 * kbytes;
+    uint32_t a_off[A_CHUNKS], b_off[B_CHUNKS], s_left[SC];
+    const uint8_t* s_src[SC];
+    const uint32_t ch = tid % CPR;                                 // T_NT is a multiple of CPR: the same chunk in every row
+    const uint32_t mlast = g.m - 1 - m0, nlast = g.n - 1 - n0;
+#pragma unroll
+    for (int u = 0; u < A_CHUNKS; ++u) a_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, mlast) * kbytes + ch * 16;
+#pragma unroll
+    for (int u = 0; u < B_CHUNKS; ++u) b_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, nlast) * kbytes + ch * 16;
+#pragma unroll
+    for (int u = 0; u < SC; ++u) {
+        const uint32_t row = min(tid + u * T_NT, SDW - 1) / DPR;
+        const bool is_a = row < BM;
+        const uint32_t lim = is_a ? g.m : g.n, r = is_a ? m0 + min(row, mlast) : n0 + min(row - BM, nlast);
+        s_src[u] = (is_a ? g.a_scales : g.b_scales) + (size_t)r * kgroups;
+        const uint64_t left = (uint64_t)(lim - r) * kgroups;
+        s_left[u] = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu;
+    }
+
+    v4i ra[A_CHUNKS], rb[B_CHUNKS];
+    uint32_t rs[SC];
+    auto gload = [&](uint32_t k0) {
+        const bool ok = k0 + ch * 32 < kend;
+        const v4i z = v4i{0, 0, 0, 0};
+        const uint8_t *pa = a_base + (k0 >> 1), *pb = b_base + (k0 >> 1);
+#pragma unroll
+        for (int u = 0; u < A_CHUNKS; ++u) ra[u] = ok ? *reinterpret_cast<const v4i*>(pa + a_off[u]) : z;
+#pragma unroll
+        for (int u = 0; u < B_CHUNKS; ++u) rb[u] = ok ? *reinterpret_cast<const v4i*>(pb + b_off[u]) : z;
+#pragma unroll
+        for (int u = 0; u < SC; ++u) {
+            const uint32_t k = k0 + (tid + u * T_NT) % DPR * 128;
+            rs[u] = k < kend && tid + u * T_NT < SDW ? load_scales4(s_src[u], k >> 5, s_left[u]) : 0u;
+        }
+    };
+    auto lstore = [&](uint8_t* st) {
+#pragma unroll
+        for (int u = 0; u < A_CHUNKS; ++u) {
+            const uint32_t row = (tid + u * T_NT) / CPR;
+            *reinterpret_cast<v4i*>(st + row * S::PITCH + S::column(row, ch)) = ra[u];
+        }
+#pragma unroll
+        for (int u = 0; u < B_CHUNKS; ++u) {
+            const uint32_t row = (tid + u * T_NT) / CPR;
+            *reinterpret_cast<v4i*>(st + (BM + row) * S::PITCH + S::column(row, ch)) = rb[u];
+        }
+#pragma unroll
+        for (int u = 0; u < SC; ++u)
+            if (tid + u * T_NT < SDW) *reinterpret_cast<uint32_t*>(st + (BM + BN) * S::PITCH + (tid + u * T_NT) / DPR * S::SPITCH + (tid + u * T_NT) % DPR * 4) = rs[u];
+    };
+
+    v16f acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto compute = [&](const uint8_t* st, uint32_t k0) {
+        const uint8_t* pa = st + (wm * (BM / 2) + lrow) * S::PITCH;
+        const uint8_t* pb = st + (BM + wn * (BN / 2) + lrow) * S::PITCH;
+        const uint8_t* sa = st + (BM + BN) * S::PITCH + (wm * (BM / 2) + lrow) * S::SPITCH;
+        const uint8_t* sb = st + (BM + BN) * S::PITCH + (BM + wn * (BN / 2) + lrow) * S::SPITCH;
+        static_for<0, DPR>([&](auto dc) {
+            constexpr int d = decltype(dc)::value;
+            if (k0 + d * 128 >= kend) return;                      // uniform: whole 128-K blocks past the end are skipped
+            uint32_t ua[TI], ub[TJ];
+#pragma unroll
+            for (int i = 0; i < TI; ++i) ua[i] = *reinterpret_cast<const uint32_t*>(sa + i * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) ub[j] = *reinterpret_cast<const uint32_t*>(sb + j * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
+            static_for<0, 2>([&](auto kc) {
+                constexpr int kk = decltype(kc)::value;
+                v4i fa[TI], fb[TJ];
+                const uint32_t col = S::column(lrow, 4 * d + 2 * kk + lhalf);
+#pragma unroll
+                for (int i = 0; i < TI; ++i) fa[i] = *reinterpret_cast<const v4i*>(pa + i * 32 * S::PITCH + col);
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) fb[j] = *reinterpret_cast<const v4i*>(pb + j * 32 * S::PITCH + col);
+#pragma unroll
+                for (int i = 0; i < TI; ++i) {
+                    const v8i xa = v8i{fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0};
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) {
+                        const v8i xb = v8i{fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0};
+                        // first operand = n side, second = m side: a lane ends up with one m and runs of 4 n
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            xb, xa, acc[i][j], 4, 4, 2 * kk, (int)ub[j], 2 * kk, (int)ua[i]);
+                    }
+                }
+            });
+        });
+    };
+
+    gload(kbeg);
+    lstore(lds);
+    __syncthreads();
+    uint32_t cur = 0;
+    for (uint32_t k0 = kbeg; k0 < kend; k0 += KS) {
+        const bool more = k0 + KS < kend;
+        if (more) gload(k0 + KS);
+        compute(lds + cur, k0);
+        cur = cur ? 0u : (uint32_t)S::STAGE;
+        if (more) lstore(lds + cur);
+        __syncthreads();
+    }
+    // (the last barrier: every wave is done reading the stage buffers, which the output strips reuse)
+    uint8_t* ep = lds + wave * 32 * S::EP_PITCH;
+    if (g.split_k == 1) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+    else                tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
 }
 
 // Sum the split-K partials in a fixed order and write the final output.
@@ -356,305 +435,6 @@ __global__ void splitk_reduce4_kernel(const float* part, int split, uint32_t m, 
     }
 }
 
-constexpr int G_BM = 256, G_BN = 256, G_WM = 128, G_WN = 64;
-
-// ---------------------------------------------------------------------------
-// Fast path (K a multiple of 128): V_MFMA_SCALE_F32_32X32X64_F8F6F4, operands
-// streamed global -> LDS by the DMA form of the load instructions.
-//
-//   workgroup 256 threads = 4 waves stacked along m; tile 256 (m) x 128 (n); wave
-//   tile 64 x 128 = 2 x 4 MFMA tiles of 32 x 32 (128 accumulator registers).
-//   Two workgroups fit on a CU (LDS 78 KB, <= 256 VGPRs): while one is waiting for
-//   its first loads, sitting at a barrier or storing its output, the other one
-//   keeps the matrix cores busy.
-//   One 32x32x64 MFMA takes, per lane, the 32 K elements (16 bytes) of row
-//   lane % 32, K block lane / 32, and that group's scale byte.
-//   A stage (K step of 128) holds A codes [256][64 B], B codes [128][64 B],
-//   A scales [256][4 B], B scales [128][4 B]; three stages.  A DMA load of 16 bytes
-//   per lane lands at lds_base + 16 * lane, so lane i of the load that covers 16
-//   rows fetches row i / 4, 16-byte chunk (i % 4) ^ ((row >> 2) & 3): the tile sits
-//   in LDS row-major with XOR-swizzled chunks and the MFMA operand reads (32 rows
-//   of one chunk per half wave) are bank-conflict free.
-//   Rows past the matrix edge read the last valid row instead (their products
-//   land in output rows/columns that are never stored).
-//   Per K step: wait for this wave's loads of the stage, barrier, issue the loads
-//   of stage +2, 12 operand reads + 16 MFMAs.
-//   Epilogue: accumulators go through a per-wave LDS strip so that every global
-//   store is 16 bytes per lane and whole 256/512-byte row segments per wave.
-// ---------------------------------------------------------------------------
-typedef float v16f __attribute__((ext_vector_type(16)));
-
-constexpr int D_BM = 256, D_BN = 128, D_STAGES = 3, D_NT = 256, D_WAVES = 4;
-constexpr int D_A_OFF = 0;
-constexpr int D_B_OFF = D_BM * 64;                          // 16384
-constexpr int D_SA_OFF = (D_BM + D_BN) * 64;                // 24576
-constexpr int D_SB_OFF = D_SA_OFF + D_BM * 4;               // 25600
-constexpr int D_STAGE_BYTES = D_SB_OFF + D_BN * 4;          // 26112
-constexpr int D_LDS_BYTES = D_STAGES * D_STAGE_BYTES;       // 78336: two workgroups per CU
-constexpr int D_LOADS_PER_STAGE = 8;                        // per wave: 4 A + 2 B code loads, 2 scale loads
-constexpr int D_EP_PITCH_F32 = 528, D_EP_PITCH_BF16 = 264;  // bytes per 128-column strip row, padded
-constexpr int D_EP_BYTES = 32 * D_EP_PITCH_F32;             // per wave
-static_assert(D_WAVES * D_EP_BYTES <= D_LDS_BYTES, "epilogue strips must fit in the stage buffers");
-
-#define MX_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
-#define MX_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-// Bias of four consecutive output columns starting at `col` (a multiple of 4), zero when there is no
-// bias or the columns lie beyond n.
-__device__ __forceinline__ v4f bias_of_columns(const GemmArgs& g, uint32_t col)
-{
-    if (g.bias != nullptr && col < g.n) return *reinterpret_cast<const v4f*>(g.bias + col);
-    return v4f{0.f, 0.f, 0.f, 0.f};
-}
-
-// Accumulators -> per-wave LDS strip (32 rows x 128 columns) -> global, so that every
-// store is 16 bytes per lane and a wave writes whole row segments.  The LDS region must
-// no longer be in use by any wave of the workgroup.  The wave owns output rows
-// [mrow0, mrow0 + 64) and columns [nbase, nbase + 128).
-__device__ __forceinline__ void gemm_epilogue_32x32(const GemmArgs& g, uint8_t* ep, v16f (&acc)[2][4],
-                                                    uint32_t mrow0, uint32_t nbase, int lane, uint32_t zsplit)
-{
-    const uint32_t lrow = lane & 31, lhalf = lane >> 5;
-    float* cf = static_cast<float*>(g.c);
-    uint16_t* ch = static_cast<uint16_t*>(g.c);
-    int64_t ldc = g.ldc;
-    if (g.split_k > 1) {
-        cf += (size_t)zsplit * g.m * g.n;
-        ldc = g.n;
-    }
-    const bool as_bf16 = g.c_bf16 && g.split_k == 1;
-    if (as_bf16) {
-        const bool vec_ok = (ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(ch) & 15) == 0;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4f bv = bias_of_columns(g, nbase + 32 * j + 8 * q + 4 * lhalf);
-                    uint2 pk;
-                    pk.x = f32x2_to_bf16x2(acc[i][j][4 * q] + bv.x, acc[i][j][4 * q + 1] + bv.y);
-                    pk.y = f32x2_to_bf16x2(acc[i][j][4 * q + 2] + bv.z, acc[i][j][4 * q + 3] + bv.w);
-                    *reinterpret_cast<uint2*>(ep + lrow * D_EP_PITCH_BF16 + (32 * j + 8 * q + 4 * lhalf) * 2) = pk;
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const uint32_t row = it * 4 + (lane >> 4), col = (lane & 15) * 8;
-                const uint32_t mm = mrow0 + i * 32 + row, nn = nbase + col;
-                uint4 v = *reinterpret_cast<const uint4*>(ep + row * D_EP_PITCH_BF16 + col * 2);
-                if (mm < g.m && nn < g.n) {
-                    uint16_t* dst = ch + (size_t)mm * ldc + nn;
-                    if (nn + 8 <= g.n && vec_ok) {
-                        *reinterpret_cast<uint4*>(dst) = v;
-                    } else {
-                        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-                        for (int e = 0; e < 8; ++e)
-                            if (nn + e < g.n) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-                    }
-                }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    } else {
-        const bool vec_ok = (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(cf) & 15) == 0;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4f bv = bias_of_columns(g, nbase + 32 * j + 8 * q + 4 * lhalf);
-                    *reinterpret_cast<float4*>(ep + lrow * D_EP_PITCH_F32 + (32 * j + 8 * q + 4 * lhalf) * 4) =
-                        make_float4(acc[i][j][4 * q] + bv.x, acc[i][j][4 * q + 1] + bv.y, acc[i][j][4 * q + 2] + bv.z,
-                                    acc[i][j][4 * q + 3] + bv.w);
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int it = 0; it < 16; ++it) {
-                const uint32_t row = it * 2 + (lane >> 5), col = (lane & 31) * 4;
-                const uint32_t mm = mrow0 + i * 32 + row, nn = nbase + col;
-                float4 v = *reinterpret_cast<const float4*>(ep + row * D_EP_PITCH_F32 + col * 4);
-                if (mm < g.m && nn < g.n) {
-                    float* dst = cf + (size_t)mm * ldc + nn;
-                    if (nn + 4 <= g.n && vec_ok) {
-                        *reinterpret_cast<float4*>(dst) = v;
-                    } else {
-                        const float w[4] = {v.x, v.y, v.z, v.w};
-                        for (int e = 0; e < 4; ++e)
-                            if (nn + e < g.n) dst[e] = w[e];
-                    }
-                }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    }
-}
-
-// Workgroup -> (K split, tile).  The grid is one-dimensional over split * tiles.  Workgroup
-// ids go round-robin over the 8 XCDs, each with its own L2, so id % 8 = XCD gets a
-// contiguous range of the logical order (split, m tile, n tile): the workgroups that share
-// an A row panel or a B panel of one K range run on the same XCD at about the same time.
-__device__ __forceinline__ void decode_tile(const GemmArgs& g, uint32_t& zsplit, uint32_t& tm, uint32_t& tn)
-{
-    const uint32_t tiles = g.tiles_m * g.tiles_n, nblk = tiles * (uint32_t)g.split_k;
-    uint32_t bid = blockIdx.x;
-    uint32_t per = nblk / 8, rem = nblk % 8;
-    uint32_t xcd = bid % 8, idx = bid / 8;
-    bid = xcd * per + (xcd < rem ? xcd : rem) + idx;       // bijection on [0, nblk)
-    zsplit = bid / tiles;
-    uint32_t t = bid - zsplit * tiles;
-    tm = t / g.tiles_n;
-    tn = t - tm * g.tiles_n;
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_then_barrier()
-{
-    // the memory clobber keeps LDS accesses on their side of the barrier
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-__global__ __launch_bounds__(D_NT, 2) void mx_gemm_dma_kernel(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[D_LDS_BYTES];
-
-    uint32_t zsplit, tm, tn;
-    decode_tile(g, zsplit, tm, tn);
-    const uint32_t m0 = tm * D_BM, n0 = tn * D_BN;
-    const uint32_t kbeg = zsplit * g.k_per_split;
-    const uint32_t kend = min(g.k, kbeg + g.k_per_split);
-    const int nk = (int)((kend - kbeg) >> 7);
-    const uint32_t kbytes = g.k >> 1, kgroups = g.k >> 5;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t lrow = lane & 31, lhalf = lane >> 5;
-    const uint32_t swz = (lrow >> 2) & 3;
-
-    // ---- DMA sources (per lane): wave w loads A rows [64w, 64w+64) and B rows [32w, 32w+32) ----
-    const uint8_t* a_src[4];
-    const uint8_t* b_src[2];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        uint32_t row = (4 * wave + u) * 16 + (lane >> 2);
-        uint32_t ch = (lane & 3) ^ ((row >> 2) & 3);
-        a_src[u] = g.a_codes + (size_t)min(m0 + row, g.m - 1) * kbytes + (kbeg >> 1) + ch * 16;
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        uint32_t row = (2 * wave + u) * 16 + (lane >> 2);
-        uint32_t ch = (lane & 3) ^ ((row >> 2) & 3);
-        b_src[u] = g.b_codes + (size_t)min(n0 + row, g.n - 1) * kbytes + (kbeg >> 1) + ch * 16;
-    }
-    const uint8_t* sa_src = g.a_scales + (size_t)min(m0 + wave * 64 + lane, g.m - 1) * kgroups + (kbeg >> 5);
-    const uint8_t* sb_src = g.b_scales + (size_t)min(n0 + wave * 32 + lrow, g.n - 1) * kgroups + (kbeg >> 5);
-
-    auto issue = [&](int buf, int kt) {
-        uint8_t* base = lds + buf * D_STAGE_BYTES;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            __builtin_amdgcn_global_load_lds(MX_GPTR(a_src[u] + kt * 64), MX_LPTR(base + D_A_OFF + (4 * wave + u) * 1024), 16, 0, 0);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            __builtin_amdgcn_global_load_lds(MX_GPTR(b_src[u] + kt * 64), MX_LPTR(base + D_B_OFF + (2 * wave + u) * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(MX_GPTR(sa_src + kt * 4), MX_LPTR(base + D_SA_OFF + wave * 256), 4, 0, 0);
-        if (lane < 32)      // 32 B rows per wave: the upper half wave sits this load out
-            __builtin_amdgcn_global_load_lds(MX_GPTR(sb_src + kt * 4), MX_LPTR(base + D_SB_OFF + wave * 128), 4, 0, 0);
-    };
-
-    v16f acc[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // Operand registers of one 64-K slice (one MFMA per accumulator tile) and the
-    // scale dwords of one K step, already shifted so that op_sel 0 / 2 picks the byte.
-    struct Frag { v4i a[2]; v4i b[4]; };
-    struct Scales { uint32_t a[2]; uint32_t b[4]; };
-    auto read_frag = [&](int buf, int kk, Frag& f) {
-        const uint8_t* base = lds + buf * D_STAGE_BYTES;
-        const uint32_t coff = ((2 * kk + lhalf) ^ swz) << 4;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            f.a[i] = *reinterpret_cast<const v4i*>(base + D_A_OFF + (wave * 64 + i * 32 + lrow) * 64 + coff);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            f.b[j] = *reinterpret_cast<const v4i*>(base + D_B_OFF + (j * 32 + lrow) * 64 + coff);
-    };
-    auto read_scales = [&](int buf, Scales& sc) {
-        const uint8_t* base = lds + buf * D_STAGE_BYTES;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            sc.a[i] = *reinterpret_cast<const uint32_t*>(base + D_SA_OFF + (wave * 64 + i * 32 + lrow) * 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            sc.b[j] = *reinterpret_cast<const uint32_t*>(base + D_SB_OFF + (j * 32 + lrow) * 4);
-    };
-    auto shift_scales = [&](Scales& sc) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) sc.a[i] >>= 8 * lhalf;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sc.b[j] >>= 8 * lhalf;
-    };
-    auto mma = [&](const Frag& f, const Scales& sc, auto kc) {
-        constexpr int kk = decltype(kc)::value;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            v8i xa = v8i{f.a[i].x, f.a[i].y, f.a[i].z, f.a[i].w, 0, 0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v8i xb = v8i{f.b[j].x, f.b[j].y, f.b[j].z, f.b[j].w, 0, 0, 0, 0};
-                // first operand = n side, second = m side: a lane ends up with one m and runs of 4 n
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    xb, xa, acc[i][j], 4, 4, 2 * kk, (int)sc.b[j], 2 * kk, (int)sc.a[i]);
-            }
-        }
-    };
-
-    // ---- main loop, software-pipelined by half K steps: the LDS reads of the next 64-K
-    //      slice are issued before the 8 MFMAs of the current one ----
-    // Three stages, two in flight: at the barrier in the middle of step kt every wave's reads of
-    // stage kt have returned (lgkmcnt(0) before the barrier), so that buffer takes stage kt+3
-    // while stage kt+2 is still on its way and stage kt+1 has just landed.
-    if (nk > 0) issue(0, 0);
-    if (nk > 1) issue(1, 1);
-    if (nk > 2) issue(2, 2);
-    if (nk > 2)      wait_vmcnt_then_barrier<2 * D_LOADS_PER_STAGE>();
-    else if (nk > 1) wait_vmcnt_then_barrier<1 * D_LOADS_PER_STAGE>();
-    else             wait_vmcnt_then_barrier<0>();
-    Frag f0, f1;
-    Scales sc, scn;
-    read_scales(0, sc);
-    read_frag(0, 0, f0);
-    shift_scales(sc);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt % D_STAGES;
-        read_frag(cur, 1, f1);
-        mma(f0, sc, std::integral_constant<int, 0>{});
-        if (kt + 1 < nk) {
-            // stage kt+1 must have landed; stage kt+2, if any, may stay in flight
-            if (kt + 2 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(D_LOADS_PER_STAGE) : "memory");
-            else             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (kt + 3 < nk) issue(cur, kt + 3);
-            const int nxt = (kt + 1) % D_STAGES;
-            read_scales(nxt, scn);
-            read_frag(nxt, 0, f0);
-        }
-        mma(f1, sc, std::integral_constant<int, 1>{});
-        if (kt + 1 < nk) {
-            shift_scales(scn);
-            sc = scn;
-        }
-    }
-    wait_vmcnt_then_barrier<0>();          // every wave is done reading the stage buffers
-
-    gemm_epilogue_32x32(g, lds + wave * D_EP_BYTES, acc, m0 + wave * 64, n0, lane, zsplit);
-}
-
-
 // ---------------------------------------------------------------------------
 // Helpers of the main path (K range of at least 512 per split; mx_gemm_pingpong_kernel below).
 // ---------------------------------------------------------------------------
@@ -677,16 +457,6 @@ __device__ __forceinline__ uint32_t fresh_lane_id()
 // Accumulators of one wave (64 rows x 128 columns) -> global through a 32-row LDS strip
 // holding 128 bytes per row: 64 bf16 or 32 fp32 columns at a time.  A store instruction
 // of the wave covers 8 whole 128-byte row segments.
-// 16-byte store.  A final output is written with the nontemporal hint: it is not read again
-// here, and without the hint an output larger than the last-level cache slows the whole kernel
-// down while it drains (split-K partials keep the default policy, the reduction reads them).
-template <bool STREAM>
-__device__ __forceinline__ void store16(void* dst, v4i v)
-{
-    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(dst));
-    else        *reinterpret_cast<v4i*>(dst) = v;
-}
-
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef int v2i __attribute__((ext_vector_type(2)));
 
@@ -1416,28 +1186,52 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
     return hipGetLastError();
 }
 
-int gemm_split_k(int64_t m, int64_t n, int64_t k)
+// Which kernel a product runs on and how many K splits it has.  The lines between the kernels come from a
+// sweep of m = 64..25216, n = 192..3072, K = 192..50432 on the card (us, each product alone in a replayed graph):
+//   main kernel: enough 256 x 256 tiles to occupy half the compute units (12672 x 768 x 768: 10.6 against 11.8 on
+//     128 x 128 tiles, 25216 x 1536 x 3072: 79 against 131), or enough work for a K split of them
+//     (768 x 768 x 50432: 36 against 42 and 46; at 1.5e10 multiply-adds it is even, 768 x 768 x 25216: 29 and 29).
+//   64 x 64 tiles: up to one tile per compute unit (224 x 192 x 768: 4.1 against 6.6 on 128 x 128 and 8.0 on the
+//     main kernel), with a K split up to two per unit (768 x 192 x 12672: 11 against 13 and 18).
+//   128 x 64 tiles: up to three per unit (9856 x 384 x 1536: 9.4 against 11.3 and 12.3).
+//   128 x 128 tiles: what is left, i.e. long m or n at K < 512 or K % 128 != 0 (25216 x 1536 x 384: 27 against 30
+//     on 256 x 128 tiles with DMA loads, the kernel that ran these sizes before).
+// K splits (K >= 4096): s partials cost s * m * n * 4 bytes written and read, the K loop is K / s long; the sum is
+// least at s ~ sqrt(K / (m n)) times the constant below, measured per kernel, within the slots of one round.
+enum class GemmKernel { pingpong, tile128, tile128x64, tile64 };
+
+struct GemmPlan {
+    GemmKernel kernel;
+    int split_k;
+};
+
+static GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k)
 {
-    // Split K only when the output has too few tiles to fill the machine and K is long.  A split
-    // product runs in the main kernel (at least 8 K steps per split): one 256 x 256 workgroup per
-    // CU, 256 slots; the split is the largest that still fits in one round of slots, so that
-    // every partial tile is written once and the second, emptier round does not exist.
-    const bool fast = (k & 127) == 0;
-    const int64_t bm = fast ? Q_BM : G_BM, bn = fast ? Q_BN : G_BN, slots = 256;
-    int64_t tiles = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-    if (tiles * 2 > slots || k < 4096) return 1;
-    int64_t s = slots / tiles;
-    int64_t max_by_k = k / 1024;                 // keep at least 8 K steps per split
-    if (s > max_by_k) s = max_by_k;
-    if (s < 1) s = 1;
-    if (s > 64) s = 64;
-    return (int)s;
+    auto tiles = [&](int64_t bm, int64_t bn) -> int64_t { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); };
+    const double mn = (double)m * (double)n, ratio = std::sqrt((double)k / mn);
+    auto splits = [&](int64_t slots, int64_t count, double scale, int64_t min_k) -> int {
+        if (k < 4096) return 1;
+        const int64_t s = std::min({slots / count, k / min_k, (int64_t)(scale * ratio), (int64_t)64});
+        return s < 1 ? 1 : (int)s;
+    };
+    const int64_t t256 = tiles(Q_BM, Q_BN), t12864 = tiles(128, 64), t64 = tiles(64, 64);
+    const bool main_ok = (k & 127) == 0 && k >= 512;
+    if (main_ok && (t256 >= 128 || mn * (double)k >= 1.6e10))
+        return {GemmKernel::pingpong, t256 * 2 <= 256 ? splits(256, t256, 60.0, 1024) : 1};
+    if (t64 <= (k >= 4096 ? 512 : 256)) return {GemmKernel::tile64, splits(512, t64, 24.0, 1024)};
+    if (t12864 <= 768) return {GemmKernel::tile128x64, splits(768, t12864, 35.0, 1024)};
+    if (main_ok) return {GemmKernel::pingpong, 1};
+    return {GemmKernel::tile128, 1};
 }
+
+int gemm_split_k(int64_t m, int64_t n, int64_t k) { return plan_gemm(m, n, k).split_k; }
 
 bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k)
 {
-    // the main kernel: K a multiple of 128 with at least four K steps, and no K split
-    return (k & 127) == 0 && k >= 512 && (n & 31) == 0 && gemm_split_k(m, n, k) == 1;
+    // The stage lives in the main kernel (K a multiple of 128 with at least four K steps), without a K split: a long K
+    // with fewer than half the units' worth of 256 x 256 tiles is a K-split product's shape.
+    return (k & 127) == 0 && k >= 512 && (n & 31) == 0 &&
+           (k < 4096 || ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN) * 2 > 256);
 }
 
 hipError_t launch_gemm(const GemmParams& p, hipStream_t st)
@@ -1453,39 +1247,41 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st)
     g.c = g.split_k > 1 ? p.workspace : p.c;
     g.ldc = p.ldc; g.c_bf16 = p.c_bf16;
     g.bias = g.split_k > 1 ? nullptr : p.bias;                  // partial sums get none: the reduction adds it
-    if ((p.k & 127) == 0) {
-        g.tiles_m = (uint32_t)((p.m + D_BM - 1) / D_BM);
-        g.tiles_n = (uint32_t)((p.n + D_BN - 1) / D_BN);
-        dim3 grid(g.tiles_m * g.tiles_n * g.split_k);
-        const uint32_t last_steps = ksteps - (uint32_t)(g.split_k - 1) * steps_per;
-        if (steps_per >= 4 && last_steps >= 4) {
-            g.tiles_m = (uint32_t)((p.m + Q_BM - 1) / Q_BM);
-            g.tiles_n = (uint32_t)((p.n + Q_BN - 1) / Q_BN);
-            const unsigned nblk = g.tiles_m * g.tiles_n * g.split_k;
-            // measured on the ViT-B products: 2.5 us (3 x 2048 clocks) gains 5-15 % at K = 768 and
-            // 3-5 % at K = 2304, nothing at K = 3072; pointless below two rounds of tiles
-            g.stagger = (g.split_k == 1 && nblk >= 2 * Q_SLOTS && p.k <= 2304) ? 3 : 0;
-            const dim3 pgrid(nblk < Q_SLOTS ? nblk : Q_SLOTS);
-            if (p.q_codes) {
-                if (!g.bias || g.split_k != 1) return hipErrorInvalidValue;
-                g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
-                hipLaunchKernelGGL((mx_gemm_pingpong_kernel<true, true>), pgrid, dim3(Q_NT), 0, st, g);
-            } else if (g.bias) {
-                hipLaunchKernelGGL(mx_gemm_pingpong_kernel<true>, pgrid, dim3(Q_NT), 0, st, g);
-            } else {
-                hipLaunchKernelGGL(mx_gemm_pingpong_kernel<false>, pgrid, dim3(Q_NT), 0, st, g);
-            }
+    GemmKernel kernel = p.q_codes ? GemmKernel::pingpong : plan_gemm(p.m, p.n, p.k).kernel;
+    // the main kernel needs four K steps in every split (the last one may be short of that)
+    if (kernel == GemmKernel::pingpong && ksteps - (uint32_t)(g.split_k - 1) * steps_per < 4) kernel = GemmKernel::tile128;
+    auto tile_grid = [&](int bm, int bn) -> unsigned {
+        g.tiles_m = (uint32_t)((p.m + bm - 1) / bm);
+        g.tiles_n = (uint32_t)((p.n + bn - 1) / bn);
+        return g.tiles_m * g.tiles_n * (unsigned)g.split_k;
+    };
+    switch (kernel) {
+    case GemmKernel::pingpong: {
+        if (p.q_codes && (!gemm_takes_fused_quantizer(p.m, p.n, p.k) || !g.bias || g.split_k != 1)) return hipErrorInvalidValue;
+        const unsigned nblk = tile_grid(Q_BM, Q_BN);
+        // measured on the ViT-B products: 2.5 us (3 x 2048 clocks) gains 5-15 % at K = 768 and
+        // 3-5 % at K = 2304, nothing at K = 3072; pointless below two rounds of tiles
+        g.stagger = (g.split_k == 1 && nblk >= 2 * Q_SLOTS && p.k <= 2304) ? 3 : 0;
+        const dim3 pgrid(nblk < Q_SLOTS ? nblk : Q_SLOTS);
+        if (p.q_codes) {
+            g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
+            hipLaunchKernelGGL((mx_gemm_pingpong_kernel<true, true>), pgrid, dim3(Q_NT), 0, st, g);
+        } else if (g.bias) {
+            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<true>, pgrid, dim3(Q_NT), 0, st, g);
         } else {
-            if (p.q_codes) return hipErrorInvalidValue;          // the fused quantizer lives in the main kernel only
-            hipLaunchKernelGGL(mx_gemm_dma_kernel, grid, dim3(D_NT), 0, st, g);
+            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<false>, pgrid, dim3(Q_NT), 0, st, g);
         }
-    } else {
-        if (p.q_codes) return hipErrorInvalidValue;
-        g.tiles_m = (uint32_t)((p.m + G_BM - 1) / G_BM);
-        g.tiles_n = (uint32_t)((p.n + G_BN - 1) / G_BN);
-        dim3 grid(g.tiles_m * g.tiles_n, 1, g.split_k);
-        dim3 block((G_BM / G_WM) * (G_BN / G_WN) * 64);
-        hipLaunchKernelGGL((mx_gemm_kernel<G_BM, G_BN, G_WM, G_WN>), grid, block, 0, st, g);
+        break;
+    }
+    case GemmKernel::tile128:
+        hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
+        break;
+    case GemmKernel::tile128x64:
+        hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 64, 256, 3>), dim3(tile_grid(128, 64)), dim3(T_NT), 0, st, g);
+        break;
+    case GemmKernel::tile64:
+        hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
+        break;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -69,3 +69,25 @@ def test_sweep_products(mx, orc):
         got = mx.mx_linear_fwd(dev(ac), dev(as_), dev(bc), dev(bs), out_dtype=out).float()
         check_product(orc, got, ac, as_, bc, bs, "case %d: %dx%dx%d" % (case, m, n, k),
                       tol=1e-5 if out == torch.float32 else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("m,n,k", [
+    # 64 x 64 tiles (up to 256 of them): one row, tile edges, one K step, several, ragged tails of 32, 64 and 96
+    (1, 4, 32), (64, 64, 512), (65, 63, 544), (63, 129, 1120), (224, 192, 768), (1024, 1024, 96),
+    # one tile more: 128 x 64 tiles, up to 768 of them
+    (1025, 1024, 96), (1031, 1030, 288), (4096, 1536, 160),
+    # one more: 128 x 128 tiles; K % 128 == 0 below and above 512
+    (4097, 1536, 160), (12801, 452, 384), (12672, 578, 416),
+    # the main kernel from 128 tiles of 256 x 256 on (ragged edges, shifted last scale block)
+    (32765, 250, 640), (32641, 36, 512), (8200, 1028, 1152),
+    # K splits of the 64 x 64 and 128 x 64 tiles (uneven, ragged K), and of the main kernel
+    (100, 132, 4128), (192, 768, 12608), (1100, 2080, 8224), (516, 764, 41088)])
+def test_products_at_the_lines_between_kernels(mx, orc, m, n, k):
+    ac, as_ = random_packed(m, k, 600 + m % 97)
+    bc, bs = random_packed(n, k, 700 + n % 89)
+    got = mx.mx_linear_fwd(dev(ac), dev(as_), dev(bc), dev(bs))
+    check_product(orc, got, ac, as_, bc, bs, "%dx%dx%d" % (m, n, k))
+    if n % 4 == 0:                                       # bf16 with bias: one rounding of the FP32 sum
+        bias = np.linspace(-2, 2, n, dtype=np.float32)
+        y = mx.mx_linear_fwd_bias(dev(ac), dev(as_), dev(bc), dev(bs), dev(bias), out_dtype=torch.bfloat16)
+        assert torch.equal(y, (got + dev(bias)).bfloat16())
