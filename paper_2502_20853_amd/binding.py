@@ -116,6 +116,28 @@ def lib():
     return L
 
 
+_host = None
+
+
+def host():
+    """The native host path of the front ends (csrc/mx_torch.cpp, built with the HIP library); raises if absent."""
+    global _host
+    if _host is None:
+        lib()
+        try:
+            from . import _mx_torch
+        except ImportError as e:
+            raise RuntimeError("the native host module of this package is not built: run `python -m paper_2502_20853_amd.build` "
+                               "(or __graft_entry__.build()): %s" % e) from e
+        _host = _mx_torch
+    return _host
+
+
+def seed_args(seed):
+    """(value, device tensor) of a seed given as an int or as a one-element int64 device tensor."""
+    return (0, seed) if torch.is_tensor(seed) else (seed & 0xFFFFFFFFFFFFFFFF, None)
+
+
 def _check(fn, rc):
     if rc != MX_OK:
         raise MxError(fn, rc, lib().mx_last_hip_error() if rc == MX_ERR_HIP else 0)

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mx_launch.hpp"
+
 namespace mxd {
 
 // ---- shared exponent (Sec. 3.2) -------------------------------------------
@@ -375,3 +377,32 @@ __device__ __forceinline__ uint32_t amax_bits8(const F8& x)
 }
 
 }  // namespace mxd
+
+namespace mxl {
+
+// Sums the per-block column sums in a fixed order: a workgroup of 256 owns 32 columns; each of its 8 parts
+// (32 lanes) adds up a contiguous eighth of the blocks in index order (independent loads, 128 bytes
+// per row of 32 lanes), then the eight parts are added in order.
+__device__ __forceinline__ void column_sum_finish(const ColumnSumTail& a, uint32_t block)
+{
+    __shared__ float part[8][32];
+    const uint32_t lc = threadIdx.x & 31u, p = threadIdx.x >> 5;
+    const uint32_t c = block * 32u + lc;
+    const uint32_t per = (a.blocks + 7u) / 8u;
+    float s = 0.f;
+    if (c < a.cols) {
+        const uint32_t b0 = min(a.blocks, p * per), b1 = min(a.blocks, b0 + per);
+        for (uint32_t b = b0; b < b1; ++b) s += a.partials[(size_t)b * a.cols + c];
+    }
+    part[p][lc] = s;
+    __syncthreads();
+    if (p == 0 && c < a.cols) {
+        float t = part[0][lc];
+#pragma unroll
+        for (int q = 1; q < 8; ++q) t += part[q][lc];
+        if (a.out_bf16) static_cast<__bf16*>(a.out)[c] = (__bf16)t;
+        else            static_cast<float*>(a.out)[c] = t;
+    }
+}
+
+}  // namespace mxl

@@ -381,9 +381,14 @@ __global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
 }
 
 // Sum the split-K partials in a fixed order and write the final output.
-__global__ void splitk_reduce_kernel(const float* part, int split, uint32_t m, uint32_t n,
-                                     void* c, int64_t ldc, int c_bf16, const float* bias)
+// Workgroups past the reduction's own (`blocks`) finish a column sum, which saves that its own launch.
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, int split, uint32_t m, uint32_t n,
+                                     void* c, int64_t ldc, int c_bf16, const float* bias, uint32_t blocks, mxl::ColumnSumTail tail)
 {
+    if (blockIdx.x >= blocks) {
+        mxl::column_sum_finish(tail, blockIdx.x - blocks);
+        return;
+    }
     size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t total = (size_t)m * n;
     if (idx >= total) return;
@@ -397,9 +402,13 @@ __global__ void splitk_reduce_kernel(const float* part, int split, uint32_t m, u
 
 // The same for n % 4 == 0 and 16-byte aligned rows of the output: four columns per thread, the
 // partial loads of a thread issued back to back (same summation order per element).
-__global__ void splitk_reduce4_kernel(const float* part, int split, uint32_t m, uint32_t n,
-                                      void* c, int64_t ldc, int c_bf16, const float* bias)
+__global__ __launch_bounds__(256) void splitk_reduce4_kernel(const float* part, int split, uint32_t m, uint32_t n,
+                                      void* c, int64_t ldc, int c_bf16, const float* bias, uint32_t blocks, mxl::ColumnSumTail tail)
 {
+    if (blockIdx.x >= blocks) {
+        mxl::column_sum_finish(tail, blockIdx.x - blocks);
+        return;
+    }
     const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;       // index of a group of 4 columns
     const size_t total = (size_t)m * n;
     if (q * 4 >= total) return;
@@ -1234,7 +1243,7 @@ bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k)
            (k < 4096 || ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN) * 2 > 256);
 }
 
-hipError_t launch_gemm(const GemmParams& p, hipStream_t st)
+hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail)
 {
     GemmArgs g{};
     g.a_codes = p.a_codes; g.a_scales = p.a_scales; g.b_codes = p.b_codes; g.b_scales = p.b_scales;
@@ -1290,16 +1299,18 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st)
         const size_t out_bytes = p.c_bf16 ? 2 : 4;
         const bool vec = (p.n & 3) == 0 && ((size_t)p.ldc * out_bytes & 15) == 0 &&
                          (reinterpret_cast<uintptr_t>(p.c) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.workspace) & 15) == 0;
-        if (vec) {
-            dim3 rgrid((unsigned)((total / 4 + 255) / 256)), rblock(256);
-            hipLaunchKernelGGL(splitk_reduce4_kernel, rgrid, rblock, 0, st,
-                               static_cast<const float*>(p.workspace), g.split_k, g.m, g.n, p.c, p.ldc, (int)p.c_bf16, p.bias);
-        } else {
-            dim3 rgrid((unsigned)((total + 255) / 256)), rblock(256);
-            hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, rblock, 0, st,
-                               static_cast<const float*>(p.workspace), g.split_k, g.m, g.n, p.c, p.ldc, (int)p.c_bf16, p.bias);
-        }
+        const unsigned blocks = (unsigned)(((vec ? total / 4 : total) + 255) / 256);
+        const ColumnSumTail t = tail ? *tail : ColumnSumTail{};
+        const dim3 rgrid(blocks + (t.cols + 31) / 32), rblock(256);
+        if (vec)
+            hipLaunchKernelGGL(splitk_reduce4_kernel, rgrid, rblock, 0, st, static_cast<const float*>(p.workspace), g.split_k, g.m, g.n,
+                               p.c, p.ldc, (int)p.c_bf16, p.bias, blocks, t);
+        else
+            hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, rblock, 0, st, static_cast<const float*>(p.workspace), g.split_k, g.m, g.n,
+                               p.c, p.ldc, (int)p.c_bf16, p.bias, blocks, t);
         e = hipGetLastError();
+    } else if (tail && tail->cols) {
+        e = launch_column_sum_finish(*tail, st);
     }
     return e;
 }

@@ -7,6 +7,21 @@
 
 namespace mxl {
 
+// bf16 -> FP32 of a short vector (a bias), done by one more workgroup of a quantizer launch.
+struct WidenJob {
+    const uint16_t* src = nullptr;
+    float* dst = nullptr;
+    uint32_t count = 0;
+};
+
+// What is left of a column sum after the quantizer's pass: [blocks][cols] FP32 partials to be added up.
+struct ColumnSumTail {
+    const float* partials = nullptr;
+    void* out = nullptr;       // cols values, FP32 or bf16 (the FP32 sum rounded to nearest even)
+    uint32_t blocks = 0, cols = 0;
+    int out_bf16 = 0;
+};
+
 struct QuantRowsParams {
     const void* src;
     bool bf16;
@@ -39,7 +54,9 @@ struct QuantTileParams {
     uint64_t seed;
     uint64_t index_base;
     const uint64_t* seed_dev = nullptr;   // device word that replaces `seed` when set
-    float* col_sums = nullptr;            // [cols] column sums of the source (needs a source), with
+    int64_t src_rows = 0;                 // rows the source has (0: all); the rest up to `rows` count as zero
+    void* col_sums = nullptr;             // [cols] column sums of the source (needs a source), FP32 or bf16, with
+    bool col_sums_bf16 = false;
     float* col_sum_workspace = nullptr;   // column_sum_workspace_bytes(rows, cols) of scratch
 };
 
@@ -66,14 +83,21 @@ struct GemmParams {
 bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k);
 
 hipError_t launch_quantize_rows(const QuantRowsParams& p, hipStream_t st);
+// round_D rows of up to two contiguous tensors of any source types, and a vector to widen, in one launch.
+hipError_t launch_quantize_rows_batch(const QuantRowsParams* p, int count, hipStream_t st, const WidenJob* widen = nullptr);
 hipError_t launch_quantize_rows_e3m0(const QuantRowsParams& p, hipStream_t st);      // E3M0 elements (Table 7)
 hipError_t launch_dequantize_e3m0(const uint8_t* codes, const uint8_t* scales, int64_t rows, int64_t cols,
                                   float* out, hipStream_t st);
 hipError_t launch_ema_quantize(const QuantRowsParams& p, float* ema, float beta, int update_ema, hipStream_t st);
 hipError_t launch_quantize_tile(const QuantTileParams& p, hipStream_t st);
 size_t column_sum_workspace_bytes(int64_t rows, int64_t cols);
-// Up to 4 tensors in one launch; they must share source kind, roundings and scale rule.
-hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st);
+// Up to 4 tensors in one launch; they must share kind of source (FP32 and bf16 may be mixed where the rows round
+// deterministically and no column sums are taken), roundings and scale rule.  finish_col_sums false: the caller adds up
+// the column sums' partials itself (column_sum_tail), e.g. in the launch that reduces a K split.
+hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st, const WidenJob* widen = nullptr,
+                                      bool finish_col_sums = true);
+ColumnSumTail column_sum_tail(const QuantTileParams& q);
+hipError_t launch_column_sum_finish(const ColumnSumTail& t, hipStream_t st);
 hipError_t launch_dequantize(const uint8_t* codes, const uint8_t* scales, int64_t rows, int64_t cols,
                              float* out, hipStream_t st);
 
@@ -141,6 +165,7 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 
 // Number of K-splits the product will use for these sizes (1 = none).
 int gemm_split_k(int64_t m, int64_t n, int64_t k);
-hipError_t launch_gemm(const GemmParams& p, hipStream_t st);
+// tail: column sums to finish as well (in the K split's reduction where there is one, else in a launch of their own).
+hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail = nullptr);
 
 }  // namespace mxl

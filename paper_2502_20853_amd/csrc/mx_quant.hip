@@ -20,6 +20,7 @@
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
+#include <type_traits>
 
 using namespace mxd;
 
@@ -137,6 +138,50 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
     }
 }
 
+// round_D rows of up to two tensors (the activation and the weight of a forward pass that needs no column groups), each
+// with its own source type, and a bias to widen, in one launch: at the sizes of serving a launch costs more than
+// its work.  The body is quantize_rows_kernel's for contiguous sources.
+struct RowsBatch {
+    RowsArgs job[2];
+    int bf16[2];
+    uint32_t first1;       // first workgroup of the second job
+    mxl::WidenJob widen;
+};
+
+template <bool FLOOR, int UNROLL>
+__global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_batch_kernel(RowsBatch b)
+{
+    if (b.widen.count != 0u && blockIdx.x == gridDim.x - 1u) {
+        for (uint32_t i = threadIdx.x; i < b.widen.count; i += ROWS_THREADS) b.widen.dst[i] = __uint_as_float((uint32_t)b.widen.src[i] << 16);
+        return;
+    }
+    set_round_mode_for<false>();
+    const int j = blockIdx.x >= b.first1 ? 1 : 0;
+    const RowsArgs& a = b.job[j];
+    const uint32_t q0 = (blockIdx.x - (j ? b.first1 : 0u)) * (ROWS_THREADS * UNROLL) + threadIdx.x;
+    auto run = [&](auto tag) {
+        const auto* src = static_cast<const decltype(tag)*>(a.src);
+        F8 x[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const uint32_t q = q0 + u * ROWS_THREADS;
+            x[u] = q < a.total ? load8(src + (size_t)q * 8) : zero8();
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const uint32_t q = q0 + u * ROWS_THREADS;
+            const uint32_t byte = scale_byte(quad_max(amax_bits8(x[u])), FLOOR);
+            const uint32_t packed = encode8<false, FLOOR>(x[u], grid_exponent(byte), U8{});
+            if (q < a.total) {
+                reinterpret_cast<uint32_t*>(a.codes)[q] = packed;
+                if ((threadIdx.x & 3) == 0) a.scales[q >> 2] = (uint8_t)byte;
+            }
+        }
+    };
+    if (b.bf16[j]) run(uint16_t{});
+    else           run(float{});
+}
+
 template <typename SrcT>
 __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 {
@@ -215,7 +260,9 @@ struct TileArgs {
     uint8_t* scales_row;
     int64_t ld;
     uint32_t rows, cols;
+    uint32_t src_rows;     // rows the source has; rows from there up to `rows` are zero
     int pre_quant;
+    int src_bf16;          // instances for both source types: which one this job reads
     // 1-D grid over macro tiles in row-major order: the first n_wide workgroups own 256 x 128 tiles
     // (two 32 x 64 tiles per wave), the rest own the two 256 x 64 halves of the tiles after those
     uint32_t n_wide;
@@ -295,19 +342,22 @@ constexpr int TILE_BATCH_MAX = 4;
 struct TileBatch {
     TileArgs job[TILE_BATCH_MAX];
     uint32_t first[TILE_BATCH_MAX];
+    mxl::WidenJob widen;   // the grid's last workgroup does this when widen.count is not zero
 };
+
+// bf16 -> FP32 of a short vector (a bias, in the launch that quantizes the layer's operands), one workgroup.
+__device__ __forceinline__ void widen_bf16(const mxl::WidenJob& j, uint32_t tid, uint32_t threads)
+{
+    for (uint32_t i = tid; i < j.count; i += threads) j.dst[i] = __uint_as_float((uint32_t)j.src[i] << 16);
+}
 
 // SRC: 0 = FP32 source, 1 = bf16 source, 2 = packed row result given
 // COLSUM: also the column sums of the source (a bias gradient is that of dY), per 256-row block; a
 // separate instance, so that the plain quantizer's code does not change with this feature.
-template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM = false>
-__global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatch batch)
+template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM>
+__device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint32_t block, uint8_t* st)      // a by value: by reference the stochastic
+                                                                            // instances take 128 registers and spill
 {
-    uint32_t job = 0;
-#pragma unroll
-    for (int i = 1; i < TILE_BATCH_MAX; ++i) job += blockIdx.x >= batch.first[i] ? 1u : 0u;
-    const TileArgs a = batch.job[job];
-    const uint32_t block = blockIdx.x - batch.first[job];
     // Philox key: the seed argument, or the 64-bit word in device memory that the caller names (a
     // captured graph then draws new numbers on every replay).  Kept in scalar registers either way.
     uint32_t k0 = a.k0, k1 = a.k1;
@@ -315,13 +365,12 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
         k0 = __builtin_amdgcn_readfirstlane(a.seed_dev[0]);
         k1 = __builtin_amdgcn_readfirstlane(a.seed_dev[1]);
     }
-    __shared__ __attribute__((aligned(16))) uint8_t st[COLSUM ? ST_BYTES_CSUM : ST_BYTES];
     // FP32 sources need the rounding mode of each rule (switched per phase when they differ).
     // bf16 and packed sources scale exactly wherever a round_D threshold is near (8 significant
     // bits), so there the mode of round_S, if any, serves the whole kernel.
     constexpr bool SWITCH_MODES = (SRC == 0) && (ROW_SR != T_SR);
     if (!SWITCH_MODES) set_round_mode_for<(ROW_SR || T_SR)>();
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int cc = lane & 7, rg = lane >> 3;
     const int wr = wave;                                  // wave position inside the macro tile
     // macro tile of this workgroup (uniform): a wide one, or one half of a wide one
@@ -341,6 +390,7 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
     const uint32_t mcol0 = (wide_index - row_block * a.wide_per_row) * 128u + (wide ? 0u : (narrow & 1u) * 64u);
     if (mcol0 >= a.cols) return;                          // second half of a tile that is only 64 columns wide
     const bool wave_has_rows = mrow0 + wr * 32 < a.rows;
+    const bool wave_rows_full = mrow0 + wr * 32 + 32 <= a.src_rows;
     const uint32_t lrow0 = wr * 32 + 4 * rg;              // first of this lane's 4 rows inside the macro tile
     const uint32_t row0 = mrow0 + lrow0;
     const bool want_row = a.codes_row != nullptr;
@@ -357,10 +407,16 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
     bf16x8_raw raw[4];
     auto fetch_raw = [&](int ci) {
         const uint32_t col = mcol0 + ci * 64 + cc * 8;
+        const uint16_t* p = static_cast<const uint16_t*>(a.src) + (int64_t)row0 * a.ld + col;
+        if (wave_rows_full && mcol0 + ci * 64 + 64 <= a.cols) {        // uniform: no masking
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            raw[j] = bf16x8_raw{0u, 0u, 0u, 0u};
-            if (col < a.cols) raw[j] = load8_raw(static_cast<const uint16_t*>(a.src) + (int64_t)(row0 + j) * a.ld + col);
+            for (int j = 0; j < 4; ++j) raw[j] = load8_raw(p + (int64_t)j * a.ld);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                raw[j] = bf16x8_raw{0u, 0u, 0u, 0u};
+                if (col < a.cols && row0 + j < a.src_rows) raw[j] = load8_raw(p + (int64_t)j * a.ld);
+            }
         }
     };
     if (PREFETCH && wave_has_rows) fetch_raw(0);
@@ -389,7 +445,8 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
 #pragma unroll
                 for (int j = 0; j < 4; ++j) x[j] = expand8(raw[j]);
                 if (ci + 1 < tiles_per_wave && mcol0 + tcol0 + 64 < a.cols) fetch_raw(ci + 1);
-            } else if (mcol0 + tcol0 + 64 <= a.cols) {    // whole tile inside the matrix (uniform): no masking, no zero fill
+            } else if (mcol0 + tcol0 + 64 <= a.cols && wave_rows_full) {
+                // whole tile inside the source (uniform): no masking, no zero fill
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     int64_t off = (int64_t)(row0 + j) * a.ld + c;
@@ -400,7 +457,7 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     x[j] = zero8();
-                    if (ok) {
+                    if (ok && row0 + j < a.src_rows) {
                         int64_t off = (int64_t)(row0 + j) * a.ld + c;
                         if (SRC == 1) x[j] = load8(static_cast<const uint16_t*>(a.src) + off);
                         else          x[j] = load8(static_cast<const float*>(a.src) + off);
@@ -512,28 +569,32 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
     }
 }
 
-// Sums the per-block column sums in a fixed order: a workgroup owns 32 columns; each of its 8 parts
-// (32 lanes) adds up a contiguous eighth of the blocks in index order (independent loads, 128 bytes
-// per row of 32 lanes), then the eight parts are added in order.
-__global__ __launch_bounds__(256) void column_sum_finish_kernel(const float* partials, uint32_t blocks, uint32_t cols, float* out)
+// SRC as above, or 3: FP32 and bf16 jobs in one launch (a bf16 activation and its FP32 master weight).
+template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM = false>
+__global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatch batch)
 {
-    __shared__ float part[8][32];
-    const uint32_t lc = threadIdx.x & 31u, p = threadIdx.x >> 5;
-    const uint32_t c = blockIdx.x * 32u + lc;
-    const uint32_t per = (blocks + 7u) / 8u;
-    float s = 0.f;
-    if (c < cols) {
-        const uint32_t b0 = min(blocks, p * per), b1 = min(blocks, b0 + per);
-        for (uint32_t b = b0; b < b1; ++b) s += partials[(size_t)b * cols + c];
+    __shared__ __attribute__((aligned(16))) uint8_t st[COLSUM ? ST_BYTES_CSUM : ST_BYTES];
+    if (batch.widen.count != 0u && blockIdx.x == gridDim.x - 1u) {
+        widen_bf16(batch.widen, threadIdx.x, TILE_THREADS);
+        return;
     }
-    part[p][lc] = s;
-    __syncthreads();
-    if (p == 0 && c < cols) {
-        float t = part[0][lc];
+    uint32_t job = 0;
 #pragma unroll
-        for (int q = 1; q < 8; ++q) t += part[q][lc];
-        out[c] = t;
+    for (int i = 1; i < TILE_BATCH_MAX; ++i) job += blockIdx.x >= batch.first[i] ? 1u : 0u;
+    const TileArgs a = batch.job[job];
+    const uint32_t block = blockIdx.x - batch.first[job];
+    if constexpr (SRC == 3) {
+        if (a.src_bf16) quantize_tile_body<1, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        else            quantize_tile_body<0, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+    } else {
+        quantize_tile_body<SRC, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
     }
+}
+
+// (the order is fixed: see mx_device.hpp)
+__global__ __launch_bounds__(256) void column_sum_finish_kernel(mxl::ColumnSumTail t)
+{
+    mxl::column_sum_finish(t, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -855,6 +916,41 @@ hipError_t launch_quantize_rows(const QuantRowsParams& p, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t launch_quantize_rows_batch(const QuantRowsParams* p, int count, hipStream_t st, const WidenJob* widen)
+{
+    if (count < 1 || count > 2) return hipErrorInvalidValue;
+    RowsBatch b{};
+    uint64_t chunks = 0;
+    for (int j = 0; j < count; ++j) {
+        RowsArgs& a = b.job[j];
+        if (p[j].ld != p[j].cols || p[j].sr || p[j].floor_mode != p[0].floor_mode) return hipErrorInvalidValue;
+        a.src = p[j].src; a.codes = p[j].codes; a.scales = p[j].scales;
+        a.total = (uint32_t)(p[j].rows * (p[j].cols / 8));
+        b.bf16[j] = p[j].bf16 ? 1 : 0;
+        chunks += a.total;
+    }
+    // one chunk per lane until that fills the chip's wave slots twice over, then four (loads in flight per lane)
+    const bool wide = chunks > 2u * 256u * 2048u;
+    const uint32_t per_block = ROWS_THREADS * (wide ? ROWS_UNROLL : 1);
+    const uint32_t n0 = (b.job[0].total + per_block - 1) / per_block;
+    const uint32_t n1 = count > 1 ? (b.job[1].total + per_block - 1) / per_block : 0u;
+    b.first1 = count > 1 ? n0 : 0xFFFFFFFFu;
+    uint32_t blocks = n0 + n1;
+    if (widen && widen->count) {
+        b.widen = *widen;
+        ++blocks;
+    }
+    dim3 grid(blocks), block(ROWS_THREADS);
+    if (p[0].floor_mode) {
+        if (wide) hipLaunchKernelGGL((quantize_rows_batch_kernel<true, ROWS_UNROLL>), grid, block, 0, st, b);
+        else      hipLaunchKernelGGL((quantize_rows_batch_kernel<true, 1>), grid, block, 0, st, b);
+    } else {
+        if (wide) hipLaunchKernelGGL((quantize_rows_batch_kernel<false, ROWS_UNROLL>), grid, block, 0, st, b);
+        else      hipLaunchKernelGGL((quantize_rows_batch_kernel<false, 1>), grid, block, 0, st, b);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_quantize_rows_e3m0(const QuantRowsParams& p, hipStream_t st)
 {
     RowsArgs a{};
@@ -930,6 +1026,7 @@ static uint32_t make_tile_args(const QuantTileParams& p, TileArgs& a)
     a.src = p.src; a.row_codes_in = p.row_codes_in; a.row_scales_in = p.row_scales_in;
     a.codes_t = p.codes_t; a.scales_t = p.scales_t; a.codes_row = p.codes_row; a.scales_row = p.scales_row;
     a.ld = p.ld; a.rows = (uint32_t)p.rows; a.cols = (uint32_t)p.cols;
+    a.src_rows = p.src_rows ? (uint32_t)p.src_rows : (uint32_t)p.rows; a.src_bf16 = p.bf16 ? 1 : 0;
     a.pre_quant = p.pre_quant;
     a.k0 = (uint32_t)p.seed; a.k1 = (uint32_t)(p.seed >> 32);
     a.seed_dev = reinterpret_cast<const uint32_t*>(p.seed_dev);
@@ -953,45 +1050,63 @@ static uint32_t make_tile_args(const QuantTileParams& p, TileArgs& a)
     return n_wide + 2u * (n_tiles - n_wide);
 }
 
-hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st)
+hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st, const WidenJob* widen,
+                                      bool finish_col_sums)
 {
     if (count < 1 || count > TILE_BATCH_MAX) return hipErrorInvalidValue;
     const QuantTileParams& p = jobs[0];
     const bool row_sr = p.row_codes_in ? false : p.sr_row;
     TileBatch b{};
     uint32_t blocks = 0;
-    bool col_sums = false;
+    bool col_sums = false, mixed = false;
     for (int j = 0; j < TILE_BATCH_MAX; ++j) {
         b.first[j] = 0xFFFFFFFFu;
         if (j >= count) continue;
         const QuantTileParams& q = jobs[j];
-        // one kernel instance serves the launch: source kind, roundings and scale rule are shared
-        if ((q.row_codes_in != nullptr) != (p.row_codes_in != nullptr) || q.bf16 != p.bf16 || q.sr_t != p.sr_t ||
+        // one kernel instance serves the launch: kind of source, roundings and scale rule are shared
+        if ((q.row_codes_in != nullptr) != (p.row_codes_in != nullptr) || q.sr_t != p.sr_t ||
             (q.row_codes_in ? false : q.sr_row) != row_sr || q.floor_mode != p.floor_mode)
             return hipErrorInvalidValue;
         b.first[j] = blocks;
         blocks += make_tile_args(q, b.job[j]);
         col_sums = col_sums || q.col_sums != nullptr;
+        mixed = mixed || (!p.row_codes_in && q.bf16 != p.bf16);
+    }
+    if (mixed && (col_sums || row_sr)) return hipErrorInvalidValue;      // only the forward pass mixes source types
+    if (widen && widen->count) {
+        b.widen = *widen;
+        ++blocks;
     }
     dim3 grid(blocks);
-    if (p.floor_mode) {
-        if (p.row_codes_in)  launch_tile_src<2, true>(b, row_sr, p.sr_t, col_sums, grid, st);
-        else if (p.bf16)     launch_tile_src<1, true>(b, row_sr, p.sr_t, col_sums, grid, st);
-        else                 launch_tile_src<0, true>(b, row_sr, p.sr_t, col_sums, grid, st);
-    } else {
-        if (p.row_codes_in)  launch_tile_src<2, false>(b, row_sr, p.sr_t, col_sums, grid, st);
-        else if (p.bf16)     launch_tile_src<1, false>(b, row_sr, p.sr_t, col_sums, grid, st);
-        else                 launch_tile_src<0, false>(b, row_sr, p.sr_t, col_sums, grid, st);
-    }
+    const int src = p.row_codes_in ? 2 : mixed ? 3 : p.bf16 ? 1 : 0;
+    auto launch = [&](auto fl) {
+        constexpr bool FL = decltype(fl)::value;
+        switch (src) {
+            case 0: launch_tile_src<0, FL>(b, row_sr, p.sr_t, col_sums, grid, st); break;
+            case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, grid, st); break;
+            case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, grid, st); break;
+            default:
+                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL>), grid, dim3(TILE_THREADS), 0, st, b);
+                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL>), grid, dim3(TILE_THREADS), 0, st, b);
+        }
+    };
+    if (p.floor_mode) launch(std::true_type{});
+    else              launch(std::false_type{});
     hipError_t e = hipGetLastError();
-    for (int j = 0; j < count && e == hipSuccess; ++j) {
-        const QuantTileParams& q = jobs[j];
-        if (!q.col_sums) continue;
-        hipLaunchKernelGGL(column_sum_finish_kernel, dim3((unsigned)((q.cols + 31) / 32)), dim3(256), 0, st,
-                           q.col_sum_workspace, (uint32_t)((q.rows + 255) / 256), (uint32_t)q.cols, q.col_sums);
-        e = hipGetLastError();
-    }
+    for (int j = 0; j < count && e == hipSuccess && finish_col_sums; ++j)
+        if (jobs[j].col_sums) e = launch_column_sum_finish(column_sum_tail(jobs[j]), st);
     return e;
+}
+
+ColumnSumTail column_sum_tail(const QuantTileParams& q)
+{
+    return {q.col_sum_workspace, q.col_sums, (uint32_t)((q.rows + 255) / 256), (uint32_t)q.cols, q.col_sums_bf16 ? 1 : 0};
+}
+
+hipError_t launch_column_sum_finish(const ColumnSumTail& t, hipStream_t st)
+{
+    hipLaunchKernelGGL(column_sum_finish_kernel, dim3((t.cols + 31) / 32), dim3(256), 0, st, t);
+    return hipGetLastError();
 }
 
 size_t column_sum_workspace_bytes(int64_t rows, int64_t cols)
@@ -1001,7 +1116,7 @@ size_t column_sum_workspace_bytes(int64_t rows, int64_t cols)
 
 hipError_t launch_quantize_tile(const QuantTileParams& p, hipStream_t st)
 {
-    return launch_quantize_tile_batch(&p, 1, st);
+    return launch_quantize_tile_batch(&p, 1, st, nullptr, true);
 }
 
 hipError_t launch_calibration_copy(void* dst, const void* src, size_t bytes, hipStream_t st)

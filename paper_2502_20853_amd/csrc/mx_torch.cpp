@@ -1,0 +1,363 @@
+// Native host path of the Python front ends: one call per pass of a layer instead of a Python call per kernel.
+// Host code only -- every quantizer and product is a launch of libmxfp4_hip.so (mx_launch.hpp); this file
+// allocates, fills the launch arguments and carries the autograd graph.
+//
+// Why it is native: a forward + backward of one layer is 8 to 11 launches, and through Python each cost 8-12 us of
+// argument handling next to 5-15 us of kernel for ViT-Tiny's sizes (270 us per layer, 110 us of it on the GPU).
+#include <torch/extension.h>
+#include <c10/hip/HIPGuard.h>
+#include <c10/hip/HIPStream.h>
+
+#include "mx_launch.hpp"
+
+namespace {
+
+using at::Tensor;
+using OptTensor = std::optional<Tensor>;
+
+// tensor ids of the six quantizers, numbered as in Eqs. 3-5
+enum : uint32_t { Q1 = 1, Q2 = 2, Q3 = 3, Q4 = 4, Q5 = 5, Q6 = 6 };
+
+void check_hip(hipError_t e, const char* what)
+{
+    TORCH_CHECK(e == hipSuccess, what, " failed: hipError_t ", (int)e);
+}
+
+bool is_bf16(const Tensor& t)
+{
+    TORCH_CHECK_TYPE(t.scalar_type() == at::kFloat || t.scalar_type() == at::kBFloat16,
+                     "source must be float32 or bfloat16, got ", t.scalar_type());
+    return t.scalar_type() == at::kBFloat16;
+}
+
+// Dense rows at a 16-byte aligned address, as the quantizers read them.
+Tensor dense_source(const Tensor& t)
+{
+    Tensor c = t.contiguous();
+    return (reinterpret_cast<uintptr_t>(c.data_ptr()) & 15) ? c.clone() : c;
+}
+
+int64_t round_up(int64_t v, int64_t to) { return (v + to - 1) / to * to; }
+
+// Pieces of one device buffer, each 256-byte aligned.
+struct Carver {
+    int64_t used = 0;
+    int64_t take(int64_t bytes)
+    {
+        const int64_t at = used;
+        used += round_up(bytes, 256);
+        return at;
+    }
+    int64_t codes(int64_t rows, int64_t cols) { return take(rows * (cols / 2)); }
+    int64_t scales(int64_t rows, int64_t cols) { return take(rows * (cols / 32)); }
+};
+
+Tensor bytes_like(const Tensor& t, int64_t n) { return at::empty({n}, t.options().dtype(at::kByte)); }
+
+struct Seed {
+    uint64_t value = 0;
+    const uint64_t* dev = nullptr;
+};
+
+Seed seed_of(int64_t value, const OptTensor& dev)
+{
+    Seed s{(uint64_t)value, nullptr};
+    if (dev) {
+        TORCH_CHECK_VALUE(dev->scalar_type() == at::kLong && dev->numel() == 1 && dev->is_cuda(),
+                          "a device seed is a one-element int64 tensor on the GPU");
+        s.dev = reinterpret_cast<const uint64_t*>(dev->data_ptr<int64_t>());
+    }
+    return s;
+}
+
+void check_sizes(int64_t rows, int64_t cols)
+{
+    TORCH_CHECK(rows > 0 && cols > 0 && rows <= (int64_t)0xFFFF0000LL * 8 / cols && rows <= 0x7FFFFFFFLL, "MX_ERR_SHAPE: ", rows, " x ", cols);
+}
+
+// One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split.
+void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
+             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const Tensor* workspace = nullptr,
+             const mxl::ColumnSumTail* tail = nullptr)
+{
+    TORCH_CHECK(m > 0 && n > 0 && k > 0 && k <= (1LL << 24), "MX_ERR_SHAPE: product ", m, " x ", n, " x ", k);
+    mxl::GemmParams p{};
+    p.a_codes = a; p.a_scales = as; p.b_codes = b; p.b_scales = bs;
+    p.m = m; p.n = n; p.k = k;
+    p.c = out.data_ptr(); p.c_bf16 = is_bf16(out); p.ldc = ldc;
+    p.bias = bias;
+    p.split_k = mxl::gemm_split_k(m, n, k);
+    Tensor own;
+    if (p.split_k > 1) {
+        const int64_t need = (int64_t)p.split_k * m * n * 4;
+        if (workspace && workspace->defined() && (int64_t)workspace->nbytes() >= need) {
+            p.workspace = workspace->data_ptr();
+        } else {
+            own = bytes_like(out, need);                    // returned to the allocator in stream order
+            p.workspace = own.data_ptr();
+        }
+    }
+    check_hip(mxl::launch_gemm(p, st, tail), "product");
+}
+
+mxl::QuantRowsParams rows_job(const Tensor& src, int64_t rows, int64_t cols, uint8_t* codes, uint8_t* scales, bool floor_mode)
+{
+    mxl::QuantRowsParams q{};
+    q.src = src.data_ptr(); q.bf16 = is_bf16(src);
+    q.rows = rows; q.cols = cols; q.ld = cols;
+    q.codes = codes; q.scales = scales;
+    q.floor_mode = floor_mode;
+    return q;
+}
+
+struct Layer {
+    double beta;
+    int update_ema;          // 0, 1, 2 as in mx_ema_weight_quant; used with a w_ema
+    bool tetra, floor_mode;
+};
+
+void ema_rows(const Tensor& w, const Tensor& w_ema, const Layer& o, int64_t C, int64_t D, uint8_t* codes, uint8_t* scales, hipStream_t st)
+{
+    TORCH_CHECK(w_ema.scalar_type() == at::kFloat && w_ema.is_contiguous() && w_ema.sizes() == w.sizes(),
+                "w_ema must be float32 with the shape and strides of w");
+    TORCH_CHECK(o.beta >= 0.0 && (float)o.beta < 1.0f, "MX_ERR_MODE: beta");
+    check_hip(mxl::launch_ema_quantize(rows_job(w, C, D, codes, scales, o.floor_mode), w_ema.data_ptr<float>(), (float)o.beta, o.update_ema, st),
+              "mx_ema_weight_quant");
+}
+
+// FP32 bias: the tensor itself, or a place in `base` that a quantizer launch widens it into.
+const float* bias_source(const OptTensor& bias, Tensor& keep, uint8_t* place, mxl::WidenJob& widen)
+{
+    if (!bias) return nullptr;
+    keep = dense_source(*bias);
+    if (!is_bf16(keep)) return keep.data_ptr<float>();
+    widen.src = static_cast<const uint16_t*>(keep.data_ptr());
+    widen.dst = reinterpret_cast<float*>(place);
+    widen.count = (uint32_t)keep.numel();
+    return widen.dst;
+}
+
+std::vector<int64_t> with_last(at::IntArrayRef sizes, int64_t last)
+{
+    std::vector<int64_t> s(sizes.begin(), sizes.end());
+    s.back() = last;
+    return s;
+}
+
+// Token rows of the packed operands: whole 32-row groups, and from 4096 rows on whole K steps (128) of the dW product,
+// so that it runs on the main kernel.  Rows past N are zero: they change no group maximum and add nothing to dW.
+int64_t padded_rows(int64_t N) { return round_up(N, N >= 4096 ? 128 : 32); }
+
+// Forward pass.  saved: null where no gradient will be asked for -- only the row codes are made then -- or
+// receives the packed transposed operands [xtq | xts | wtq | wts] of the backward pass.
+Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bias, const OptTensor& w_ema, const Layer& o, const Seed& seed,
+                    Tensor* saved)
+{
+    const Tensor x = dense_source(x_in), w = dense_source(w_in);
+    const int64_t D = w.size(1), C = w.size(0), N = x.numel() / D;
+    check_sizes(N, D);
+    check_sizes(C, D);
+    const int64_t Np = saved ? padded_rows(N) : N;
+    hipStream_t st = c10::hip::getCurrentHIPStream(x.get_device()).stream();
+
+    Carver t;
+    const int64_t o_xq = t.codes(Np, D), o_xs = t.scales(Np, D), o_wq = t.codes(C, D), o_ws = t.scales(C, D), o_b = t.take(C * 4);
+    Tensor row = bytes_like(x, t.used), keep;
+    uint8_t* r = row.data_ptr<uint8_t>();
+    mxl::WidenJob widen;
+    const float* b32 = bias_source(bias, keep, r + o_b, widen);
+
+    if (!saved) {
+        mxl::QuantRowsParams q[2] = {rows_job(x, N, D, r + o_xq, r + o_xs, o.floor_mode), rows_job(w, C, D, r + o_wq, r + o_ws, o.floor_mode)};
+        check_hip(mxl::launch_quantize_rows_batch(q, w_ema ? 1 : 2, st, &widen), "mx_quantize");
+        if (w_ema) ema_rows(w, *w_ema, o, C, D, r + o_wq, r + o_ws, st);
+    } else {
+        Carver v;
+        const int64_t o_xtq = v.codes(D, Np), o_xts = v.scales(D, Np), o_wtq = v.codes(D, C), o_wts = v.scales(D, C);
+        *saved = bytes_like(x, v.used);
+        uint8_t* s = saved->data_ptr<uint8_t>();
+        mxl::QuantTileParams q[2] = {};
+        auto job = [&](mxl::QuantTileParams& j, const Tensor& src, int64_t rows, int64_t src_rows, uint32_t tid_t, uint32_t tid_row) {
+            j.src = src.data_ptr(); j.bf16 = is_bf16(src);
+            j.rows = rows; j.src_rows = src_rows; j.cols = D; j.ld = D;
+            j.sr_t = o.tetra; j.tensor_id_t = tid_t; j.pre_quant = o.tetra; j.tensor_id_row = tid_row;
+            j.floor_mode = o.floor_mode; j.seed = seed.value; j.seed_dev = seed.dev;
+        };
+        job(q[0], x, Np, N, Q6, Q1);
+        q[0].codes_t = s + o_xtq; q[0].scales_t = s + o_xts; q[0].codes_row = r + o_xq; q[0].scales_row = r + o_xs;
+        job(q[1], w, C, C, Q4, Q2);
+        q[1].codes_t = s + o_wtq; q[1].scales_t = s + o_wts; q[1].codes_row = r + o_wq; q[1].scales_row = r + o_ws;
+        check_hip(mxl::launch_quantize_tile_batch(q, w_ema ? 1 : 2, st, &widen), "mx_quantize_transposed");
+        if (w_ema) {
+            ema_rows(w, *w_ema, o, C, D, r + o_wq, r + o_ws, st);
+            q[1].codes_row = q[1].scales_row = nullptr;
+            if (o.tetra) {                                   // double quantization of the codes the forward product uses
+                q[1].src = nullptr; q[1].bf16 = false;
+                q[1].row_codes_in = r + o_wq; q[1].row_scales_in = r + o_ws;
+            }
+            check_hip(mxl::launch_quantize_tile_batch(q + 1, 1, st), "mx_quantize_transposed");
+        }
+    }
+    Tensor y = at::empty(with_last(x_in.sizes(), C), x.options());
+    product(r + o_xq, r + o_xs, r + o_wq, r + o_ws, N, C, D, y, C, b32, st);
+    return y;
+}
+
+struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
+    static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema,
+                          int64_t update_ema, double beta, bool tetra, bool floor_mode, int64_t seed, const OptTensor& seed_dev)
+    {
+        at::AutoDispatchBelowADInplaceOrView guard;
+        Tensor saved;
+        Tensor y = forward_pass(x, w, bias, w_ema, Layer{beta, (int)update_ema, tetra, floor_mode}, seed_of(seed, seed_dev), &saved);
+        torch::autograd::variable_list keep{saved};
+        if (seed_dev) keep.push_back(*seed_dev);
+        ctx->save_for_backward(keep);
+        ctx->saved_data["shape"] = x.sizes().vec();
+        ctx->saved_data["meta"] = std::vector<int64_t>{w.size(0), w.size(1), (int64_t)tetra, (int64_t)floor_mode, seed,
+                                                       (int64_t)w.scalar_type(), bias ? (int64_t)bias->scalar_type() : -1};
+        return y;
+    }
+
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads)
+    {
+        at::AutoDispatchBelowADInplaceOrView guard;
+        const auto keep = ctx->get_saved_variables();
+        const auto shape = ctx->saved_data["shape"].toIntVector(), meta = ctx->saved_data["meta"].toIntVector();
+        const int64_t C = meta[0], D = meta[1], seed_value = meta[4];
+        const bool tetra = meta[2] != 0, floor_mode = meta[3] != 0, has_bias = meta[6] >= 0;
+        const bool want_dx = ctx->needs_input_grad(0), want_dw = ctx->needs_input_grad(1), want_db = has_bias && ctx->needs_input_grad(2);
+        const Seed seed = seed_of(seed_value, keep.size() > 1 ? OptTensor(keep[1]) : OptTensor());
+
+        const Tensor dy = dense_source(grads[0]);
+        c10::hip::HIPGuard device((c10::DeviceIndex)dy.get_device());
+        const int64_t N = dy.numel() / C, Np = padded_rows(N);
+        check_sizes(Np, C);
+        hipStream_t st = c10::hip::getCurrentHIPStream(dy.get_device()).stream();
+        Carver v;
+        const int64_t o_xtq = v.codes(D, Np), o_xts = v.scales(D, Np), o_wtq = v.codes(D, C), o_wts = v.scales(D, C);
+        const uint8_t* s = keep[0].data_ptr<uint8_t>();
+
+        Carver t;
+        const int64_t o_q = t.codes(Np, C), o_s = t.scales(Np, C), o_tq = t.codes(C, Np), o_ts = t.scales(C, Np);
+        const int64_t o_cs = t.take(want_db ? (int64_t)mxl::column_sum_workspace_bytes(Np, C) : 0);
+        Tensor packed = bytes_like(dy, t.used);
+        uint8_t* p = packed.data_ptr<uint8_t>();
+
+        Tensor dx, dw, db;
+        mxl::ColumnSumTail tail{};
+        if (want_dw || want_db) {
+            mxl::QuantTileParams q{};
+            q.src = dy.data_ptr(); q.bf16 = is_bf16(dy);
+            q.rows = Np; q.src_rows = N; q.cols = C; q.ld = C;
+            q.codes_t = p + o_tq; q.scales_t = p + o_ts; q.sr_t = tetra; q.tensor_id_t = Q5;
+            q.codes_row = want_dx ? p + o_q : nullptr; q.scales_row = want_dx ? p + o_s : nullptr;
+            q.sr_row = tetra; q.tensor_id_row = Q3;
+            q.floor_mode = floor_mode; q.seed = seed.value; q.seed_dev = seed.dev;
+            if (want_db) {
+                db = at::empty({C}, dy.options().dtype((at::ScalarType)meta[6]));
+                q.col_sums = db.data_ptr(); q.col_sums_bf16 = is_bf16(db);
+                q.col_sum_workspace = reinterpret_cast<float*>(p + o_cs);
+                tail = mxl::column_sum_tail(q);
+            }
+            check_hip(mxl::launch_quantize_tile_batch(&q, 1, st, nullptr, false), "mx_quantize_transposed");
+        } else if (want_dx && !seed.dev) {
+            mxl::QuantRowsParams q = rows_job(dy, N, C, p + o_q, p + o_s, floor_mode);
+            q.sr = tetra; q.seed = seed.value; q.tensor_id = Q3;
+            check_hip(mxl::launch_quantize_rows(q, st), "mx_quantize");
+        } else if (want_dx) {                                // the row quantizer takes its seed by value only
+            mxl::QuantTileParams q{};
+            q.src = dy.data_ptr(); q.bf16 = is_bf16(dy);
+            q.rows = Np; q.src_rows = N; q.cols = C; q.ld = C;
+            q.codes_t = p + o_tq; q.scales_t = p + o_ts; q.sr_t = tetra; q.tensor_id_t = Q5;
+            q.codes_row = p + o_q; q.scales_row = p + o_s; q.sr_row = tetra; q.tensor_id_row = Q3;
+            q.floor_mode = floor_mode; q.seed_dev = seed.dev;
+            check_hip(mxl::launch_quantize_tile_batch(&q, 1, st), "mx_quantize_transposed");
+        }
+        if (want_dx) {
+            dx = at::empty(shape, dy.options());
+            product(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, st);
+        }
+        if (want_dw) {
+            dw = at::empty({C, D}, dy.options().dtype((at::ScalarType)meta[5]));
+            product(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, st, nullptr, want_db ? &tail : nullptr);
+        } else if (want_db) {
+            check_hip(mxl::launch_column_sum_finish(tail, st), "column sums");
+        }
+        return {dx, dw, db, Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
+    }
+};
+
+Tensor linear(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, bool tetra,
+              bool floor_mode, uint64_t seed, const OptTensor& seed_dev)
+{
+    TORCH_CHECK(x.is_cuda() && w.is_cuda() && x.get_device() == w.get_device(), "MxLinear runs on the GPU: x and weight must be on one");
+    TORCH_CHECK(w.dim() == 2 && x.dim() >= 1 && x.size(-1) == w.size(1), "input of ", w.size(1), " features expected, got ", x.sizes());
+    TORCH_CHECK(!bias || bias->numel() == w.size(0), "bias must have ", w.size(0), " values");
+    c10::hip::HIPGuard device((c10::DeviceIndex)x.get_device());
+    const bool grad = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias && bias->requires_grad()));
+    if (!grad) {
+        at::AutoDispatchBelowADInplaceOrView guard;
+        return forward_pass(x, w, bias, w_ema, Layer{beta, (int)update_ema, tetra, floor_mode}, Seed{}, nullptr);
+    }
+    return MxLinearFn::apply(x, w, bias, w_ema, update_ema, beta, tetra, floor_mode, (int64_t)seed, seed_dev);
+}
+
+// ---- MxLinearStep: the same passes on the caller's buffers ----
+
+uint8_t* u8(const Tensor& t) { return t.data_ptr<uint8_t>(); }
+
+void check_source(const Tensor& t, int64_t rows, int64_t cols, const char* name)
+{
+    TORCH_CHECK_VALUE(t.is_cuda() && t.dim() == 2 && t.size(0) == rows && t.size(1) == cols && t.stride(1) == 1 && t.stride(0) >= cols, name,
+                      " must be a [", rows, ", ", cols, "] matrix with unit column stride on the GPU");
+    TORCH_CHECK((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) == 0 && t.stride(0) % (is_bf16(t) ? 8 : 4) == 0,
+                "mx_quantize_transposed failed: MX_ERR_ALIGN (-5)");
+}
+
+mxl::QuantTileParams tile_job(const Tensor& src, int64_t rows, int64_t cols, const std::vector<Tensor>& out, bool sr_t, uint32_t tid_t,
+                              bool pre, bool sr_row, uint32_t tid_row, bool floor_mode, const Seed& seed)
+{
+    mxl::QuantTileParams j{};
+    j.src = src.data_ptr(); j.bf16 = is_bf16(src);
+    j.rows = rows; j.cols = cols; j.ld = src.stride(0);
+    j.codes_row = u8(out[0]); j.scales_row = u8(out[1]); j.codes_t = u8(out[2]); j.scales_t = u8(out[3]);
+    j.sr_t = sr_t; j.tensor_id_t = tid_t; j.pre_quant = pre; j.sr_row = sr_row; j.tensor_id_row = tid_row;
+    j.floor_mode = floor_mode; j.seed = seed.value; j.seed_dev = seed.dev;
+    return j;
+}
+
+// xb, wb: (row codes, row scales, transposed codes, transposed scales) of X and W.
+void step_forward(const Tensor& X, const Tensor& W, int64_t N, int64_t D, int64_t C, uint64_t seed_value, const OptTensor& seed_dev,
+                  const std::vector<Tensor>& xb, const std::vector<Tensor>& wb, const Tensor& y, const Tensor& workspace, bool floor_mode)
+{
+    check_source(X, N, D, "X");
+    check_source(W, C, D, "W");
+    const Seed seed = seed_of((int64_t)seed_value, seed_dev);
+    hipStream_t st = c10::hip::getCurrentHIPStream().stream();
+    const mxl::QuantTileParams q[2] = {tile_job(X, N, D, xb, true, Q6, true, false, Q1, floor_mode, seed),
+                                       tile_job(W, C, D, wb, true, Q4, true, false, Q2, floor_mode, seed)};
+    check_hip(mxl::launch_quantize_tile_batch(q, 2, st), "mx_quantize_transposed_batch");
+    product(u8(xb[0]), u8(xb[1]), u8(wb[0]), u8(wb[1]), N, C, D, y, y.stride(0), nullptr, st, &workspace);
+}
+
+void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t seed_value, const OptTensor& seed_dev, const std::vector<Tensor>& dyb,
+                   const std::vector<Tensor>& wt, const std::vector<Tensor>& xt, const Tensor& dx, const Tensor& dw, const Tensor& workspace,
+                   bool floor_mode)
+{
+    check_source(dY, N, C, "dY");
+    hipStream_t st = c10::hip::getCurrentHIPStream().stream();
+    const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
+    check_hip(mxl::launch_quantize_tile_batch(&q, 1, st), "mx_quantize_transposed");
+    product(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, st, &workspace);
+    product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, &workspace);
+}
+
+}  // namespace
+
+PYBIND11_MODULE(_mx_torch, m)
+{
+    m.def("linear", &linear, py::call_guard<py::gil_scoped_release>());
+    m.def("step_forward", &step_forward, py::call_guard<py::gil_scoped_release>());
+    m.def("step_backward", &step_backward, py::call_guard<py::gil_scoped_release>());
+}

@@ -64,14 +64,20 @@ class MxLinearStep:
             self.quantize_weight(W, seed)
 
     def forward(self, X, W, seed):
+        if not self.qema:                                  # one native call: Q1/Q6 and Q2/Q4 in one launch, then the product
+            value, dev = B.seed_args(seed)
+            B.host().step_forward(X, W, self.N, self.D, self.C, value, dev, (self.xq, self.xs, self.xtq, self.xts),
+                                  (self.wq, self.ws, self.wtq, self.wts), self.y, self.workspace,
+                                  self.scale_mode == B.SCALE_FLOOR)
+            return self.y
         self.quantize_inputs(X, W, seed)
         return B.mx_linear_fwd(self.xq, self.xs, self.wq, self.ws, out=self.y, workspace=self.workspace)
 
     def backward(self, dY, seed):
-        B.mx_quantize_transposed(dY, B.ROUND_SR, Q5, 0, True, B.ROUND_SR, Q3, scale_mode=self.scale_mode,
-                                 seed=seed, out=(self.dytq, self.dyts, self.dyq, self.dys))
-        B.mx_linear_bwd_dx(self.dyq, self.dys, self.wtq, self.wts, out=self.dx, workspace=self.workspace)
-        B.mx_linear_bwd_dw(self.dytq, self.dyts, self.xtq, self.xts, out=self.dw, workspace=self.workspace)
+        value, dev = B.seed_args(seed)
+        B.host().step_backward(dY, self.N, self.D, self.C, value, dev, (self.dyq, self.dys, self.dytq, self.dyts),
+                               (self.wtq, self.wts), (self.xtq, self.xts), self.dx, self.dw, self.workspace,
+                               self.scale_mode == B.SCALE_FLOOR)
         return self.dx, self.dw
 
     def step_two_streams(self, X, W, dY, seed, side, dw_workspace=None):

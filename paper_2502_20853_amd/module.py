@@ -1,12 +1,13 @@
 """torch.autograd / nn.Module front end of the MXFP4 linear layer: the forward and backward of Eqs. 3-5
-(Sec. 3.3) as calls of the C ABI.  Plumbing only -- every quantizer and every product runs in the HIP
-library; what is saved for the backward pass is the packed 4-bit operands, not the activations."""
+(Sec. 3.3).  Plumbing only -- the pass itself is one native call (csrc/mx_torch.cpp), every quantizer and
+every product in it a kernel of the HIP library; what is saved for the backward pass is the packed 4-bit
+operands, not the activations.  Where no gradient will be asked for (torch.no_grad(), or nothing requires
+one) only the row codes are made, which is all the forward product reads."""
 import itertools
 
 import torch
 
 from . import binding as B
-from .layer import Q1, Q2, Q3, Q4, Q5, Q6
 
 TETRAJET, MICROSCALING = "tetrajet", "microscaling"
 
@@ -15,88 +16,11 @@ TETRAJET, MICROSCALING = "tetrajet", "microscaling"
 _layer_ids = itertools.count()
 
 
-def _pad_rows(t, rows):
-    """t[N, K] with zero rows appended up to `rows` (a 32x1 group along the tokens must be whole; zero
-    rows change no group maximum and add nothing to dW)."""
-    if t.shape[0] == rows:
-        return t
-    out = t.new_zeros((rows, t.shape[1]))
-    out[: t.shape[0]] = t
-    return out
-
-
-class _MxLinearFn(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, x2d, weight, bias, mod, seed):
-        N, D = x2d.shape
-        C = weight.shape[0]
-        Np = (N + 31) // 32 * 32
-        x2d = _pad_rows(x2d.contiguous(), Np)
-        tetra = mod.flow == TETRAJET
-        rnd_t = B.ROUND_SR if tetra else B.ROUND_RTN           # Eqs. 4-5 vs Eqs. 6-7
-        pre = 1 if tetra else 0
-        if not mod.qema and x2d.dtype == weight.dtype:
-            # activation and weight in one launch
-            u8 = lambda *shape: torch.empty(shape, dtype=torch.uint8, device=x2d.device)
-            xtq, xts, xq, xs = u8(D, Np // 2), u8(D, Np // 32), u8(Np, D // 2), u8(Np, D // 32)
-            wtq, wts, wq, ws = u8(D, C // 2), u8(D, C // 32), u8(C, D // 2), u8(C, D // 32)
-            B.mx_quantize_transposed_batch(
-                [{"src": x2d, "out": (xtq, xts, xq, xs), "tensor_id_t": Q6, "tensor_id_row": Q1, "pre_quant": pre, "seed": seed},
-                 {"src": weight.detach(), "out": (wtq, wts, wq, ws), "tensor_id_t": Q4, "tensor_id_row": Q2, "pre_quant": pre,
-                  "seed": seed}], rnd_t, B.ROUND_RTN, mod.scale_mode)
-        else:
-            xtq, xts, xq, xs = B.mx_quantize_transposed(x2d, rnd_t, Q6, pre, True, B.ROUND_RTN, Q1,
-                                                        scale_mode=mod.scale_mode, seed=seed)
-            wq, ws, wtq, wts = mod._quantize_weight(weight, rnd_t, pre, seed)
-        ws_fwd = mod._workspace(B.GEMM_FWD, Np, C, D)
-        if bias is None:
-            y = B.mx_linear_fwd(xq, xs, wq, ws, out_dtype=x2d.dtype, workspace=ws_fwd)
-        else:                                              # added in the product's output stage
-            y = B.mx_linear_fwd_bias(xq, xs, wq, ws, bias.detach().float().contiguous(), out_dtype=x2d.dtype,
-                                     workspace=ws_fwd)
-        ctx.save_for_backward(xtq, xts, wtq, wts)
-        ctx.bias_dtype = None if bias is None else bias.dtype
-        ctx.mod, ctx.seed, ctx.N, ctx.x_dtype, ctx.w_dtype = mod, seed, N, x2d.dtype, weight.dtype
-        return y[:N]
-
-    @staticmethod
-    def backward(ctx, dy):
-        xtq, xts, wtq, wts = ctx.saved_tensors
-        mod, N = ctx.mod, ctx.N
-        D, C, Np = xtq.shape[0], wtq.shape[1] * 2, xtq.shape[1] * 2
-        dy = _pad_rows(dy.contiguous(), Np)
-        rnd = B.ROUND_SR if mod.flow == TETRAJET else B.ROUND_RTN
-        dbias = None
-        if ctx.bias_dtype is not None and ctx.needs_input_grad[2]:
-            # the bias gradient is the column sum of dY: taken by the quantizer from the values it loads
-            # (the zero rows of the padding add nothing)
-            u8 = lambda *shape: torch.empty(shape, dtype=torch.uint8, device=dy.device)
-            dytq, dyts, dyq, dys = u8(C, Np // 2), u8(C, Np // 32), u8(Np, C // 2), u8(Np, C // 32)
-            dbias = torch.empty(C, dtype=torch.float32, device=dy.device)
-            B.mx_quantize_transposed_batch(
-                [{"src": dy, "out": (dytq, dyts, dyq, dys), "tensor_id_t": Q5, "tensor_id_row": Q3, "pre_quant": 0,
-                  "seed": ctx.seed, "col_sums": dbias}], rnd, rnd, mod.scale_mode)
-            dbias = dbias.to(ctx.bias_dtype)
-        else:
-            dytq, dyts, dyq, dys = B.mx_quantize_transposed(dy, rnd, Q5, 0, True, rnd, Q3,
-                                                            scale_mode=mod.scale_mode, seed=ctx.seed)
-        dx = dw = None
-        if ctx.needs_input_grad[0]:
-            dx = B.mx_linear_bwd_dx(dyq, dys, wtq, wts, out_dtype=ctx.x_dtype,
-                                    workspace=mod._workspace(B.GEMM_BWD_DX, Np, C, D))[:N]
-        if ctx.needs_input_grad[1]:
-            dw = B.mx_linear_bwd_dw(dytq, dyts, xtq, xts, out_dtype=torch.float32,
-                                    workspace=mod._workspace(B.GEMM_BWD_DW, Np, C, D))
-            if ctx.w_dtype != torch.float32:
-                dw = dw.to(ctx.w_dtype)
-        return dx, dw, dbias, None, None
-
-
 class MxLinear(torch.nn.Module):
     """y = x W^T (+ bias) with the three products in MXFP4 (Eqs. 3-5).
 
     in_features and out_features must be multiples of 32; the token count (product of the leading
-    dimensions of x) is padded with zero rows to a multiple of 32.  x and weight are float32 or
+    dimensions of x) is padded with zero rows to whole groups of 32 inside the quantizer.  x and weight are float32 or
     bfloat16.  flow="tetrajet": deterministic forward quantizers, stochastic backward quantizers,
     double quantization (Sec. 3.3); flow="microscaling": Eqs. 6-7 (all deterministic, the backward
     operands quantized from the full-precision tensors).  qema=True takes the forward weight codes
@@ -136,47 +60,22 @@ class MxLinear(torch.nn.Module):
         self.register_buffer("seed_state", torch.tensor([start - (1 << 64) if start >> 63 else start], dtype=torch.int64,
                                                         device=device) if device_seed else None)
         self._ema_started = False
-        self._ws = None
 
-    def _workspace(self, which, N, C, D):
-        need = B.mx_linear_workspace_bytes(which, N, C, D)
-        if need == 0:
-            return None
-        if self._ws is None or self._ws.numel() < need:
-            self._ws = torch.empty(need, dtype=torch.uint8, device=self.weight.device)
-        return self._ws
-
-    def _quantize_weight(self, weight, rnd_t, pre, seed):
-        """Row codes (Q2, or Q-EMA) and transposed codes (Q4) of the weight."""
-        if self.qema:
-            update = 0
-            if self.training:
-                update = 1 if self._ema_started else 2
-                self._ema_started = True
-            elif not self._ema_started:
-                update, self._ema_started = 2, True
-            wq, ws = B.mx_ema_weight_quant(weight.detach(), self.w_ema, self.beta, update, self.scale_mode)
-            if pre:
-                wtq, wts, _, _ = B.mx_quantize_transposed(None, rnd_t, Q4, 1, False, row_in=(wq, ws),
-                                                          scale_mode=self.scale_mode, seed=seed,
-                                                          shape=tuple(weight.shape))
-            else:
-                wtq, wts, _, _ = B.mx_quantize_transposed(weight.detach(), rnd_t, Q4, 0, False,
-                                                          scale_mode=self.scale_mode, seed=seed)
-            return wq, ws, wtq, wts
-        wtq, wts, wq, ws = B.mx_quantize_transposed(weight.detach(), rnd_t, Q4, pre, True, B.ROUND_RTN, Q2,
-                                                    scale_mode=self.scale_mode, seed=seed)
-        return wq, ws, wtq, wts
+    def _ema_update(self):
+        """How this forward call treats the moving average: 2 starts it from the weight, 1 advances it, 0 leaves it."""
+        if not self._ema_started:
+            self._ema_started = True
+            return 2
+        return 1 if self.training else 0
 
     def forward(self, x):
-        lead = x.shape[:-1]
-        x2d = x.reshape(-1, self.in_features)
+        seed_dev = None
         if self.seed_state is not None:
             # the word the kernels read: this call's own copy, which its backward pass reads too, so
             # that later forward calls (which advance seed_state) do not change it
-            seed = self.seed_state.add_(1).clone()
+            seed, seed_dev = 0, self.seed_state.add_(1).clone()
         else:
             seed = (self.key_high << 32) + (self.calls & 0xFFFFFFFF)
         self.calls += 1
-        y = _MxLinearFn.apply(x2d, self.weight, self.bias, self, seed)
-        return y.reshape(*lead, self.out_features)
+        return B.host().linear(x, self.weight, self.bias, self.w_ema, self._ema_update() if self.qema else 0, self.beta,
+                               self.flow == TETRAJET, self.scale_mode == B.SCALE_FLOOR, seed, seed_dev)

@@ -200,3 +200,56 @@ def test_device_seed_backward_uses_the_key_of_its_own_forward(mx):
         grads.append((x1.grad.clone(), x2.grad.clone()))
     assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
     assert not torch.equal(grads[0][0], grads[0][1])
+
+
+@pytest.mark.parametrize("tokens,xt,wt,flow,qema", [
+    (1, "bf16", "f32", "tetrajet", False), (33, "f32", "f32", "tetrajet", False), (200, "bf16", "bf16", "microscaling", False),
+    (255, "bf16", "f32", "microscaling", True), (300, "bf16", "bf16", "tetrajet", True), (4095, "bf16", "f32", "tetrajet", False),
+    (4097, "bf16", "f32", "tetrajet", False), (4225, "f32", "f32", "microscaling", False)])
+def test_module_equals_the_calls_on_padded_tensors(mx, tokens, xt, wt, flow, qema):
+    """Ragged token counts, mixed source types, column sums and every subset of wanted gradients: bit for bit what the
+    separate calls give on explicitly padded tensors (which the parity tests hold against the oracle)."""
+    D, C, tdt = 160, 96, {"f32": torch.float32, "bf16": torch.bfloat16}
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tokens)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, dy = rnd(tokens, D).to(tdt[xt]), (rnd(tokens, C) * 1e-3).to(tdt[xt])
+    lin = mx.MxLinear(D, C, bias=True, dtype=tdt[wt], flow=flow, qema=qema, seed=7, layer_id=3)
+    with torch.no_grad():
+        lin.bias.copy_(rnd(C))
+    seed, tetra, Np = ((7 << 16) | 3) << 32, flow == "tetrajet", (tokens + 31) // 32 * 32
+    pad = lambda t: torch.cat([t, t.new_zeros((Np - tokens, t.shape[1]))])
+    rt, pre = (mx.ROUND_SR if tetra else mx.ROUND_RTN), int(tetra)
+    xtq, xts, xq, xs = mx.mx_quantize_transposed(pad(x), rt, 6, pre, True, mx.ROUND_RTN, 1, seed=seed)
+    w = lin.weight.detach()
+    if qema:
+        wq, ws = mx.mx_ema_weight_quant(w, torch.zeros(C, D, device="cuda"), lin.beta, 2)
+        if tetra:
+            wtq, wts, _, _ = mx.mx_quantize_transposed(None, rt, 4, 1, False, row_in=(wq, ws), seed=seed, shape=(C, D))
+        else:
+            wtq, wts, _, _ = mx.mx_quantize_transposed(w, rt, 4, 0, False, seed=seed)
+    else:
+        wtq, wts, wq, ws = mx.mx_quantize_transposed(w, rt, 4, pre, True, mx.ROUND_RTN, 2, seed=seed)
+    y0 = mx.mx_linear_fwd_bias(xq, xs, wq, ws, lin.bias.detach().float(), out_dtype=x.dtype)[:tokens]
+    u8 = lambda *s: torch.empty(s, dtype=torch.uint8, device="cuda")
+    out, db0 = (u8(C, Np // 2), u8(C, Np // 32), u8(Np, C // 2), u8(Np, C // 32)), torch.empty(C, device="cuda")
+    mx.mx_quantize_transposed_batch([{"src": pad(dy), "out": out, "tensor_id_t": 5, "tensor_id_row": 3, "pre_quant": 0, "seed": seed,
+                                      "col_sums": db0}], rt, rt)
+    dx0 = mx.mx_linear_bwd_dx(out[2], out[3], wtq, wts, out_dtype=x.dtype)[:tokens]
+    dw0 = mx.mx_linear_bwd_dw(out[0], out[1], xtq, xts).to(w.dtype)
+    for want in range(1, 8):
+        lin.calls, lin._ema_started = 0, False
+        xg = x.clone().requires_grad_(bool(want & 1))
+        lin.weight.requires_grad_(bool(want & 2))
+        lin.bias.requires_grad_(bool(want & 4))
+        y = lin(xg)
+        asked = [t for t in (xg, lin.weight, lin.bias) if t.requires_grad]
+        grads = iter(torch.autograd.grad(y, asked, dy))
+        assert torch.equal(y, y0), want
+        for t, ref in ((xg, dx0), (lin.weight, dw0), (lin.bias, db0.to(w.dtype))):
+            if t.requires_grad:
+                assert torch.equal(next(grads), ref), want
+    lin.calls, lin._ema_started = 0, False
+    with torch.no_grad():
+        assert torch.equal(lin(x), y0)
+        assert torch.equal(lin(x.reshape(1, tokens, 1, D)).reshape(tokens, C), y0)
