@@ -298,6 +298,153 @@ __device__ __forceinline__ float dequant_e3m0(uint32_t code, uint32_t byte)
     return __uint_as_float(__float_as_uint(mag) | ((code & 8u) << 28));
 }
 
+// ---- FP4 conversion instructions of gfx950 -----------------------------------
+// What the quantizers use of them, each checked exhaustively against the integer forms above (all bf16 values x all
+// scale bytes; all 16 codes x all scale bytes), in every rounding mode: the mode does not enter.
+//   v_cvt_scalef32_pk_fp4_bf16   two bf16 values / 2^s, round to nearest even, saturated at 6  -> one byte
+//   v_cvt_scalef32_pk_fp4_f32    the same from FP32; here only a packer of values that are already on the grid
+//   v_cvt_scalef32_pk_{f32,bf16}_fp4   two codes x 2^s -> two values, exact
+// 2^s is given as the FP32 pattern byte << 23 (byte 0 means 2^-127).  Cost, in cycles of a SIMD per wave instruction
+// with four waves on it: 9, 9 and 4.5 for two elements; a three-operand integer instruction takes 5, a two-operand
+// one 3.  Taking a code apart from the grid sum and packing it took about 15 per element, so both the deterministic
+// rounding of bf16 sources (12.5 against 33 with double quantization) and the packing go through them.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_hw __attribute__((ext_vector_type(2)));
+typedef float f32x2_hw __attribute__((ext_vector_type(2)));
+
+template <typename D, typename S>
+__device__ __forceinline__ D bits_as(S s)
+{
+    static_assert(sizeof(D) == sizeof(S), "same size");
+    return __builtin_bit_cast(D, s);
+}
+
+__device__ __forceinline__ float scale_operand(uint32_t byte) { return __uint_as_float(byte << 23); }
+
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b)
+{
+    return bits_as<uint32_t>(__builtin_elementwise_max(bits_as<u16x2>(a), bits_as<u16x2>(b)));
+}
+
+// round_D sends a tie to the larger value, the conversion to the even code.  A threshold of E2M1 has at most 3
+// significant bits, so of two neighbouring bf16 values at most the one with an even last bit is a threshold: moving
+// every even pattern one unit toward +infinity (positive: last bit set; negative: magnitude less one) takes ties to
+// the right side and moves nothing across a threshold.  +0 becomes the smallest positive value (code 0); -0 stays
+// at the saturation bound of the signed addition and becomes the smallest negative value (code 8).
+__device__ __forceinline__ uint32_t ties_to_larger(uint32_t w)
+{
+    const s16x2 v = bits_as<s16x2>(w);
+    return bits_as<uint32_t>(__builtin_elementwise_add_sat(v, v >> (short)15)) | 0x00010001u;
+}
+
+// byte SEL of `old` <- codes of the two bf16 values in w (low half first), scale as scale_operand()
+template <int SEL>
+__device__ __forceinline__ uint32_t cvt_fp4_bf16(uint32_t old, uint32_t w, float scale)
+{
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(old, bits_as<bf16x2_hw>(w), scale, SEL);
+}
+
+// byte SEL of `old` <- codes of two values on the grid layout, sign << 31 | code << 22
+template <int SEL>
+__device__ __forceinline__ uint32_t pack_grid(uint32_t old, uint32_t g0, uint32_t g1)
+{
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, __uint_as_float(g0), __uint_as_float(g1), __uint_as_float(1u << 23), SEL);
+}
+
+template <int SEL>
+__device__ __forceinline__ f32x2_hw cvt_f32_fp4(uint32_t codes, float scale)
+{
+    return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, scale, SEL);
+}
+
+template <int SEL>
+__device__ __forceinline__ uint32_t cvt_bf16_fp4(uint32_t codes, float scale)
+{
+    return bits_as<uint32_t>(__builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, SEL));
+}
+
+// round_S onto the grid layout.  Rounding mode toward plus infinity.  x: any value; x2: a value with at most two
+// significant bits (a dequantized one), whose low pattern bits are zero, so that one select merges sign and grid.
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t sr_grid_sum(float x, int e, uint32_t rinv)
+{
+    uint32_t mag = __float_as_uint(__builtin_ldexpf(__builtin_fabsf(x), e));
+    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
+    return mag + rinv;
+}
+
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t sr_grid(float x, int e, uint32_t rinv)
+{
+    return __builtin_amdgcn_bitop3_b32(0x80000000u, sr_grid_sum<FLOOR>(x, e, rinv) & 0x7FC00000u, __float_as_uint(x), 0xEC);   // b | (a & c)
+}
+
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t sr_grid_x2(float x2, int e, uint32_t rinv)
+{
+    return __builtin_amdgcn_bitop3_b32(0x7FC00000u, sr_grid_sum<FLOOR>(x2, e, rinv), __float_as_uint(x2), 0xCA);               // a ? b : c
+}
+
+// round_D onto the grid layout (see rtn_code_keep).
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t rtn_grid(float x, int e)
+{
+    uint32_t vb = __float_as_uint(__builtin_ldexpf(x, e));
+    if (FLOOR) {
+        uint32_t mag = vb & 0x7FFFFFFFu;
+        mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
+        vb = mag | (vb & 0x80000000u);
+    }
+    return (vb + 0x200000u + (uint32_t)((int32_t)vb >> 31)) & 0xFFC00000u;
+}
+
+// Scale bytes of two group maxima at once, given as bf16 patterns of |x| in the halves of m (see scale_byte: a bf16
+// mantissa exceeds 1.5 iff adding 0x3F carries).
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t scale_bytes_bf16(uint32_t m)
+{
+    const u16x2 v = bits_as<u16x2>(m);
+    const u16x2 field = (FLOOR ? v : (u16x2)(v + (unsigned short)0x3F)) >> (unsigned short)7;
+    const u16x2 nonzero = __builtin_elementwise_min(v, (u16x2)(unsigned short)1);
+    const u16x2 b = __builtin_elementwise_sub_sat(field, (u16x2)(unsigned short)2);
+    return bits_as<uint32_t>((u16x2)(b + (u16x2)(nonzero * (unsigned short)(0u - 98u) + (unsigned short)98)));
+}
+
+// |x| maximum of 8 bf16 values as a bf16 pattern in both halves, over the 4 lanes of a row group
+__device__ __forceinline__ uint32_t quad_amax_bf16(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
+{
+    const uint32_t k = 0x7FFF7FFFu;
+    uint32_t m = pk_max(pk_max(w0 & k, w1 & k), pk_max(w2 & k, w3 & k));
+    m = pk_max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xB1, 0xF, 0xF, true));      // lane ^ 1
+    m = pk_max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, true));      // lane ^ 2
+    return pk_max(m, __builtin_amdgcn_alignbit(m, m, 16));
+}
+
+// Maxima over the 8 lanes that share lane % 8 (the row groups of a wave tile), of four values at once.  A lane-swap
+// instruction of two different values leaves half of each beside its partner, so each step halves the number of
+// registers instead of repeating the reduction per value (8 instructions for four values; one by one it is 32).
+// Returned: rows of 16 lanes 0..3 hold the maxima of m[0], m[2], m[1], m[3].
+template <typename MAX>
+__device__ __forceinline__ uint32_t reduce_row_groups4(const uint32_t (&m)[4], MAX&& mx)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(m[0], m[1], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(m[2], m[3], false, false);
+    const uint32_t u0 = mx(a[0], a[1]), u1 = mx(b[0], b[1]);
+    const auto c = __builtin_amdgcn_permlane16_swap(u0, u1, false, false);
+    const uint32_t v = mx(c[0], c[1]);
+    return mx(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true));      // row_ror:8 = lane ^ 8
+}
+
+// The way back: every lane gets the four values that reduce_row_groups4 left in the four rows of 16 lanes.
+__device__ __forceinline__ void spread_row_groups4(uint32_t v, uint32_t (&q)[4])
+{
+    const auto w = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
+    q[0] = a[0]; q[1] = a[1]; q[2] = b[0]; q[3] = b[1];
+}
+
 // ---- cross-lane max over aligned groups of 4 lanes (one 32-element group) ---
 __device__ __forceinline__ uint32_t quad_max(uint32_t v)
 {

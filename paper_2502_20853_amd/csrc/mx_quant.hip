@@ -273,12 +273,6 @@ struct TileArgs {
     float* col_sum_partials;   // COLSUM instances: [ceil(rows / 256)][cols] sums of the source over 256-row blocks, or null
 };
 
-__device__ __forceinline__ uint32_t xor_lane_max(uint32_t v, int mask)
-{
-    uint32_t o = (uint32_t)__shfl_xor((int)v, mask, 64);
-    return v > o ? v : o;
-}
-
 // Copies one staged result of a macro tile to memory: `lines` staged lines (rows of row codes, or
 // columns of transposed codes), each `pieces` 16-byte pieces of codes (ST_PITCH apart in LDS,
 // `code_pitch` bytes apart in memory) and `pieces` scale bytes (8 apart in LDS, `scale_pitch` apart
@@ -322,17 +316,38 @@ __device__ __forceinline__ void write_staged(const uint8_t* codes_st, const uint
     }
 }
 
-// Sum of v over the 8 lanes that share lane % 8 (the 8 row groups of a wave tile), in a fixed order,
-// returned in all of them: the partner 8 lanes away inside a row of 16 (DPP rotate), then the rows of
-// 16 and the halves of the wave (lane-swap instructions; a swap of a register with its copy leaves
-// the two partners' values side by side).
-__device__ __forceinline__ float sum_over_row_groups(float v)
+// Sums over the 8 lanes that share lane % 8 (the 8 row groups of a wave tile), of the lane's eight columns at once,
+// in the fixed order ((g0+g1) + (g2+g3)) + ((g4+g5) + (g6+g7)).  Two values meet in one register at each step: lanes
+// whose bit 3 is clear keep the first of a pair, the others the second; then lane-swap instructions pair rows
+// of 16 and halves (18 instructions where a reduction per column takes 56).  Returned: the sum of column
+// column_of_sum(lane) of the lane's eight.
+__device__ __forceinline__ float sum_row_groups8(const float (&v)[8], uint32_t lane)
 {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));   // row_ror:8
-    const auto p16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(p16[0]) + __uint_as_float(p16[1]);
-    const auto p32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(p32[0]) + __uint_as_float(p32[1]);
+    float p[4];
+    const bool second = (lane & 8u) != 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float mine = second ? v[2 * i + 1] : v[2 * i], other = second ? v[2 * i] : v[2 * i + 1];
+        p[i] = mine + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(other), 0x128, 0xF, 0xF, true));   // row_ror:8
+    }
+    float h[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(p[2 * i]), __float_as_uint(p[2 * i + 1]), false, false);
+        h[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(h[0]), __float_as_uint(h[1]), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+__device__ __forceinline__ uint32_t column_of_sum(uint32_t lane) { return ((lane >> 3) & 1u) + ((lane >> 4) & 1u) * 2u + (lane >> 5) * 4u; }
+
+// f(0), f(1) with compile-time arguments (the byte a conversion writes is an immediate)
+template <typename F>
+__device__ __forceinline__ void static_for_pair(F&& f)
+{
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
 }
 
 // Up to TILE_BATCH_MAX tensors per launch (e.g. the activation and the weight of a layer: one launch,
@@ -365,11 +380,6 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
         k0 = __builtin_amdgcn_readfirstlane(a.seed_dev[0]);
         k1 = __builtin_amdgcn_readfirstlane(a.seed_dev[1]);
     }
-    // FP32 sources need the rounding mode of each rule (switched per phase when they differ).
-    // bf16 and packed sources scale exactly wherever a round_D threshold is near (8 significant
-    // bits), so there the mode of round_S, if any, serves the whole kernel.
-    constexpr bool SWITCH_MODES = (SRC == 0) && (ROW_SR != T_SR);
-    if (!SWITCH_MODES) set_round_mode_for<(ROW_SR || T_SR)>();
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int cc = lane & 7, rg = lane >> 3;
     const int wr = wave;                                  // wave position inside the macro tile
@@ -397,154 +407,235 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
     const uint32_t half_rows = a.rows >> 1, grp_rows = a.rows >> 5;
     const uint32_t half_cols = a.cols >> 1, grp_cols = a.cols >> 5;
 
-    // bf16 sources with a deterministic row quantizer: the raw 16 bytes per row of the wave's next tile are
-    // fetched while the current tile is being encoded (16 registers), so that only the first load of a
-    // workgroup is waited for: -8 to -10 % on those passes.  The instances with a stochastic row quantizer
-    // have no registers to spare under the 128 that two workgroups per compute unit allow (3 spilled,
-    // +2-5 %); issuing their fetch later in the tile, where registers are free, hides too little of the
-    // latency to pay for the instructions it adds (measured: no change in the sum of those passes).
-    constexpr bool PREFETCH = (SRC == 1) && !ROW_SR;
-    bf16x8_raw raw[4];
-    auto fetch_raw = [&](int ci) {
+    // Element (row0 + j, c + t) has index index_base + (row0 + j) * cols + c + t: one Philox block of 8 per row.
+    const uint64_t blk0 = (a.index_base + (uint64_t)row0 * a.cols + mcol0 + cc * 8) >> 3;
+    const uint32_t blk_row = a.cols >> 3;
+
+    // A lane's four rows of 8 elements, as loaded: bf16 values stay packed in pairs, packed results stay codes.
+    // The next tile's are fetched while the current one is encoded.
+    using Row = std::conditional_t<SRC == 0, F8, bf16x8_raw>;
+    struct Tile {
+        Row x[SRC == 2 ? 1 : 4];
+        uint32_t pk[SRC == 2 ? 4 : 1], byte[SRC == 2 ? 4 : 1];
+    };
+    auto load_row = [&](Row& r, int j, uint32_t col) {
+        if constexpr (SRC == 0)      r = load8(static_cast<const float*>(a.src) + (int64_t)(row0 + j) * a.ld + col);
+        else if constexpr (SRC == 1) r = load8_raw(static_cast<const uint16_t*>(a.src) + (int64_t)(row0 + j) * a.ld + col);
+    };
+    auto fetch = [&](Tile& d, int ci) {
         const uint32_t col = mcol0 + ci * 64 + cc * 8;
-        const uint16_t* p = static_cast<const uint16_t*>(a.src) + (int64_t)row0 * a.ld + col;
-        if (wave_rows_full && mcol0 + ci * 64 + 64 <= a.cols) {        // uniform: no masking
+        if constexpr (SRC == 2) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) raw[j] = load8_raw(p + (int64_t)j * a.ld);
+            for (int j = 0; j < 4; ++j) {
+                d.pk[j] = 0u; d.byte[j] = 98u;
+                if (col < a.cols) {
+                    d.pk[j] = *reinterpret_cast<const uint32_t*>(a.row_codes_in + (size_t)(row0 + j) * half_cols + (col >> 1));
+                    d.byte[j] = a.row_scales_in[(size_t)(row0 + j) * grp_cols + (col >> 5)];
+                }
+            }
+        } else if (wave_rows_full && mcol0 + ci * 64 + 64 <= a.cols) {       // uniform: no masking
+#pragma unroll
+            for (int j = 0; j < 4; ++j) load_row(d.x[j], j, col);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                raw[j] = bf16x8_raw{0u, 0u, 0u, 0u};
-                if (col < a.cols && row0 + j < a.src_rows) raw[j] = load8_raw(p + (int64_t)j * a.ld);
+                if constexpr (SRC == 0) d.x[j] = zero8();
+                else                    d.x[j] = bf16x8_raw{0u, 0u, 0u, 0u};
+                if (col < a.cols && row0 + j < a.src_rows) load_row(d.x[j], j, col);
             }
         }
     };
-    if (PREFETCH && wave_has_rows) fetch_raw(0);
+    auto element = [](const Row& r, int t) -> float {
+        if constexpr (SRC == 0) return r.v[t];
+        else                    return __uint_as_float((t & 1) ? r[t >> 1] & 0xFFFF0000u : r[t >> 1] << 16);
+    };
+
+    constexpr bool PREFETCH = SRC != 0;                   // an FP32 tile's 32 registers do not fit twice in 128
+    Tile cur, nxt;
+    if (PREFETCH && wave_has_rows) fetch(cur, 0);
     for (int ci = 0; ci < tiles_per_wave && wave_has_rows; ++ci) {
         const uint32_t tcol0 = ci * 64;
         const uint32_t lcol0 = tcol0 + cc * 8;            // first of this lane's 8 columns inside the macro tile
-        const uint32_t c = mcol0 + lcol0;
         if (mcol0 + tcol0 >= a.cols) break;               // uniform over the wave
-        const bool ok = c < a.cols;
-        F8 x[4];
-        // ---- load -----------------------------------------------------------
-        if (SRC == 2) {
+        if (!PREFETCH) fetch(cur, ci);
+        else if (ci + 1 < tiles_per_wave && mcol0 + tcol0 + 64 < a.cols) fetch(nxt, ci + 1);
+        // ---- column sums of the source over this wave's 32 rows -------------
+        if (COLSUM && SRC != 2 && a.col_sum_partials != nullptr) {
+            f32_round_to_nearest_even();
+            float cs[8];
+            Row x[4] = {cur.x[0], cur.x[1], cur.x[2], cur.x[3]};
+            if constexpr (SRC == 1) {
+                // opaque copies: the values unpacked here are not kept (32 registers) for the phases below
+#pragma unroll
+                for (int j = 0; j < 4; ++j) asm("" : "+v"(x[j]));
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                cs[t] = ((element(x[0], t) + element(x[1], t)) + element(x[2], t)) + element(x[3], t);
+            reinterpret_cast<float*>(st + ST_CSUM_OFF)[wr * 128 + lcol0 + column_of_sum(lane)] = sum_row_groups8(cs, lane);
+            __builtin_amdgcn_sched_barrier(0);            // the random numbers of later phases stay out of this one's registers
+        }
+        // ---- 1x32 quantizer: codes of the lane's four rows and their scales ----
+        uint32_t pk[4];
+        float row_scale[4];
+        if constexpr (SRC == 2) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { pk[j] = cur.pk[j]; row_scale[j] = scale_operand(cur.byte[j]); }
+        } else if (want_row || a.pre_quant) {
+            set_round_mode_for<ROW_SR>();
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                x[j] = zero8();
-                if (ok) {
-                    uint32_t r = row0 + j;
-                    uint32_t pk = *reinterpret_cast<const uint32_t*>(a.row_codes_in + (size_t)r * half_cols + (c >> 1));
-                    uint32_t byte = a.row_scales_in[(size_t)r * grp_cols + (c >> 5)];
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) x[j].v[t] = dequant((pk >> (4 * t)) & 15u, byte);
-                }
-            }
-        } else {
-            if (PREFETCH) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = expand8(raw[j]);
-                if (ci + 1 < tiles_per_wave && mcol0 + tcol0 + 64 < a.cols) fetch_raw(ci + 1);
-            } else if (mcol0 + tcol0 + 64 <= a.cols && wave_rows_full) {
-                // whole tile inside the source (uniform): no masking, no zero fill
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    int64_t off = (int64_t)(row0 + j) * a.ld + c;
-                    if (SRC == 1) x[j] = load8(static_cast<const uint16_t*>(a.src) + off);
-                    else          x[j] = load8(static_cast<const float*>(a.src) + off);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    x[j] = zero8();
-                    if (ok && row0 + j < a.src_rows) {
-                        int64_t off = (int64_t)(row0 + j) * a.ld + c;
-                        if (SRC == 1) x[j] = load8(static_cast<const uint16_t*>(a.src) + off);
-                        else          x[j] = load8(static_cast<const float*>(a.src) + off);
-                    }
-                }
-            }
-            // ---- column sums of the source over this wave's 32 rows -------------
-            if (COLSUM && a.col_sum_partials != nullptr) {
-                f32_round_to_nearest_even();
-                float cs[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    cs[t] = sum_over_row_groups(((x[0].v[t] + x[1].v[t]) + x[2].v[t]) + x[3].v[t]);
-                if (rg == 0) {
-                    float* dst = reinterpret_cast<float*>(st + ST_CSUM_OFF) + wr * 128 + lcol0;
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) dst[t] = cs[t];
-                }
-                if (!SWITCH_MODES) set_round_mode_for<(ROW_SR || T_SR)>();
-            }
-            // ---- 1x32 quantizer of the same elements ---------------------------
-            if (want_row || a.pre_quant) {
-                if (SWITCH_MODES) set_round_mode_for<ROW_SR>();
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    uint32_t r = row0 + j;
-                    uint32_t byte = scale_byte(quad_max(amax_bits8(x[j])), FLOOR);
+                const Row& x = cur.x[j];
+                uint32_t byte;
+                if constexpr (SRC == 0) byte = scale_byte(quad_max(amax_bits8(x)), FLOOR);
+                else                    byte = scale_bytes_bf16<FLOOR>(quad_amax_bf16(x[0], x[1], x[2], x[3])) & 0xFFu;
+                row_scale[j] = scale_operand(byte);
+                uint32_t p = 0u;
+                if constexpr (SRC == 1 && !ROW_SR) {
+                    p = cvt_fp4_bf16<0>(p, ties_to_larger(x[0]), row_scale[j]);
+                    p = cvt_fp4_bf16<1>(p, ties_to_larger(x[1]), row_scale[j]);
+                    p = cvt_fp4_bf16<2>(p, ties_to_larger(x[2]), row_scale[j]);
+                    p = cvt_fp4_bf16<3>(p, ties_to_larger(x[3]), row_scale[j]);
+                } else {
                     const int e = grid_exponent(byte);
-                    U8 rnd;
-                    if (ROW_SR) rnd = sr_addends((a.index_base + (uint64_t)r * a.cols + c) >> 3, a.tensor_id_row, k0, k1);
-                    uint32_t pk = 0;
-                    if (a.pre_quant) {
-                        // keep sign in the value: the next quantizer takes |x| and the sign from it
+                    uint32_t g[8];
+                    if constexpr (ROW_SR) {
+                        const U8 rnd = sr_addends(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_row, k0, k1);
 #pragma unroll
-                        for (int t = 0; t < 8; ++t) {
-                            uint32_t gb;
-                            if (ROW_SR) {
-                                uint32_t code = sr_code_keep<FLOOR>(x[j].v[t], e, rnd.w[t], gb);
-                                pk |= code << (4 * t);
-                                float mag = __builtin_ldexpf(__uint_as_float(gb), (int)byte - 1);  // m * 2^s, exact
-                                x[j].v[t] = __builtin_copysignf(mag, x[j].v[t]);
-                            } else {
-                                pk |= rtn_code_keep<FLOOR>(x[j].v[t], e, gb) << (4 * t);           // gb carries the sign
-                                x[j].v[t] = __builtin_ldexpf(__uint_as_float(gb), (int)byte - 1);  // +-m * 2^s, exact
-                            }
-                        }
+                        for (int t = 0; t < 8; ++t) g[t] = sr_grid<FLOOR>(element(x, t), e, rnd.w[t]);
                     } else {
-                        pk = encode8<ROW_SR, FLOOR>(x[j], e, rnd);
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) g[t] = rtn_grid<FLOOR>(element(x, t), e);
                     }
-                    if (want_row) {
-                        *reinterpret_cast<uint32_t*>(st + ST_ROW_OFF + (lrow0 + j) * ST_PITCH + (lcol0 >> 1)) = pk;
-                        if ((cc & 3) == 0) st[ST_SROW_OFF + (lrow0 + j) * 8 + (lcol0 >> 5)] = (uint8_t)byte;
-                    }
+                    p = pack_grid<0>(p, g[0], g[1]);
+                    p = pack_grid<1>(p, g[2], g[3]);
+                    p = pack_grid<2>(p, g[4], g[5]);
+                    p = pack_grid<3>(p, g[6], g[7]);
+                }
+                pk[j] = p;
+                if (want_row) {
+                    *reinterpret_cast<uint32_t*>(st + ST_ROW_OFF + (lrow0 + j) * ST_PITCH + (lcol0 >> 1)) = p;
+                    if ((cc & 3) == 0) st[ST_SROW_OFF + (lrow0 + j) * 8 + (lcol0 >> 5)] = (uint8_t)byte;
                 }
             }
         }
-        // ---- 32x1 quantizer: group = this lane's 4 rows x the 8 lanes sharing cc --
-        uint32_t sb[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            uint32_t m = absmax3_bits(x[0].v[t], x[1].v[t], 0u);
-            m = absmax3_bits(x[2].v[t], x[3].v[t], m);
-            m = xor_lane_max(m, 8);
-            m = xor_lane_max(m, 16);
-            m = xor_lane_max(m, 32);
-            sb[t] = scale_byte(m, FLOOR);
-        }
-        if (SWITCH_MODES) set_round_mode_for<T_SR>();
+        // ---- 32x1 quantizer: group = this lane's 4 rows x the 8 lanes sharing cc ----
+        // Scale bytes of the lane's eight columns, two per register: byte_of(t).
+        uint32_t sb[4];
+        auto store_column_bytes = [&](uint32_t two, uint32_t first, uint32_t step) {
+            // rows of 16 lanes 0..3 hold the columns first + step * {0, 2, 1, 3}: the lanes of each row's first half write
+            if ((lane & 8) == 0) {
+                st[ST_SCOL_OFF + (lcol0 + first) * 8 + wr] = (uint8_t)two;
+                st[ST_SCOL_OFF + (lcol0 + first + step) * 8 + wr] = (uint8_t)(two >> 16);
+            }
+        };
+        const uint32_t row16 = (uint32_t)lane >> 4, place = ((row16 & 1u) << 1) | (row16 >> 1);
+        auto column_bytes_bf16 = [&](const uint32_t (&m)[4]) {
+            const uint32_t two = scale_bytes_bf16<FLOOR>(reduce_row_groups4(m, [](uint32_t p, uint32_t q) { return pk_max(p, q); }));
+            store_column_bytes(two, 2u * place, 1u);
+            spread_row_groups4(two, sb);
+        };
         uint32_t colpk[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) colpk[t] = 0;
+        for (int t = 0; t < 8; ++t) colpk[t] = 0u;
+        auto addends = [&](int j) { return sr_addends(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_t, k0, k1); };
+        if (SRC == 2 || a.pre_quant) {
+            uint32_t m[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            U8 rnd;
-            if (T_SR) rnd = sr_addends((a.index_base + (uint64_t)(row0 + j) * a.cols + c) >> 3, a.tensor_id_t, k0, k1);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                int e = grid_exponent(sb[t]);
-                uint32_t code = T_SR ? sr_code<FLOOR>(x[j].v[t], e, rnd.w[t]) : rtn_code<FLOOR>(x[j].v[t], e);
-                colpk[t] |= code << (4 * j);
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t mags = pk[j] & 0x77777777u;
+                m[0] = pk_max(m[0], cvt_bf16_fp4<0>(mags, row_scale[j]));
+                m[1] = pk_max(m[1], cvt_bf16_fp4<1>(mags, row_scale[j]));
+                m[2] = pk_max(m[2], cvt_bf16_fp4<2>(mags, row_scale[j]));
+                m[3] = pk_max(m[3], cvt_bf16_fp4<3>(mags, row_scale[j]));
             }
+            column_bytes_bf16(m);
+            set_round_mode_for<T_SR>();
+            static_for_pair([&](auto jp_c) {
+                constexpr int jp = decltype(jp_c)::value;
+                uint32_t g[2][8];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const int j = 2 * jp + r;
+                    U8 rnd;
+                    if (T_SR) rnd = addends(j);
+                    const f32x2_hw v[4] = {cvt_f32_fp4<0>(pk[j], row_scale[j]), cvt_f32_fp4<1>(pk[j], row_scale[j]),
+                                           cvt_f32_fp4<2>(pk[j], row_scale[j]), cvt_f32_fp4<3>(pk[j], row_scale[j])};
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const int e = 1 - (int)((t & 1) ? sb[t >> 1] >> 16 : sb[t >> 1] & 0xFFFFu);
+                        g[r][t] = T_SR ? sr_grid_x2<FLOOR>(v[t >> 1][t & 1], e, rnd.w[t]) : rtn_grid<FLOOR>(v[t >> 1][t & 1], e);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+            });
+        } else if constexpr (SRC == 1) {
+            const uint32_t k = 0x7FFF7FFFu;
+            uint32_t m[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i] = pk_max(pk_max(cur.x[0][i] & k, cur.x[1][i] & k), pk_max(cur.x[2][i] & k, cur.x[3][i] & k));
+            column_bytes_bf16(m);
+            set_round_mode_for<T_SR>();
+            static_for_pair([&](auto jp_c) {
+                constexpr int jp = decltype(jp_c)::value;
+                if constexpr (T_SR) {
+                    uint32_t g[2][8];
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const U8 rnd = addends(2 * jp + r);
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) {
+                            const int e = 1 - (int)((t & 1) ? sb[t >> 1] >> 16 : sb[t >> 1] & 0xFFFFu);
+                            g[r][t] = sr_grid<FLOOR>(element(cur.x[2 * jp + r], t), e, rnd.w[t]);
+                        }
+                    }
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t n0 = ties_to_larger(cur.x[2 * jp][i]), n1 = ties_to_larger(cur.x[2 * jp + 1][i]);
+                        // the two rows of one column side by side
+                        colpk[2 * i] = cvt_fp4_bf16<jp>(colpk[2 * i], __builtin_amdgcn_perm(n1, n0, 0x05040100u), scale_operand(sb[i] & 0xFFFFu));
+                        colpk[2 * i + 1] = cvt_fp4_bf16<jp>(colpk[2 * i + 1], __builtin_amdgcn_perm(n1, n0, 0x07060302u), scale_operand(sb[i] >> 16));
+                    }
+                }
+            });
+        } else if constexpr (SRC == 0) {
+            // FP32 maxima: eight values, reduced four at a time and packed as bytes: registers hold columns (i, i + 4)
+            uint32_t lo[4], hi[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                lo[i] = absmax3_bits(cur.x[2].v[i], cur.x[3].v[i], absmax3_bits(cur.x[0].v[i], cur.x[1].v[i], 0u));
+                hi[i] = absmax3_bits(cur.x[2].v[i + 4], cur.x[3].v[i + 4], absmax3_bits(cur.x[0].v[i + 4], cur.x[1].v[i + 4], 0u));
+            }
+            auto umax = [](uint32_t p, uint32_t q) { return p > q ? p : q; };
+            const uint32_t two = scale_byte(reduce_row_groups4(lo, umax), FLOOR) | scale_byte(reduce_row_groups4(hi, umax), FLOOR) << 16;
+            store_column_bytes(two, place, 4u);
+            spread_row_groups4(two, sb);
+            set_round_mode_for<T_SR>();
+            static_for_pair([&](auto jp_c) {
+                constexpr int jp = decltype(jp_c)::value;
+                uint32_t g[2][8];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    U8 rnd;
+                    if (T_SR) rnd = addends(2 * jp + r);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const int e = 1 - (int)(t >= 4 ? sb[t & 3] >> 16 : sb[t & 3] & 0xFFFFu);
+                        g[r][t] = T_SR ? sr_grid<FLOOR>(cur.x[2 * jp + r].v[t], e, rnd.w[t]) : rtn_grid<FLOOR>(cur.x[2 * jp + r].v[t], e);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+            });
         }
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
+        for (int t = 0; t < 8; ++t)
             *reinterpret_cast<uint16_t*>(st + ST_COL_OFF + (lcol0 + t) * ST_PITCH + (lrow0 >> 1)) = (uint16_t)colpk[t];
-            if (rg == 0) st[ST_SCOL_OFF + (lcol0 + t) * 8 + wr] = (uint8_t)sb[t];
-        }
+        if (PREFETCH) cur = nxt;
     }
     __syncthreads();
 
