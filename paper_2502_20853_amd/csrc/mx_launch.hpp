@@ -156,6 +156,34 @@ struct RampingAdamwParams {
     float lr, beta1, beta2, eps, weight_decay;
 };
 hipError_t launch_ramping_adamw(const RampingAdamwParams& p, hipStream_t st);
+// Any number of tensors (ADAM_BATCH_MAX per launch), all with factors or all without, the first one's hyper-parameters.
+constexpr int ADAM_BATCH_MAX = 32;
+hipError_t launch_ramping_adamw_batch(const RampingAdamwParams* p, int count, hipStream_t st);
+
+// One step of a detection window for dense FP32 weights whose rows are a multiple of 32 long.
+struct WindowTensor {
+    float* w;
+    const void* grad;          // null: the weight stands still
+    float* m;
+    float* v;
+    int32_t* updates;
+    float* g_acc;
+    int32_t* acc_steps;
+    float* w_prev;
+    float* dist_w;
+    float* dist_q;
+    uint8_t* codes;
+    uint8_t* scales;
+    uint8_t* codes_prev;
+    uint8_t* scales_prev;
+};
+struct RampingWindowParams {
+    float lr, beta1, beta2, eps, weight_decay;
+    bool opens, floor_mode;
+};
+constexpr int WINDOW_BATCH_MAX = 24;
+hipError_t launch_ramping_window_batch(const RampingWindowParams& p, const WindowTensor* tensors, const int64_t* counts,
+                                       const bool* grad_bf16, int count, hipStream_t st);
 
 hipError_t launch_calibration_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 

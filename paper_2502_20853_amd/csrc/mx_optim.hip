@@ -16,10 +16,18 @@
 // ln(beta) come from the host in double precision, and 1 - beta^u = -expm1(u * ln(beta)) keeps its
 // relative accuracy when u is small.
 //
-// Work split: one lane owns 4 consecutive elements (16-byte accesses on every array).
+// Work split: one launch serves up to 32 (in a detection window 24) tensors, whose addresses travel in the kernel's
+// arguments; a ViT's step is then 2 to 5 launches instead of one to four per parameter (ViT-Tiny, 144 parameters:
+// 240 launches of 3-5 us each for 5.3 M elements).  A lane owns 4 consecutive elements (16-byte accesses on every
+// array), in a detection window 8, a quarter of a 1x32 group.
+//
+// Bytes per element: 28 read + 16 written where no gradient is held.  The held sum is read only by lanes whose step
+// count is not zero (the two are zero together, an element's update clears both), and sum and count are written only
+// where they change, so the weights with factor 1 -- all but a few percent -- cost 44 B instead of 56.
 #include <hip/hip_runtime.h>
 #include <cmath>
 #include <cstdint>
+#include "mx_device.hpp"
 #include "mx_launch.hpp"
 
 namespace {
@@ -30,95 +38,287 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-struct AdamArgs {
-    float* w;
-    const void* grad;
-    float* m;
-    float* v;
-    float* g_acc;                 // null iff factor is null
-    const int32_t* factor;        // null: 1 everywhere
-    int32_t* acc_steps;           // null iff factor is null
-    int32_t* updates;
-    int64_t quads;                // count / 4
+struct AdamHyper {
     float lr, beta1, beta2, eps, weight_decay;
     float one_minus_beta1, one_minus_beta2, ln_beta1, ln_beta2;
 };
 
-__device__ __forceinline__ float4 load_grad4(const float* g, int64_t q)
+AdamHyper hyper_of(float lr, float beta1, float beta2, float eps, float weight_decay)
 {
-    const v4f r = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(g) + q);
-    return make_float4(r.x, r.y, r.z, r.w);
+    AdamHyper h{};
+    h.lr = lr; h.beta1 = beta1; h.beta2 = beta2; h.eps = eps; h.weight_decay = weight_decay;
+    h.one_minus_beta1 = (float)(1.0 - (double)beta1);
+    h.one_minus_beta2 = (float)(1.0 - (double)beta2);
+    h.ln_beta1 = (float)std::log((double)beta1);
+    h.ln_beta2 = (float)std::log((double)beta2);
+    return h;
 }
 
-__device__ __forceinline__ float4 load_grad4(const uint16_t* g, int64_t q)       // bf16 bit patterns
+// every array is touched once per step and the state of a model is far larger than the
+// last-level cache: all accesses are marked streaming
+__device__ __forceinline__ v4f load4(const float* p, int64_t q) { return __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p) + q); }
+__device__ __forceinline__ v4i load4(const int32_t* p, int64_t q) { return __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p) + q); }
+__device__ __forceinline__ void store4(float* p, int64_t q, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(p) + q); }
+__device__ __forceinline__ void store4(int32_t* p, int64_t q, v4i v) { __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(p) + q); }
+
+__device__ __forceinline__ v4f load_grad4(const void* g, bool bf16, int64_t q)
 {
-    const v2u r = __builtin_nontemporal_load(reinterpret_cast<const v2u*>(g) + q);
-    return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u),
-                       __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xFFFF0000u));
+    if (!bf16) return load4(static_cast<const float*>(g), q);
+    const v2u r = __builtin_nontemporal_load(static_cast<const v2u*>(g) + q);
+    return v4f{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xFFFF0000u)};
 }
 
-struct ElemState { float w, m, v, acc; int32_t steps, upd; };
+// What an update needs besides the gradient, for an element that makes its u-th update with factor n_w.
+struct StepScale { float lr_w, step_size, root_bc2; };
 
-__device__ __forceinline__ void adamw_element(const AdamArgs& a, ElemState& s, float g, int32_t n_w)
+__device__ __forceinline__ StepScale step_scale(const AdamHyper& a, int32_t u, int32_t n_w)
 {
-    s.acc = s.acc + g;
-    s.steps += 1;
-    if (s.steps < n_w) return;                          // this element's batch is not full yet
-    const float gm = __fdiv_rn(s.acc, (float)s.steps);
+    const float bc1 = -expm1f((float)u * a.ln_beta1);
+    const float bc2 = -expm1f((float)u * a.ln_beta2);
     const float lr_w = (float)n_w * a.lr;
-    s.upd += 1;
-    const float u = (float)s.upd;
-    s.w = s.w * (1.0f - lr_w * a.weight_decay);
-    s.m = a.beta1 * s.m + a.one_minus_beta1 * gm;
-    s.v = a.beta2 * s.v + a.one_minus_beta2 * gm * gm;
-    const float bc1 = -expm1f(u * a.ln_beta1);
-    const float bc2 = -expm1f(u * a.ln_beta2);
-    const float denom = __fdiv_rn(__fsqrt_rn(s.v), __fsqrt_rn(bc2)) + a.eps;
-    s.w = s.w - __fdiv_rn(__fdiv_rn(lr_w, bc1) * s.m, denom);
-    s.acc = 0.0f;
-    s.steps = 0;
+    return {lr_w, __fdiv_rn(lr_w, bc1), __fsqrt_rn(bc2)};
 }
 
-template <typename GradT, bool RAMPING>
-__global__ __launch_bounds__(OPT_THREADS) void ramping_adamw_kernel(AdamArgs a)
+__device__ __forceinline__ void adamw_update(const AdamHyper& a, float& w, float& m, float& v, float gm, const StepScale& k)
 {
-    const int64_t q = (int64_t)blockIdx.x * OPT_THREADS + threadIdx.x;
-    if (q >= a.quads) return;
-    // every array is touched once per step and the state of a model is far larger than the
-    // last-level cache: all accesses are marked streaming
-    const float4 g4 = load_grad4(static_cast<const GradT*>(a.grad), q);
-    v4f* wp = reinterpret_cast<v4f*>(a.w) + q;
-    v4f* mp = reinterpret_cast<v4f*>(a.m) + q;
-    v4f* vp = reinterpret_cast<v4f*>(a.v) + q;
-    v4i* up = reinterpret_cast<v4i*>(a.updates) + q;
-    const v4f w4 = __builtin_nontemporal_load(wp), m4 = __builtin_nontemporal_load(mp),
-              v4 = __builtin_nontemporal_load(vp);
-    const v4i u4 = __builtin_nontemporal_load(up);
-    v4f acc4 = {0.f, 0.f, 0.f, 0.f};
-    v4i n4 = {1, 1, 1, 1}, c4 = {0, 0, 0, 0};
-    if (RAMPING) {
-        acc4 = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(a.g_acc) + q);
-        n4 = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(a.factor) + q);
-        c4 = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(a.acc_steps) + q);
-    }
-    ElemState e[4] = {{w4.x, m4.x, v4.x, acc4.x, c4.x, u4.x}, {w4.y, m4.y, v4.y, acc4.y, c4.y, u4.y},
-                      {w4.z, m4.z, v4.z, acc4.z, c4.z, u4.z}, {w4.w, m4.w, v4.w, acc4.w, c4.w, u4.w}};
-    const float g[4] = {g4.x, g4.y, g4.z, g4.w};
-    const int32_t n[4] = {n4.x, n4.y, n4.z, n4.w};
+    w = w * (1.0f - k.lr_w * a.weight_decay);
+    m = a.beta1 * m + a.one_minus_beta1 * gm;
+    v = a.beta2 * v + a.one_minus_beta2 * gm * gm;
+    const float denom = __fdiv_rn(__fsqrt_rn(v), k.root_bc2) + a.eps;
+    w = w - __fdiv_rn(k.step_size * m, denom);
+}
+
+// Whether the four elements of every lane of the wave have made the same number of updates and take this one at
+// factor 1 with nothing held (then u is that number).  The bias corrections -- two expm1, a square root, a division --
+// are then computed once per lane instead of once per element.
+__device__ __forceinline__ bool uniform_updates(const v4i& u)
+{
+    const int first = __builtin_amdgcn_readfirstlane(u.x);
+    return __all(u.x == first && u.y == first && u.z == first && u.w == first);
+}
+
+constexpr int ADAM_BATCH = mxl::ADAM_BATCH_MAX;
+
+struct AdamTensor {
+    float* w;
+    const void* grad;
+    float* m;
+    float* v;
+    int32_t* updates;
+    float* g_acc;                 // null iff factor is null
+    const int32_t* factor;        // null: 1 everywhere
+    int32_t* acc_steps;           // null iff factor is null
+};
+
+struct AdamBatch {
+    AdamHyper h;
+    uint32_t grad_bf16;           // bit i: tensor i's gradient
+    uint32_t end[ADAM_BATCH];     // first workgroup past tensor i
+    int64_t quads[ADAM_BATCH];    // count / 4
+    AdamTensor t[ADAM_BATCH];
+};
+
+template <bool RAMPING>
+__global__ __launch_bounds__(OPT_THREADS) void ramping_adamw_kernel(AdamBatch b)
+{
+    uint32_t i = 0;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) adamw_element(a, e[t], g[t], n[t]);
-    const v4f wo = {e[0].w, e[1].w, e[2].w, e[3].w}, mo = {e[0].m, e[1].m, e[2].m, e[3].m},
-              vo = {e[0].v, e[1].v, e[2].v, e[3].v};
-    const v4i uo = {e[0].upd, e[1].upd, e[2].upd, e[3].upd};
-    __builtin_nontemporal_store(wo, wp);
-    __builtin_nontemporal_store(mo, mp);
-    __builtin_nontemporal_store(vo, vp);
-    __builtin_nontemporal_store(uo, up);
+    for (int k = 0; k + 1 < ADAM_BATCH; ++k) i += blockIdx.x >= b.end[k] ? 1u : 0u;
+    const AdamTensor t = b.t[i];
+    const AdamHyper& a = b.h;
+    const int64_t q = (int64_t)(blockIdx.x - (i ? b.end[i - 1] : 0u)) * OPT_THREADS + threadIdx.x;
+    if (q >= b.quads[i]) return;
+    v4f w = load4(t.w, q), m = load4(t.m, q), v = load4(t.v, q);
+    const v4f g = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q);
+    v4i u = load4(t.updates, q);
     if (RAMPING) {
-        const v4f ao = {e[0].acc, e[1].acc, e[2].acc, e[3].acc};
-        const v4i co = {e[0].steps, e[1].steps, e[2].steps, e[3].steps};
-        __builtin_nontemporal_store(ao, reinterpret_cast<v4f*>(a.g_acc) + q);
-        __builtin_nontemporal_store(co, reinterpret_cast<v4i*>(a.acc_steps) + q);
+        const v4i n = load4(t.factor, q);
+        v4i c = load4(t.acc_steps, q);
+        const bool plain = n.x == 1 && n.y == 1 && n.z == 1 && n.w == 1 && (c.x | c.y | c.z | c.w) == 0;
+        if (!__all(plain) || !uniform_updates(u)) {
+            v4f acc = {0.f, 0.f, 0.f, 0.f};
+            if ((c.x | c.y | c.z | c.w) != 0) acc = load4(t.g_acc, q);
+            const v4i c0 = c;
+            bool any = false;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[e] = acc[e] + g[e];
+                c[e] += 1;
+                if (c[e] < n[e]) continue;                  // this element's batch is not full yet
+                any = true;
+                u[e] += 1;
+                float we = w[e], me = m[e], ve = v[e];
+                adamw_update(a, we, me, ve, __fdiv_rn(acc[e], (float)c[e]), step_scale(a, u[e], n[e]));
+                w[e] = we; m[e] = me; v[e] = ve;
+                acc[e] = 0.0f;
+                c[e] = 0;
+            }
+            if (any) {
+                store4(t.w, q, w);
+                store4(t.m, q, m);
+                store4(t.v, q, v);
+                store4(t.updates, q, u);
+            }
+            if ((c.x | c.y | c.z | c.w | c0.x | c0.y | c0.z | c0.w) != 0) {
+                store4(t.g_acc, q, acc);
+                store4(t.acc_steps, q, c);
+            }
+            return;
+        }
+    }
+    // factor 1, nothing held
+    if (uniform_updates(u)) {
+        const StepScale k = step_scale(a, u.x + 1, 1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float we = w[e], me = m[e], ve = v[e];
+            adamw_update(a, we, me, ve, 0.0f + g[e], k);
+            w[e] = we; m[e] = me; v[e] = ve;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float we = w[e], me = m[e], ve = v[e];
+            adamw_update(a, we, me, ve, 0.0f + g[e], step_scale(a, u[e] + 1, 1));
+            w[e] = we; m[e] = me; v[e] = ve;
+        }
+    }
+    u += 1;
+    store4(t.w, q, w);
+    store4(t.m, q, m);
+    store4(t.v, q, v);
+    store4(t.updates, q, u);
+}
+
+// One step inside a detection window: the AdamW step at factor 1 (gradients still held are applied with it), the 1x32
+// quantization of the new weight and the step of the trajectory lengths dist_W, dist_Q (Sec. 6.1), in one pass:
+// w crosses memory once instead of four times and the codes are not read back.  The arithmetic is that of
+// ramping_adamw_kernel, quantize_rows_kernel (round_D) and oscillation_kernel.  `opens` (the window's first step): the
+// lengths start from the weight as it is before the step.
+constexpr int WINDOW_BATCH = mxl::WINDOW_BATCH_MAX;
+
+struct WindowBatch {
+    AdamHyper h;
+    uint32_t grad_bf16;
+    int opens;
+    uint32_t end[WINDOW_BATCH];
+    uint32_t chunks[WINDOW_BATCH];      // count / 8
+    mxl::WindowTensor t[WINDOW_BATCH];
+};
+
+// round_D codes of 8 elements of a group and the group's scale byte
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t rtn_codes8(const float (&x)[8], uint32_t& byte)
+{
+    using namespace mxd;
+    F8 f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) f.v[t] = x[t];
+    byte = scale_byte(quad_max(amax_bits8(f)), FLOOR);
+    const int e = grid_exponent(byte);
+    f32_round_toward_minus_inf();
+    uint32_t g[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) g[t] = rtn_grid<FLOOR>(x[t], e);
+    f32_round_to_nearest_even();
+    uint32_t p = pack_grid<0>(0u, g[0], g[1]);
+    p = pack_grid<1>(p, g[2], g[3]);
+    p = pack_grid<2>(p, g[4], g[5]);
+    return pack_grid<3>(p, g[6], g[7]);
+}
+
+__device__ __forceinline__ void dequantize8(uint32_t codes, uint32_t byte, float (&x)[8])
+{
+    using namespace mxd;
+    const float s = scale_operand(byte);
+    const f32x2_hw a = cvt_f32_fp4<0>(codes, s), b = cvt_f32_fp4<1>(codes, s), c = cvt_f32_fp4<2>(codes, s), d = cvt_f32_fp4<3>(codes, s);
+    x[0] = a.x; x[1] = a.y; x[2] = b.x; x[3] = b.y; x[4] = c.x; x[5] = c.y; x[6] = d.x; x[7] = d.y;
+}
+
+__device__ __forceinline__ void load8f(const float* p, uint32_t q, float (&x)[8])
+{
+    const v4f a = load4(p, 2 * (int64_t)q), b = load4(p, 2 * (int64_t)q + 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { x[e] = a[e]; x[4 + e] = b[e]; }
+}
+
+__device__ __forceinline__ void store8f(float* p, uint32_t q, const float (&x)[8])
+{
+    store4(p, 2 * (int64_t)q, v4f{x[0], x[1], x[2], x[3]});
+    store4(p, 2 * (int64_t)q + 1, v4f{x[4], x[5], x[6], x[7]});
+}
+
+template <bool FLOOR>
+__global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch b)
+{
+    uint32_t i = 0;
+#pragma unroll
+    for (int k = 0; k + 1 < WINDOW_BATCH; ++k) i += blockIdx.x >= b.end[k] ? 1u : 0u;
+    const mxl::WindowTensor t = b.t[i];
+    const AdamHyper& a = b.h;
+    const uint32_t q = (blockIdx.x - (i ? b.end[i - 1] : 0u)) * OPT_THREADS + threadIdx.x;
+    if (q >= b.chunks[i]) return;       // chunks % 4 == 0: the four lanes of a group stay together
+    float w[8], prev[8], dw[8], dq[8], wq_prev[8];
+    uint32_t byte;
+    load8f(t.w, q, w);
+    if (b.opens) {
+        const uint32_t p = rtn_codes8<FLOOR>(w, byte);
+        dequantize8(p, byte, wq_prev);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { prev[e] = w[e]; dw[e] = 0.0f; dq[e] = 0.0f; }
+    } else {
+        load8f(t.w_prev, q, prev);
+        load8f(t.dist_w, q, dw);
+        load8f(t.dist_q, q, dq);
+        dequantize8(reinterpret_cast<const uint32_t*>(t.codes_prev)[q], t.scales_prev[q >> 2], wq_prev);
+    }
+    if (t.grad != nullptr) {            // a weight without a gradient stands still
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int64_t q4 = 2 * (int64_t)q + half;
+            const v4f g = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q4);
+            v4f m = load4(t.m, q4), v = load4(t.v, q4);
+            v4i u = load4(t.updates, q4), c = load4(t.acc_steps, q4);
+            const bool held = (c.x | c.y | c.z | c.w) != 0;
+            v4f acc = {0.f, 0.f, 0.f, 0.f};
+            if (held) acc = load4(t.g_acc, q4);
+            u += 1;
+            const bool uniform = uniform_updates(u);
+            StepScale k = step_scale(a, u.x, 1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!uniform && e > 0) k = step_scale(a, u[e], 1);
+                const float gm = held ? __fdiv_rn(acc[e] + g[e], (float)(c[e] + 1)) : 0.0f + g[e];
+                float we = w[4 * half + e], me = m[e], ve = v[e];
+                adamw_update(a, we, me, ve, gm, k);
+                w[4 * half + e] = we; m[e] = me; v[e] = ve;
+            }
+            store4(t.m, q4, m);
+            store4(t.v, q4, v);
+            store4(t.updates, q4, u);
+            if (held) {
+                store4(t.g_acc, q4, v4f{0.f, 0.f, 0.f, 0.f});
+                store4(t.acc_steps, q4, v4i{0, 0, 0, 0});
+            }
+        }
+        store8f(t.w, q, w);
+    }
+    const uint32_t p = rtn_codes8<FLOOR>(w, byte);
+    float wq[8];
+    dequantize8(p, byte, wq);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        dw[e] = __fadd_rn(dw[e], __builtin_fabsf(__fsub_rn(w[e], prev[e])));
+        dq[e] = __fadd_rn(dq[e], __builtin_fabsf(__fsub_rn(wq[e], wq_prev[e])));
+    }
+    store8f(t.w_prev, q, w);
+    store8f(t.dist_w, q, dw);
+    store8f(t.dist_q, q, dq);
+    reinterpret_cast<uint32_t*>(t.codes)[q] = p;
+    reinterpret_cast<uint32_t*>(t.codes_prev)[q] = p;
+    if ((threadIdx.x & 3) == 0) {
+        t.scales[q >> 2] = (uint8_t)byte;
+        t.scales_prev[q >> 2] = (uint8_t)byte;
     }
 }
 
@@ -126,26 +326,60 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_adamw_kernel(AdamArgs a)
 
 namespace mxl {
 
-hipError_t launch_ramping_adamw(const RampingAdamwParams& p, hipStream_t st)
+hipError_t launch_ramping_adamw_batch(const RampingAdamwParams* p, int count, hipStream_t st)
 {
-    AdamArgs a{};
-    a.w = p.w; a.grad = p.grad; a.m = p.m; a.v = p.v; a.g_acc = p.g_acc; a.factor = p.factor;
-    a.acc_steps = p.acc_steps; a.updates = p.updates; a.quads = p.count / 4;
-    a.lr = p.lr; a.beta1 = p.beta1; a.beta2 = p.beta2; a.eps = p.eps; a.weight_decay = p.weight_decay;
-    a.one_minus_beta1 = (float)(1.0 - (double)p.beta1);
-    a.one_minus_beta2 = (float)(1.0 - (double)p.beta2);
-    a.ln_beta1 = (float)std::log((double)p.beta1);
-    a.ln_beta2 = (float)std::log((double)p.beta2);
-    dim3 grid((unsigned)((a.quads + OPT_THREADS - 1) / OPT_THREADS)), block(OPT_THREADS);
-    const bool ramping = p.factor != nullptr;
-    if (p.grad_bf16) {
-        if (ramping) hipLaunchKernelGGL((ramping_adamw_kernel<uint16_t, true>), grid, block, 0, st, a);
-        else         hipLaunchKernelGGL((ramping_adamw_kernel<uint16_t, false>), grid, block, 0, st, a);
-    } else {
-        if (ramping) hipLaunchKernelGGL((ramping_adamw_kernel<float, true>), grid, block, 0, st, a);
-        else         hipLaunchKernelGGL((ramping_adamw_kernel<float, false>), grid, block, 0, st, a);
+    for (int at = 0; at < count; at += ADAM_BATCH) {
+        AdamBatch b{};
+        b.h = hyper_of(p[at].lr, p[at].beta1, p[at].beta2, p[at].eps, p[at].weight_decay);
+        const int n = count - at < ADAM_BATCH ? count - at : ADAM_BATCH;
+        const bool ramping = p[at].factor != nullptr;
+        uint32_t blocks = 0;
+        for (int i = 0; i < ADAM_BATCH; ++i) {
+            b.end[i] = 0xFFFFFFFFu;
+            if (i >= n) continue;
+            const RampingAdamwParams& q = p[at + i];
+            if ((q.factor != nullptr) != ramping) return hipErrorInvalidValue;
+            b.t[i] = {q.w, q.grad, q.m, q.v, q.updates, q.g_acc, q.factor, q.acc_steps};
+            b.quads[i] = q.count / 4;
+            if (q.grad_bf16) b.grad_bf16 |= 1u << i;
+            blocks += (uint32_t)((b.quads[i] + OPT_THREADS - 1) / OPT_THREADS);
+            b.end[i] = blocks;
+        }
+        if (blocks == 0) continue;
+        if (ramping) hipLaunchKernelGGL(ramping_adamw_kernel<true>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+        else         hipLaunchKernelGGL(ramping_adamw_kernel<false>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
+
+hipError_t launch_ramping_window_batch(const RampingWindowParams& p, const WindowTensor* tensors, const int64_t* counts,
+                                       const bool* grad_bf16, int count, hipStream_t st)
+{
+    for (int at = 0; at < count; at += WINDOW_BATCH) {
+        WindowBatch b{};
+        b.h = hyper_of(p.lr, p.beta1, p.beta2, p.eps, p.weight_decay);
+        b.opens = p.opens ? 1 : 0;
+        const int n = count - at < WINDOW_BATCH ? count - at : WINDOW_BATCH;
+        uint32_t blocks = 0;
+        for (int i = 0; i < WINDOW_BATCH; ++i) {
+            b.end[i] = 0xFFFFFFFFu;
+            if (i >= n) continue;
+            b.t[i] = tensors[at + i];
+            b.chunks[i] = (uint32_t)(counts[at + i] / 8);
+            if (grad_bf16[at + i]) b.grad_bf16 |= 1u << i;
+            blocks += (b.chunks[i] + OPT_THREADS - 1) / OPT_THREADS;
+            b.end[i] = blocks;
+        }
+        if (p.floor_mode) hipLaunchKernelGGL(ramping_window_kernel<true>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+        else              hipLaunchKernelGGL(ramping_window_kernel<false>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_ramping_adamw(const RampingAdamwParams& p, hipStream_t st) { return launch_ramping_adamw_batch(&p, 1, st); }
 
 }  // namespace mxl

@@ -7,6 +7,7 @@
 #include <torch/extension.h>
 #include <c10/hip/HIPGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
 
 #include "mx_launch.hpp"
 
@@ -353,11 +354,103 @@ void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t s
     product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, &workspace);
 }
 
+// ---- QRampingAdamW: one call per parameter group ----
+
+// A tensor of an optimizer state dict.
+const Tensor& state_tensor(PyObject* state, PyObject* key)
+{
+    PyObject* v = PyDict_GetItem(state, key);               // borrowed
+    TORCH_CHECK(v != nullptr && THPVariable_Check(v), "optimizer state is incomplete");
+    return THPVariable_Unpack(v);
+}
+
+template <typename T>
+T* checked(const Tensor& t, int64_t count, at::ScalarType type, const char* what)
+{
+    TORCH_CHECK(t.is_cuda() && t.numel() == count && t.scalar_type() == type && t.is_contiguous(), what, ": a contiguous tensor on the GPU expected");
+    TORCH_CHECK((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) == 0, "mx_ramping_adamw_step failed: MX_ERR_ALIGN (-5)");
+    return reinterpret_cast<T*>(t.data_ptr());
+}
+
+// mode 0: plain AdamW, 1: with amplification factors, 2: a step inside a detection window (`opens`: its first).
+// params and states are parallel lists; a parameter without a gradient is skipped (mode 2: only tracked).
+void ramping_step(const py::list& params, const py::list& states, int mode, bool opens, bool floor_mode, float lr, float beta1, float beta2,
+                  float eps, float weight_decay)
+{
+    static PyObject *k_m = PyUnicode_InternFromString("m"), *k_v = PyUnicode_InternFromString("v"), *k_u = PyUnicode_InternFromString("updates"),
+                    *k_acc = PyUnicode_InternFromString("g_acc"), *k_steps = PyUnicode_InternFromString("acc_steps"),
+                    *k_factor = PyUnicode_InternFromString("factor"), *k_prev = PyUnicode_InternFromString("w_prev"),
+                    *k_dw = PyUnicode_InternFromString("dist_w"), *k_dq = PyUnicode_InternFromString("dist_q"),
+                    *k_codes = PyUnicode_InternFromString("codes"), *k_scales = PyUnicode_InternFromString("scales"),
+                    *k_codes0 = PyUnicode_InternFromString("codes_prev"), *k_scales0 = PyUnicode_InternFromString("scales_prev");
+    const Py_ssize_t n = PyList_GET_SIZE(params.ptr());
+    TORCH_CHECK(PyList_GET_SIZE(states.ptr()) == n, "one state per parameter");
+    TORCH_CHECK(lr >= 0.0f && beta1 > 0.0f && beta1 < 1.0f && beta2 > 0.0f && beta2 < 1.0f && eps >= 0.0f && weight_decay >= 0.0f,
+                "mx_ramping_adamw_step failed: MX_ERR_MODE (-4)");
+    // one batch per device, in order
+    std::vector<mxl::RampingAdamwParams> adam;
+    std::vector<mxl::WindowTensor> window;
+    std::vector<int64_t> counts;
+    std::vector<Tensor> keep;                                // gradients made contiguous here live until the launch is enqueued
+    std::unique_ptr<bool[]> bf16(new bool[n > 0 ? n : 1]);
+    int device = -1;
+    auto flush = [&]() {
+        if (device < 0) return;
+        c10::hip::HIPGuard guard((c10::DeviceIndex)device);
+        hipStream_t st = c10::hip::getCurrentHIPStream((c10::DeviceIndex)device).stream();
+        if (mode == 2) {
+            const mxl::RampingWindowParams p{lr, beta1, beta2, eps, weight_decay, opens, floor_mode};
+            check_hip(mxl::launch_ramping_window_batch(p, window.data(), counts.data(), bf16.get(), (int)window.size(), st), "mx_ramping_adamw_step");
+        } else {
+            check_hip(mxl::launch_ramping_adamw_batch(adam.data(), (int)adam.size(), st), "mx_ramping_adamw_step");
+        }
+        adam.clear(); window.clear(); counts.clear(); keep.clear();
+    };
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        PyObject* pp = PyList_GET_ITEM(params.ptr(), i);
+        TORCH_CHECK(THPVariable_Check(pp), "parameters must be tensors");
+        const Tensor& p = THPVariable_Unpack(pp);
+        PyObject* st = PyList_GET_ITEM(states.ptr(), i);
+        TORCH_CHECK(PyDict_Check(st), "states must be dicts");
+        Tensor grad = p.grad();
+        if (!grad.defined() && mode != 2) continue;
+        if (p.get_device() != device) { flush(); device = p.get_device(); }
+        const int64_t count = p.numel();
+        float* w = checked<float>(p, count, at::kFloat, "parameter");
+        bool gb = false;
+        if (grad.defined()) {
+            TORCH_CHECK_VALUE(grad.sizes() == p.sizes(), "shape mismatch");
+            gb = is_bf16(grad);
+            grad = grad.contiguous();
+            TORCH_CHECK(grad.is_cuda() && (reinterpret_cast<uintptr_t>(grad.data_ptr()) & (gb ? 7 : 15)) == 0, "mx_ramping_adamw_step failed: MX_ERR_ALIGN (-5)");
+            keep.push_back(grad);
+        }
+        auto f32 = [&](PyObject* k) { return checked<float>(state_tensor(st, k), count, at::kFloat, "state"); };
+        auto i32 = [&](PyObject* k) { return checked<int32_t>(state_tensor(st, k), count, at::kInt, "state"); };
+        if (mode == 2) {
+            auto u8s = [&](PyObject* k, int64_t per) { return checked<uint8_t>(state_tensor(st, k), count / per, at::kByte, "state"); };
+            bf16[window.size()] = gb;
+            window.push_back({w, grad.defined() ? grad.data_ptr() : nullptr, f32(k_m), f32(k_v), i32(k_u), f32(k_acc), i32(k_steps), f32(k_prev),
+                              f32(k_dw), f32(k_dq), u8s(k_codes, 2), u8s(k_scales, 32), u8s(k_codes0, 2), u8s(k_scales0, 32)});
+            counts.push_back(count);
+        } else {
+            mxl::RampingAdamwParams a{};
+            a.w = w; a.grad = grad.data_ptr(); a.grad_bf16 = gb; a.count = count;
+            a.m = f32(k_m); a.v = f32(k_v); a.updates = i32(k_u);
+            if (mode == 1) { a.g_acc = f32(k_acc); a.acc_steps = i32(k_steps); a.factor = i32(k_factor); }
+            a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps; a.weight_decay = weight_decay;
+            adam.push_back(a);
+        }
+    }
+    flush();
+}
+
 }  // namespace
 
 PYBIND11_MODULE(_mx_torch, m)
 {
     m.def("linear", &linear, py::call_guard<py::gil_scoped_release>());
     m.def("step_forward", &step_forward, py::call_guard<py::gil_scoped_release>());
+    m.def("ramping_step", &ramping_step);
     m.def("step_backward", &step_backward, py::call_guard<py::gil_scoped_release>());
 }

@@ -1,5 +1,6 @@
 """Q-Ramping as a torch optimizer (Algorithm 2, Sec. 6): the schedule of the algorithm around the
-library's kernels.  Plumbing only: every array operation is one of the C-ABI calls.
+library's kernels.  Plumbing only: every array operation is one of the library's kernels, which take the tensors
+of a parameter group many at a time.
 
 Every t_update steps a detection window of t0 steps opens.  Inside it the quantized weights take plain
 AdamW steps (amplification factor 1 for every element) and the trajectory lengths dist_W, dist_Q of
@@ -17,13 +18,6 @@ as one update).  t0 = 30 is the paper's value; t_update and n_max are not printe
 import torch
 
 from . import binding as B
-
-
-def _view(cls, **fields):
-    obj = cls.__new__(cls)
-    for k, v in fields.items():
-        setattr(obj, k, v)
-    return obj
 
 
 class QRampingAdamW(torch.optim.Optimizer):
@@ -65,13 +59,6 @@ class QRampingAdamW(torch.optim.Optimizer):
                           codes=u8(rows, cols // 2), scales=u8(rows, cols // 32))
         return st
 
-    @staticmethod
-    def _track(p, st, scale_mode, init):
-        B.mx_quantize(p.data, B.ROUND_RTN, scale_mode, out=(st["codes"], st["scales"]))
-        osc = _view(B.OscillationState, w_prev=st["w_prev"], dist_w=st["dist_w"], dist_q=st["dist_q"],
-                    codes_prev=st["codes_prev"], scales_prev=st["scales_prev"], started=True)
-        B.mx_oscillation_accumulate(p.data, st["codes"], st["scales"], osc, init=init)
-
     def amplification_factors(self):
         """{parameter: N_w tensor in use} for the quantized weights (all ones before the first window closes)."""
         return {p: self.state[p]["factor"] for g in self.param_groups if g["quantized"] for p in g["params"] if self.state[p]}
@@ -100,23 +87,18 @@ class QRampingAdamW(torch.optim.Optimizer):
         for g in self.param_groups:
             phase = g["steps_done"] % g["t_update"]
             detecting = g["quantized"] and phase < g["t0"]
-            for p in g["params"]:
-                if p.grad is None and not detecting:
-                    continue
-                st = self._state(p, g["quantized"])
-                adam = _view(B.RampingAdamwState, shape=tuple(p.shape), m=st["m"], v=st["v"], updates=st["updates"],
-                             g_acc=st.get("g_acc"), acc_steps=st.get("acc_steps"))
-                if detecting and phase == 0:
-                    self._track(p, st, g["scale_mode"], True)          # the window's starting point w^0
-                factor = None
-                if g["quantized"]:
-                    factor = st["ones"] if detecting else st["factor"]
-                if p.grad is not None:                                 # a weight without a gradient stands still
-                    B.mx_ramping_adamw_step(p.data, p.grad.contiguous(), adam, factor, g["lr"], g["betas"][0],
-                                            g["betas"][1], g["eps"], g["weight_decay"])
-                if detecting:
-                    self._track(p, st, g["scale_mode"], False)
-                    if phase == g["t0"] - 1:
-                        B.mx_ramping_factor(st["dist_w"], st["dist_q"], g["k1"], g["k2"], g["n_max"], out=st["factor"])
+            (beta1, beta2), lr, eps, decay = g["betas"], g["lr"], g["eps"], g["weight_decay"]
+            if not (lr >= 0 and 0 < beta1 < 1 and 0 < beta2 < 1 and eps >= 0 and decay >= 0):
+                raise B.MxError("mx_ramping_adamw_step", B.MX_ERR_MODE)
+            # one native call for the group: AdamW at the factors in use or, inside a window (whose first step also
+            # sets the starting point w^0), AdamW at factor 1 with quantization and path lengths in the same pass.
+            # A weight without a gradient stands still.
+            params = g["params"] if detecting else [p for p in g["params"] if p.grad is not None]
+            states = [self.state[p] or self._state(p, g["quantized"]) for p in params]
+            B.host().ramping_step(params, states, 2 if detecting else int(g["quantized"]), phase == 0, g["scale_mode"] == B.SCALE_FLOOR,
+                                  lr, beta1, beta2, eps, decay)
+            if detecting and phase == g["t0"] - 1:
+                for st in states:
+                    B.mx_ramping_factor(st["dist_w"], st["dist_q"], g["k1"], g["k2"], g["n_max"], out=st["factor"])
             g["steps_done"] += 1
         return loss

@@ -124,3 +124,52 @@ def test_plain_adamw_when_nothing_oscillates(mx):
         ref.step()
     assert np.allclose(host(w.data), wr.detach().numpy(), rtol=2e-5, atol=2e-6)
     assert np.allclose(host(b.data), br.detach().numpy(), rtol=2e-5, atol=2e-6)
+
+
+@pytest.mark.parametrize("scale_mode", [0, 1])
+def test_many_tensors_per_launch_equal_one_by_one(mx, scale_mode):
+    """More weights (27) and other parameters (35) than one launch takes, from one group of 32 elements up, some without a
+    gradient: two windows and the steps between them equal the calls per tensor, bit for bit, in every state array."""
+    B = mx.binding
+    t0, tu, steps, kw = 2, 5, 8, dict(lr=2e-3, weight_decay=0.03)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(scale_mode)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    shapes = [(1, 32), (3, 64), (8, 32), (64, 1056), (257, 96)] + [(5 + i, 32 * (1 + i % 4)) for i in range(22)]
+    sizes = [4, 1024, 1028, 4100] + [4 * (1 + 3 * i) for i in range(31)]
+    ws = [torch.nn.Parameter(rnd(*s) * 0.1) for s in shapes]
+    os_ = [torch.nn.Parameter(rnd(n)) for n in sizes]
+    opt = mx.QRampingAdamW(ws, os_, k1=1.0, k2=2, n_max=6, t0=t0, t_update=tu, scale_mode=scale_mode, **kw)
+    w_ref, o_ref = [w.detach().clone() for w in ws], [o.detach().clone() for o in os_]
+    ad = [B.RampingAdamwState(s) for s in shapes]
+    ad_o = [B.RampingAdamwState((n,), ramping=False) for n in sizes]
+    osc = [B.OscillationState(*s) for s in shapes]
+    ones = [torch.ones(s, dtype=torch.int32, device="cuda") for s in shapes]
+    factor = [f.clone() for f in ones]
+    track = lambda i, init: B.mx_oscillation_accumulate(w_ref[i], *B.mx_quantize(w_ref[i], scale_mode=scale_mode), osc[i], init=init)
+    for t in range(steps):
+        phase = t % tu
+        for i, p in enumerate(ws + os_):
+            p.grad = None if (i + t) % 9 == 8 else rnd(*p.shape) * (1.0 if t % 2 else -1.0)
+        opt.step()
+        for i, p in enumerate(ws):
+            if phase == 0:
+                track(i, True)
+            if p.grad is not None:
+                B.mx_ramping_adamw_step(w_ref[i], p.grad, ad[i], ones[i] if phase < t0 else factor[i], **kw)
+            if phase < t0:
+                track(i, False)
+                if phase == t0 - 1:
+                    factor[i] = B.mx_ramping_factor(osc[i].dist_w, osc[i].dist_q, 1.0, 2, 6)
+            st = opt.state[p]
+            assert torch.equal(p.data, w_ref[i]), (t, i)
+            if st:
+                for k, ref in (("m", ad[i].m), ("v", ad[i].v), ("updates", ad[i].updates), ("g_acc", ad[i].g_acc), ("acc_steps", ad[i].acc_steps),
+                               ("w_prev", osc[i].w_prev), ("dist_w", osc[i].dist_w), ("dist_q", osc[i].dist_q),
+                               ("codes_prev", osc[i].codes_prev), ("scales_prev", osc[i].scales_prev)):
+                    assert torch.equal(st[k], ref), (t, i, k)
+        for i, p in enumerate(os_):
+            if p.grad is not None:
+                B.mx_ramping_adamw_step(o_ref[i], p.grad, ad_o[i], None, **kw)
+            assert torch.equal(p.data, o_ref[i]), (t, i)
+    assert max(int(f.max()) for f in factor) > 1            # some elements did hold gradients between the windows
