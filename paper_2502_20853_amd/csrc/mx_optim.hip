@@ -258,44 +258,64 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch
     const AdamHyper& a = b.h;
     const uint32_t q = (blockIdx.x - (i ? b.end[i - 1] : 0u)) * OPT_THREADS + threadIdx.x;
     if (q >= b.chunks[i]) return;       // chunks % 4 == 0: the four lanes of a group stay together
+    // every load before the first store: the arrays could overlap for all the compiler knows, and a wave that waits
+    // for its stores before it loads again reaches half the memory rate
+    const bool has_grad = t.grad != nullptr;            // a weight without a gradient stands still
     float w[8], prev[8], dw[8], dq[8], wq_prev[8];
-    uint32_t byte;
+    v4f g[2], m[2], v[2], acc[2];
+    v4i u[2], c[2];
+    uint32_t byte = 0u, codes_prev = 0u;
     load8f(t.w, q, w);
-    if (b.opens) {
-        const uint32_t p = rtn_codes8<FLOOR>(w, byte);
-        dequantize8(p, byte, wq_prev);
+    if (has_grad) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { prev[e] = w[e]; dw[e] = 0.0f; dq[e] = 0.0f; }
-    } else {
+        for (int h = 0; h < 2; ++h) {
+            const int64_t q4 = 2 * (int64_t)q + h;
+            c[h] = load4(t.acc_steps, q4);
+            u[h] = load4(t.updates, q4);
+            g[h] = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q4);
+            m[h] = load4(t.m, q4);
+            v[h] = load4(t.v, q4);
+        }
+    }
+    if (!b.opens) {
         load8f(t.w_prev, q, prev);
         load8f(t.dist_w, q, dw);
         load8f(t.dist_q, q, dq);
-        dequantize8(reinterpret_cast<const uint32_t*>(t.codes_prev)[q], t.scales_prev[q >> 2], wq_prev);
+        codes_prev = reinterpret_cast<const uint32_t*>(t.codes_prev)[q];
+        byte = t.scales_prev[q >> 2];
     }
-    if (t.grad != nullptr) {            // a weight without a gradient stands still
+    if (has_grad) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int64_t q4 = 2 * (int64_t)q + half;
-            const v4f g = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q4);
-            v4f m = load4(t.m, q4), v = load4(t.v, q4);
-            v4i u = load4(t.updates, q4), c = load4(t.acc_steps, q4);
-            const bool held = (c.x | c.y | c.z | c.w) != 0;
-            v4f acc = {0.f, 0.f, 0.f, 0.f};
-            if (held) acc = load4(t.g_acc, q4);
-            u += 1;
-            const bool uniform = uniform_updates(u);
-            StepScale k = step_scale(a, u.x, 1);
+        for (int h = 0; h < 2; ++h) {
+            acc[h] = v4f{0.f, 0.f, 0.f, 0.f};
+            if ((c[h].x | c[h].y | c[h].z | c[h].w) != 0) acc[h] = load4(t.g_acc, 2 * (int64_t)q + h);
+        }
+    }
+    if (b.opens) {
+        codes_prev = rtn_codes8<FLOOR>(w, byte);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { prev[e] = w[e]; dw[e] = 0.0f; dq[e] = 0.0f; }
+    }
+    dequantize8(codes_prev, byte, wq_prev);
+    if (has_grad) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t q4 = 2 * (int64_t)q + h;
+            const bool held = (c[h].x | c[h].y | c[h].z | c[h].w) != 0;
+            u[h] += 1;
+            const bool uniform = uniform_updates(u[h]);
+            StepScale k = step_scale(a, u[h].x, 1);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (!uniform && e > 0) k = step_scale(a, u[e], 1);
-                const float gm = held ? __fdiv_rn(acc[e] + g[e], (float)(c[e] + 1)) : 0.0f + g[e];
-                float we = w[4 * half + e], me = m[e], ve = v[e];
+                if (!uniform && e > 0) k = step_scale(a, u[h][e], 1);
+                const float gm = held ? __fdiv_rn(acc[h][e] + g[h][e], (float)(c[h][e] + 1)) : 0.0f + g[h][e];
+                float we = w[4 * h + e], me = m[h][e], ve = v[h][e];
                 adamw_update(a, we, me, ve, gm, k);
-                w[4 * half + e] = we; m[e] = me; v[e] = ve;
+                w[4 * h + e] = we; m[h][e] = me; v[h][e] = ve;
             }
-            store4(t.m, q4, m);
-            store4(t.v, q4, v);
-            store4(t.updates, q4, u);
+            store4(t.m, q4, m[h]);
+            store4(t.v, q4, v[h]);
+            store4(t.updates, q4, u[h]);
             if (held) {
                 store4(t.g_acc, q4, v4f{0.f, 0.f, 0.f, 0.f});
                 store4(t.acc_steps, q4, v4i{0, 0, 0, 0});
