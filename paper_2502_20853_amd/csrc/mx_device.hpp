@@ -66,78 +66,6 @@ constexpr uint32_t GRID_MAX_BITS = 0x01C00000u;      // 6 * 2^-126
 // Exponent to hand to ldexp for scale byte b = s + 127:  -s - 126 = 1 - b.
 __device__ __forceinline__ int grid_exponent(uint32_t byte) { return 1 - (int)byte; }
 
-// round_D.  Call with the rounding mode set toward minus infinity.  e = grid_exponent(byte).
-// FLOOR: Eq. 2's scale, which truncates to |y| <= 6.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t rtn_code(float x, int e)
-{
-    uint32_t vb = __float_as_uint(__builtin_ldexpf(x, e));
-    uint32_t mag = vb & 0x7FFFFFFFu;
-    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    // + 2^21, minus 1 for negative values: a negative midpoint stays at the smaller magnitude
-    uint32_t t = mag + 0x200000u + (uint32_t)((int32_t)vb >> 31);
-    return (t >> 22) | ((vb >> 28) & 8u);
-}
-
-// round_S.  Call with the rounding mode set toward plus infinity.
-// rinv = ((65535 - r16) << 6) | 63: the add carries into bit 22 iff p * 2^22 > 64 * r16.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_code(float x, int e, uint32_t rinv)
-{
-    uint32_t mag = __float_as_uint(__builtin_ldexpf(__builtin_fabsf(x), e));
-    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    return ((mag + rinv) >> 22) | ((__float_as_uint(x) >> 28) & 8u);
-}
-
-// round_D that also hands back the rounded value on the grid's bit layout with its sign,
-// i.e. sign | (code & 7) << 22 = +-m * 2^-126, for the double quantization that follows.
-// The sum keeps the sign in bit 31 (the magnitude stays below 2^25, so nothing carries into it, and
-// the -1 of a negative value only borrows from the low bits), which saves taking |v| apart first;
-// bits 30..25 of the sum are zero, so sum >> 28 is the sign nibble as it stands.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t rtn_code_keep(float x, int e, uint32_t& grid_bits)
-{
-    uint32_t vb = __float_as_uint(__builtin_ldexpf(x, e));
-    if (FLOOR) {
-        uint32_t mag = vb & 0x7FFFFFFFu;
-        mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-        vb = mag | (vb & 0x80000000u);
-    }
-    uint32_t t = vb + 0x200000u + (uint32_t)((int32_t)vb >> 31);
-    grid_bits = t & 0xFFC00000u;
-    return ((t >> 22) & 7u) | (t >> 28);
-}
-
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_code_keep(float x, int e, uint32_t rinv, uint32_t& grid_bits)
-{
-    uint32_t mag = __float_as_uint(__builtin_ldexpf(__builtin_fabsf(x), e));
-    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    uint32_t t = mag + rinv;
-    grid_bits = t & 0xFFC00000u;
-    return (t >> 22) | ((__float_as_uint(x) >> 28) & 8u);
-}
-
-// round_S of a non-negative value whose sign nibble (0 or 8) is supplied separately.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_code_mag(float a, int e, uint32_t rinv, uint32_t sign8)
-{
-    uint32_t mag = __float_as_uint(__builtin_ldexpf(a, e));
-    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    return ((mag + rinv) >> 22) | sign8;
-}
-
-// round_D of a non-negative value a with the sign supplied separately (sign8 = 0 or 8).
-// Only for values whose scaled form is exact (E2M1 x 2^s or bf16 sources near a
-// threshold are): the tie then goes up in magnitude for +, down for -.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t rtn_code_mag(float a, int e, uint32_t sign8)
-{
-    uint32_t mag = __float_as_uint(__builtin_ldexpf(a, e));
-    if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    return ((mag + 0x200000u - (sign8 >> 3)) >> 22) | sign8;
-}
-
 // |value| of an E2M1 code times 2^s, from the same bit layout: (code & 7) << 22 is
 // m * 2^-126 as an FP32 pattern.  Exact in any rounding mode.
 __device__ __forceinline__ float dequant_mag(uint32_t code, uint32_t byte)
@@ -212,28 +140,29 @@ __device__ __forceinline__ uint32_t sr_field(const U4& r, int t)
     return (t & 1) ? (w >> 16) : (w & 0xFFFFu);
 }
 
-// The eight rounding addends ((65535 - r16) << 6) | 63 of an 8-element block, for sr_code().
+// The eight terms 64 * r16 - (2^22 - 1) of an 8-element block, which sr_grid() subtracts: mag - term carries into bit 22
+// iff p * 2^22 > 64 * r16.  (Subtracting takes r16 as it stands; adding ((65535 - r16) << 6) | 63 instead costs an
+// inversion of each random word, 4 of the 105 instructions a block takes.)
 struct U8 { uint32_t w[8]; };
 
-// (16-bit field of w) * 64 + 63 in one instruction; HIGH selects the upper field.
+// (16-bit field of w) * 64 - (2^22 - 1) in one instruction; HIGH selects the upper field.
 template <bool HIGH>
-__device__ __forceinline__ uint32_t field16_times64_plus63(uint32_t w)
+__device__ __forceinline__ uint32_t sr_term(uint32_t w)
 {
     uint32_t r;
-    if (HIGH) asm("v_mad_u32_u16 %0, %1, 64, 63 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w));
-    else      asm("v_mad_u32_u16 %0, %1, 64, 63" : "=v"(r) : "v"(w));
+    if (HIGH) asm("v_mad_u32_u16 %0, %1, 64, %2 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "s"(0xFFC00001u));
+    else      asm("v_mad_u32_u16 %0, %1, 64, %2" : "=v"(r) : "v"(w), "s"(0xFFC00001u));
     return r;
 }
 
-__device__ __forceinline__ U8 sr_addends(uint64_t blk, uint32_t tensor_id, uint32_t k0, uint32_t k1)
+__device__ __forceinline__ U8 sr_terms(uint64_t blk, uint32_t tensor_id, uint32_t k0, uint32_t k1)
 {
     U4 r = sr_block(blk, tensor_id, k0, k1);
     U8 a;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        uint32_t inv = ~r.w[i];                       // both 16-bit fields become 65535 - r16
-        a.w[2 * i] = field16_times64_plus63<false>(inv);
-        a.w[2 * i + 1] = field16_times64_plus63<true>(inv);
+        a.w[2 * i] = sr_term<false>(r.w[i]);
+        a.w[2 * i + 1] = sr_term<true>(r.w[i]);
     }
     return a;
 }
@@ -302,7 +231,7 @@ __device__ __forceinline__ float dequant_e3m0(uint32_t code, uint32_t byte)
 // What the quantizers use of them, each checked exhaustively against the integer forms above (all bf16 values x all
 // scale bytes; all 16 codes x all scale bytes), in every rounding mode: the mode does not enter.
 //   v_cvt_scalef32_pk_fp4_bf16   two bf16 values / 2^s, round to nearest even, saturated at 6  -> one byte
-//   v_cvt_scalef32_pk_fp4_f32    the same from FP32; here only a packer of values that are already on the grid
+//   v_cvt_scalef32_pk_fp4_f32    the same from FP32; also a packer of values that are already on the grid
 //   v_cvt_scalef32_pk_{f32,bf16}_fp4   two codes x 2^s -> two values, exact
 // 2^s is given as the FP32 pattern byte << 23 (byte 0 means 2^-127).  Cost, in cycles of a SIMD per wave instruction
 // with four waves on it: 9, 9 and 4.5 for two elements; a three-operand integer instruction takes 5, a two-operand
@@ -367,36 +296,50 @@ __device__ __forceinline__ uint32_t cvt_bf16_fp4(uint32_t codes, float scale)
 // round_S onto the grid layout.  Rounding mode toward plus infinity.  x: any value; x2: a value with at most two
 // significant bits (a dequantized one), whose low pattern bits are zero, so that one select merges sign and grid.
 template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_grid_sum(float x, int e, uint32_t rinv)
+__device__ __forceinline__ uint32_t sr_grid_sum(float x, int e, uint32_t term)
 {
     uint32_t mag = __float_as_uint(__builtin_ldexpf(__builtin_fabsf(x), e));
     if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    return mag + rinv;
+    return mag - term;
 }
 
 template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_grid(float x, int e, uint32_t rinv)
+__device__ __forceinline__ uint32_t sr_grid(float x, int e, uint32_t term)
 {
-    return __builtin_amdgcn_bitop3_b32(0x80000000u, sr_grid_sum<FLOOR>(x, e, rinv) & 0x7FC00000u, __float_as_uint(x), 0xEC);   // b | (a & c)
+    return __builtin_amdgcn_bitop3_b32(0x80000000u, sr_grid_sum<FLOOR>(x, e, term) & 0x7FC00000u, __float_as_uint(x), 0xEC);   // b | (a & c)
 }
 
 template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_grid_x2(float x2, int e, uint32_t rinv)
+__device__ __forceinline__ uint32_t sr_grid_x2(float x2, int e, uint32_t term)
 {
-    return __builtin_amdgcn_bitop3_b32(0x7FC00000u, sr_grid_sum<FLOOR>(x2, e, rinv), __float_as_uint(x2), 0xCA);               // a ? b : c
+    return __builtin_amdgcn_bitop3_b32(0x7FC00000u, sr_grid_sum<FLOOR>(x2, e, term), __float_as_uint(x2), 0xCA);               // a ? b : c
 }
 
-// round_D onto the grid layout (see rtn_code_keep).
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t rtn_grid(float x, int e)
+// round_D of FP32 values.  The conversion sends ties to the even code; as for bf16 (ties_to_larger), a threshold's FP32
+// pattern is even, so moving even patterns one unit toward +infinity decides ties and moves nothing else across a
+// threshold.  -0 stays a negative zero through the saturating addition.  Checked against the integer form (scale to the
+// grid, add half a unit, cut) on 7.7e8 values: all scale bytes, thresholds and their neighbours, subnormals, both scale
+// rules.  3.5 instructions per element instead of 5.
+__device__ __forceinline__ float ties_to_larger_f32(float x)
 {
-    uint32_t vb = __float_as_uint(__builtin_ldexpf(x, e));
-    if (FLOOR) {
-        uint32_t mag = vb & 0x7FFFFFFFu;
-        mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-        vb = mag | (vb & 0x80000000u);
-    }
-    return (vb + 0x200000u + (uint32_t)((int32_t)vb >> 31)) & 0xFFC00000u;
+    const int32_t v = (int32_t)__float_as_uint(x);
+    return __uint_as_float((uint32_t)__builtin_elementwise_add_sat(v, v >> 31) | 1u);
+}
+
+// byte SEL of `old` <- codes of round_D(x0 / 2^s), round_D(x1 / 2^s), scale as scale_operand()
+template <int SEL>
+__device__ __forceinline__ uint32_t cvt_rtn_f32(uint32_t old, float x0, float x1, float scale)
+{
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, ties_to_larger_f32(x0), ties_to_larger_f32(x1), scale, SEL);
+}
+
+__device__ __forceinline__ uint32_t rtn_codes8_f32(const float (&x)[8], uint32_t byte)
+{
+    const float s = scale_operand(byte);
+    uint32_t p = cvt_rtn_f32<0>(0u, x[0], x[1], s);
+    p = cvt_rtn_f32<1>(p, x[2], x[3], s);
+    p = cvt_rtn_f32<2>(p, x[4], x[5], s);
+    return cvt_rtn_f32<3>(p, x[6], x[7], s);
 }
 
 // Scale bytes of two group maxima at once, given as bf16 patterns of |x| in the halves of m (see scale_byte: a bf16
@@ -411,14 +354,13 @@ __device__ __forceinline__ uint32_t scale_bytes_bf16(uint32_t m)
     return bits_as<uint32_t>((u16x2)(b + (u16x2)(nonzero * (unsigned short)(0u - 98u) + (unsigned short)98)));
 }
 
-// |x| maximum of 8 bf16 values as a bf16 pattern in both halves, over the 4 lanes of a row group
-__device__ __forceinline__ uint32_t quad_amax_bf16(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
+// |x| maxima of two rows over the 4 lanes of a row group, row 0 in the low half and row 1 in the high half.  m0, m1: a
+// lane's maxima of each row as bf16 patterns, two partial ones per register.
+__device__ __forceinline__ uint32_t quad_amax_bf16_rows(uint32_t m0, uint32_t m1)
 {
-    const uint32_t k = 0x7FFF7FFFu;
-    uint32_t m = pk_max(pk_max(w0 & k, w1 & k), pk_max(w2 & k, w3 & k));
+    uint32_t m = pk_max(__builtin_amdgcn_perm(m1, m0, 0x05040100u), __builtin_amdgcn_perm(m1, m0, 0x07060302u));
     m = pk_max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xB1, 0xF, 0xF, true));      // lane ^ 1
-    m = pk_max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, true));      // lane ^ 2
-    return pk_max(m, __builtin_amdgcn_alignbit(m, m, 16));
+    return pk_max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, true));   // lane ^ 2
 }
 
 // Maxima over the 8 lanes that share lane % 8 (the row groups of a wave tile), of four values at once.  A lane-swap

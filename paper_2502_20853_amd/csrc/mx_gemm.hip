@@ -640,16 +640,13 @@ __device__ __forceinline__ void gemm_epilogue_gelu_quant(const GemmArgs& g, lds_
             const auto sw = __builtin_amdgcn_permlane32_swap(m, m, false, false);
             m = sw[0] > sw[1] ? sw[0] : sw[1];
             const uint32_t byte = mxd::scale_byte(m, FLOOR);
-            const int e = mxd::grid_exponent(byte);
-            mxd::f32_round_toward_minus_inf();              // round_D's mode for inexact subnormal scalings
+            const float scale = mxd::scale_operand(byte);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                uint32_t pk = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) pk |= mxd::rtn_code<FLOOR>(v[4 * q + r], e) << (4 * r);
+                uint32_t pk = mxd::cvt_rtn_f32<0>(0u, v[4 * q], v[4 * q + 1], scale);
+                pk = mxd::cvt_rtn_f32<1>(pk, v[4 * q + 2], v[4 * q + 3], scale);
                 *reinterpret_cast<lds_u16*>(ep + (i * 32 + lrow) * 64 + 16 * j + 4 * q + 2 * lhalf) = (uint16_t)pk;
             }
-            mxd::f32_round_to_nearest_even();
             if (lhalf == 0) scale_strip[(i * 32 + lrow) * 4 + j] = (uint8_t)byte;
         }
     asm volatile("" ::: "memory");          // the strip is read back below through other lanes' addresses

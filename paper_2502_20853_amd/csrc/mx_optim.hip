@@ -215,16 +215,7 @@ __device__ __forceinline__ uint32_t rtn_codes8(const float (&x)[8], uint32_t& by
 #pragma unroll
     for (int t = 0; t < 8; ++t) f.v[t] = x[t];
     byte = scale_byte(quad_max(amax_bits8(f)), FLOOR);
-    const int e = grid_exponent(byte);
-    f32_round_toward_minus_inf();
-    uint32_t g[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) g[t] = rtn_grid<FLOOR>(x[t], e);
-    f32_round_to_nearest_even();
-    uint32_t p = pack_grid<0>(0u, g[0], g[1]);
-    p = pack_grid<1>(p, g[2], g[3]);
-    p = pack_grid<2>(p, g[4], g[5]);
-    return pack_grid<3>(p, g[6], g[7]);
+    return rtn_codes8_f32(x, byte);
 }
 
 __device__ __forceinline__ void dequantize8(uint32_t codes, uint32_t byte, float (&x)[8])

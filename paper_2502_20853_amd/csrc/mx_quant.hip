@@ -45,25 +45,66 @@ struct RowsArgs {
     int update_ema;
 };
 
-// Encode 8 elements of one group (inv = 2^-s) and pack them low nibble first.  The FP32
-// rounding mode must be set for the rounding in use (see rtn_code / sr_code).
-template <bool SR, bool FLOOR>
-__device__ __forceinline__ uint32_t encode8(const F8& x, int e, const U8& add)
-{
-    uint32_t packed = 0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        uint32_t c = SR ? sr_code<FLOOR>(x.v[t], e, add.w[t]) : rtn_code<FLOOR>(x.v[t], e);
-        packed |= c << (4 * t);
-    }
-    return packed;
-}
-
+// Rounding mode of the integer forms (see mx_device.hpp); round_D of E2M1 goes through the conversion instructions, in
+// any mode.
 template <bool SR>
 __device__ __forceinline__ void set_round_mode_for()
 {
     if (SR) f32_round_toward_plus_inf();
     else    f32_round_toward_minus_inf();
+}
+
+// Eight source elements of one row, as loaded: bf16 values stay packed in pairs.
+template <typename SrcT> using Raw8 = std::conditional_t<std::is_same_v<SrcT, float>, F8, bf16x8_raw>;
+
+__device__ __forceinline__ F8 load_raw8(const float* p) { return load8(p); }
+__device__ __forceinline__ bf16x8_raw load_raw8(const uint16_t* p) { return load8_raw(p); }
+
+__device__ __forceinline__ float element_of(const F8& r, int t) { return r.v[t]; }
+__device__ __forceinline__ float element_of(const bf16x8_raw& r, int t)
+{
+    return __uint_as_float((t & 1) ? r[t >> 1] & 0xFFFF0000u : r[t >> 1] << 16);
+}
+
+__device__ __forceinline__ uint32_t abs_max_bf16(const bf16x8_raw& x)                 // two partial maxima
+{
+    const uint32_t k = 0x7FFF7FFFu;
+    return pk_max(pk_max(x[0] & k, x[1] & k), pk_max(x[2] & k, x[3] & k));
+}
+
+// Scale byte of a row group from the lane's own eight elements.
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t row_scale_byte(const F8& x) { return scale_byte(quad_max(amax_bits8(x)), FLOOR); }
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t row_scale_byte(const bf16x8_raw& x)
+{
+    const uint32_t m = abs_max_bf16(x);
+    return scale_bytes_bf16<FLOOR>(quad_amax_bf16_rows(m, m)) & 0xFFFFu;
+}
+
+// Codes of eight elements of a row, low nibble first.  SR: with sr_terms() of the block, in the rounding mode of round_S.
+__device__ __forceinline__ uint32_t rtn_codes8(const bf16x8_raw& x, uint32_t byte)
+{
+    const float s = scale_operand(byte);
+    uint32_t p = cvt_fp4_bf16<0>(0u, ties_to_larger(x[0]), s);
+    p = cvt_fp4_bf16<1>(p, ties_to_larger(x[1]), s);
+    p = cvt_fp4_bf16<2>(p, ties_to_larger(x[2]), s);
+    return cvt_fp4_bf16<3>(p, ties_to_larger(x[3]), s);
+}
+
+__device__ __forceinline__ uint32_t rtn_codes8(const F8& x, uint32_t byte) { return rtn_codes8_f32(x.v, byte); }
+
+template <bool FLOOR, typename RAW>
+__device__ __forceinline__ uint32_t sr_codes8(const RAW& x, uint32_t byte, const U8& rnd)
+{
+    const int e = grid_exponent(byte);
+    uint32_t g[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) g[t] = sr_grid<FLOOR>(element_of(x, t), e, rnd.w[t]);
+    uint32_t p = pack_grid<0>(0u, g[0], g[1]);
+    p = pack_grid<1>(p, g[2], g[3]);
+    p = pack_grid<2>(p, g[4], g[5]);
+    return pack_grid<3>(p, g[6], g[7]);
 }
 
 // The 1x32 quantizer with E3M0 elements (format ablation, Table 7): same work split as
@@ -98,18 +139,21 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_e3m0_kernel(RowsAr
     }
 }
 
+// Bound by memory: 25216 x 1536 bf16 in 18 us (round_D) and 20 us (round_S), 5.1 TB/s, the rate of a large copy on the
+// card.  With codes taken from the grid sums and packed by shifts it was bound by the vector ALUs, 22.8 and 26.7 us.
 template <typename SrcT, bool SR, bool FLOOR>
 __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
 {
-    set_round_mode_for<SR>();
+    if (SR) f32_round_toward_plus_inf();
     const SrcT* src = static_cast<const SrcT*>(a.src);
     const uint32_t q0 = blockIdx.x * (ROWS_THREADS * ROWS_UNROLL) + threadIdx.x;
-    F8 x[ROWS_UNROLL];
+    Raw8<SrcT> x[ROWS_UNROLL];
     bool ok[ROWS_UNROLL];
 #pragma unroll
     for (int u = 0; u < ROWS_UNROLL; ++u) {
         uint32_t q = q0 + u * ROWS_THREADS;
         ok[u] = q < a.total && q >= q0;
+        x[u] = Raw8<SrcT>{};
         if (ok[u]) {
             int64_t off;
             if (a.contiguous) {
@@ -118,19 +162,16 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
                 uint32_t r = q / a.cpr;
                 off = (int64_t)r * a.ld + (int64_t)(q - r * a.cpr) * 8;
             }
-            x[u] = load8(src + off);
-        } else {
-            x[u] = zero8();
+            x[u] = load_raw8(src + off);
         }
     }
 #pragma unroll
     for (int u = 0; u < ROWS_UNROLL; ++u) {
         uint32_t q = q0 + u * ROWS_THREADS;
-        uint32_t m = quad_max(amax_bits8(x[u]));
-        uint32_t byte = scale_byte(m, FLOOR);
-        U8 rnd;
-        if (SR) rnd = sr_addends(a.base_blk + q, a.tensor_id, a.k0, a.k1);
-        uint32_t packed = encode8<SR, FLOOR>(x[u], grid_exponent(byte), rnd);
+        const uint32_t byte = row_scale_byte<FLOOR>(x[u]);
+        uint32_t packed;
+        if constexpr (SR) packed = sr_codes8<FLOOR>(x[u], byte, sr_terms(a.base_blk + q, a.tensor_id, a.k0, a.k1));
+        else              packed = rtn_codes8(x[u], byte);
         if (ok[u]) {
             reinterpret_cast<uint32_t*>(a.codes)[q] = packed;
             if ((threadIdx.x & 3) == 0) a.scales[q >> 2] = (uint8_t)byte;
@@ -155,23 +196,24 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_batch_kernel(RowsB
         for (uint32_t i = threadIdx.x; i < b.widen.count; i += ROWS_THREADS) b.widen.dst[i] = __uint_as_float((uint32_t)b.widen.src[i] << 16);
         return;
     }
-    set_round_mode_for<false>();
     const int j = blockIdx.x >= b.first1 ? 1 : 0;
     const RowsArgs& a = b.job[j];
     const uint32_t q0 = (blockIdx.x - (j ? b.first1 : 0u)) * (ROWS_THREADS * UNROLL) + threadIdx.x;
     auto run = [&](auto tag) {
-        const auto* src = static_cast<const decltype(tag)*>(a.src);
-        F8 x[UNROLL];
+        using SrcT = decltype(tag);
+        const SrcT* src = static_cast<const SrcT*>(a.src);
+        Raw8<SrcT> x[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const uint32_t q = q0 + u * ROWS_THREADS;
-            x[u] = q < a.total ? load8(src + (size_t)q * 8) : zero8();
+            x[u] = Raw8<SrcT>{};
+            if (q < a.total) x[u] = load_raw8(src + (size_t)q * 8);
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const uint32_t q = q0 + u * ROWS_THREADS;
-            const uint32_t byte = scale_byte(quad_max(amax_bits8(x[u])), FLOOR);
-            const uint32_t packed = encode8<false, FLOOR>(x[u], grid_exponent(byte), U8{});
+            const uint32_t byte = row_scale_byte<FLOOR>(x[u]);
+            const uint32_t packed = rtn_codes8(x[u], byte);
             if (q < a.total) {
                 reinterpret_cast<uint32_t*>(a.codes)[q] = packed;
                 if ((threadIdx.x & 3) == 0) a.scales[q >> 2] = (uint8_t)byte;
@@ -413,7 +455,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 
     // A lane's four rows of 8 elements, as loaded: bf16 values stay packed in pairs, packed results stay codes.
     // The next tile's are fetched while the current one is encoded.
-    using Row = std::conditional_t<SRC == 0, F8, bf16x8_raw>;
+    using Row = Raw8<std::conditional_t<SRC == 0, float, uint16_t>>;
     struct Tile {
         Row x[SRC == 2 ? 1 : 4];
         uint32_t pk[SRC == 2 ? 4 : 1], byte[SRC == 2 ? 4 : 1];
@@ -445,10 +487,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
             }
         }
     };
-    auto element = [](const Row& r, int t) -> float {
-        if constexpr (SRC == 0) return r.v[t];
-        else                    return __uint_as_float((t & 1) ? r[t >> 1] & 0xFFFF0000u : r[t >> 1] << 16);
-    };
+    auto element = [](const Row& r, int t) -> float { return element_of(r, t); };
 
     constexpr bool PREFETCH = SRC != 0;                   // an FP32 tile's 32 registers do not fit twice in 128
     Tile cur, nxt;
@@ -475,46 +514,53 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
             reinterpret_cast<float*>(st + ST_CSUM_OFF)[wr * 128 + lcol0 + column_of_sum(lane)] = sum_row_groups8(cs, lane);
             __builtin_amdgcn_sched_barrier(0);            // the random numbers of later phases stay out of this one's registers
         }
+        // ---- bf16: group maxima, scale bytes of two rows per register ----
+        // The magnitudes serve the row maxima and, where the column groups take the source itself, the column maxima.
+        const bool rows_wanted = want_row || a.pre_quant;
+        uint32_t rbytes[2], cmax[4];
+        if constexpr (SRC == 1) {
+            auto maxima = [&](auto rows_c, auto cols_c) {
+                uint32_t rm[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t k[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) k[i] = cur.x[j][i] & 0x7FFF7FFFu;
+                    if constexpr (rows_c.value) rm[j] = pk_max(pk_max(k[0], k[1]), pk_max(k[2], k[3]));
+                    if constexpr (cols_c.value) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) cmax[i] = j ? pk_max(cmax[i], k[i]) : k[i];
+                    }
+                }
+                if constexpr (rows_c.value) {
+                    rbytes[0] = scale_bytes_bf16<FLOOR>(quad_amax_bf16_rows(rm[0], rm[1]));
+                    rbytes[1] = scale_bytes_bf16<FLOOR>(quad_amax_bf16_rows(rm[2], rm[3]));
+                }
+            };
+            if (a.pre_quant)   maxima(std::true_type{}, std::false_type{});
+            else if (want_row) maxima(std::true_type{}, std::true_type{});
+            else               maxima(std::false_type{}, std::true_type{});
+        }
         // ---- 1x32 quantizer: codes of the lane's four rows and their scales ----
         uint32_t pk[4];
         float row_scale[4];
         if constexpr (SRC == 2) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) { pk[j] = cur.pk[j]; row_scale[j] = scale_operand(cur.byte[j]); }
-        } else if (want_row || a.pre_quant) {
-            set_round_mode_for<ROW_SR>();
+        } else if (rows_wanted) {
+            if (ROW_SR) f32_round_toward_plus_inf();
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const Row& x = cur.x[j];
                 uint32_t byte;
-                if constexpr (SRC == 0) byte = scale_byte(quad_max(amax_bits8(x)), FLOOR);
-                else                    byte = scale_bytes_bf16<FLOOR>(quad_amax_bf16(x[0], x[1], x[2], x[3])) & 0xFFu;
+                if constexpr (SRC == 0) byte = row_scale_byte<FLOOR>(cur.x[j]);
+                else                    byte = (j & 1) ? rbytes[j >> 1] >> 16 : rbytes[j >> 1] & 0xFFFFu;
                 row_scale[j] = scale_operand(byte);
-                uint32_t p = 0u;
-                if constexpr (SRC == 1 && !ROW_SR) {
-                    p = cvt_fp4_bf16<0>(p, ties_to_larger(x[0]), row_scale[j]);
-                    p = cvt_fp4_bf16<1>(p, ties_to_larger(x[1]), row_scale[j]);
-                    p = cvt_fp4_bf16<2>(p, ties_to_larger(x[2]), row_scale[j]);
-                    p = cvt_fp4_bf16<3>(p, ties_to_larger(x[3]), row_scale[j]);
-                } else {
-                    const int e = grid_exponent(byte);
-                    uint32_t g[8];
-                    if constexpr (ROW_SR) {
-                        const U8 rnd = sr_addends(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_row, k0, k1);
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) g[t] = sr_grid<FLOOR>(element(x, t), e, rnd.w[t]);
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) g[t] = rtn_grid<FLOOR>(element(x, t), e);
-                    }
-                    p = pack_grid<0>(p, g[0], g[1]);
-                    p = pack_grid<1>(p, g[2], g[3]);
-                    p = pack_grid<2>(p, g[4], g[5]);
-                    p = pack_grid<3>(p, g[6], g[7]);
-                }
-                pk[j] = p;
+                if constexpr (ROW_SR)
+                    pk[j] = sr_codes8<FLOOR>(cur.x[j], byte, sr_terms(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_row, k0, k1));
+                else
+                    pk[j] = rtn_codes8(cur.x[j], byte);
                 if (want_row) {
-                    *reinterpret_cast<uint32_t*>(st + ST_ROW_OFF + (lrow0 + j) * ST_PITCH + (lcol0 >> 1)) = p;
+                    *reinterpret_cast<uint32_t*>(st + ST_ROW_OFF + (lrow0 + j) * ST_PITCH + (lcol0 >> 1)) = pk[j];
                     if ((cc & 3) == 0) st[ST_SROW_OFF + (lrow0 + j) * 8 + (lcol0 >> 5)] = (uint8_t)byte;
                 }
             }
@@ -522,6 +568,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
         // ---- 32x1 quantizer: group = this lane's 4 rows x the 8 lanes sharing cc ----
         // Scale bytes of the lane's eight columns, two per register: byte_of(t).
         uint32_t sb[4];
+        auto column_byte = [&](int t) { return (t & 1) ? sb[t >> 1] >> 16 : sb[t >> 1] & 0xFFFFu; };      // (FP32 sources: see there)
         auto store_column_bytes = [&](uint32_t two, uint32_t first, uint32_t step) {
             // rows of 16 lanes 0..3 hold the columns first + step * {0, 2, 1, 3}: the lanes of each row's first half write
             if ((lane & 8) == 0) {
@@ -538,7 +585,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
         uint32_t colpk[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) colpk[t] = 0u;
-        auto addends = [&](int j) { return sr_addends(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_t, k0, k1); };
+        auto terms = [&](int j) { return sr_terms(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_t, k0, k1); };
         if (SRC == 2 || a.pre_quant) {
             uint32_t m[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -550,44 +597,41 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                 m[3] = pk_max(m[3], cvt_bf16_fp4<3>(mags, row_scale[j]));
             }
             column_bytes_bf16(m);
-            set_round_mode_for<T_SR>();
+            if (T_SR) f32_round_toward_plus_inf();
             static_for_pair([&](auto jp_c) {
                 constexpr int jp = decltype(jp_c)::value;
-                uint32_t g[2][8];
+                float d[2][8];                            // T_SR: on the grid; otherwise the dequantized values
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     const int j = 2 * jp + r;
                     U8 rnd;
-                    if (T_SR) rnd = addends(j);
+                    if (T_SR) rnd = terms(j);
                     const f32x2_hw v[4] = {cvt_f32_fp4<0>(pk[j], row_scale[j]), cvt_f32_fp4<1>(pk[j], row_scale[j]),
                                            cvt_f32_fp4<2>(pk[j], row_scale[j]), cvt_f32_fp4<3>(pk[j], row_scale[j])};
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        const int e = 1 - (int)((t & 1) ? sb[t >> 1] >> 16 : sb[t >> 1] & 0xFFFFu);
-                        g[r][t] = T_SR ? sr_grid_x2<FLOOR>(v[t >> 1][t & 1], e, rnd.w[t]) : rtn_grid<FLOOR>(v[t >> 1][t & 1], e);
+                        d[r][t] = v[t >> 1][t & 1];
+                        if (T_SR) d[r][t] = __uint_as_float(sr_grid_x2<FLOOR>(d[r][t], 1 - (int)column_byte(t), rnd.w[t]));
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                for (int t = 0; t < 8; ++t)
+                    colpk[t] = T_SR ? pack_grid<jp>(colpk[t], __float_as_uint(d[0][t]), __float_as_uint(d[1][t]))
+                                    : cvt_rtn_f32<jp>(colpk[t], d[0][t], d[1][t], scale_operand(column_byte(t)));
             });
         } else if constexpr (SRC == 1) {
-            const uint32_t k = 0x7FFF7FFFu;
-            uint32_t m[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) m[i] = pk_max(pk_max(cur.x[0][i] & k, cur.x[1][i] & k), pk_max(cur.x[2][i] & k, cur.x[3][i] & k));
-            column_bytes_bf16(m);
-            set_round_mode_for<T_SR>();
+            column_bytes_bf16(cmax);
+            if (T_SR) f32_round_toward_plus_inf();
             static_for_pair([&](auto jp_c) {
                 constexpr int jp = decltype(jp_c)::value;
                 if constexpr (T_SR) {
                     uint32_t g[2][8];
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
-                        const U8 rnd = addends(2 * jp + r);
+                        const U8 rnd = terms(2 * jp + r);
 #pragma unroll
                         for (int t = 0; t < 8; ++t) {
-                            const int e = 1 - (int)((t & 1) ? sb[t >> 1] >> 16 : sb[t >> 1] & 0xFFFFu);
-                            g[r][t] = sr_grid<FLOOR>(element(cur.x[2 * jp + r], t), e, rnd.w[t]);
+                            g[r][t] = sr_grid<FLOOR>(element(cur.x[2 * jp + r], t), 1 - (int)column_byte(t), rnd.w[t]);
                         }
                     }
 #pragma unroll
@@ -614,22 +658,25 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
             const uint32_t two = scale_byte(reduce_row_groups4(lo, umax), FLOOR) | scale_byte(reduce_row_groups4(hi, umax), FLOOR) << 16;
             store_column_bytes(two, place, 4u);
             spread_row_groups4(two, sb);
-            set_round_mode_for<T_SR>();
+            if (T_SR) f32_round_toward_plus_inf();
             static_for_pair([&](auto jp_c) {
                 constexpr int jp = decltype(jp_c)::value;
-                uint32_t g[2][8];
+                auto byte_f32 = [&](int t) { return t >= 4 ? sb[t & 3] >> 16 : sb[t & 3] & 0xFFFFu; };
+                if constexpr (T_SR) {
+                    uint32_t g[2][8];
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    U8 rnd;
-                    if (T_SR) rnd = addends(2 * jp + r);
+                    for (int r = 0; r < 2; ++r) {
+                        const U8 rnd = terms(2 * jp + r);
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        const int e = 1 - (int)(t >= 4 ? sb[t & 3] >> 16 : sb[t & 3] & 0xFFFFu);
-                        g[r][t] = T_SR ? sr_grid<FLOOR>(cur.x[2 * jp + r].v[t], e, rnd.w[t]) : rtn_grid<FLOOR>(cur.x[2 * jp + r].v[t], e);
+                        for (int t = 0; t < 8; ++t) g[r][t] = sr_grid<FLOOR>(cur.x[2 * jp + r].v[t], 1 - (int)byte_f32(t), rnd.w[t]);
                     }
-                }
 #pragma unroll
-                for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        colpk[t] = cvt_rtn_f32<jp>(colpk[t], cur.x[2 * jp].v[t], cur.x[2 * jp + 1].v[t], scale_operand(byte_f32(t)));
+                }
             });
         }
 #pragma unroll
