@@ -66,10 +66,10 @@ def gelu_fp32(x, coef, t0):
     yl = fma(s, l2, yl)
     e = np.exp2(-yh.astype(np.float64)).astype(F32)
     e = np.where(e < F32(1.1754944e-38), F32(0), e)            # results below the normal range are flushed
-    c = fma(yl, -float(F32(np.log(2.0))), 1.0)
-    c = fma(r, -0.5, c)
-    h = mul(mul(mul(g, e), c), 0.5)
-    return mul(x, np.where(x < 0, h, (F32(1) - h).astype(F32)))
+    c = fma(yl, -float(F32(np.log(2.0) / 2)), 0.5)
+    c = fma(r, -0.25, c)
+    h = mul(mul(g, e), c)
+    return fma(-np.abs(x), h, np.where(x < 0, F32(-0.0), x))
 
 
 def main():
