@@ -271,26 +271,36 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 // ---------------------------------------------------------------------------
 // Transposed / fused quantizer.
 //
-// A workgroup of 8 waves owns a 256 x 128 macro tile of the source (256 x 64 for small tensors
-// and for the tiles of a sparsely filled last round); wave w owns rows [32w, 32w+32) of it and
+// A workgroup of 4 waves owns a 128 x 128 macro tile of the source (128 x 64 for small tensors and for the tiles of a
+// sparsely filled last round); with column sums, which are kept per 256 rows, it has 8 waves and 256 rows.  Wave w owns rows [32w, 32w+32) of it and
 // walks over its 32 x 64 tiles.  The grid is one-dimensional over the macro tiles in row-major order.
 // Inside a tile, lane l holds rows 4*(l/8)+j (j = 0..3) x columns 8*(l%8)+t (t = 0..7):
 //   - each load instruction reads 8 full rows of 64 elements,
 //   - a 1x32 row group is 4 neighbouring lanes (DPP quad reduction),
 //   - a 32x1 column group is 4 registers x 8 lanes (l/8 = 0..7) of one column.
 // The 32 elements of a lane stay in registers through both quantizers.  Codes and scale
-// bytes are collected in LDS ([256 rows][128 B] row codes, [256 columns][128 B] transposed
-// codes) and written out at the end as whole 128-byte lines, 16 bytes per lane.
+// bytes are collected in LDS and written out at the end in lines of 64 bytes (8 waves: transposed codes 128), 16 bytes per
+// lane.  Registers allow 16 waves on a compute unit (20 from packed codes, which keep fewer).  Four small workgroups there
+// are seldom all loading or all storing at once, two large ones often are, and a small tensor's waves spread over
+// more units.  8 -> 4 waves: 50432 x 768 bf16 activation 39 -> 37 us, 50432 x 3072 121 -> 112, 25216 x 384 FP32
+// 20 -> 18, from packed codes 25216 x 3072 49 -> 42, 256 x 192 FP32 with its weight 7.0 -> 5.7.  Two waves, 64 columns, or five waves per
+// SIMD (spills) are slower: 39, 40 and 43 us for the first of these.
 // ---------------------------------------------------------------------------
-constexpr int TILE_THREADS = 512;
-constexpr int ST_PITCH = 144;                       // bytes per staged row / column of codes (128 + pad)
-constexpr int ST_ROW_OFF = 0;                       // row codes      [256][ST_PITCH]
-constexpr int ST_COL_OFF = 256 * ST_PITCH;          // transposed     [256][ST_PITCH]
-constexpr int ST_SROW_OFF = 2 * 256 * ST_PITCH;     // row scales     [256][8]
-constexpr int ST_SCOL_OFF = ST_SROW_OFF + 256 * 8;  // transposed scales [256][8]
-constexpr int ST_BYTES = ST_SCOL_OFF + 256 * 8;     // 77824: two workgroups per CU
-constexpr int ST_CSUM_OFF = ST_BYTES;               // COLSUM instances: column sums per wave, [8][128] floats
-constexpr int ST_BYTES_CSUM = ST_BYTES + 8 * 128 * 4; // 81920: still two workgroups per CU
+// Waves of a macro tile and what it stages in LDS, sized for macro tiles of 32 * WAVES rows x 128 columns.
+constexpr int tile_waves(bool colsum) { return colsum ? 8 : 4; }
+
+template <int WAVES, bool ROWS, bool COLSUM>
+struct TileShape {
+    static constexpr int THREADS = 64 * WAVES, MACRO_ROWS = 32 * WAVES, MACRO_COLS = 128;
+    static constexpr int ROW_PITCH = MACRO_COLS / 2 + 16, COL_PITCH = MACRO_ROWS / 2 + 16;   // bytes per staged line (codes + pad)
+    static constexpr int ROW_SCALES = MACRO_COLS / 32, COL_SCALES = MACRO_ROWS / 32;         // scale bytes of a line
+    static constexpr int ROW_OFF = 0;                                                        // row codes     [MACRO_ROWS][ROW_PITCH]
+    static constexpr int SROW_OFF = ROW_OFF + (ROWS ? MACRO_ROWS * ROW_PITCH : 0);           // row scales    [MACRO_ROWS][ROW_SCALES]
+    static constexpr int COL_OFF = SROW_OFF + (ROWS ? MACRO_ROWS * ROW_SCALES : 0);          // transposed    [MACRO_COLS][COL_PITCH]
+    static constexpr int SCOL_OFF = COL_OFF + MACRO_COLS * COL_PITCH;                        // their scales  [MACRO_COLS][COL_SCALES]
+    static constexpr int CSUM_OFF = SCOL_OFF + MACRO_COLS * COL_SCALES;                      // column sums per wave [WAVES][MACRO_COLS] floats
+    static constexpr int BYTES = CSUM_OFF + (COLSUM ? WAVES * MACRO_COLS * 4 : 0);
+};
 
 struct TileArgs {
     const void* src;
@@ -305,10 +315,10 @@ struct TileArgs {
     uint32_t src_rows;     // rows the source has; rows from there up to `rows` are zero
     int pre_quant;
     int src_bf16;          // instances for both source types: which one this job reads
-    // 1-D grid over macro tiles in row-major order: the first n_wide workgroups own 256 x 128 tiles
-    // (two 32 x 64 tiles per wave), the rest own the two 256 x 64 halves of the tiles after those
+    // 1-D grid over macro tiles in row-major order: the first n_wide workgroups own tiles of 128 columns
+    // (two 32 x 64 tiles per wave), the rest own the two halves of 64 columns of the tiles after those
     uint32_t n_wide;
-    uint32_t wide_per_row; // 256 x 128 tiles per block of 256 rows = ceil(cols / 128)
+    uint32_t wide_per_row; // tiles per block of rows = ceil(cols / 128)
     uint32_t k0, k1, tensor_id_t, tensor_id_row;
     uint64_t index_base;
     const uint32_t* seed_dev;  // when set: the two key words are read from here instead of k0, k1
@@ -316,11 +326,12 @@ struct TileArgs {
 };
 
 // Copies one staged result of a macro tile to memory: `lines` staged lines (rows of row codes, or
-// columns of transposed codes), each `pieces` 16-byte pieces of codes (ST_PITCH apart in LDS,
-// `code_pitch` bytes apart in memory) and `pieces` scale bytes (8 apart in LDS, `scale_pitch` apart
-// in memory); pieces <= 8.  A lane keeps its piece and steps over the lines, so the loop has no
+// columns of transposed codes), each `pieces` 16-byte pieces of codes (PITCH apart in LDS,
+// `code_pitch` bytes apart in memory) and `pieces` scale bytes (SCALES apart in LDS, `scale_pitch` apart
+// in memory); pieces <= SCALES.  A lane keeps its piece and steps over the lines, so the loop has no
 // index arithmetic beyond two additions; when a line's scale bytes form an aligned 8- or 4-byte
 // word they leave as one store.
+template <int THREADS, int PITCH, int SCALES>
 __device__ __forceinline__ void write_staged(const uint8_t* codes_st, const uint8_t* scales_st,
                                              uint32_t lines, uint32_t pieces,
                                              uint8_t* codes, size_t code_pitch,
@@ -328,32 +339,32 @@ __device__ __forceinline__ void write_staged(const uint8_t* codes_st, const uint
 {
     if ((pieces & (pieces - 1u)) == 0u) {
         const uint32_t sh = (uint32_t)__builtin_ctz(pieces);
-        const uint32_t lstep = (uint32_t)TILE_THREADS >> sh;
+        const uint32_t lstep = (uint32_t)THREADS >> sh;
         uint32_t l = tid >> sh;
         const uint32_t pc = tid & (pieces - 1u);
-        const uint8_t* s = codes_st + l * ST_PITCH + pc * 16;
+        const uint8_t* s = codes_st + l * PITCH + pc * 16;
         uint8_t* d = codes + (size_t)l * code_pitch + pc * 16;
         const size_t dstep = (size_t)lstep * code_pitch;
-        for (; l < lines; l += lstep, s += lstep * ST_PITCH, d += dstep)
+        for (; l < lines; l += lstep, s += lstep * PITCH, d += dstep)
             *reinterpret_cast<uint4*>(d) = *reinterpret_cast<const uint4*>(s);
     } else {
-        for (uint32_t q = tid; q < lines * pieces; q += TILE_THREADS) {
+        for (uint32_t q = tid; q < lines * pieces; q += THREADS) {
             const uint32_t l = q / pieces, pc = q - l * pieces;
             *reinterpret_cast<uint4*>(codes + (size_t)l * code_pitch + pc * 16) =
-                *reinterpret_cast<const uint4*>(codes_st + l * ST_PITCH + pc * 16);
+                *reinterpret_cast<const uint4*>(codes_st + l * PITCH + pc * 16);
         }
     }
     const bool word_ok = ((reinterpret_cast<uintptr_t>(scales) | scale_pitch) & (pieces - 1u)) == 0u;
-    if (pieces == 8u && word_ok) {
-        for (uint32_t l = tid; l < lines; l += TILE_THREADS)
-            *reinterpret_cast<uint2*>(scales + (size_t)l * scale_pitch) = *reinterpret_cast<const uint2*>(scales_st + l * 8);
+    if (SCALES == 8 && pieces == 8u && word_ok) {
+        for (uint32_t l = tid; l < lines; l += THREADS)
+            *reinterpret_cast<uint2*>(scales + (size_t)l * scale_pitch) = *reinterpret_cast<const uint2*>(scales_st + l * SCALES);
     } else if (pieces == 4u && word_ok) {
-        for (uint32_t l = tid; l < lines; l += TILE_THREADS)
-            *reinterpret_cast<uint32_t*>(scales + (size_t)l * scale_pitch) = *reinterpret_cast<const uint32_t*>(scales_st + l * 8);
+        for (uint32_t l = tid; l < lines; l += THREADS)
+            *reinterpret_cast<uint32_t*>(scales + (size_t)l * scale_pitch) = *reinterpret_cast<const uint32_t*>(scales_st + l * SCALES);
     } else {
-        for (uint32_t q = tid; q < lines * 8u; q += TILE_THREADS) {
-            const uint32_t l = q >> 3, pc = q & 7u;
-            if (pc < pieces) scales[(size_t)l * scale_pitch + pc] = scales_st[l * 8 + pc];
+        for (uint32_t q = tid; q < lines * SCALES; q += THREADS) {
+            const uint32_t l = q / SCALES, pc = q % SCALES;
+            if (pc < pieces) scales[(size_t)l * scale_pitch + pc] = scales_st[l * SCALES + pc];
         }
     }
 }
@@ -411,7 +422,7 @@ __device__ __forceinline__ void widen_bf16(const mxl::WidenJob& j, uint32_t tid,
 // SRC: 0 = FP32 source, 1 = bf16 source, 2 = packed row result given
 // COLSUM: also the column sums of the source (a bias gradient is that of dY), per 256-row block; a
 // separate instance, so that the plain quantizer's code does not change with this feature.
-template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM>
+template <typename S, int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM>
 __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint32_t block, uint8_t* st)      // a by value: by reference the stochastic
                                                                             // instances take 128 registers and spill
 {
@@ -437,7 +448,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                                      : a.n_wide + (narrow >> 1);
     const uint32_t row_block = wide_index / a.wide_per_row;
     const int tiles_per_wave = wide ? 2 : 1;
-    const uint32_t macro_rows = 256u, macro_cols = 64u * tiles_per_wave;
+    const uint32_t macro_rows = S::MACRO_ROWS, macro_cols = 64u * tiles_per_wave;
     const uint32_t mrow0 = row_block * macro_rows;        // macro tile origin
     const uint32_t mcol0 = (wide_index - row_block * a.wide_per_row) * 128u + (wide ? 0u : (narrow & 1u) * 64u);
     if (mcol0 >= a.cols) return;                          // second half of a tile that is only 64 columns wide
@@ -445,7 +456,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
     const bool wave_rows_full = mrow0 + wr * 32 + 32 <= a.src_rows;
     const uint32_t lrow0 = wr * 32 + 4 * rg;              // first of this lane's 4 rows inside the macro tile
     const uint32_t row0 = mrow0 + lrow0;
-    const bool want_row = a.codes_row != nullptr;
+    const bool want_row = SRC != 2 && a.codes_row != nullptr;
     const uint32_t half_rows = a.rows >> 1, grp_rows = a.rows >> 5;
     const uint32_t half_cols = a.cols >> 1, grp_cols = a.cols >> 5;
 
@@ -511,7 +522,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 #pragma unroll
             for (int t = 0; t < 8; ++t)
                 cs[t] = ((element(x[0], t) + element(x[1], t)) + element(x[2], t)) + element(x[3], t);
-            reinterpret_cast<float*>(st + ST_CSUM_OFF)[wr * 128 + lcol0 + column_of_sum(lane)] = sum_row_groups8(cs, lane);
+            reinterpret_cast<float*>(st + S::CSUM_OFF)[wr * 128 + lcol0 + column_of_sum(lane)] = sum_row_groups8(cs, lane);
             __builtin_amdgcn_sched_barrier(0);            // the random numbers of later phases stay out of this one's registers
         }
         // ---- bf16: group maxima, scale bytes of two rows per register ----
@@ -560,8 +571,8 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                 else
                     pk[j] = rtn_codes8(cur.x[j], byte);
                 if (want_row) {
-                    *reinterpret_cast<uint32_t*>(st + ST_ROW_OFF + (lrow0 + j) * ST_PITCH + (lcol0 >> 1)) = pk[j];
-                    if ((cc & 3) == 0) st[ST_SROW_OFF + (lrow0 + j) * 8 + (lcol0 >> 5)] = (uint8_t)byte;
+                    *reinterpret_cast<uint32_t*>(st + S::ROW_OFF + (lrow0 + j) * S::ROW_PITCH + (lcol0 >> 1)) = pk[j];
+                    if ((cc & 3) == 0) st[S::SROW_OFF + (lrow0 + j) * S::ROW_SCALES + (lcol0 >> 5)] = (uint8_t)byte;
                 }
             }
         }
@@ -572,8 +583,8 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
         auto store_column_bytes = [&](uint32_t two, uint32_t first, uint32_t step) {
             // rows of 16 lanes 0..3 hold the columns first + step * {0, 2, 1, 3}: the lanes of each row's first half write
             if ((lane & 8) == 0) {
-                st[ST_SCOL_OFF + (lcol0 + first) * 8 + wr] = (uint8_t)two;
-                st[ST_SCOL_OFF + (lcol0 + first + step) * 8 + wr] = (uint8_t)(two >> 16);
+                st[S::SCOL_OFF + (lcol0 + first) * S::COL_SCALES + wr] = (uint8_t)two;
+                st[S::SCOL_OFF + (lcol0 + first + step) * S::COL_SCALES + wr] = (uint8_t)(two >> 16);
             }
         };
         const uint32_t row16 = (uint32_t)lane >> 4, place = ((row16 & 1u) << 1) | (row16 >> 1);
@@ -681,7 +692,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t)
-            *reinterpret_cast<uint16_t*>(st + ST_COL_OFF + (lcol0 + t) * ST_PITCH + (lrow0 >> 1)) = (uint16_t)colpk[t];
+            *reinterpret_cast<uint16_t*>(st + S::COL_OFF + (lcol0 + t) * S::COL_PITCH + (lrow0 >> 1)) = (uint16_t)colpk[t];
         if (PREFETCH) cur = nxt;
     }
     __syncthreads();
@@ -690,17 +701,17 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
     const uint32_t ncols_here = min(macro_cols, a.cols - mcol0);    // multiples of 32
     const uint32_t nrows_here = min(macro_rows, a.rows - mrow0);    // multiples of 32
     if (want_row)
-        write_staged(st + ST_ROW_OFF, st + ST_SROW_OFF, nrows_here, ncols_here >> 5,
+        write_staged<S::THREADS, S::ROW_PITCH, S::ROW_SCALES>(st + S::ROW_OFF, st + S::SROW_OFF, nrows_here, ncols_here >> 5,
                      a.codes_row + (size_t)mrow0 * half_cols + (mcol0 >> 1), half_cols,
                      a.scales_row + (size_t)mrow0 * grp_cols + (mcol0 >> 5), grp_cols, tid);
-    write_staged(st + ST_COL_OFF, st + ST_SCOL_OFF, ncols_here, nrows_here >> 5,
+    write_staged<S::THREADS, S::COL_PITCH, S::COL_SCALES>(st + S::COL_OFF, st + S::SCOL_OFF, ncols_here, nrows_here >> 5,
                  a.codes_t + (size_t)mcol0 * half_rows + (mrow0 >> 1), half_rows,
                  a.scales_t + (size_t)mcol0 * grp_rows + (mrow0 >> 5), grp_rows, tid);
     if (COLSUM && a.col_sum_partials != nullptr && (uint32_t)tid < ncols_here) {
         // the waves that had rows, in order; one value per column of this 256-row block.  Round to
         // nearest like the per-wave sums (no quantizer arithmetic follows, the mode is not restored).
         f32_round_to_nearest_even();
-        const float* cs = reinterpret_cast<const float*>(st + ST_CSUM_OFF) + tid;
+        const float* cs = reinterpret_cast<const float*>(st + S::CSUM_OFF) + tid;
         float s = cs[0];
         for (uint32_t w = 1; w < (nrows_here >> 5); ++w) s += cs[w * 128];
         a.col_sum_partials[(size_t)row_block * a.cols + mcol0 + tid] = s;
@@ -709,11 +720,12 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 
 // SRC as above, or 3: FP32 and bf16 jobs in one launch (a bf16 activation and its FP32 master weight).
 template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM = false>
-__global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatch batch)
+__global__ __launch_bounds__(64 * tile_waves(COLSUM), SRC == 2 ? 5 : 4) void quantize_tile_kernel(TileBatch batch)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t st[COLSUM ? ST_BYTES_CSUM : ST_BYTES];
+    using S = TileShape<tile_waves(COLSUM), SRC != 2, COLSUM>;
+    __shared__ __attribute__((aligned(16))) uint8_t st[S::BYTES];
     if (batch.widen.count != 0u && blockIdx.x == gridDim.x - 1u) {
-        widen_bf16(batch.widen, threadIdx.x, TILE_THREADS);
+        widen_bf16(batch.widen, threadIdx.x, S::THREADS);
         return;
     }
     uint32_t job = 0;
@@ -722,10 +734,10 @@ __global__ __launch_bounds__(TILE_THREADS, 4) void quantize_tile_kernel(TileBatc
     const TileArgs a = batch.job[job];
     const uint32_t block = blockIdx.x - batch.first[job];
     if constexpr (SRC == 3) {
-        if (a.src_bf16) quantize_tile_body<1, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
-        else            quantize_tile_body<0, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        if (a.src_bf16) quantize_tile_body<S, 1, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        else            quantize_tile_body<S, 0, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
     } else {
-        quantize_tile_body<SRC, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        quantize_tile_body<S, SRC, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
     }
 }
 
@@ -1140,7 +1152,7 @@ hipError_t launch_ema_quantize(const QuantRowsParams& p, float* ema, float beta,
 template <int SRC, bool FL, bool CS>
 static void launch_tile_flags(const TileBatch& a, bool row_sr, bool t_sr, dim3 grid, hipStream_t st)
 {
-    dim3 block(TILE_THREADS);
+    dim3 block(64 * tile_waves(CS));
     if (row_sr) {
         if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, true, FL, CS>), grid, block, 0, st, a);
         else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, false, FL, CS>), grid, block, 0, st, a);
@@ -1158,7 +1170,7 @@ static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col
 }
 
 // Fills the kernel arguments of one tensor; returns its number of workgroups.
-static uint32_t make_tile_args(const QuantTileParams& p, TileArgs& a)
+static uint32_t make_tile_args(const QuantTileParams& p, int waves, TileArgs& a)
 {
     a = TileArgs{};
     a.src = p.src; a.row_codes_in = p.row_codes_in; a.row_scales_in = p.row_scales_in;
@@ -1170,19 +1182,17 @@ static uint32_t make_tile_args(const QuantTileParams& p, TileArgs& a)
     a.seed_dev = reinterpret_cast<const uint32_t*>(p.seed_dev);
     a.col_sum_partials = p.col_sums ? p.col_sum_workspace : nullptr;
     a.tensor_id_t = p.tensor_id_t; a.tensor_id_row = p.tensor_id_row; a.index_base = p.index_base;
-    // Macro tile of a workgroup (8 waves): 256 rows x 128 columns (whole 128-byte lines of the
-    // transposed codes, 64-byte pieces of the row codes; measured a few percent faster than
-    // 256 x 256), 256 x 64 for small tensors such as weights, where latency counts.
-    // Two workgroups fit a compute unit (LDS), so 512 run at a time and a launch proceeds in rounds
-    // of 512 equal tiles.  When the last round would be less than half full, its tiles are issued as
-    // their 256 x 64 halves: twice the workgroups, half the time, and the round ends earlier.
+    // Macro tile of a workgroup: 128 columns, 64 for small tensors such as weights, where latency counts.  16 waves run
+    // on a compute unit, so a launch proceeds in rounds of `slots` equal tiles.  When the last round would be less than
+    // half full, its tiles are issued as their halves: twice the workgroups, half the time, and the round ends earlier.
     const uint32_t wide_per_row = (uint32_t)((p.cols + 127) / 128);
-    const uint32_t n_tiles = (uint32_t)((p.rows + 255) / 256) * wide_per_row;
+    const uint32_t macro_rows = 32u * (uint32_t)waves, slots = 256u * (16u / (uint32_t)waves);
+    const uint32_t n_tiles = (uint32_t)((p.rows + macro_rows - 1) / macro_rows) * wide_per_row;
     const int64_t tiles32 = (p.rows / 32) * ((p.cols + 63) / 64);
     uint32_t n_wide = 0;
     if (tiles32 >= 8192) {
-        const uint32_t rem = n_tiles % 512u;
-        n_wide = (rem > 0u && rem <= 256u) ? n_tiles - rem : n_tiles;
+        const uint32_t rem = n_tiles % slots;
+        n_wide = (rem > 0u && rem <= slots / 2u) ? n_tiles - rem : n_tiles;
     }
     a.n_wide = n_wide; a.wide_per_row = wide_per_row;
     return n_wide + 2u * (n_tiles - n_wide);
@@ -1197,6 +1207,8 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
     TileBatch b{};
     uint32_t blocks = 0;
     bool col_sums = false, mixed = false;
+    for (int j = 0; j < count; ++j) col_sums = col_sums || jobs[j].col_sums != nullptr;
+    const int waves = tile_waves(!p.row_codes_in && col_sums);
     for (int j = 0; j < TILE_BATCH_MAX; ++j) {
         b.first[j] = 0xFFFFFFFFu;
         if (j >= count) continue;
@@ -1206,8 +1218,7 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
             (q.row_codes_in ? false : q.sr_row) != row_sr || q.floor_mode != p.floor_mode)
             return hipErrorInvalidValue;
         b.first[j] = blocks;
-        blocks += make_tile_args(q, b.job[j]);
-        col_sums = col_sums || q.col_sums != nullptr;
+        blocks += make_tile_args(q, waves, b.job[j]);
         mixed = mixed || (!p.row_codes_in && q.bf16 != p.bf16);
     }
     if (mixed && (col_sums || row_sr)) return hipErrorInvalidValue;      // only the forward pass mixes source types
@@ -1224,8 +1235,8 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
             case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, grid, st); break;
             case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, grid, st); break;
             default:
-                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL>), grid, dim3(TILE_THREADS), 0, st, b);
-                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL>), grid, dim3(TILE_THREADS), 0, st, b);
+                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL>), grid, dim3(64 * tile_waves(false)), 0, st, b);
+                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL>), grid, dim3(64 * tile_waves(false)), 0, st, b);
         }
     };
     if (p.floor_mode) launch(std::true_type{});
