@@ -2,7 +2,7 @@
 // block-scaled FP4 matrix cores.  All three products of the layer (Eqs. 3-5, Sec. 3.3) have
 // this form because every operand is stored along its own contraction dimension.
 //
-// Two kernels, chosen by plan_gemm at the end of the file:
+// Two kernels, chosen by plan_gemm (plan_fused for products with the GELU stage) at the end of the file:
 //   mx_gemm_pingpong_kernel  the main path (K a multiple of 128, at least 4 K steps per K split;
 //       every ViT-B/L product): one persistent workgroup of 8 waves per compute unit, tile 256 x 256,
 //       operands global -> LDS by DMA loads, two wave groups alternating between their MFMA burst and
@@ -64,7 +64,7 @@ struct GemmArgs {
     uint32_t tiles_m, tiles_n;
     int stagger;             // start delay of every other workgroup of an XCD, in s_sleep(32) units
     const float* bias;       // n values added to every row of a final output (n % 4 == 0), or null
-    uint8_t* q_codes;        // fused GELU + 1x32 quantizer of the output rows (main kernel only): packed codes
+    uint8_t* q_codes;        // fused GELU + 1x32 quantizer of the output rows: packed codes
     uint8_t* q_scales;       //   [m x n/2] and scale bytes [m x n/32] of Q(GELU(product + bias)), or null
     int q_floor;             //   its scale rule: 0 truncation-free, 1 Eq. 2
 };
@@ -242,7 +242,122 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, uint8_t* ep, v1
     }
 }
 
-template <int BM, int BN, int KS, int OCC>
+// GELU(x) = x * Phi(x) with Phi(x) = erfc(-x / sqrt(2)) / 2 (the exact form, not the tanh approximation),
+// FP32, branch-free, 26 instructions.  With z = |x| / sqrt(2):
+//     erfc(z) = exp(-z^2) * G(z),   G(z) = t * P8(t - t0),   t = 1 / (1 + z / 2),
+// where P8 is a degree-8 fit of the scaled complementary error function over z in [0, 12.1] (relative error
+// 4.4e-8 in exact arithmetic; coefficients from fit_gelu_erfcx.py beside the package's Python files).
+// erfc keeps its relative accuracy in the negative tail, where 1 + erf would cancel; to keep it through the
+// exponential, z^2 = x^2 / 2 is carried as an FP32 product and its exact remainder, and the exponent of two as
+// a rounded product and its remainder, both folded in as first-order corrections.  Against the FP64 value the
+// result is within 5.5e-7 |GELU(x)| (2^-18 is 3.8e-6) for every x where |GELU(x)| >= 2^-100, and below
+// 2^-120 in absolute terms beyond (checked on 6e6 points by the fitting script's FP32 emulation).  |x| is
+// clamped at 17 before squaring: erfc has long underflowed there, and no infinity can arise.
+//
+// The operation sequence of float gelu_f32(float x) as the fitting script emulates it, four values side by side: the stage
+// is bound by the vector ALUs, two waves share a SIMD, and one dependent chain per value (two of its instructions
+// transcendental) leaves it idle.  25216 x 3072 x 768: 150 us value by value with 30 instructions each and codes packed
+// by shifts, 140 us now (the product alone takes 45).
+__device__ __forceinline__ void gelu4_f32(const float (&x)[4], float (&y)[4])
+{
+    constexpr float T0 = 0.5709219574928284f;
+    constexpr float C0 = 0.562385082244873f, C1 = 0.768385112285614f, C2 = 0.584431529045105f,
+                    C3 = 0.09252145141363144f, C4 = -0.20070798695087433f, C5 = -0.058531392365694046f,
+                    C6 = 0.11107011884450912f, C7 = 0.014878340996801853f, C8 = -0.05936833471059799f;
+    constexpr float C[9] = {C0, C1, C2, C3, C4, C5, C6, C7, C8};
+    constexpr float HALF_LOG2E_HI = 0.72134751f;                    // log2(e) / 2 rounded to FP32 ...
+    constexpr float HALF_LOG2E_LO = (float)(0.72134752044448170368 - (double)HALF_LOG2E_HI);   // ... and what it lost
+    float ax[4], t[4], w[4], g[4], s[4], e[4], c[4], yl[4];
+    auto each = [](auto&& f) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f(i);
+        __builtin_amdgcn_sched_barrier(0);                          // the four stay side by side
+    };
+    each([&](int i) { ax[i] = __builtin_fminf(__builtin_fabsf(x[i]), 17.0f); });
+    each([&](int i) { t[i] = __builtin_fmaf(ax[i], 0.35355339059327376f, 1.0f); });
+    each([&](int i) { t[i] = __builtin_amdgcn_rcpf(t[i]); });                                       // 1 / (1 + z / 2)
+    each([&](int i) { s[i] = __fmul_rn(ax[i], ax[i]); });
+    each([&](int i) { e[i] = __fmul_rn(s[i], -HALF_LOG2E_HI); });                                   // -yh
+    each([&](int i) { yl[i] = __builtin_fmaf(s[i], HALF_LOG2E_HI, e[i]); });        // z^2 log2(e) = yh + yl + r log2(e) / 2 (to first order)
+    each([&](int i) { yl[i] = __builtin_fmaf(s[i], HALF_LOG2E_LO, yl[i]); });
+    each([&](int i) { e[i] = __builtin_amdgcn_exp2f(e[i]); });
+    each([&](int i) { c[i] = __builtin_fmaf(yl[i], -0.34657359f, 0.5f); });                         // 2^-yl / 2
+    each([&](int i) { s[i] = __builtin_fmaf(ax[i], ax[i], -s[i]); });                               // r: x^2 = s + r exactly
+    each([&](int i) { c[i] = __builtin_fmaf(s[i], -0.25f, c[i]); });                                // exp(-r / 2) / 2
+    each([&](int i) { w[i] = t[i] - T0; });
+    each([&](int i) { g[i] = __builtin_fmaf(C[8], w[i], C[7]); });
+#pragma unroll
+    for (int k = 6; k >= 0; --k) each([&](int i) { g[i] = __builtin_fmaf(g[i], w[i], C[k]); });
+    each([&](int i) { g[i] = __fmul_rn(g[i], t[i]); });
+    each([&](int i) { g[i] = __fmul_rn(g[i], e[i]); });
+    each([&](int i) { g[i] = __fmul_rn(g[i], c[i]); });                                             // erfc / 2
+    // x Phi(|x|) = x - x erfc / 2 for x >= 0, -|x| erfc / 2 below; the maximum with -0 keeps a zero result's sign
+    each([&](int i) { asm("v_max_f32_e32 %0, %1, %2" : "=v"(y[i]) : "v"(x[i]), "v"(-0.0f)); });
+    each([&](int i) { y[i] = __builtin_fmaf(-__builtin_fabsf(x[i]), g[i], y[i]); });
+}
+
+// The tile kernel's second output stage: the next layer's forward quantizer applied to GELU(product + bias) from the FP32
+// accumulators (see gemm_epilogue_gelu_quant for the layout of a lane's values).  Codes go through the wave's strip
+// ([32 * TI rows], 16 * TJ bytes each) and leave as 16-byte pieces, then the scale bytes, TJ per row.
+template <bool FLOOR, int TI, int TJ>
+__device__ __forceinline__ void tile_gelu_quant(const GemmArgs& g, uint8_t* ep, v16f (&acc)[TI][TJ], uint32_t mrow0, uint32_t nbase)
+{
+    constexpr int PITCH = 16 * TJ + 16, SCALES = 32 * TI * PITCH;
+    const uint32_t lane = threadIdx.x & 63, lrow = lane & 31, lhalf = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+        v4f bias[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)                                                     // n % 32 == 0
+            bias[q] = nbase + 32 * j < g.n ? *reinterpret_cast<const v4f*>(g.bias + nbase + 32 * j + 8 * q + 4 * lhalf) : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            float v[16];
+            uint32_t m = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float pre[4], post[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pre[r] = acc[i][j][4 * q + r] + bias[q][r];
+                gelu4_f32(pre, post);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[4 * q + r] = post[r];
+                m = mxd::absmax3_bits(v[4 * q], v[4 * q + 1], m);
+                m = mxd::absmax3_bits(v[4 * q + 2], v[4 * q + 3], m);
+            }
+            const auto sw = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+            m = sw[0] > sw[1] ? sw[0] : sw[1];
+            const uint32_t byte = mxd::scale_byte(m, FLOOR);
+            const float scale = mxd::scale_operand(byte);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t pk = mxd::cvt_rtn_f32<0>(0u, v[4 * q], v[4 * q + 1], scale);
+                pk = mxd::cvt_rtn_f32<1>(pk, v[4 * q + 2], v[4 * q + 3], scale);
+                *reinterpret_cast<uint16_t*>(ep + (i * 32 + lrow) * PITCH + 16 * j + 4 * q + 2 * lhalf) = (uint16_t)pk;
+            }
+            if (lhalf == 0) ep[SCALES + (i * 32 + lrow) * TJ + j] = (uint8_t)byte;
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the strip is read through other lanes' addresses
+    const uint32_t half_n = g.n >> 1, grp_n = g.n >> 5;
+    constexpr int RPI = 64 / TJ;                                // rows per instruction
+    const uint32_t piece = lane % TJ;
+#pragma unroll
+    for (int it = 0; it < (32 * TI + RPI - 1) / RPI; ++it) {
+        const uint32_t row = it * RPI + lane / TJ;
+        if (row < 32 * TI && mrow0 + row < g.m && nbase + 32 * piece < g.n) {
+            const v4i c = *reinterpret_cast<const v4i*>(ep + row * PITCH + piece * 16);
+            *reinterpret_cast<v4i*>(g.q_codes + (size_t)(mrow0 + row) * half_n + (nbase >> 1) + piece * 16) = c;
+        }
+    }
+    if (lane < 32 * TI && mrow0 + lane < g.m) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+            if (nbase + 32 * j < g.n) g.q_scales[(size_t)(mrow0 + lane) * grp_n + (nbase >> 5) + j] = ep[SCALES + lane * TJ + j];
+    }
+}
+
+template <int BM, int BN, int KS, int OCC, bool GELUQ = false>
 __global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
 {
     using S = TileShape<BM, BN, KS>;
@@ -376,6 +491,13 @@ __global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
     }
     // (the last barrier: every wave is done reading the stage buffers, which the output strips reuse)
     uint8_t* ep = lds + wave * 32 * S::EP_PITCH;
+    if constexpr (GELUQ) {                                         // no K split
+        static_assert(32 * TI * (16 * TJ + 16) + 32 * TI * TJ <= 32 * S::EP_PITCH, "strip");
+        tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+        if (g.q_floor) tile_gelu_quant<true, TI, TJ>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2));
+        else           tile_gelu_quant<false, TI, TJ>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2));
+        return;
+    }
     if (g.split_k == 1) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
     else                tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
 }
@@ -559,60 +681,6 @@ __device__ __forceinline__ void gemm_epilogue_interior(const GemmArgs& g, lds_u8
             }
         }
     }
-}
-
-// GELU(x) = x * Phi(x) with Phi(x) = erfc(-x / sqrt(2)) / 2 (the exact form, not the tanh approximation),
-// FP32, branch-free, 26 instructions.  With z = |x| / sqrt(2):
-//     erfc(z) = exp(-z^2) * G(z),   G(z) = t * P8(t - t0),   t = 1 / (1 + z / 2),
-// where P8 is a degree-8 fit of the scaled complementary error function over z in [0, 12.1] (relative error
-// 4.4e-8 in exact arithmetic; coefficients from fit_gelu_erfcx.py beside the package's Python files).
-// erfc keeps its relative accuracy in the negative tail, where 1 + erf would cancel; to keep it through the
-// exponential, z^2 = x^2 / 2 is carried as an FP32 product and its exact remainder, and the exponent of two as
-// a rounded product and its remainder, both folded in as first-order corrections.  Against the FP64 value the
-// result is within 5.5e-7 |GELU(x)| (2^-18 is 3.8e-6) for every x where |GELU(x)| >= 2^-100, and below
-// 2^-120 in absolute terms beyond (checked on 6e6 points by the fitting script's FP32 emulation).  |x| is
-// clamped at 17 before squaring: erfc has long underflowed there, and no infinity can arise.
-//
-// The operation sequence of float gelu_f32(float x) as the fitting script emulates it, four values side by side: the stage
-// is bound by the vector ALUs, two waves share a SIMD, and one dependent chain per value (two of its instructions
-// transcendental) leaves it idle.  25216 x 3072 x 768: 150 us value by value with 30 instructions each and codes packed
-// by shifts, 140 us now (the product alone takes 45).
-__device__ __forceinline__ void gelu4_f32(const float (&x)[4], float (&y)[4])
-{
-    constexpr float T0 = 0.5709219574928284f;
-    constexpr float C0 = 0.562385082244873f, C1 = 0.768385112285614f, C2 = 0.584431529045105f,
-                    C3 = 0.09252145141363144f, C4 = -0.20070798695087433f, C5 = -0.058531392365694046f,
-                    C6 = 0.11107011884450912f, C7 = 0.014878340996801853f, C8 = -0.05936833471059799f;
-    constexpr float C[9] = {C0, C1, C2, C3, C4, C5, C6, C7, C8};
-    constexpr float HALF_LOG2E_HI = 0.72134751f;                    // log2(e) / 2 rounded to FP32 ...
-    constexpr float HALF_LOG2E_LO = (float)(0.72134752044448170368 - (double)HALF_LOG2E_HI);   // ... and what it lost
-    float ax[4], t[4], w[4], g[4], s[4], e[4], c[4], yl[4];
-    auto each = [](auto&& f) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f(i);
-        __builtin_amdgcn_sched_barrier(0);                          // the four stay side by side
-    };
-    each([&](int i) { ax[i] = __builtin_fminf(__builtin_fabsf(x[i]), 17.0f); });
-    each([&](int i) { t[i] = __builtin_fmaf(ax[i], 0.35355339059327376f, 1.0f); });
-    each([&](int i) { t[i] = __builtin_amdgcn_rcpf(t[i]); });                                       // 1 / (1 + z / 2)
-    each([&](int i) { s[i] = __fmul_rn(ax[i], ax[i]); });
-    each([&](int i) { e[i] = __fmul_rn(s[i], -HALF_LOG2E_HI); });                                   // -yh
-    each([&](int i) { yl[i] = __builtin_fmaf(s[i], HALF_LOG2E_HI, e[i]); });        // z^2 log2(e) = yh + yl + r log2(e) / 2 (to first order)
-    each([&](int i) { yl[i] = __builtin_fmaf(s[i], HALF_LOG2E_LO, yl[i]); });
-    each([&](int i) { e[i] = __builtin_amdgcn_exp2f(e[i]); });
-    each([&](int i) { c[i] = __builtin_fmaf(yl[i], -0.34657359f, 0.5f); });                         // 2^-yl / 2
-    each([&](int i) { s[i] = __builtin_fmaf(ax[i], ax[i], -s[i]); });                               // r: x^2 = s + r exactly
-    each([&](int i) { c[i] = __builtin_fmaf(s[i], -0.25f, c[i]); });                                // exp(-r / 2) / 2
-    each([&](int i) { w[i] = t[i] - T0; });
-    each([&](int i) { g[i] = __builtin_fmaf(C[8], w[i], C[7]); });
-#pragma unroll
-    for (int k = 6; k >= 0; --k) each([&](int i) { g[i] = __builtin_fmaf(g[i], w[i], C[k]); });
-    each([&](int i) { g[i] = __fmul_rn(g[i], t[i]); });
-    each([&](int i) { g[i] = __fmul_rn(g[i], e[i]); });
-    each([&](int i) { g[i] = __fmul_rn(g[i], c[i]); });                                             // erfc / 2
-    // x Phi(|x|) = x - x erfc / 2 for x >= 0, -|x| erfc / 2 below; the maximum with -0 keeps a zero result's sign
-    each([&](int i) { asm("v_max_f32_e32 %0, %1, %2" : "=v"(y[i]) : "v"(x[i]), "v"(-0.0f)); });
-    each([&](int i) { y[i] = __builtin_fmaf(-__builtin_fabsf(x[i]), g[i], y[i]); });
 }
 
 // Second output stage of the fused forward product of an MLP's first layer: the next layer's forward
@@ -1250,10 +1318,25 @@ int gemm_split_k(int64_t m, int64_t n, int64_t k) { return plan_gemm(m, n, k).sp
 
 bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k)
 {
-    // The stage lives in the main kernel (K a multiple of 128 with at least four K steps), without a K split: a long K
+    // K a multiple of 128 with at least four K steps (what the main kernel takes), without a K split: a long K
     // with fewer than half the units' worth of 256 x 256 tiles is a K-split product's shape.
     return (k & 127) == 0 && k >= 512 && (n & 31) == 0 &&
            (k < 4096 || ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN) * 2 > 256);
+}
+
+// Kernel of a product with the fused GELU stage (no K split).  All give the same bytes.  The main kernel takes 25 us for
+// any number of tiles up to one per compute unit, because both wave groups of a unit go through the stage at once; with
+// 64 x 64 tiles up to two rounds of 512 take 9-13 us, with 128 x 128 tiles waves of three workgroups share a unit and one
+// multiplies while another is in the stage.  Main kernel / 128 x 128 / 64 x 64 tiles in us (m x n x k):
+//   224x3072x768 24 13 9    1312x3072x1024 26 19 15    2048x3072x1024 26 19.9 20.4    6304x3072x1024 52 41 -
+//   33000x1024x1024 71 64   6304x3072x2048 64 57       12608x1024x512 26 30           25216x3072x768 116 123
+//   3136x3072x3072 39 49    25216x3072x3072 216 300
+// 128 x 128 tiles win where the main kernel's rounds of 256 tiles would be filled to less than 70 % and K is not long.
+static GemmKernel plan_fused(int64_t m, int64_t n, int64_t k)
+{
+    if (((m + 63) / 64) * ((n + 63) / 64) <= 1024) return GemmKernel::tile64;
+    const int64_t t256 = ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN), rounds = (t256 + Q_SLOTS - 1) / Q_SLOTS;
+    return k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7 ? GemmKernel::tile128 : GemmKernel::pingpong;
 }
 
 hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail)
@@ -1269,7 +1352,7 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
     g.c = g.split_k > 1 ? p.workspace : p.c;
     g.ldc = p.ldc; g.c_bf16 = p.c_bf16;
     g.bias = g.split_k > 1 ? nullptr : p.bias;                  // partial sums get none: the reduction adds it
-    GemmKernel kernel = p.q_codes ? GemmKernel::pingpong : plan_gemm(p.m, p.n, p.k).kernel;
+    GemmKernel kernel = p.q_codes ? plan_fused(p.m, p.n, p.k) : plan_gemm(p.m, p.n, p.k).kernel;
     // the main kernel needs four K steps in every split (the last one may be short of that)
     if (kernel == GemmKernel::pingpong && ksteps - (uint32_t)(g.split_k - 1) * steps_per < 4) kernel = GemmKernel::tile128;
     auto tile_grid = [&](int bm, int bn) -> unsigned {
@@ -1277,16 +1360,18 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
         g.tiles_n = (uint32_t)((p.n + bn - 1) / bn);
         return g.tiles_m * g.tiles_n * (unsigned)g.split_k;
     };
+    if (p.q_codes) {
+        if (!gemm_takes_fused_quantizer(p.m, p.n, p.k) || !g.bias || g.split_k != 1) return hipErrorInvalidValue;
+        g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
+    }
     switch (kernel) {
     case GemmKernel::pingpong: {
-        if (p.q_codes && (!gemm_takes_fused_quantizer(p.m, p.n, p.k) || !g.bias || g.split_k != 1)) return hipErrorInvalidValue;
         const unsigned nblk = tile_grid(Q_BM, Q_BN);
         // measured on the ViT-B products: 2.5 us (3 x 2048 clocks) gains 5-15 % at K = 768 and
         // 3-5 % at K = 2304, nothing at K = 3072; pointless below two rounds of tiles
         g.stagger = (g.split_k == 1 && nblk >= 2 * Q_SLOTS && p.k <= 2304) ? 3 : 0;
         const dim3 pgrid(nblk < Q_SLOTS ? nblk : Q_SLOTS);
         if (p.q_codes) {
-            g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
             hipLaunchKernelGGL((mx_gemm_pingpong_kernel<true, true>), pgrid, dim3(Q_NT), 0, st, g);
         } else if (g.bias) {
             hipLaunchKernelGGL(mx_gemm_pingpong_kernel<true>, pgrid, dim3(Q_NT), 0, st, g);
@@ -1296,13 +1381,15 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
         break;
     }
     case GemmKernel::tile128:
-        hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
+        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3, true>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
+        else           hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
         break;
     case GemmKernel::tile128x64:
         hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 64, 256, 3>), dim3(tile_grid(128, 64)), dim3(T_NT), 0, st, g);
         break;
     case GemmKernel::tile64:
-        hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
+        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2, true>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
+        else           hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
         break;
     }
     hipError_t e = hipGetLastError();

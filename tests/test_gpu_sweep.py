@@ -91,3 +91,31 @@ def test_products_at_the_lines_between_kernels(mx, orc, m, n, k):
         bias = np.linspace(-2, 2, n, dtype=np.float32)
         y = mx.mx_linear_fwd_bias(dev(ac), dev(as_), dev(bc), dev(bs), dev(bias), out_dtype=torch.bfloat16)
         assert torch.equal(y, (got + dev(bias)).bfloat16())
+
+
+@pytest.mark.parametrize("m,n,k", [
+    # 64 x 64 tiles, up to 1024 of them: one row, edges, a column count that ends inside a tile
+    (1, 32, 512), (33, 544, 640), (1000, 4096, 512),
+    # 128 x 128 tiles: one row of tiles more, edges in rows and columns (scale rows of odd length)
+    (1025, 4096, 512), (1632, 2720, 512),
+    # the main kernel, edges in rows and columns
+    (4063, 3040, 512), (4100, 1120, 2176)])
+def test_fused_gelu_at_the_lines_between_kernels(mx, orc, m, n, k):
+    """The pre-activation is what mx_linear_fwd_bias stores, and the codes are round_D of GELU of it: every kernel of the
+    fused stage takes the FP32 sum, so dequantized values differ from the oracle's only next to a threshold
+    (GELU's error is below 2^-18 of the value; a threshold is met with that probability)."""
+    xc, xs = random_packed(m, k, 800 + m % 97)
+    wc, ws = random_packed(n, k, 900 + n % 89)
+    ws[:] = 127 - 8                                      # pre-activations of order 1 and 10
+    xs[:] = 127 + np.arange(m, dtype=np.int64)[:, None] % 4
+    bias = np.linspace(-3, 3, n, dtype=np.float32)
+    args = (dev(xc), dev(xs), dev(wc), dev(ws), dev(bias))
+    for mode in (0, 1):
+        y, aq, as_ = mx.mx_linear_fwd_gelu_quant(*args, out_dtype=torch.float32, scale_mode=mode)
+        assert torch.equal(y, mx.mx_linear_fwd_bias(*args, out_dtype=torch.float32))
+        A = orc.gelu(y.cpu().numpy().astype(np.float64)).astype(np.float32)
+        want_c, want_s = orc.quantize(A, scale_mode=mode)
+        got, want = orc.dequantize(host(aq), host(as_)), orc.dequantize(want_c, want_s)
+        # one group's scale may move with its maximum, one value's code at a threshold: 2^-17 of the values, and a few
+        assert np.count_nonzero(got != want) <= 32 * (1 + m * n // 2 ** 17), (m, n, k, mode)
+        assert np.count_nonzero(host(as_) != want_s) <= 1 + m * n // 2 ** 22, (m, n, k, mode)
