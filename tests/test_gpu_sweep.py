@@ -119,3 +119,20 @@ def test_fused_gelu_at_the_lines_between_kernels(mx, orc, m, n, k):
         # one group's scale may move with its maximum, one value's code at a threshold: 2^-17 of the values, and a few
         assert np.count_nonzero(got != want) <= 32 * (1 + m * n // 2 ** 17), (m, n, k, mode)
         assert np.count_nonzero(host(as_) != want_s) <= 1 + m * n // 2 ** 22, (m, n, k, mode)
+
+
+@pytest.mark.parametrize("rows,cols", [(32, 32), (96, 64), (128, 128), (160, 96), (256, 160), (288, 2080), (2112, 8256)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_fused_quantizer_at_the_edges_of_its_tiles(mx, orc, rows, cols, dtype):
+    """Macro tiles of 128 rows x 128 or 64 columns (the last shape has 128-column tiles and a tail of halves): both sources and
+    packed codes, both roundings, bit for bit."""
+    x = mixed_matrix(rows, cols, seed=1000 + rows + cols, dtype=dtype)
+    for rnd, pre in ((1, 1), (1, 0), (0, 0), (0, 1)):
+        kw = dict(round_t=rnd, tensor_id_t=6, pre_quant=pre, round_row=rnd if pre == 0 else 0, tensor_id_row=1, seed=7)
+        got, want = mx.mx_quantize_transposed(dev(x, dtype), **kw), orc.quantize_transposed(x, **kw)
+        for g, w, nm in zip(got, want, ("codes_t", "scales_t", "codes_row", "scales_row")):
+            assert_same_bytes(g, w, "%s round %d pre %d %s" % (dtype, rnd, pre, nm))
+        if pre:
+            t = mx.mx_quantize_transposed(None, rnd, 6, 1, False, row_in=(got[2], got[3]), seed=7, shape=(rows, cols))
+            assert_same_bytes(t[0], want[0], "codes_t from packed codes")
+            assert_same_bytes(t[1], want[1], "scales_t from packed codes")
