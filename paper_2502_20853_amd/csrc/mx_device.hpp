@@ -42,7 +42,8 @@ __device__ __forceinline__ float fwd_scale(uint32_t byte)
 }
 
 // ---- E2M1 rounding (Sec. 3.2) ----------------------------------------------
-// The quantizers never form y = x / S itself.  They form v = x * 2^(-s-126) (one ldexp), which
+// The integer form, which round_S uses (round_D of E2M1 goes through conversion instructions further down, E3M0 uses the
+// integer form for both).  It never forms y = x / S itself but v = x * 2^(-s-126) (one ldexp), which
 // puts |y| in [0, 6] onto FP32 bit patterns whose layout IS the E2M1 grid: |y| < 1 lands
 // in FP32's subnormal range (uniform spacing, like E2M1's subnormals 0 and 0.5), [1,2)
 // in the first normal binade, and so on, so that
@@ -188,7 +189,7 @@ constexpr uint32_t GRID_MAX_BITS_E3M0 = 7u << 23;     // 16 * 2^-124
 
 __device__ __forceinline__ int grid_exponent_e3m0(uint32_t byte) { return 3 - (int)byte; }
 
-// round_D; rounding mode toward minus infinity (see rtn_code).
+// round_D; rounding mode toward minus infinity: on the signed value it floors the magnitude of y > 0 and ceils that of y < 0.
 template <bool FLOOR>
 __device__ __forceinline__ uint32_t rtn_code_e3m0(float x, int e)
 {
@@ -429,16 +430,6 @@ __device__ __forceinline__ bf16x8_raw load8_raw(const uint16_t* p)
 {
     return __builtin_nontemporal_load(reinterpret_cast<const bf16x8_raw*>(p));
 }
-__device__ __forceinline__ F8 expand8(bf16x8_raw a)
-{
-    F8 r;
-    r.v[0] = __uint_as_float(a.x << 16); r.v[1] = __uint_as_float(a.x & 0xFFFF0000u);
-    r.v[2] = __uint_as_float(a.y << 16); r.v[3] = __uint_as_float(a.y & 0xFFFF0000u);
-    r.v[4] = __uint_as_float(a.z << 16); r.v[5] = __uint_as_float(a.z & 0xFFFF0000u);
-    r.v[6] = __uint_as_float(a.w << 16); r.v[7] = __uint_as_float(a.w & 0xFFFF0000u);
-    return r;
-}
-
 __device__ __forceinline__ F8 zero8()
 {
     F8 r;
