@@ -622,7 +622,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
                         d[r][t] = v[t >> 1][t & 1];
-                        if (T_SR) d[r][t] = __uint_as_float(sr_grid_x2<FLOOR>(d[r][t], 1 - (int)column_byte(t), rnd.w[t]));
+                        if (T_SR) d[r][t] = __uint_as_float(sr_grid<FLOOR>(d[r][t], 1 - (int)column_byte(t), rnd.w[t]));
                     }
                 }
 #pragma unroll

@@ -144,6 +144,36 @@ def test_tiny_elements_under_a_large_scale(mx, orc):
     assert_same_bytes(got[0], want[0], "ema codes")
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_double_quantization_of_tiny_groups(mx, orc, dtype, mode):
+    """Row groups of 2^-133 .. 2^-120: dequantized values of the smallest scales are FP32 subnormals.  Column groups that
+    are as tiny, and column groups with one large value, where the other elements go up only on a zero draw."""
+    import mx_workloads as wl
+    rng = np.random.default_rng(17 + mode)
+    rows, cols = 1024, 2048
+    x = rng.uniform(-1, 1, (rows, cols // 32, 32)) * 2.0 ** rng.integers(-133, -120, (rows, cols // 32, 1))
+    x = x.astype(np.float32).reshape(rows, cols)
+    large = np.arange(5, rows, 64)                                    # one row of every second column group
+    x[large] = rng.standard_normal((large.size, cols)) * 2.0 ** rng.integers(-60, 60, (large.size, 1))
+    x = wl.round_to_bf16(x) if dtype == "bf16" else x
+    for rt in (0, 1):
+        kw = dict(round_t=rt, tensor_id_t=6, pre_quant=1, round_row=0, tensor_id_row=1, scale_mode=mode, seed=3)
+        want, got = orc.quantize_transposed(x, **kw), mx.mx_quantize_transposed(dev(x, dtype), **kw)
+        assert np.count_nonzero(want[3] == 0) > want[3].size // 4
+        for g, w, nm in zip(got, want, ("codes_t", "scales_t", "codes_row", "scales_row")):
+            assert_same_bytes(g, w, "round %d %s" % (rt, nm))
+        got = mx.mx_quantize_transposed(None, rt, 6, 1, False, row_in=(dev(want[2]), dev(want[3])), scale_mode=mode, seed=3,
+                                        shape=x.shape)
+        assert_same_bytes(got[0], want[0], "round %d codes_t from packed codes" % rt)
+        assert_same_bytes(got[1], want[1], "round %d scales_t from packed codes" % rt)
+        if rt:                                                        # some elements under a large scale did go up
+            under = orc.dequantize(*want[:2]).T.reshape(rows // 64, 64, cols)[:, :32]
+            tiny = np.ones(32, bool)
+            tiny[5] = False
+            assert np.count_nonzero(under[:, tiny]) > 0
+
+
 # ------------------------------------------------------------ transposed ----
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
