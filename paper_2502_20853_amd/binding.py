@@ -129,6 +129,7 @@ def host():
         except ImportError as e:
             raise RuntimeError("the native host module of this package is not built: run `python -m paper_2502_20853_amd.build` "
                                "(or __graft_entry__.build()): %s" % e) from e
+        _mx_torch.set_error_class(MxError)
         _host = _mx_torch
     return _host
 

@@ -7,8 +7,10 @@
 #include <torch/extension.h>
 #include <c10/hip/HIPGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "../../include/mxfp4.h"
 #include "mx_launch.hpp"
 
 namespace {
@@ -19,9 +21,36 @@ using OptTensor = std::optional<Tensor>;
 // tensor ids of the six quantizers, numbered as in Eqs. 3-5
 enum : uint32_t { Q1 = 1, Q2 = 2, Q3 = 3, Q4 = 4, Q5 = 5, Q6 = 6 };
 
-void check_hip(hipError_t e, const char* what)
+// A refusal or a launch failure, with the C interface's code: binding.MxError in Python.
+struct Status : std::runtime_error {
+    std::string fn;
+    int code, hip;
+    Status(const char* f, int c, int h = 0) : std::runtime_error(std::string(f) + " failed: code " + std::to_string(c)), fn(f), code(c), hip(h) {}
+};
+
+PyObject* mx_error_class = nullptr;          // set once, when binding.py loads this module
+
+// Sets the Python error of a Status; the caller holds the GIL.
+void raise_in_python(const Status& s)
 {
-    TORCH_CHECK(e == hipSuccess, what, " failed: hipError_t ", (int)e);
+    if (mx_error_class == nullptr) {
+        PyErr_SetString(PyExc_RuntimeError, s.what());
+        return;
+    }
+    PyObject* e = PyObject_CallFunction(mx_error_class, "sii", s.fn.c_str(), s.code, s.hip);
+    if (e == nullptr) return;                // the failure to make it is the error then
+    PyErr_SetObject(mx_error_class, e);
+    Py_DECREF(e);
+}
+
+void check(int code, const char* fn)
+{
+    if (code != MX_OK) throw Status(fn, code);
+}
+
+void check_hip(hipError_t e, const char* fn)
+{
+    if (e != hipSuccess) throw Status(fn, MX_ERR_HIP, (int)e);
 }
 
 bool is_bf16(const Tensor& t)
@@ -71,17 +100,17 @@ Seed seed_of(int64_t value, const OptTensor& dev)
     return s;
 }
 
-void check_sizes(int64_t rows, int64_t cols)
+void check_sizes(int64_t rows, int64_t cols, const char* fn)
 {
-    TORCH_CHECK(rows > 0 && cols > 0 && rows <= (int64_t)0xFFFF0000LL * 8 / cols && rows <= 0x7FFFFFFFLL, "MX_ERR_SHAPE: ", rows, " x ", cols);
+    if (!(rows > 0 && cols > 0 && rows <= (int64_t)0xFFFF0000LL * 8 / cols && rows <= 0x7FFFFFFFLL)) throw Status(fn, MX_ERR_SHAPE);
 }
 
 // One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split.
 void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
-             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const Tensor* workspace = nullptr,
+             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr,
              const mxl::ColumnSumTail* tail = nullptr)
 {
-    TORCH_CHECK(m > 0 && n > 0 && k > 0 && k <= (1LL << 24), "MX_ERR_SHAPE: product ", m, " x ", n, " x ", k);
+    if (!(m > 0 && n > 0 && k > 0 && k <= (1LL << 24))) throw Status(fn, MX_ERR_SHAPE);
     mxl::GemmParams p{};
     p.a_codes = a; p.a_scales = as; p.b_codes = b; p.b_scales = bs;
     p.m = m; p.n = n; p.k = k;
@@ -98,7 +127,7 @@ void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_
             p.workspace = own.data_ptr();
         }
     }
-    check_hip(mxl::launch_gemm(p, st, tail), "product");
+    check_hip(mxl::launch_gemm(p, st, tail), fn);
 }
 
 mxl::QuantRowsParams rows_job(const Tensor& src, int64_t rows, int64_t cols, uint8_t* codes, uint8_t* scales, bool floor_mode)
@@ -119,9 +148,9 @@ struct Layer {
 
 void ema_rows(const Tensor& w, const Tensor& w_ema, const Layer& o, int64_t C, int64_t D, uint8_t* codes, uint8_t* scales, hipStream_t st)
 {
-    TORCH_CHECK(w_ema.scalar_type() == at::kFloat && w_ema.is_contiguous() && w_ema.sizes() == w.sizes(),
-                "w_ema must be float32 with the shape and strides of w");
-    TORCH_CHECK(o.beta >= 0.0 && (float)o.beta < 1.0f, "MX_ERR_MODE: beta");
+    TORCH_CHECK_VALUE(w_ema.scalar_type() == at::kFloat && w_ema.is_contiguous() && w_ema.sizes() == w.sizes(),
+                      "w_ema must be float32 with the shape and strides of w");
+    if (!(o.beta >= 0.0 && (float)o.beta < 1.0f)) throw Status("mx_ema_weight_quant", MX_ERR_MODE);
     check_hip(mxl::launch_ema_quantize(rows_job(w, C, D, codes, scales, o.floor_mode), w_ema.data_ptr<float>(), (float)o.beta, o.update_ema, st),
               "mx_ema_weight_quant");
 }
@@ -156,8 +185,6 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
 {
     const Tensor x = dense_source(x_in), w = dense_source(w_in);
     const int64_t D = w.size(1), C = w.size(0), N = x.numel() / D;
-    check_sizes(N, D);
-    check_sizes(C, D);
     const int64_t Np = saved ? padded_rows(N) : N;
     hipStream_t st = c10::hip::getCurrentHIPStream(x.get_device()).stream();
 
@@ -200,7 +227,7 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
         }
     }
     Tensor y = at::empty(with_last(x_in.sizes(), C), x.options());
-    product(r + o_xq, r + o_xs, r + o_wq, r + o_ws, N, C, D, y, C, b32, st);
+    product(r + o_xq, r + o_xs, r + o_wq, r + o_ws, N, C, D, y, C, b32, st, bias ? "mx_linear_fwd_bias" : "mx_linear_fwd");
     return y;
 }
 
@@ -220,7 +247,21 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         return y;
     }
 
+    // The engine carries a Python error to the caller of backward() as it is, any other exception as a RuntimeError.
     static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads)
+    {
+        try {
+            return backward_pass(ctx, grads);
+        } catch (const Status& s) {
+            py::gil_scoped_acquire gil;
+            raise_in_python(s);
+            python_error e;
+            e.persist();
+            throw e;
+        }
+    }
+
+    static torch::autograd::variable_list backward_pass(torch::autograd::AutogradContext* ctx, const torch::autograd::variable_list& grads)
     {
         at::AutoDispatchBelowADInplaceOrView guard;
         const auto keep = ctx->get_saved_variables();
@@ -233,7 +274,7 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         const Tensor dy = dense_source(grads[0]);
         c10::hip::HIPGuard device((c10::DeviceIndex)dy.get_device());
         const int64_t N = dy.numel() / C, Np = padded_rows(N);
-        check_sizes(Np, C);
+        check_sizes(Np, C, "mx_quantize_transposed");
         hipStream_t st = c10::hip::getCurrentHIPStream(dy.get_device()).stream();
         Carver v;
         const int64_t o_xtq = v.codes(D, Np), o_xts = v.scales(D, Np), o_wtq = v.codes(D, C), o_wts = v.scales(D, C);
@@ -277,13 +318,13 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         }
         if (want_dx) {
             dx = at::empty(shape, dy.options());
-            product(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, st);
+            product(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, st, "mx_linear_bwd_dx");
         }
         if (want_dw) {
             dw = at::empty({C, D}, dy.options().dtype((at::ScalarType)meta[5]));
-            product(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, st, nullptr, want_db ? &tail : nullptr);
+            product(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, st, "mx_linear_bwd_dw", nullptr, want_db ? &tail : nullptr);
         } else if (want_db) {
-            check_hip(mxl::launch_column_sum_finish(tail, st), "column sums");
+            check_hip(mxl::launch_column_sum_finish(tail, st), "mx_quantize_transposed_batch");
         }
         return {dx, dw, db, Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
     }
@@ -292,9 +333,11 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
 Tensor linear(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, bool tetra,
               bool floor_mode, uint64_t seed, const OptTensor& seed_dev)
 {
-    TORCH_CHECK(x.is_cuda() && w.is_cuda() && x.get_device() == w.get_device(), "MxLinear runs on the GPU: x and weight must be on one");
     TORCH_CHECK(w.dim() == 2 && x.dim() >= 1 && x.size(-1) == w.size(1), "input of ", w.size(1), " features expected, got ", x.sizes());
     TORCH_CHECK(!bias || bias->numel() == w.size(0), "bias must have ", w.size(0), " values");
+    check_sizes(w.size(0), w.size(1), "mx_quantize_transposed");
+    check_sizes(x.numel() / w.size(1), w.size(1), "mx_quantize_transposed");
+    TORCH_CHECK(x.is_cuda() && w.is_cuda() && x.get_device() == w.get_device(), "MxLinear runs on the GPU: x and weight must be on one");
     c10::hip::HIPGuard device((c10::DeviceIndex)x.get_device());
     const bool grad = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias && bias->requires_grad()));
     if (!grad) {
@@ -310,10 +353,12 @@ uint8_t* u8(const Tensor& t) { return t.data_ptr<uint8_t>(); }
 
 void check_source(const Tensor& t, int64_t rows, int64_t cols, const char* name)
 {
-    TORCH_CHECK_VALUE(t.is_cuda() && t.dim() == 2 && t.size(0) == rows && t.size(1) == cols && t.stride(1) == 1 && t.stride(0) >= cols, name,
-                      " must be a [", rows, ", ", cols, "] matrix with unit column stride on the GPU");
-    TORCH_CHECK((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) == 0 && t.stride(0) % (is_bf16(t) ? 8 : 4) == 0,
-                "mx_quantize_transposed failed: MX_ERR_ALIGN (-5)");
+    TORCH_CHECK_VALUE(t.dim() == 2 && t.size(0) == rows && t.size(1) == cols && t.stride(1) == 1, name, " must be a [", rows, ", ", cols,
+                      "] matrix with unit column stride");
+    const bool bf16 = is_bf16(t);
+    if (t.stride(0) < cols) throw Status("mx_quantize_transposed", MX_ERR_SHAPE);
+    if ((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) != 0 || t.stride(0) % (bf16 ? 8 : 4) != 0) throw Status("mx_quantize_transposed", MX_ERR_ALIGN);
+    TORCH_CHECK_VALUE(t.is_cuda(), name, " must be on the GPU");
 }
 
 mxl::QuantTileParams tile_job(const Tensor& src, int64_t rows, int64_t cols, const std::vector<Tensor>& out, bool sr_t, uint32_t tid_t,
@@ -339,7 +384,7 @@ void step_forward(const Tensor& X, const Tensor& W, int64_t N, int64_t D, int64_
     const mxl::QuantTileParams q[2] = {tile_job(X, N, D, xb, true, Q6, true, false, Q1, floor_mode, seed),
                                        tile_job(W, C, D, wb, true, Q4, true, false, Q2, floor_mode, seed)};
     check_hip(mxl::launch_quantize_tile_batch(q, 2, st), "mx_quantize_transposed_batch");
-    product(u8(xb[0]), u8(xb[1]), u8(wb[0]), u8(wb[1]), N, C, D, y, y.stride(0), nullptr, st, &workspace);
+    product(u8(xb[0]), u8(xb[1]), u8(wb[0]), u8(wb[1]), N, C, D, y, y.stride(0), nullptr, st, "mx_linear_fwd", &workspace);
 }
 
 void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t seed_value, const OptTensor& seed_dev, const std::vector<Tensor>& dyb,
@@ -350,8 +395,8 @@ void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t s
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
     check_hip(mxl::launch_quantize_tile_batch(&q, 1, st), "mx_quantize_transposed");
-    product(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, st, &workspace);
-    product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, &workspace);
+    product(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, st, "mx_linear_bwd_dx", &workspace);
+    product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, "mx_linear_bwd_dw", &workspace);
 }
 
 // ---- QRampingAdamW: one call per parameter group ----
@@ -365,10 +410,11 @@ const Tensor& state_tensor(PyObject* state, PyObject* key)
 }
 
 template <typename T>
-T* checked(const Tensor& t, int64_t count, at::ScalarType type, const char* what)
+T* checked(const Tensor& t, int64_t count, at::ScalarType type, const char* what, int device)
 {
-    TORCH_CHECK(t.is_cuda() && t.numel() == count && t.scalar_type() == type && t.is_contiguous(), what, ": a contiguous tensor on the GPU expected");
-    TORCH_CHECK((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) == 0, "mx_ramping_adamw_step failed: MX_ERR_ALIGN (-5)");
+    TORCH_CHECK_VALUE(t.numel() == count && t.scalar_type() == type && t.is_contiguous(), what, ": a contiguous ", type, " tensor of ", count, " values expected");
+    if ((reinterpret_cast<uintptr_t>(t.data_ptr()) & 15) != 0) throw Status("mx_ramping_adamw_step", MX_ERR_ALIGN);
+    TORCH_CHECK(t.get_device() == device, what, ": not on the parameter's device");
     return reinterpret_cast<T*>(t.data_ptr());
 }
 
@@ -385,8 +431,9 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
                     *k_codes0 = PyUnicode_InternFromString("codes_prev"), *k_scales0 = PyUnicode_InternFromString("scales_prev");
     const Py_ssize_t n = PyList_GET_SIZE(params.ptr());
     TORCH_CHECK(PyList_GET_SIZE(states.ptr()) == n, "one state per parameter");
-    TORCH_CHECK(lr >= 0.0f && beta1 > 0.0f && beta1 < 1.0f && beta2 > 0.0f && beta2 < 1.0f && eps >= 0.0f && weight_decay >= 0.0f,
-                "mx_ramping_adamw_step failed: MX_ERR_MODE (-4)");
+    // written so that NaN fails
+    if (!(lr >= 0.0f && beta1 > 0.0f && beta1 < 1.0f && beta2 > 0.0f && beta2 < 1.0f && eps >= 0.0f && weight_decay >= 0.0f))
+        throw Status("mx_ramping_adamw_step", MX_ERR_MODE);
     // one batch per device, in order
     std::vector<mxl::RampingAdamwParams> adam;
     std::vector<mxl::WindowTensor> window;
@@ -416,19 +463,21 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
         if (!grad.defined() && mode != 2) continue;
         if (p.get_device() != device) { flush(); device = p.get_device(); }
         const int64_t count = p.numel();
-        float* w = checked<float>(p, count, at::kFloat, "parameter");
+        float* w = checked<float>(p, count, at::kFloat, "parameter", device);
         bool gb = false;
         if (grad.defined()) {
             TORCH_CHECK_VALUE(grad.sizes() == p.sizes(), "shape mismatch");
             gb = is_bf16(grad);
             grad = grad.contiguous();
-            TORCH_CHECK(grad.is_cuda() && (reinterpret_cast<uintptr_t>(grad.data_ptr()) & (gb ? 7 : 15)) == 0, "mx_ramping_adamw_step failed: MX_ERR_ALIGN (-5)");
+            if ((reinterpret_cast<uintptr_t>(grad.data_ptr()) & (gb ? 7 : 15)) != 0) throw Status("mx_ramping_adamw_step", MX_ERR_ALIGN);
+            TORCH_CHECK(grad.get_device() == device, "gradient: not on the parameter's device");
             keep.push_back(grad);
         }
-        auto f32 = [&](PyObject* k) { return checked<float>(state_tensor(st, k), count, at::kFloat, "state"); };
-        auto i32 = [&](PyObject* k) { return checked<int32_t>(state_tensor(st, k), count, at::kInt, "state"); };
+        auto f32 = [&](PyObject* k) { return checked<float>(state_tensor(st, k), count, at::kFloat, "state", device); };
+        auto i32 = [&](PyObject* k) { return checked<int32_t>(state_tensor(st, k), count, at::kInt, "state", device); };
+        TORCH_CHECK(p.is_cuda(), "the optimizer's kernels run on the GPU");
         if (mode == 2) {
-            auto u8s = [&](PyObject* k, int64_t per) { return checked<uint8_t>(state_tensor(st, k), count / per, at::kByte, "state"); };
+            auto u8s = [&](PyObject* k, int64_t per) { return checked<uint8_t>(state_tensor(st, k), count / per, at::kByte, "state", device); };
             bf16[window.size()] = gb;
             window.push_back({w, grad.defined() ? grad.data_ptr() : nullptr, f32(k_m), f32(k_v), i32(k_u), f32(k_acc), i32(k_steps), f32(k_prev),
                               f32(k_dw), f32(k_dq), u8s(k_codes, 2), u8s(k_scales, 32), u8s(k_codes0, 2), u8s(k_scales0, 32)});
@@ -449,6 +498,17 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
 
 PYBIND11_MODULE(_mx_torch, m)
 {
+    py::register_local_exception_translator([](std::exception_ptr p) {
+        try {
+            if (p) std::rethrow_exception(p);
+        } catch (const Status& s) {
+            raise_in_python(s);
+        }
+    });
+    m.def("set_error_class", [](py::object cls) {            // keeps the class for the life of the process
+        Py_XDECREF(mx_error_class);
+        mx_error_class = cls.release().ptr();
+    });
     m.def("linear", &linear, py::call_guard<py::gil_scoped_release>());
     m.def("step_forward", &step_forward, py::call_guard<py::gil_scoped_release>());
     m.def("ramping_step", &ramping_step);

@@ -1,0 +1,52 @@
+"""Host-side checks of the native front ends (no GPU: each call is refused before anything is launched)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def mx():
+    import paper_2502_20853_amd as mx
+    from paper_2502_20853_amd import build
+    if build.is_stale():
+        build.build()
+    mx.binding.host()
+    return mx
+
+
+def refused(mx, code, call, *args, **kw):
+    """The call raises MxError with this code of the C interface."""
+    with pytest.raises(mx.MxError) as e:
+        call(*args, **kw)
+    assert e.value.code == code, e.value
+    return str(e.value)
+
+
+def misaligned(*shape):
+    n = 1
+    for s in shape:
+        n *= s
+    return torch.zeros(n + 1)[1:].view(shape)
+
+
+def test_refusals_carry_the_code_of_the_c_interface(mx):
+    B = mx.binding
+    lin = mx.MxLinear(64, 96, device="cpu")
+    assert "MX_ERR_SHAPE (-2)" in refused(mx, B.MX_ERR_SHAPE, lin, torch.zeros(0, 64))
+    step = mx.MxLinearStep(64, 64, 96, device="cpu")
+    X, W, dY = torch.zeros(64, 64), torch.zeros(96, 64), torch.zeros(64, 96)
+    refused(mx, B.MX_ERR_ALIGN, step.forward, misaligned(64, 64), W, 1)
+    refused(mx, B.MX_ERR_ALIGN, step.forward, torch.zeros(64, 66)[:, :64], W, 1)
+    refused(mx, B.MX_ERR_SHAPE, step.forward, X[:1].expand(64, 64), W, 1)
+    refused(mx, B.MX_ERR_ALIGN, step.backward, misaligned(64, 96), 1)
+    p = torch.nn.Parameter(misaligned(32))
+    p.grad = torch.zeros(32)
+    refused(mx, B.MX_ERR_ALIGN, mx.QRampingAdamW([], [p]).step)
+    q = torch.nn.Parameter(torch.zeros(32))
+    q.grad = misaligned(32)
+    refused(mx, B.MX_ERR_ALIGN, mx.QRampingAdamW([], [q]).step)
+    state = [{}]
+    for bad in (dict(lr=-1.0), dict(b1=1.0), dict(b2=0.0), dict(eps=-1.0), dict(wd=float("nan"))):
+        h = dict(lr=1e-3, b1=0.9, b2=0.999, eps=1e-8, wd=0.0, **{})
+        h.update(bad)
+        refused(mx, B.MX_ERR_MODE, B.host().ramping_step, [q], state, 0, False, False, h["lr"], h["b1"], h["b2"], h["eps"], h["wd"])
