@@ -27,48 +27,45 @@ int check_rows_call(const void* src, int dtype, int64_t rows, int64_t cols, int6
     if (!src || !codes || !scales) return MX_ERR_NULL;
     if (dtype != MX_DTYPE_F32 && dtype != MX_DTYPE_BF16) return MX_ERR_DTYPE;
     if (scale_mode != MX_SCALE_TRUNCFREE && scale_mode != MX_SCALE_FLOOR) return MX_ERR_MODE;
-    if (rows <= 0 || cols <= 0 || (cols % 32) != 0 || ld < cols) return MX_ERR_SHAPE;
-    if (rows > MAX_ELEMS / cols) return MX_ERR_SHAPE;
-    if (!aligned(src, 16) || !aligned(codes, 4)) return MX_ERR_ALIGN;
-    if (ld % (dtype == MX_DTYPE_BF16 ? 8 : 4) != 0) return MX_ERR_ALIGN;
-    return MX_OK;
+    mxl::QuantRowsParams p{};
+    p.src = src; p.bf16 = dtype == MX_DTYPE_BF16; p.rows = rows; p.cols = cols; p.ld = ld;
+    p.codes = const_cast<uint8_t*>(codes); p.scales = const_cast<uint8_t*>(scales);
+    return mxl::check_rows(p);
 }
 
-int check_gemm_call(const uint8_t* aq, const uint8_t* as, const uint8_t* bq, const uint8_t* bs,
-                    int64_t m, int64_t n, int64_t k, const void* out, int out_dtype, int64_t ldo)
+mxl::GemmParams gemm_params(const uint8_t* aq, const uint8_t* as, const uint8_t* bq, const uint8_t* bs,
+                            int64_t m, int64_t n, int64_t k, void* out, int out_dtype, int64_t ldo)
 {
-    if (!aq || !as || !bq || !bs || !out) return MX_ERR_NULL;
+    mxl::GemmParams p{};
+    p.a_codes = aq; p.a_scales = as; p.b_codes = bq; p.b_scales = bs;
+    p.m = m; p.n = n; p.k = k;
+    p.c = out; p.c_bf16 = out_dtype == MX_DTYPE_BF16; p.ldc = ldo;
+    p.split_k = 1;
+    return p;
+}
+
+int check_gemm_call(const mxl::GemmParams& p, int out_dtype)
+{
+    if (!p.a_codes || !p.a_scales || !p.b_codes || !p.b_scales || !p.c) return MX_ERR_NULL;
     if (out_dtype != MX_DTYPE_F32 && out_dtype != MX_DTYPE_BF16) return MX_ERR_DTYPE;
-    if (m <= 0 || n <= 0 || k <= 0 || (k % 32) != 0 || ldo < n) return MX_ERR_SHAPE;
-    // the kernels index with 32 bits: tile counts, and byte offsets of up to 256 packed rows
-    if (m > 0x7FFFFFFFLL || n > 0x7FFFFFFFLL || k > (1LL << 24)) return MX_ERR_SHAPE;
-    if (((m + 255) / 256) * ((n + 127) / 128) > 0x3FFFFFFFLL) return MX_ERR_SHAPE;
-    if (!aligned(aq, 16) || !aligned(bq, 16) || !aligned(as, 4) || !aligned(bs, 4)) return MX_ERR_ALIGN;
-    if (!aligned(out, out_dtype == MX_DTYPE_BF16 ? 8 : 16)) return MX_ERR_ALIGN;
-    return MX_OK;
+    return mxl::check_gemm(p);
 }
 
 int run_gemm(const uint8_t* aq, const uint8_t* as, const uint8_t* bq, const uint8_t* bs,
              int64_t m, int64_t n, int64_t k, void* out, int out_dtype, int64_t ldo,
              void* workspace, size_t workspace_bytes, void* stream, const float* bias = nullptr)
 {
-    int rc = check_gemm_call(aq, as, bq, bs, m, n, k, out, out_dtype, ldo);
+    mxl::GemmParams p = gemm_params(aq, as, bq, bs, m, n, k, out, out_dtype, ldo);
+    p.bias = bias;
+    int rc = check_gemm_call(p, out_dtype);
     if (rc != MX_OK) return rc;
-    if (bias) {
-        if ((n % 4) != 0) return MX_ERR_SHAPE;               // the kernels read the bias four columns at a time
-        if (!aligned(bias, 16)) return MX_ERR_ALIGN;
-    }
     int split = mxl::gemm_split_k(m, n, k);
     size_t need = split > 1 ? (size_t)split * (size_t)m * (size_t)n * sizeof(float) : 0;
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return MX_ERR_WORKSPACE;
         if (!aligned(workspace, 256)) return MX_ERR_ALIGN;
     }
-    mxl::GemmParams p{};
-    p.a_codes = aq; p.a_scales = as; p.b_codes = bq; p.b_scales = bs;
-    p.m = m; p.n = n; p.k = k;
-    p.c = out; p.c_bf16 = out_dtype == MX_DTYPE_BF16; p.ldc = ldo;
-    p.workspace = workspace; p.split_k = split; p.bias = bias;
+    p.workspace = workspace; p.split_k = split;
     return hip_status(mxl::launch_gemm(p, static_cast<hipStream_t>(stream)));
 }
 
@@ -100,6 +97,60 @@ int scratch_of_current_device(void** out)
 }
 
 }  // namespace
+
+namespace mxl {
+
+int check_rows(const QuantRowsParams& p)
+{
+    if (p.rows <= 0 || p.cols <= 0 || (p.cols % 32) != 0 || p.ld < p.cols) return MX_ERR_SHAPE;
+    if (p.rows > MAX_ELEMS / p.cols) return MX_ERR_SHAPE;
+    if (!aligned(p.src, 16) || !aligned(p.codes, 4)) return MX_ERR_ALIGN;
+    if (p.ld % (p.bf16 ? 8 : 4) != 0) return MX_ERR_ALIGN;
+    return MX_OK;
+}
+
+int check_ema(const QuantRowsParams& p, const float* ema, float beta, int update_ema)
+{
+    if (update_ema < 0 || update_ema > 2) return MX_ERR_MODE;
+    if (!(beta >= 0.0f && beta < 1.0f)) return MX_ERR_MODE;
+    if (!aligned(ema, 16) || (p.ld % 4) != 0) return MX_ERR_ALIGN;
+    return MX_OK;
+}
+
+int check_tile(const QuantTileParams& p)
+{
+    const bool given = p.row_codes_in != nullptr;
+    if (p.rows <= 0 || p.cols <= 0 || (p.rows % 32) != 0 || (p.cols % 32) != 0) return MX_ERR_SHAPE;
+    if (!given && (p.ld < p.cols || p.src_rows < 0 || p.src_rows > p.rows)) return MX_ERR_SHAPE;
+    if (p.rows > MAX_ELEMS / p.cols || p.rows > 65535LL * 128) return MX_ERR_SHAPE;
+    if (!aligned(p.codes_t, 16)) return MX_ERR_ALIGN;
+    if (p.codes_row && !aligned(p.codes_row, 16)) return MX_ERR_ALIGN;
+    if (given && !aligned(p.row_codes_in, 16)) return MX_ERR_ALIGN;
+    if (!given) {
+        if (!aligned(p.src, 16)) return MX_ERR_ALIGN;
+        if (p.ld % (p.bf16 ? 8 : 4) != 0) return MX_ERR_ALIGN;
+    }
+    const bool any_sr = p.sr_t || (!given && p.sr_row && (p.pre_quant || p.codes_row));
+    if (any_sr && (p.index_base & 7u) != 0) return MX_ERR_ALIGN;
+    return MX_OK;
+}
+
+int check_gemm(const GemmParams& p)
+{
+    if (p.m <= 0 || p.n <= 0 || p.k <= 0 || (p.k % 32) != 0 || p.ldc < p.n) return MX_ERR_SHAPE;
+    // the kernels index with 32 bits: tile counts, and byte offsets of up to 256 packed rows
+    if (p.m > 0x7FFFFFFFLL || p.n > 0x7FFFFFFFLL || p.k > (1LL << 24)) return MX_ERR_SHAPE;
+    if (((p.m + 255) / 256) * ((p.n + 127) / 128) > 0x3FFFFFFFLL) return MX_ERR_SHAPE;
+    if (!aligned(p.a_codes, 16) || !aligned(p.b_codes, 16) || !aligned(p.a_scales, 4) || !aligned(p.b_scales, 4)) return MX_ERR_ALIGN;
+    if (!aligned(p.c, p.c_bf16 ? 8 : 16)) return MX_ERR_ALIGN;
+    if (p.bias) {
+        if ((p.n % 4) != 0) return MX_ERR_SHAPE;               // the kernels read the bias four columns at a time
+        if (!aligned(p.bias, 16)) return MX_ERR_ALIGN;
+    }
+    return MX_OK;
+}
+
+}  // namespace mxl
 
 extern "C" {
 
@@ -163,18 +214,6 @@ static int make_transposed_job(const void* src, int dtype, int64_t rows, int64_t
     if (round_row != MX_ROUND_RTN && round_row != MX_ROUND_SR) return MX_ERR_MODE;
     if (scale_mode != MX_SCALE_TRUNCFREE && scale_mode != MX_SCALE_FLOOR) return MX_ERR_MODE;
     if (!given && dtype != MX_DTYPE_F32 && dtype != MX_DTYPE_BF16) return MX_ERR_DTYPE;
-    if (rows <= 0 || cols <= 0 || (rows % 32) != 0 || (cols % 32) != 0) return MX_ERR_SHAPE;
-    if (!given && ld < cols) return MX_ERR_SHAPE;
-    if (rows > MAX_ELEMS / cols || rows > 65535LL * 128) return MX_ERR_SHAPE;
-    if (!aligned(codes_t, 16)) return MX_ERR_ALIGN;
-    if (codes_row && !aligned(codes_row, 16)) return MX_ERR_ALIGN;
-    if (given && !aligned(row_codes_in, 16)) return MX_ERR_ALIGN;
-    if (!given) {
-        if (!aligned(src, 16)) return MX_ERR_ALIGN;
-        if (ld % (dtype == MX_DTYPE_BF16 ? 8 : 4) != 0) return MX_ERR_ALIGN;
-    }
-    const bool any_sr = round_t == MX_ROUND_SR || (!given && round_row == MX_ROUND_SR && (pre_quant || codes_row));
-    if (any_sr && (index_base & 7u) != 0) return MX_ERR_ALIGN;
     p = mxl::QuantTileParams{};
     p.src = src; p.bf16 = !given && dtype == MX_DTYPE_BF16; p.rows = rows; p.cols = cols; p.ld = ld;
     p.codes_t = codes_t; p.scales_t = scales_t; p.sr_t = round_t == MX_ROUND_SR; p.tensor_id_t = tensor_id_t;
@@ -182,7 +221,7 @@ static int make_transposed_job(const void* src, int dtype, int64_t rows, int64_t
     p.sr_row = round_row == MX_ROUND_SR; p.tensor_id_row = tensor_id_row;
     p.row_codes_in = row_codes_in; p.row_scales_in = row_scales_in;
     p.floor_mode = scale_mode == MX_SCALE_FLOOR; p.seed = seed; p.index_base = index_base;
-    return MX_OK;
+    return mxl::check_tile(p);
 }
 
 int mx_quantize_transposed(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld,
@@ -256,16 +295,13 @@ int mx_linear_fwd_gelu_quant(const uint8_t* xq, const uint8_t* xs, const uint8_t
 {
     if (!bias || !aq || !as) return MX_ERR_NULL;
     if (N <= 0 || C <= 0 || D <= 0) return (!xq || !xs || !wq || !ws || !y) ? MX_ERR_NULL : MX_ERR_SHAPE;
-    int rc = check_gemm_call(xq, xs, wq, ws, N, C, D, y, y_dtype, ldy);
+    mxl::GemmParams p = gemm_params(xq, xs, wq, ws, N, C, D, y, y_dtype, ldy);
+    int rc = check_gemm_call(p, y_dtype);
     if (rc != MX_OK) return rc;
     if (scale_mode != MX_SCALE_TRUNCFREE && scale_mode != MX_SCALE_FLOOR) return MX_ERR_MODE;
     if ((C % 32) != 0 || !mxl::gemm_takes_fused_quantizer(N, C, D)) return MX_ERR_SHAPE;
     if (!aligned(bias, 16) || !aligned(aq, 16)) return MX_ERR_ALIGN;
-    mxl::GemmParams p{};
-    p.a_codes = xq; p.a_scales = xs; p.b_codes = wq; p.b_scales = ws;
-    p.m = N; p.n = C; p.k = D;
-    p.c = y; p.c_bf16 = y_dtype == MX_DTYPE_BF16; p.ldc = ldy;
-    p.workspace = nullptr; p.split_k = 1; p.bias = bias;
+    p.bias = bias;
     p.q_codes = aq; p.q_scales = as; p.q_floor = scale_mode == MX_SCALE_FLOOR;
     return hip_status(mxl::launch_gemm(p, static_cast<hipStream_t>(stream)));
 }
@@ -291,7 +327,7 @@ int mx_linear_bwd_dw_noalloc(const uint8_t* dytq, const uint8_t* dyts, const uin
 {
     if (N <= 0 || C <= 0 || D <= 0) return (!dytq || !dyts || !xtq || !xts || !dw) ? MX_ERR_NULL : MX_ERR_SHAPE;
     // every argument check of the product first: an invalid call returns before the scratch is looked up
-    int rc = check_gemm_call(dytq, dyts, xtq, xts, C, D, N, dw, dw_dtype, lddw);
+    int rc = check_gemm_call(gemm_params(dytq, dyts, xtq, xts, C, D, N, dw, dw_dtype, lddw), dw_dtype);
     if (rc != MX_OK) return rc;
     const int split = mxl::gemm_split_k(C, D, N);
     const size_t need = split > 1 ? (size_t)split * (size_t)C * (size_t)D * sizeof(float) : 0;
@@ -312,12 +348,11 @@ int mx_ema_weight_quant(const void* w, int dtype, float* w_ema, float beta, int 
     int rc = check_rows_call(w, dtype, rows, cols, ld, codes, scales, scale_mode);
     if (rc != MX_OK) return rc;
     if (!w_ema) return MX_ERR_NULL;
-    if (update_ema < 0 || update_ema > 2) return MX_ERR_MODE;
-    if (!(beta >= 0.0f && beta < 1.0f)) return MX_ERR_MODE;
-    if (!aligned(w_ema, 16) || (ld % 4) != 0) return MX_ERR_ALIGN;
     mxl::QuantRowsParams p{};
     p.src = w; p.bf16 = dtype == MX_DTYPE_BF16; p.rows = rows; p.cols = cols; p.ld = ld;
     p.codes = codes; p.scales = scales; p.sr = false; p.floor_mode = scale_mode == MX_SCALE_FLOOR;
+    rc = mxl::check_ema(p, w_ema, beta, update_ema);
+    if (rc != MX_OK) return rc;
     return hip_status(mxl::launch_ema_quantize(p, w_ema, beta, update_ema, static_cast<hipStream_t>(stream)));
 }
 

@@ -82,6 +82,13 @@ struct GemmParams {
 // Whether launch_gemm runs these sizes on the kernel that carries the fused output quantizer.
 bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k);
 
+// What every caller's arguments must satisfy before a launch (MX_OK or an MX_ERR_* code), for the C interface and the
+// native front ends alike: the kernels themselves rely on it.
+int check_rows(const QuantRowsParams& p);
+int check_ema(const QuantRowsParams& p, const float* ema, float beta, int update_ema);
+int check_tile(const QuantTileParams& p);
+int check_gemm(const GemmParams& p);                    // without the workspace, whose size the caller knows
+
 hipError_t launch_quantize_rows(const QuantRowsParams& p, hipStream_t st);
 // round_D rows of up to two contiguous tensors of any source types, and a vector to widen, in one launch.
 hipError_t launch_quantize_rows_batch(const QuantRowsParams* p, int count, hipStream_t st, const WidenJob* widen = nullptr);

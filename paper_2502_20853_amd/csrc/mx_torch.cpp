@@ -100,22 +100,17 @@ Seed seed_of(int64_t value, const OptTensor& dev)
     return s;
 }
 
-void check_sizes(int64_t rows, int64_t cols, const char* fn)
-{
-    if (!(rows > 0 && cols > 0 && rows <= (int64_t)0xFFFF0000LL * 8 / cols && rows <= 0x7FFFFFFFLL)) throw Status(fn, MX_ERR_SHAPE);
-}
-
 // One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split.
 void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
              const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr,
              const mxl::ColumnSumTail* tail = nullptr)
 {
-    if (!(m > 0 && n > 0 && k > 0 && k <= (1LL << 24))) throw Status(fn, MX_ERR_SHAPE);
     mxl::GemmParams p{};
     p.a_codes = a; p.a_scales = as; p.b_codes = b; p.b_scales = bs;
     p.m = m; p.n = n; p.k = k;
     p.c = out.data_ptr(); p.c_bf16 = is_bf16(out); p.ldc = ldc;
     p.bias = bias;
+    check(mxl::check_gemm(p), fn);
     p.split_k = mxl::gemm_split_k(m, n, k);
     Tensor own;
     if (p.split_k > 1) {
@@ -126,6 +121,7 @@ void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_
             own = bytes_like(out, need);                    // returned to the allocator in stream order
             p.workspace = own.data_ptr();
         }
+        if ((reinterpret_cast<uintptr_t>(p.workspace) & 255) != 0) throw Status(fn, MX_ERR_ALIGN);
     }
     check_hip(mxl::launch_gemm(p, st, tail), fn);
 }
@@ -148,11 +144,22 @@ struct Layer {
 
 void ema_rows(const Tensor& w, const Tensor& w_ema, const Layer& o, int64_t C, int64_t D, uint8_t* codes, uint8_t* scales, hipStream_t st)
 {
-    TORCH_CHECK_VALUE(w_ema.scalar_type() == at::kFloat && w_ema.is_contiguous() && w_ema.sizes() == w.sizes(),
-                      "w_ema must be float32 with the shape and strides of w");
-    if (!(o.beta >= 0.0 && (float)o.beta < 1.0f)) throw Status("mx_ema_weight_quant", MX_ERR_MODE);
     check_hip(mxl::launch_ema_quantize(rows_job(w, C, D, codes, scales, o.floor_mode), w_ema.data_ptr<float>(), (float)o.beta, o.update_ema, st),
               "mx_ema_weight_quant");
+}
+
+// The row and tile quantizers' launches behind their argument checks.
+void launch_rows(const mxl::QuantRowsParams* q, int count, hipStream_t st, const mxl::WidenJob* widen)
+{
+    for (int j = 0; j < count; ++j) check(mxl::check_rows(q[j]), "mx_quantize");
+    check_hip(mxl::launch_quantize_rows_batch(q, count, st, widen), "mx_quantize");
+}
+
+void launch_tiles(const mxl::QuantTileParams* q, int count, hipStream_t st, const mxl::WidenJob* widen = nullptr, bool finish_col_sums = true)
+{
+    const char* fn = count > 1 ? "mx_quantize_transposed_batch" : "mx_quantize_transposed";
+    for (int j = 0; j < count; ++j) check(mxl::check_tile(q[j]), fn);
+    check_hip(mxl::launch_quantize_tile_batch(q, count, st, widen, finish_col_sums), fn);
 }
 
 // FP32 bias: the tensor itself, or a place in `base` that a quantizer launch widens it into.
@@ -197,7 +204,7 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
 
     if (!saved) {
         mxl::QuantRowsParams q[2] = {rows_job(x, N, D, r + o_xq, r + o_xs, o.floor_mode), rows_job(w, C, D, r + o_wq, r + o_ws, o.floor_mode)};
-        check_hip(mxl::launch_quantize_rows_batch(q, w_ema ? 1 : 2, st, &widen), "mx_quantize");
+        launch_rows(q, w_ema ? 1 : 2, st, &widen);
         if (w_ema) ema_rows(w, *w_ema, o, C, D, r + o_wq, r + o_ws, st);
     } else {
         Carver v;
@@ -215,7 +222,7 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
         q[0].codes_t = s + o_xtq; q[0].scales_t = s + o_xts; q[0].codes_row = r + o_xq; q[0].scales_row = r + o_xs;
         job(q[1], w, C, C, Q4, Q2);
         q[1].codes_t = s + o_wtq; q[1].scales_t = s + o_wts; q[1].codes_row = r + o_wq; q[1].scales_row = r + o_ws;
-        check_hip(mxl::launch_quantize_tile_batch(q, w_ema ? 1 : 2, st, &widen), "mx_quantize_transposed");
+        launch_tiles(q, w_ema ? 1 : 2, st, &widen);
         if (w_ema) {
             ema_rows(w, *w_ema, o, C, D, r + o_wq, r + o_ws, st);
             q[1].codes_row = q[1].scales_row = nullptr;
@@ -223,7 +230,7 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
                 q[1].src = nullptr; q[1].bf16 = false;
                 q[1].row_codes_in = r + o_wq; q[1].row_scales_in = r + o_ws;
             }
-            check_hip(mxl::launch_quantize_tile_batch(q + 1, 1, st), "mx_quantize_transposed");
+            launch_tiles(q + 1, 1, st);
         }
     }
     Tensor y = at::empty(with_last(x_in.sizes(), C), x.options());
@@ -274,7 +281,6 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         const Tensor dy = dense_source(grads[0]);
         c10::hip::HIPGuard device((c10::DeviceIndex)dy.get_device());
         const int64_t N = dy.numel() / C, Np = padded_rows(N);
-        check_sizes(Np, C, "mx_quantize_transposed");
         hipStream_t st = c10::hip::getCurrentHIPStream(dy.get_device()).stream();
         Carver v;
         const int64_t o_xtq = v.codes(D, Np), o_xts = v.scales(D, Np), o_wtq = v.codes(D, C), o_wts = v.scales(D, C);
@@ -302,10 +308,11 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
                 q.col_sum_workspace = reinterpret_cast<float*>(p + o_cs);
                 tail = mxl::column_sum_tail(q);
             }
-            check_hip(mxl::launch_quantize_tile_batch(&q, 1, st, nullptr, false), "mx_quantize_transposed");
+            launch_tiles(&q, 1, st, nullptr, false);
         } else if (want_dx && !seed.dev) {
             mxl::QuantRowsParams q = rows_job(dy, N, C, p + o_q, p + o_s, floor_mode);
             q.sr = tetra; q.seed = seed.value; q.tensor_id = Q3;
+            check(mxl::check_rows(q), "mx_quantize");
             check_hip(mxl::launch_quantize_rows(q, st), "mx_quantize");
         } else if (want_dx) {                                // the row quantizer takes its seed by value only
             mxl::QuantTileParams q{};
@@ -314,7 +321,7 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
             q.codes_t = p + o_tq; q.scales_t = p + o_ts; q.sr_t = tetra; q.tensor_id_t = Q5;
             q.codes_row = p + o_q; q.scales_row = p + o_s; q.sr_row = tetra; q.tensor_id_row = Q3;
             q.floor_mode = floor_mode; q.seed_dev = seed.dev;
-            check_hip(mxl::launch_quantize_tile_batch(&q, 1, st), "mx_quantize_transposed");
+            launch_tiles(&q, 1, st);
         }
         if (want_dx) {
             dx = at::empty(shape, dy.options());
@@ -330,14 +337,30 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
     }
 };
 
-Tensor linear(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, bool tetra,
-              bool floor_mode, uint64_t seed, const OptTensor& seed_dev)
+// What the pass relies on, looked at before any of it runs (and before the device, so that it can be tested without one).
+// weight is a parameter that a program may replace: its sizes are looked at on every call.
+void check_layer(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, const OptTensor& seed_dev)
 {
     TORCH_CHECK(w.dim() == 2 && x.dim() >= 1 && x.size(-1) == w.size(1), "input of ", w.size(1), " features expected, got ", x.sizes());
     TORCH_CHECK(!bias || bias->numel() == w.size(0), "bias must have ", w.size(0), " values");
-    check_sizes(w.size(0), w.size(1), "mx_quantize_transposed");
-    check_sizes(x.numel() / w.size(1), w.size(1), "mx_quantize_transposed");
-    TORCH_CHECK(x.is_cuda() && w.is_cuda() && x.get_device() == w.get_device(), "MxLinear runs on the GPU: x and weight must be on one");
+    if (x.numel() == 0 || w.numel() == 0 || w.size(0) % 32 != 0 || w.size(1) % 32 != 0) throw Status("mx_quantize_transposed", MX_ERR_SHAPE);
+    if (w_ema) {
+        TORCH_CHECK_VALUE(w_ema->scalar_type() == at::kFloat && w_ema->is_contiguous() && w_ema->sizes() == w.sizes(),
+                          "w_ema must be float32 with the shape and strides of w");
+        mxl::QuantRowsParams q{};
+        q.rows = w.size(0); q.cols = q.ld = w.size(1);
+        check(mxl::check_ema(q, w_ema->data_ptr<float>(), (float)beta, (int)update_ema), "mx_ema_weight_quant");
+    }
+    TORCH_CHECK(x.is_cuda(), "MxLinear runs on the GPU");
+    auto there = [&](const Tensor& t) { return t.get_device() == x.get_device(); };
+    TORCH_CHECK(there(w) && (!bias || there(*bias)) && (!w_ema || there(*w_ema)) && (!seed_dev || there(*seed_dev)),
+                "MxLinear: x, weight, bias, moving average and seed must be on one GPU");
+}
+
+Tensor linear(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, bool tetra,
+              bool floor_mode, uint64_t seed, const OptTensor& seed_dev)
+{
+    check_layer(x, w, bias, w_ema, update_ema, beta, seed_dev);
     c10::hip::HIPGuard device((c10::DeviceIndex)x.get_device());
     const bool grad = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias && bias->requires_grad()));
     if (!grad) {
@@ -383,7 +406,7 @@ void step_forward(const Tensor& X, const Tensor& W, int64_t N, int64_t D, int64_
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q[2] = {tile_job(X, N, D, xb, true, Q6, true, false, Q1, floor_mode, seed),
                                        tile_job(W, C, D, wb, true, Q4, true, false, Q2, floor_mode, seed)};
-    check_hip(mxl::launch_quantize_tile_batch(q, 2, st), "mx_quantize_transposed_batch");
+    launch_tiles(q, 2, st);
     product(u8(xb[0]), u8(xb[1]), u8(wb[0]), u8(wb[1]), N, C, D, y, y.stride(0), nullptr, st, "mx_linear_fwd", &workspace);
 }
 
@@ -394,7 +417,7 @@ void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t s
     check_source(dY, N, C, "dY");
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
-    check_hip(mxl::launch_quantize_tile_batch(&q, 1, st), "mx_quantize_transposed");
+    launch_tiles(&q, 1, st);
     product(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, st, "mx_linear_bwd_dx", &workspace);
     product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, "mx_linear_bwd_dw", &workspace);
 }

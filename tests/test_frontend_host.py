@@ -50,3 +50,21 @@ def test_refusals_carry_the_code_of_the_c_interface(mx):
         h = dict(lr=1e-3, b1=0.9, b2=0.999, eps=1e-8, wd=0.0, **{})
         h.update(bad)
         refused(mx, B.MX_ERR_MODE, B.host().ramping_step, [q], state, 0, False, False, h["lr"], h["b1"], h["b2"], h["eps"], h["wd"])
+
+
+def test_linear_refuses_sizes_the_kernels_do_not_take(mx):
+    """weight is a parameter that a program may replace after the constructor's checks."""
+    B = mx.binding
+    for c, d in ((40, 64), (96, 48), (96, 0), (0, 64)):
+        lin = mx.MxLinear(64, 96, bias=False, device="cpu")
+        lin.weight = torch.nn.Parameter(torch.zeros(c, d))
+        for grad in (True, False):
+            with torch.set_grad_enabled(grad):
+                refused(mx, B.MX_ERR_SHAPE, lin, torch.zeros(32, d))
+    lin = mx.MxLinear(64, 96, qema=True, device="cpu")
+    lin.w_ema = misaligned(96, 64)
+    refused(mx, B.MX_ERR_ALIGN, lin, torch.zeros(32, 64))
+    for beta in (1.0, -0.1, float("nan")):
+        refused(mx, B.MX_ERR_MODE, mx.MxLinear(64, 96, qema=True, beta=beta, device="cpu"), torch.zeros(32, 64))
+    with pytest.raises(ValueError):
+        mx.MxLinear(64, 96, qema=True, device="cpu").to(torch.bfloat16)(torch.zeros(32, 64))

@@ -253,3 +253,32 @@ def test_module_equals_the_calls_on_padded_tensors(mx, tokens, xt, wt, flow, qem
     with torch.no_grad():
         assert torch.equal(lin(x), y0)
         assert torch.equal(lin(x.reshape(1, tokens, 1, D)).reshape(tokens, C), y0)
+
+
+def test_step_refuses_what_the_c_interface_refuses(mx):
+    """MxLinearStep's buffers are attributes that a program may replace; each call is refused before anything is launched."""
+    B = mx.binding
+
+    def refused(code, call, *args):
+        with pytest.raises(mx.MxError) as e:
+            call(*args)
+        assert e.value.code == code, e.value
+
+    z = lambda *s, **kw: torch.zeros(s, device="cuda", **kw)
+    X, W, dY = z(64, 64), z(96, 64), z(64, 96)
+    step = lambda: mx.MxLinearStep(64, 64, 96, out_dtype=torch.float32)
+    shifted = lambda t, by: torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")[by:].view(t.shape)
+    for name, by, call, arg in (("y", 1, "forward", (X, W)), ("dx", 1, "backward", (dY,)), ("dw", 1, "backward", (dY,)),
+                                ("xtq", 4, "forward", (X, W)), ("wq", 4, "forward", (X, W)), ("dyq", 4, "backward", (dY,))):
+        s = step()
+        setattr(s, name, shifted(getattr(s, name), by))
+        refused(B.MX_ERR_ALIGN, getattr(s, call), *arg, 1)
+    s = step()
+    s.y = z(64, 96, dtype=torch.float16)
+    with pytest.raises(TypeError):
+        s.forward(X, W, 1)
+    # more rows than the tile quantizer's index takes
+    n = 65535 * 128 + 32
+    s = mx.MxLinearStep(n, 32, 32)
+    refused(B.MX_ERR_SHAPE, s.forward, z(n, 32, dtype=torch.bfloat16), z(32, 32, dtype=torch.bfloat16), 1)
+    refused(B.MX_ERR_SHAPE, s.backward, z(n, 32, dtype=torch.bfloat16), 1)
