@@ -48,6 +48,12 @@ void check(int code, const char* fn)
     if (code != MX_OK) throw Status(fn, code);
 }
 
+bool floor_of(int scale_mode, const char* fn)
+{
+    if (scale_mode != MX_SCALE_TRUNCFREE && scale_mode != MX_SCALE_FLOOR) throw Status(fn, MX_ERR_MODE);
+    return scale_mode == MX_SCALE_FLOOR;
+}
+
 void check_hip(hipError_t e, const char* fn)
 {
     if (e != hipSuccess) throw Status(fn, MX_ERR_HIP, (int)e);
@@ -358,8 +364,9 @@ void check_layer(const Tensor& x, const Tensor& w, const OptTensor& bias, const 
 }
 
 Tensor linear(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, bool tetra,
-              bool floor_mode, uint64_t seed, const OptTensor& seed_dev)
+              int scale_mode, uint64_t seed, const OptTensor& seed_dev)
 {
+    const bool floor_mode = floor_of(scale_mode, "mx_quantize_transposed");
     check_layer(x, w, bias, w_ema, update_ema, beta, seed_dev);
     c10::hip::HIPGuard device((c10::DeviceIndex)x.get_device());
     const bool grad = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias && bias->requires_grad()));
@@ -398,8 +405,9 @@ mxl::QuantTileParams tile_job(const Tensor& src, int64_t rows, int64_t cols, con
 
 // xb, wb: (row codes, row scales, transposed codes, transposed scales) of X and W.
 void step_forward(const Tensor& X, const Tensor& W, int64_t N, int64_t D, int64_t C, uint64_t seed_value, const OptTensor& seed_dev,
-                  const std::vector<Tensor>& xb, const std::vector<Tensor>& wb, const Tensor& y, const Tensor& workspace, bool floor_mode)
+                  const std::vector<Tensor>& xb, const std::vector<Tensor>& wb, const Tensor& y, const Tensor& workspace, int scale_mode)
 {
+    const bool floor_mode = floor_of(scale_mode, "mx_quantize_transposed");
     check_source(X, N, D, "X");
     check_source(W, C, D, "W");
     const Seed seed = seed_of((int64_t)seed_value, seed_dev);
@@ -412,8 +420,9 @@ void step_forward(const Tensor& X, const Tensor& W, int64_t N, int64_t D, int64_
 
 void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t seed_value, const OptTensor& seed_dev, const std::vector<Tensor>& dyb,
                    const std::vector<Tensor>& wt, const std::vector<Tensor>& xt, const Tensor& dx, const Tensor& dw, const Tensor& workspace,
-                   bool floor_mode)
+                   int scale_mode)
 {
+    const bool floor_mode = floor_of(scale_mode, "mx_quantize_transposed");
     check_source(dY, N, C, "dY");
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
@@ -443,9 +452,10 @@ T* checked(const Tensor& t, int64_t count, at::ScalarType type, const char* what
 
 // mode 0: plain AdamW, 1: with amplification factors, 2: a step inside a detection window (`opens`: its first).
 // params and states are parallel lists; a parameter without a gradient is skipped (mode 2: only tracked).
-void ramping_step(const py::list& params, const py::list& states, int mode, bool opens, bool floor_mode, float lr, float beta1, float beta2,
+void ramping_step(const py::list& params, const py::list& states, int mode, bool opens, int scale_mode, float lr, float beta1, float beta2,
                   float eps, float weight_decay)
 {
+    const bool floor_mode = mode == 2 && floor_of(scale_mode, "mx_quantize");       // used inside a window only
     static PyObject *k_m = PyUnicode_InternFromString("m"), *k_v = PyUnicode_InternFromString("v"), *k_u = PyUnicode_InternFromString("updates"),
                     *k_acc = PyUnicode_InternFromString("g_acc"), *k_steps = PyUnicode_InternFromString("acc_steps"),
                     *k_factor = PyUnicode_InternFromString("factor"), *k_prev = PyUnicode_InternFromString("w_prev"),

@@ -67,8 +67,7 @@ class MxLinearStep:
         if not self.qema:                                  # one native call: Q1/Q6 and Q2/Q4 in one launch, then the product
             value, dev = B.seed_args(seed)
             B.host().step_forward(X, W, self.N, self.D, self.C, value, dev, (self.xq, self.xs, self.xtq, self.xts),
-                                  (self.wq, self.ws, self.wtq, self.wts), self.y, self.workspace,
-                                  self.scale_mode == B.SCALE_FLOOR)
+                                  (self.wq, self.ws, self.wtq, self.wts), self.y, self.workspace, self.scale_mode)
             return self.y
         self.quantize_inputs(X, W, seed)
         return B.mx_linear_fwd(self.xq, self.xs, self.wq, self.ws, out=self.y, workspace=self.workspace)
@@ -76,8 +75,7 @@ class MxLinearStep:
     def backward(self, dY, seed):
         value, dev = B.seed_args(seed)
         B.host().step_backward(dY, self.N, self.D, self.C, value, dev, (self.dyq, self.dys, self.dytq, self.dyts),
-                               (self.wtq, self.wts), (self.xtq, self.xts), self.dx, self.dw, self.workspace,
-                               self.scale_mode == B.SCALE_FLOOR)
+                               (self.wtq, self.wts), (self.xtq, self.xts), self.dx, self.dw, self.workspace, self.scale_mode)
         return self.dx, self.dw
 
     def step_two_streams(self, X, W, dY, seed, side, dw_workspace=None):

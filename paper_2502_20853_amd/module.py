@@ -78,4 +78,4 @@ class MxLinear(torch.nn.Module):
             seed = (self.key_high << 32) + (self.calls & 0xFFFFFFFF)
         self.calls += 1
         return B.host().linear(x, self.weight, self.bias, self.w_ema, self._ema_update() if self.qema else 0, self.beta,
-                               self.flow == TETRAJET, self.scale_mode == B.SCALE_FLOOR, seed, seed_dev)
+                               self.flow == TETRAJET, self.scale_mode, seed, seed_dev)

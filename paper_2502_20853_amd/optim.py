@@ -95,7 +95,7 @@ class QRampingAdamW(torch.optim.Optimizer):
             # A weight without a gradient stands still.
             params = g["params"] if detecting else [p for p in g["params"] if p.grad is not None]
             states = [self.state[p] or self._state(p, g["quantized"]) for p in params]
-            B.host().ramping_step(params, states, 2 if detecting else int(g["quantized"]), phase == 0, g["scale_mode"] == B.SCALE_FLOOR,
+            B.host().ramping_step(params, states, 2 if detecting else int(g["quantized"]), phase == 0, g["scale_mode"],
                                   lr, beta1, beta2, eps, decay)
             if detecting and phase == g["t0"] - 1:
                 for st in states:

@@ -49,7 +49,7 @@ def test_refusals_carry_the_code_of_the_c_interface(mx):
     for bad in (dict(lr=-1.0), dict(b1=1.0), dict(b2=0.0), dict(eps=-1.0), dict(wd=float("nan"))):
         h = dict(lr=1e-3, b1=0.9, b2=0.999, eps=1e-8, wd=0.0, **{})
         h.update(bad)
-        refused(mx, B.MX_ERR_MODE, B.host().ramping_step, [q], state, 0, False, False, h["lr"], h["b1"], h["b2"], h["eps"], h["wd"])
+        refused(mx, B.MX_ERR_MODE, B.host().ramping_step, [q], state, 0, False, 0, h["lr"], h["b1"], h["b2"], h["eps"], h["wd"])
 
 
 def test_linear_refuses_sizes_the_kernels_do_not_take(mx):
@@ -68,3 +68,15 @@ def test_linear_refuses_sizes_the_kernels_do_not_take(mx):
         refused(mx, B.MX_ERR_MODE, mx.MxLinear(64, 96, qema=True, beta=beta, device="cpu"), torch.zeros(32, 64))
     with pytest.raises(ValueError):
         mx.MxLinear(64, 96, qema=True, device="cpu").to(torch.bfloat16)(torch.zeros(32, 64))
+
+
+def test_unknown_scale_modes_are_refused(mx):
+    B = mx.binding
+    X, W, dY = torch.zeros(64, 64), torch.zeros(96, 64), torch.zeros(64, 96)
+    for mode in (-1, 2, 7):
+        step = mx.MxLinearStep(64, 64, 96, device="cpu", scale_mode=mode)
+        refused(mx, B.MX_ERR_MODE, mx.MxLinear(64, 96, device="cpu", scale_mode=mode), X)
+        refused(mx, B.MX_ERR_MODE, step.forward, X, W, 1)
+        refused(mx, B.MX_ERR_MODE, step.backward, dY, 1)
+        w = torch.nn.Parameter(torch.zeros(4, 64))
+        refused(mx, B.MX_ERR_MODE, mx.QRampingAdamW([w], scale_mode=mode).step)          # the first step opens a window
