@@ -495,7 +495,10 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
         Tensor grad = p.grad();
         if (!grad.defined() && mode != 2) continue;
         if (p.get_device() != device) { flush(); device = p.get_device(); }
+        // a group added later has not passed the constructor's checks
         const int64_t count = p.numel();
+        if (mode == 2 && (p.dim() != 2 || p.size(1) % 32 != 0)) throw Status("mx_quantize", MX_ERR_SHAPE);
+        if (count <= 0 || count % 4 != 0) throw Status("mx_ramping_adamw_step", MX_ERR_SHAPE);
         float* w = checked<float>(p, count, at::kFloat, "parameter", device);
         bool gb = false;
         if (grad.defined()) {

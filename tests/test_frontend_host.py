@@ -80,3 +80,18 @@ def test_unknown_scale_modes_are_refused(mx):
         refused(mx, B.MX_ERR_MODE, step.backward, dY, 1)
         w = torch.nn.Parameter(torch.zeros(4, 64))
         refused(mx, B.MX_ERR_MODE, mx.QRampingAdamW([w], scale_mode=mode).step)          # the first step opens a window
+
+
+def test_optimizer_refuses_lengths_the_kernels_do_not_take(mx):
+    """A parameter group that is added later does not pass the constructor's checks."""
+    B = mx.binding
+    for shape, quantized in (((10,), False), ((0,), False), ((2, 48), True), ((1, 40), True), ((64,), True), ((0, 32), True)):
+        opt = mx.QRampingAdamW([], [torch.nn.Parameter(torch.zeros(32))])
+        p = torch.nn.Parameter(torch.zeros(shape))
+        opt.add_param_group({"params": [p], "quantized": quantized})
+        p.grad = torch.zeros(shape)
+        if len(shape) == 2 or not quantized:
+            refused(mx, B.MX_ERR_SHAPE, opt.step)
+        else:
+            with pytest.raises(ValueError):                                  # no rows and columns to make a state for
+                opt.step()
