@@ -6,6 +6,7 @@ have the same names as the C entry points.  A missing or unloadable library is
 an error -- there is no fallback path.
 """
 import ctypes
+import operator
 import os
 
 import torch
@@ -136,7 +137,7 @@ def host():
 
 def seed_args(seed):
     """(value, device tensor) of a seed given as an int or as a one-element int64 device tensor."""
-    return (0, seed) if torch.is_tensor(seed) else (seed & 0xFFFFFFFFFFFFFFFF, None)
+    return (0, seed) if torch.is_tensor(seed) else (operator.index(seed) & 0xFFFFFFFFFFFFFFFF, None)
 
 
 def _check(fn, rc):

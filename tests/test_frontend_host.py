@@ -95,3 +95,15 @@ def test_optimizer_refuses_lengths_the_kernels_do_not_take(mx):
         else:
             with pytest.raises(ValueError):                                  # no rows and columns to make a state for
                 opt.step()
+
+
+def test_seeds_of_any_integer_type(mx):
+    """What ctypes takes as a 64-bit word: any integer, modulo 2^64."""
+    np = pytest.importorskip("numpy")
+    for seed, word in ((3, 3), (True, 1), (-1, 2 ** 64 - 1), (2 ** 64 + 5, 5), (np.int64(7), 7), (np.uint64(2 ** 63), 2 ** 63), (np.int32(-2), 2 ** 64 - 2)):
+        assert mx.binding.seed_args(seed) == (word, None)
+    for seed in (1.5, "1", None):
+        with pytest.raises(TypeError):
+            mx.binding.seed_args(seed)
+    t = torch.zeros(1, dtype=torch.int64)
+    assert mx.binding.seed_args(t)[1] is t
