@@ -168,11 +168,13 @@ void launch_tiles(const mxl::QuantTileParams* q, int count, hipStream_t st, cons
     check_hip(mxl::launch_quantize_tile_batch(q, count, st, widen, finish_col_sums), fn);
 }
 
-// FP32 bias: the tensor itself, or a place in `base` that a quantizer launch widens it into.
+bool is_f32_or_bf16(at::ScalarType t) { return t == at::kFloat || t == at::kBFloat16; }
+
+// FP32 bias: the tensor itself, a place in `base` that a quantizer launch widens bf16 into, or a converted copy.
 const float* bias_source(const OptTensor& bias, Tensor& keep, uint8_t* place, mxl::WidenJob& widen)
 {
     if (!bias) return nullptr;
-    keep = dense_source(*bias);
+    keep = dense_source(is_f32_or_bf16(bias->scalar_type()) ? *bias : bias->to(at::kFloat));
     if (!is_bf16(keep)) return keep.data_ptr<float>();
     widen.src = static_cast<const uint16_t*>(keep.data_ptr());
     widen.dst = reinterpret_cast<float*>(place);
@@ -309,7 +311,8 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
             q.sr_row = tetra; q.tensor_id_row = Q3;
             q.floor_mode = floor_mode; q.seed = seed.value; q.seed_dev = seed.dev;
             if (want_db) {
-                db = at::empty({C}, dy.options().dtype((at::ScalarType)meta[6]));
+                const at::ScalarType type = (at::ScalarType)meta[6];
+                db = at::empty({C}, dy.options().dtype(is_f32_or_bf16(type) ? type : at::kFloat));
                 q.col_sums = db.data_ptr(); q.col_sums_bf16 = is_bf16(db);
                 q.col_sum_workspace = reinterpret_cast<float*>(p + o_cs);
                 tail = mxl::column_sum_tail(q);
@@ -339,6 +342,7 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         } else if (want_db) {
             check_hip(mxl::launch_column_sum_finish(tail, st), "mx_quantize_transposed_batch");
         }
+        if (want_db) db = db.to((at::ScalarType)meta[6]);
         return {dx, dw, db, Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
     }
 };

@@ -282,3 +282,20 @@ def test_step_refuses_what_the_c_interface_refuses(mx):
     s = mx.MxLinearStep(n, 32, 32)
     refused(B.MX_ERR_SHAPE, s.forward, z(n, 32, dtype=torch.bfloat16), z(32, 32, dtype=torch.bfloat16), 1)
     refused(B.MX_ERR_SHAPE, s.backward, z(n, 32, dtype=torch.bfloat16), 1)
+
+
+@pytest.mark.parametrize("dt", [torch.float16, torch.float64])
+@pytest.mark.parametrize("tokens", [33, 4100])
+def test_bias_of_another_floating_type(mx, dt, tokens):
+    """The bias enters the product as FP32 and its gradient comes back in its own type."""
+    torch.manual_seed(tokens)
+    lin, ref = (mx.MxLinear(64, 96, seed=1, layer_id=2) for _ in range(2))
+    ref.load_state_dict(lin.state_dict())
+    lin.bias = torch.nn.Parameter(torch.randn(96, device="cuda").to(dt))
+    ref.bias = torch.nn.Parameter(lin.bias.detach().float())
+    x, dy = torch.randn(tokens, 64, device="cuda"), torch.randn(tokens, 96, device="cuda")
+    y, y0 = lin(x), ref(x)
+    g, g0 = (torch.autograd.grad(v, (m.weight, m.bias), dy) for v, m in ((y, lin), (y0, ref)))
+    assert torch.equal(y, y0) and torch.equal(g[0], g0[0]) and g[1].dtype == dt and torch.equal(g[1], g0[1].to(dt))
+    with torch.no_grad():
+        assert torch.equal(lin(x), y0)
