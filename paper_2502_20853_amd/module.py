@@ -61,13 +61,6 @@ class MxLinear(torch.nn.Module):
                                                         device=device) if device_seed else None)
         self._ema_started = False
 
-    def _ema_update(self):
-        """How this forward call treats the moving average: 2 starts it from the weight, 1 advances it, 0 leaves it."""
-        if not self._ema_started:
-            self._ema_started = True
-            return 2
-        return 1 if self.training else 0
-
     def forward(self, x):
         seed_dev = None
         if self.seed_state is not None:
@@ -77,5 +70,8 @@ class MxLinear(torch.nn.Module):
         else:
             seed = (self.key_high << 32) + (self.calls & 0xFFFFFFFF)
         self.calls += 1
-        return B.host().linear(x, self.weight, self.bias, self.w_ema, self._ema_update() if self.qema else 0, self.beta,
-                               self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
+        # the moving average: 2 starts it from the weight, 1 advances it, 0 leaves it
+        update = 0 if not self.qema else 2 if not self._ema_started else 1 if self.training else 0
+        y = B.host().linear(x, self.weight, self.bias, self.w_ema, update, self.beta, self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
+        self._ema_started = self._ema_started or self.qema      # not before: a refused call has started nothing
+        return y

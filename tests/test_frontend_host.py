@@ -107,3 +107,11 @@ def test_seeds_of_any_integer_type(mx):
             mx.binding.seed_args(seed)
     t = torch.zeros(1, dtype=torch.int64)
     assert mx.binding.seed_args(t)[1] is t
+
+
+def test_a_refused_call_does_not_start_the_moving_average(mx):
+    lin = mx.MxLinear(64, 96, qema=True, device="cpu")
+    for x in (torch.zeros(32, 32), torch.zeros(32, 64, dtype=torch.float16), torch.zeros(0, 64)):
+        with pytest.raises(Exception):
+            lin(x)
+    assert not lin._ema_started                              # the next call starts it from the weight
