@@ -70,8 +70,11 @@ class MxLinear(torch.nn.Module):
         else:
             seed = (self.key_high << 32) + (self.calls & 0xFFFFFFFF)
         self.calls += 1
-        # the moving average: 2 starts it from the weight, 1 advances it, 0 leaves it
-        update = 0 if not self.qema else 2 if not self._ema_started else 1 if self.training else 0
-        y = B.host().linear(x, self.weight, self.bias, self.w_ema, update, self.beta, self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
+        w_ema, update = None, 0
+        if self.qema:                       # 2 starts the moving average from the weight, 1 advances it, 0 leaves it
+            w_ema, update = self.w_ema, 2 if not self._ema_started else 1 if self.training else 0
+            if w_ema is None:
+                raise ValueError("Q-EMA needs the buffer w_ema, which the layer was made without")
+        y = B.host().linear(x, self.weight, self.bias, w_ema, update, self.beta, self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
         self._ema_started = self._ema_started or self.qema      # not before: a refused call has started nothing
         return y

@@ -115,3 +115,16 @@ def test_a_refused_call_does_not_start_the_moving_average(mx):
         with pytest.raises(Exception):
             lin(x)
     assert not lin._ema_started                              # the next call starts it from the weight
+
+
+def test_qema_is_looked_at_on_every_call(mx):
+    lin = mx.MxLinear(64, 96, qema=True, device="cpu")
+    lin.w_ema = misaligned(96, 64)
+    refused(mx, mx.binding.MX_ERR_ALIGN, lin, torch.zeros(32, 64))
+    lin.qema = False
+    with pytest.raises(RuntimeError, match="runs on the GPU"):               # switched off: the buffer plays no part
+        lin(torch.zeros(32, 64))
+    lin = mx.MxLinear(64, 96, device="cpu")
+    lin.qema = True
+    with pytest.raises(ValueError):                                          # switched on without one
+        lin(torch.zeros(32, 64))
