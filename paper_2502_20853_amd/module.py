@@ -16,6 +16,24 @@ TETRAJET, MICROSCALING = "tetrajet", "microscaling"
 _layer_ids = itertools.count()
 
 
+class _TracedLinear(torch.autograd.Function):
+    """The pass as torch.jit.trace records it: one call of this function, made again on every replay.  The native call
+    itself would leave nothing but its allocations in a trace, because its kernels are launched past the dispatcher."""
+
+    @staticmethod
+    def forward(ctx, x, weight, bias, mod, seed, seed_dev):
+        with torch.enable_grad():
+            ctx.inputs = [None if t is None else t.detach().requires_grad_(need)
+                          for t, need in zip((x, weight, bias), ctx.needs_input_grad)]
+            ctx.y = mod._pass(*ctx.inputs, seed, seed_dev)
+        return ctx.y.detach()
+
+    @staticmethod
+    def backward(ctx, dy):
+        grads = iter(torch.autograd.grad(ctx.y, [t for t, need in zip(ctx.inputs, ctx.needs_input_grad) if need], dy, retain_graph=True))
+        return tuple(next(grads) if need else None for need in ctx.needs_input_grad)
+
+
 class MxLinear(torch.nn.Module):
     """y = x W^T (+ bias) with the three products in MXFP4 (Eqs. 3-5).
 
@@ -61,6 +79,18 @@ class MxLinear(torch.nn.Module):
                                                         device=device) if device_seed else None)
         self._ema_started = False
 
+    def _pass(self, x, weight, bias, seed, seed_dev):
+        """The native call.  The call's key is seed, or the word in seed_dev where that is a tensor."""
+        w_ema, update = None, 0
+        if self.qema:                       # 2 starts the moving average from the weight, 1 advances it, 0 leaves it
+            w_ema, update = self.w_ema, 2 if not self._ema_started else 1 if self.training else 0
+            if w_ema is None:
+                raise ValueError("Q-EMA needs the buffer w_ema, which the layer was made without")
+        y = B.host().linear(x, weight, bias, w_ema, update, self.beta, self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
+        if update == 2:                     # not before: a refused call has started nothing
+            self._ema_started = True
+        return y
+
     def forward(self, x):
         seed_dev = None
         if self.seed_state is not None:
@@ -70,11 +100,6 @@ class MxLinear(torch.nn.Module):
         else:
             seed = (self.key_high << 32) + (self.calls & 0xFFFFFFFF)
         self.calls += 1
-        w_ema, update = None, 0
-        if self.qema:                       # 2 starts the moving average from the weight, 1 advances it, 0 leaves it
-            w_ema, update = self.w_ema, 2 if not self._ema_started else 1 if self.training else 0
-            if w_ema is None:
-                raise ValueError("Q-EMA needs the buffer w_ema, which the layer was made without")
-        y = B.host().linear(x, self.weight, self.bias, w_ema, update, self.beta, self.flow == TETRAJET, self.scale_mode, seed, seed_dev)
-        self._ema_started = self._ema_started or self.qema      # not before: a refused call has started nothing
-        return y
+        if torch.jit.is_tracing():
+            return _TracedLinear.apply(x, self.weight, self.bias, self, seed, seed_dev)
+        return self._pass(x, self.weight, self.bias, seed, seed_dev)

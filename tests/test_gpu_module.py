@@ -299,3 +299,30 @@ def test_bias_of_another_floating_type(mx, dt, tokens):
     assert torch.equal(y, y0) and torch.equal(g[0], g0[0]) and g[1].dtype == dt and torch.equal(g[1], g0[1].to(dt))
     with torch.no_grad():
         assert torch.equal(lin(x), y0)
+
+
+@pytest.mark.parametrize("options", [{}, {"bias": False}, {"device_seed": True}, {"qema": True}])
+def test_traced_module_replays_the_pass(mx, options):
+    """torch.jit.trace records the pass as one call: outputs and gradients on other inputs are the module's own."""
+    torch.manual_seed(5)
+    lin, ref = (mx.MxLinear(64, 96, seed=1, layer_id=2, **options) for _ in range(2))
+    ref.load_state_dict(lin.state_dict())
+    xs = [torch.randn(3, 32, 64, device="cuda") for _ in range(4)]
+    lin.eval()
+    with torch.no_grad():
+        traced = torch.jit.trace(lin, xs[0], check_trace=False)
+        want = [ref.eval()(x) for x in xs]
+        for x, y in zip(xs, want):
+            assert torch.equal(traced(x), y)
+    traced = torch.jit.trace(lin, xs[0].clone().requires_grad_(True), check_trace=False)     # one forward call of its own
+    key, dy = lin.calls - 1, torch.randn(3, 32, 96, device="cuda")
+    for x in xs:
+        got, ours = x.clone().requires_grad_(True), x.clone().requires_grad_(True)
+        if lin.seed_state is not None:
+            ref.seed_state.copy_(lin.seed_state)             # the trace advances the word that it shares with the module
+        ref.calls = key                                      # a key from the host is a constant of the trace
+        y, y0 = traced(got), ref(ours)
+        assert torch.equal(y, y0)
+        g = torch.autograd.grad(y, (got, *lin.parameters()), dy)
+        for a, b in zip(g, torch.autograd.grad(y0, (ours, *ref.parameters()), dy)):
+            assert torch.equal(a, b)
