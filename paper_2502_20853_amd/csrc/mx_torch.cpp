@@ -351,6 +351,9 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
 // weight is a parameter that a program may replace: its sizes are looked at on every call.
 void check_layer(const Tensor& x, const Tensor& w, const OptTensor& bias, const OptTensor& w_ema, int64_t update_ema, double beta, const OptTensor& seed_dev)
 {
+    // without a gradient to record the pass goes past the autograd node, which would refuse a tangent
+    for (const Tensor* t : {&x, &w, bias ? &*bias : &x})
+        TORCH_CHECK_NOT_IMPLEMENTED(!t->_fw_grad(0).defined(), "MxLinear has no forward-mode derivative");
     TORCH_CHECK(w.dim() == 2 && x.dim() >= 1 && x.size(-1) == w.size(1), "input of ", w.size(1), " features expected, got ", x.sizes());
     TORCH_CHECK(!bias || bias->numel() == w.size(0), "bias must have ", w.size(0), " values");
     if (x.numel() == 0 || w.numel() == 0 || w.size(0) % 32 != 0 || w.size(1) % 32 != 0) throw Status("mx_quantize_transposed", MX_ERR_SHAPE);

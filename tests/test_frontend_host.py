@@ -128,3 +128,27 @@ def test_qema_is_looked_at_on_every_call(mx):
     lin.qema = True
     with pytest.raises(ValueError):                                          # switched on without one
         lin(torch.zeros(32, 64))
+
+
+@pytest.mark.parametrize("which", ["x", "weight", "bias"])
+@pytest.mark.parametrize("frozen", [True, False])
+def test_forward_mode_tangents_are_refused(mx, which, frozen):
+    """A dual tensor does not require grad: with frozen weights, or under no_grad, nothing but this check sees it."""
+    import torch.autograd.forward_ad as fwd
+    lin, x = mx.MxLinear(64, 96, device="cpu").requires_grad_(not frozen), torch.zeros(32, 64)
+    w, b = lin.weight.detach(), lin.bias.detach()
+    with fwd.dual_level():
+        dual = lambda t: fwd.make_dual(t, torch.ones_like(t))
+        if which == "x":
+            x = dual(x)
+        elif which == "weight":
+            del lin.weight
+            lin.weight = dual(w)
+        else:
+            del lin.bias
+            lin.bias = dual(b)
+        for grad in (True, False):
+            with torch.set_grad_enabled(grad), pytest.raises(NotImplementedError):
+                lin(x)
+        with fwd._set_fwd_grad_enabled(False), pytest.raises(RuntimeError, match="runs on the GPU"):     # tangents switched off
+            lin(x)
