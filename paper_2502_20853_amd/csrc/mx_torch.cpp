@@ -292,6 +292,9 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         hipStream_t st = c10::hip::getCurrentHIPStream(dy.get_device()).stream();
         Carver v;
         const int64_t o_xtq = v.codes(D, Np), o_xts = v.scales(D, Np), o_wtq = v.codes(D, C), o_wts = v.scales(D, C);
+        // what the forward pass saved may have gone through a program's pack and unpack hooks
+        if (keep[0].scalar_type() != at::kByte || keep[0].numel() != v.used || !keep[0].is_contiguous() || keep[0].get_device() != dy.get_device())
+            throw Status("mx_linear_bwd", MX_ERR_SHAPE);
         const uint8_t* s = keep[0].data_ptr<uint8_t>();
 
         Carver t;

@@ -326,3 +326,22 @@ def test_traced_module_replays_the_pass(mx, options):
         g = torch.autograd.grad(y, (got, *lin.parameters()), dy)
         for a, b in zip(g, torch.autograd.grad(y0, (ours, *ref.parameters()), dy)):
             assert torch.equal(a, b)
+
+
+def test_saved_operands_through_hooks(mx):
+    """Hooks that move the saved operands away and back change nothing; what does not come back as it was is refused, as MxError
+    out of the backward pass."""
+    lin = mx.MxLinear(64, 96, seed=1, layer_id=2)
+    x, dy = torch.randn(40, 64, device="cuda", requires_grad=True), torch.randn(40, 96, device="cuda")
+    want = torch.autograd.grad(lin(x), (x, lin.weight, lin.bias), dy)
+    for whole, unpack in ((True, lambda t: t.cuda()), (False, lambda t: t.cuda()[:-256]), (False, lambda t: t), (False, lambda t: t.cuda().float())):
+        lin.calls = 0
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), unpack):
+            y = lin(x)
+        backward = lambda: torch.autograd.grad(y, (x, lin.weight, lin.bias), dy)
+        if whole:
+            assert all(torch.equal(a, b) for a, b in zip(backward(), want))
+        else:
+            with pytest.raises(mx.MxError) as e:
+                backward()
+            assert e.value.code == mx.binding.MX_ERR_SHAPE
