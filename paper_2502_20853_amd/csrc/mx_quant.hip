@@ -20,6 +20,7 @@
 #include "mx_device.hpp"
 #include "mx_launch.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 using namespace mxd;
@@ -272,8 +273,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 // Transposed / fused quantizer.
 //
 // A workgroup of 4 waves owns a 128 x 128 macro tile of the source (128 x 64 for small tensors and for the tiles of a
-// sparsely filled last round); with column sums, which are kept per 256 rows, it has 8 waves and 256 rows.  Wave w owns rows [32w, 32w+32) of it and
-// walks over its 32 x 64 tiles.  The grid is one-dimensional over the macro tiles in row-major order.
+// sparsely filled last round); with column sums, and for large FP32 sources (tile_waves), it has 8 waves and 256 rows.
+// Wave w owns rows [32w, 32w+32) of it and walks over its 32 x 64 tiles.  The grid is one-dimensional over the macro tiles in row-major order.
 // Inside a tile, lane l holds rows 4*(l/8)+j (j = 0..3) x columns 8*(l%8)+t (t = 0..7):
 //   - each load instruction reads 8 full rows of 64 elements,
 //   - a 1x32 row group is 4 neighbouring lanes (DPP quad reduction),
@@ -286,9 +287,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 // 20 -> 18, from packed codes 25216 x 3072 49 -> 42, 256 x 192 FP32 with its weight 7.0 -> 5.7.  Two waves, 64 columns, or five waves per
 // SIMD (spills) are slower: 39, 40 and 43 us for the first of these.
 // ---------------------------------------------------------------------------
-// Waves of a macro tile and what it stages in LDS, sized for macro tiles of 32 * WAVES rows x 128 columns.
-constexpr int tile_waves(bool colsum) { return colsum ? 8 : 4; }
-
+// What a macro tile of 32 * WAVES rows x 128 columns stages in LDS.
 template <int WAVES, bool ROWS, bool COLSUM>
 struct TileShape {
     static constexpr int THREADS = 64 * WAVES, MACRO_ROWS = 32 * WAVES, MACRO_COLS = 128;
@@ -719,10 +718,10 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 }
 
 // SRC as above, or 3: FP32 and bf16 jobs in one launch (a bf16 activation and its FP32 master weight).
-template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM = false>
-__global__ __launch_bounds__(64 * tile_waves(COLSUM), SRC == 2 ? 5 : 4) void quantize_tile_kernel(TileBatch batch)
+template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, SRC == 2 ? 5 : 4) void quantize_tile_kernel(TileBatch batch)
 {
-    using S = TileShape<tile_waves(COLSUM), SRC != 2, COLSUM>;
+    using S = TileShape<WAVES, SRC != 2, COLSUM>;
     __shared__ __attribute__((aligned(16))) uint8_t st[S::BYTES];
     if (batch.widen.count != 0u && blockIdx.x == gridDim.x - 1u) {
         widen_bf16(batch.widen, threadIdx.x, S::THREADS);
@@ -1149,24 +1148,41 @@ hipError_t launch_ema_quantize(const QuantRowsParams& p, float* ema, float beta,
     return hipGetLastError();
 }
 
-template <int SRC, bool FL, bool CS>
+template <int SRC, bool FL, bool CS, int WAVES>
 static void launch_tile_flags(const TileBatch& a, bool row_sr, bool t_sr, dim3 grid, hipStream_t st)
 {
-    dim3 block(64 * tile_waves(CS));
+    dim3 block(64 * WAVES);
     if (row_sr) {
-        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, true, FL, CS>), grid, block, 0, st, a);
-        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, false, FL, CS>), grid, block, 0, st, a);
+        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, true, FL, CS, WAVES>), grid, block, 0, st, a);
+        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, false, FL, CS, WAVES>), grid, block, 0, st, a);
     } else {
-        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, true, FL, CS>), grid, block, 0, st, a);
-        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, false, FL, CS>), grid, block, 0, st, a);
+        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, true, FL, CS, WAVES>), grid, block, 0, st, a);
+        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, false, FL, CS, WAVES>), grid, block, 0, st, a);
     }
 }
 
 template <int SRC, bool FL>
-static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col_sums, dim3 grid, hipStream_t st)
+static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col_sums, int waves, dim3 grid, hipStream_t st)
 {
-    if (SRC != 2 && col_sums) launch_tile_flags<SRC, FL, (SRC != 2)>(a, row_sr, t_sr, grid, st);
-    else                      launch_tile_flags<SRC, FL, false>(a, row_sr, t_sr, grid, st);
+    if (SRC != 2 && col_sums)        launch_tile_flags<SRC, FL, (SRC != 2), 8>(a, row_sr, t_sr, grid, st);
+    else if (SRC == 0 && waves == 8) launch_tile_flags<SRC, FL, false, (SRC == 0 ? 8 : 4)>(a, row_sr, t_sr, grid, st);
+    else                             launch_tile_flags<SRC, FL, false, 4>(a, row_sr, t_sr, grid, st);
+}
+
+// Waves of a macro tile.  Column sums are kept per 256 rows: eight.  Otherwise four (see above), except for FP32 sources so
+// large that memory bounds them: eight waves write the transposed codes in whole lines of 128 bytes.  Four against eight
+// waves, in us: deterministic 50432 x 3072 184 / 169, 25216 x 1536 49.2 / 47.2, 12608 x 3072 51.5 / 48.3, below that
+// either way (18912 x 2304 53.4 / 54.0, 18912 x 1536 34.9 / 36.7); stochastic column groups, which the vector ALUs bound
+// longer, 50432 x 3072 176 / 170, 37824 x 3072 135 / 132, 25216 x 3072 90 / 91, 25216 x 1024 31.9 / 34.3.
+static int tile_waves(const QuantTileParams* jobs, int count, bool col_sums)
+{
+    if (col_sums) return 8;
+    int64_t largest = 0;
+    for (int j = 0; j < count; ++j) {
+        if (jobs[j].row_codes_in || jobs[j].bf16) return 4;
+        largest = std::max(largest, jobs[j].rows * jobs[j].cols);
+    }
+    return largest >= ((int64_t)(jobs[0].sr_t ? 112 : 36) << 20) ? 8 : 4;
 }
 
 // Fills the kernel arguments of one tensor; returns its number of workgroups.
@@ -1208,7 +1224,7 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
     uint32_t blocks = 0;
     bool col_sums = false, mixed = false;
     for (int j = 0; j < count; ++j) col_sums = col_sums || jobs[j].col_sums != nullptr;
-    const int waves = tile_waves(!p.row_codes_in && col_sums);
+    const int waves = tile_waves(jobs, count, !p.row_codes_in && col_sums);
     for (int j = 0; j < TILE_BATCH_MAX; ++j) {
         b.first[j] = 0xFFFFFFFFu;
         if (j >= count) continue;
@@ -1231,12 +1247,12 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
     auto launch = [&](auto fl) {
         constexpr bool FL = decltype(fl)::value;
         switch (src) {
-            case 0: launch_tile_src<0, FL>(b, row_sr, p.sr_t, col_sums, grid, st); break;
-            case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, grid, st); break;
-            case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, grid, st); break;
+            case 0: launch_tile_src<0, FL>(b, row_sr, p.sr_t, col_sums, waves, grid, st); break;
+            case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, waves, grid, st); break;
+            case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, waves, grid, st); break;
             default:
-                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL>), grid, dim3(64 * tile_waves(false)), 0, st, b);
-                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL>), grid, dim3(64 * tile_waves(false)), 0, st, b);
+                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL, false, 4>), grid, dim3(256), 0, st, b);
+                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL, false, 4>), grid, dim3(256), 0, st, b);
         }
     };
     if (p.floor_mode) launch(std::true_type{});

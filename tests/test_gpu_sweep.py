@@ -136,3 +136,14 @@ def test_fused_quantizer_at_the_edges_of_its_tiles(mx, orc, rows, cols, dtype):
             t = mx.mx_quantize_transposed(None, rnd, 6, 1, False, row_in=(got[2], got[3]), seed=7, shape=(rows, cols))
             assert_same_bytes(t[0], want[0], "codes_t from packed codes")
             assert_same_bytes(t[1], want[1], "scales_t from packed codes")
+
+
+@pytest.mark.parametrize("rows,cols,rt,pre", [(9248, 4128, 0, 0), (9248, 4128, 0, 1), (14368, 8224, 1, 1), (14368, 8224, 1, 0)])
+def test_fused_quantizer_of_large_f32_sources(mx, orc, rows, cols, rt, pre):
+    """From 36 Mi elements on (112 Mi with stochastic column groups) macro tiles of 256 rows: the last one 32 rows tall and
+    32 columns wide, bit for bit."""
+    x = np.tile(mixed_matrix(rows // 4, cols // 4, seed=rows + pre, dtype="f32"), (4, 4))
+    kw = dict(round_t=rt, tensor_id_t=6, pre_quant=pre, round_row=rt if pre == 0 else 0, tensor_id_row=1, seed=7)
+    got, want = mx.mx_quantize_transposed(dev(x), **kw), orc.quantize_transposed(x, **kw)
+    for g, w, nm in zip(got, want, ("codes_t", "scales_t", "codes_row", "scales_row")):
+        assert_same_bytes(g, w, nm)
