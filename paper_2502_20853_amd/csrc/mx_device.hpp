@@ -294,15 +294,30 @@ __device__ __forceinline__ uint32_t cvt_bf16_fp4(uint32_t codes, float scale)
     return bits_as<uint32_t>(__builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, SEL));
 }
 
-// round_S onto the grid layout, sign << 31 | code << 22.  Rounding mode toward plus infinity.  Everything below bit 22 is
-// cleared, not merged from x: a dequantized 0.5 or 1.5 of scale byte 0 is an FP32 subnormal whose bit 21 is set.
+// round_S onto the grid layout, sign << 31 | code << 22.  Rounding mode toward plus infinity.
 template <bool FLOOR>
-__device__ __forceinline__ uint32_t sr_grid(float x, int e, uint32_t term)
+__device__ __forceinline__ uint32_t sr_grid_sum(float x, int e, uint32_t term)
 {
     uint32_t mag = __float_as_uint(__builtin_ldexpf(__builtin_fabsf(x), e));
     if (FLOOR) mag = mag > GRID_MAX_BITS ? GRID_MAX_BITS : mag;
-    return __builtin_amdgcn_bitop3_b32(0x80000000u, (mag - term) & 0x7FC00000u, __float_as_uint(x), 0xEC);   // b | (a & c)
+    return mag - term;
 }
+
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t sr_grid(float x, int e, uint32_t term)
+{
+    return __builtin_amdgcn_bitop3_b32(0x80000000u, sr_grid_sum<FLOOR>(x, e, term) & 0x7FC00000u, __float_as_uint(x), 0xEC);   // b | (a & c)
+}
+
+// The same in one instruction less, except that the 22 low bits are those of x.  A dequantized x has none but with scale
+// byte 0, whose 0.5 and 1.5 times 2^-127 are FP32 subnormals with bit 21 set: there the caller clears them (& ON_GRID).
+template <bool FLOOR>
+__device__ __forceinline__ uint32_t sr_grid_dequantized(float x, int e, uint32_t term)
+{
+    return __builtin_amdgcn_bitop3_b32(0x7FC00000u, sr_grid_sum<FLOOR>(x, e, term), __float_as_uint(x), 0xCA);               // a ? b : c
+}
+
+constexpr uint32_t ON_GRID = 0xFFC00000u;
 
 // round_D of FP32 values.  The conversion sends ties to the even code; as for bf16 (ties_to_larger), a threshold's FP32
 // pattern is even, so moving even patterns one unit toward +infinity decides ties and moves nothing else across a

@@ -607,6 +607,9 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                 m[3] = pk_max(m[3], cvt_bf16_fp4<3>(mags, row_scale[j]));
             }
             column_bytes_bf16(m);
+            // Uniform and rare (the scale operand of byte 0 is zero).  With the mask on every element instead, 50432 x 3072 from
+            // packed codes takes 70.9 us against 67.4.
+            const bool any_byte_0 = T_SR && __any(__builtin_fminf(__builtin_fminf(row_scale[0], row_scale[1]), __builtin_fminf(row_scale[2], row_scale[3])) == 0.0f);
             if (T_SR) f32_round_toward_plus_inf();
             static_for_pair([&](auto jp_c) {
                 constexpr int jp = decltype(jp_c)::value;
@@ -621,8 +624,14 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
                         d[r][t] = v[t >> 1][t & 1];
-                        if (T_SR) d[r][t] = __uint_as_float(sr_grid<FLOOR>(d[r][t], 1 - (int)column_byte(t), rnd.w[t]));
+                        if (T_SR) d[r][t] = __uint_as_float(sr_grid_dequantized<FLOOR>(d[r][t], 1 - (int)column_byte(t), rnd.w[t]));
                     }
+                }
+                if (T_SR && any_byte_0) {
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) d[r][t] = __uint_as_float(__float_as_uint(d[r][t]) & ON_GRID);
                 }
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
@@ -1164,9 +1173,13 @@ static void launch_tile_flags(const TileBatch& a, bool row_sr, bool t_sr, dim3 g
 template <int SRC, bool FL>
 static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col_sums, int waves, dim3 grid, hipStream_t st)
 {
-    if (SRC != 2 && col_sums)        launch_tile_flags<SRC, FL, (SRC != 2), 8>(a, row_sr, t_sr, grid, st);
-    else if (SRC == 0 && waves == 8) launch_tile_flags<SRC, FL, false, (SRC == 0 ? 8 : 4)>(a, row_sr, t_sr, grid, st);
-    else                             launch_tile_flags<SRC, FL, false, 4>(a, row_sr, t_sr, grid, st);
+    if constexpr (SRC != 2) {
+        if (col_sums) return launch_tile_flags<SRC, FL, true, 8>(a, row_sr, t_sr, grid, st);
+    }
+    if constexpr (SRC == 0) {
+        if (waves == 8) return launch_tile_flags<SRC, FL, false, 8>(a, row_sr, t_sr, grid, st);
+    }
+    launch_tile_flags<SRC, FL, false, 4>(a, row_sr, t_sr, grid, st);
 }
 
 // Waves of a macro tile.  Column sums are kept per 256 rows: eight.  Otherwise four (see above), except for FP32 sources so
