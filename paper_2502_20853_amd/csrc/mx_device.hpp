@@ -35,12 +35,6 @@ __device__ __forceinline__ float inv_scale(uint32_t byte)
     return __uint_as_float((254u - byte) << 23);
 }
 
-// 2^s as FP32 (s = -127 is the subnormal 2^-127).
-__device__ __forceinline__ float fwd_scale(uint32_t byte)
-{
-    return __uint_as_float(byte ? (byte << 23) : 0x00400000u);
-}
-
 // ---- E2M1 rounding (Sec. 3.2) ----------------------------------------------
 // The integer form, which round_S uses (round_D of E2M1 goes through conversion instructions further down, E3M0 uses the
 // integer form for both).  It never forms y = x / S itself but v = x * 2^(-s-126) (one ldexp), which
@@ -135,12 +129,6 @@ __device__ __forceinline__ U4 sr_block(uint64_t blk, uint32_t tensor_id, uint32_
     return philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), tensor_id, 0u, k0, k1);
 }
 
-__device__ __forceinline__ uint32_t sr_field(const U4& r, int t)
-{
-    uint32_t w = r.w[t >> 1];
-    return (t & 1) ? (w >> 16) : (w & 0xFFFFu);
-}
-
 // The eight terms 64 * r16 - (2^22 - 1) of an 8-element block, which sr_grid() subtracts: mag - term carries into bit 22
 // iff p * 2^22 > 64 * r16.  (Subtracting takes r16 as it stands; adding ((65535 - r16) << 6) | 63 instead costs an
 // inversion of each random word, 4 of the 105 instructions a block takes.)
@@ -229,8 +217,10 @@ __device__ __forceinline__ float dequant_e3m0(uint32_t code, uint32_t byte)
 }
 
 // ---- FP4 conversion instructions of gfx950 -----------------------------------
-// What the quantizers use of them, each checked exhaustively against the integer forms above (all bf16 values x all
-// scale bytes; all 16 codes x all scale bytes), in every rounding mode: the mode does not enter.
+// What the quantizers use of them.  tests/test_gpu_codec.py holds the quantizers that stand on them against the oracle:
+// every bf16 value under every scale that a group with it can have, FP32 thresholds with three neighbours on either side at
+// every scale, and all 16 codes at every pair of row and column scales.  The FP32 rounding mode does not enter (round_S
+// kernels convert with the mode toward plus infinity).
 //   v_cvt_scalef32_pk_fp4_bf16   two bf16 values / 2^s, round to nearest even, saturated at 6  -> one byte
 //   v_cvt_scalef32_pk_fp4_f32    the same from FP32; also a packer of values that are already on the grid
 //   v_cvt_scalef32_pk_{f32,bf16}_fp4   two codes x 2^s -> two values, exact
@@ -321,9 +311,8 @@ constexpr uint32_t ON_GRID = 0xFFC00000u;
 
 // round_D of FP32 values.  The conversion sends ties to the even code; as for bf16 (ties_to_larger), a threshold's FP32
 // pattern is even, so moving even patterns one unit toward +infinity decides ties and moves nothing else across a
-// threshold.  -0 stays a negative zero through the saturating addition.  Checked against the integer form (scale to the
-// grid, add half a unit, cut) on 7.7e8 values: all scale bytes, thresholds and their neighbours, subnormals, both scale
-// rules.  3.5 instructions per element instead of 5.
+// threshold.  -0 stays a negative zero through the saturating addition.  3.5 instructions per element instead of the 5
+// of the integer form (scale to the grid, add half a unit, cut).
 __device__ __forceinline__ float ties_to_larger_f32(float x)
 {
     const int32_t v = (int32_t)__float_as_uint(x);
