@@ -217,7 +217,7 @@ __device__ __forceinline__ float dequant_e3m0(uint32_t code, uint32_t byte)
 }
 
 // ---- FP4 conversion instructions of gfx950 -----------------------------------
-// What the quantizers use of them.  tests/test_gpu_codec.py holds the quantizers that stand on them against the oracle:
+// What the quantizers use of them.  tests/test_gpu_codec.py holds the quantizers that stand on them against a plain C form:
 // every bf16 value under every scale that a group with it can have, FP32 thresholds with three neighbours on either side at
 // every scale, and all 16 codes at every pair of row and column scales.  The FP32 rounding mode does not enter (round_S
 // kernels convert with the mode toward plus infinity).
