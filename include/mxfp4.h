@@ -334,7 +334,8 @@ int mx_ramping_factor(const float* dist_w, const float* dist_q, int64_t count,
  *   factor       device, int32: N_w >= 1 per element (mx_ramping_factor's output), or NULL for 1
  *                everywhere (plain AdamW; g_acc and acc_steps are then not used and may be NULL)
  *   g_acc, acc_steps   device in/out, FP32 / int32: the gradient sum an element holds and the number
- *                of steps in it; all zero at the start
+ *                of steps in it; all zero at the start, and zero together (an element with acc_steps 0
+ *                holds nothing, its g_acc is not read)
  *   count % 4 == 0; every array 16-byte aligned (grad in BF16: 8).
  *   lr >= 0, 0 < beta1, beta2 < 1, eps >= 0, weight_decay >= 0, else MX_ERR_MODE.
  */
