@@ -179,8 +179,6 @@ struct WindowTensor {
     float* w_prev;
     float* dist_w;
     float* dist_q;
-    uint8_t* codes;
-    uint8_t* scales;
     uint8_t* codes_prev;
     uint8_t* scales_prev;
 };

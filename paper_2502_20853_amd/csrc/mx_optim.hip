@@ -325,12 +325,8 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch
     store8f(t.w_prev, q, w);
     store8f(t.dist_w, q, dw);
     store8f(t.dist_q, q, dq);
-    reinterpret_cast<uint32_t*>(t.codes)[q] = p;
     reinterpret_cast<uint32_t*>(t.codes_prev)[q] = p;
-    if ((threadIdx.x & 3) == 0) {
-        t.scales[q >> 2] = (uint8_t)byte;
-        t.scales_prev[q >> 2] = (uint8_t)byte;
-    }
+    if ((threadIdx.x & 3) == 0) t.scales_prev[q >> 2] = (uint8_t)byte;
 }
 
 }  // namespace

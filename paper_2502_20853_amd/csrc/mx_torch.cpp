@@ -470,8 +470,7 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
                     *k_acc = PyUnicode_InternFromString("g_acc"), *k_steps = PyUnicode_InternFromString("acc_steps"),
                     *k_factor = PyUnicode_InternFromString("factor"), *k_prev = PyUnicode_InternFromString("w_prev"),
                     *k_dw = PyUnicode_InternFromString("dist_w"), *k_dq = PyUnicode_InternFromString("dist_q"),
-                    *k_codes = PyUnicode_InternFromString("codes"), *k_scales = PyUnicode_InternFromString("scales"),
-                    *k_codes0 = PyUnicode_InternFromString("codes_prev"), *k_scales0 = PyUnicode_InternFromString("scales_prev");
+                    *k_codes = PyUnicode_InternFromString("codes_prev"), *k_scales = PyUnicode_InternFromString("scales_prev");
     const Py_ssize_t n = PyList_GET_SIZE(params.ptr());
     TORCH_CHECK(PyList_GET_SIZE(states.ptr()) == n, "one state per parameter");
     // written so that NaN fails
@@ -526,7 +525,7 @@ void ramping_step(const py::list& params, const py::list& states, int mode, bool
             auto u8s = [&](PyObject* k, int64_t per) { return checked<uint8_t>(state_tensor(st, k), count / per, at::kByte, "state", device); };
             bf16[window.size()] = gb;
             window.push_back({w, grad.defined() ? grad.data_ptr() : nullptr, f32(k_m), f32(k_v), i32(k_u), f32(k_acc), i32(k_steps), f32(k_prev),
-                              f32(k_dw), f32(k_dq), u8s(k_codes, 2), u8s(k_scales, 32), u8s(k_codes0, 2), u8s(k_scales0, 32)});
+                              f32(k_dw), f32(k_dq), u8s(k_codes, 2), u8s(k_scales, 32)});
             counts.push_back(count);
         } else {
             mxl::RampingAdamwParams a{};

@@ -53,10 +53,8 @@ class QRampingAdamW(torch.optim.Optimizer):
                 u8 = lambda *s: torch.empty(s, dtype=torch.uint8, device=p.device)
                 st.update(g_acc=z(torch.float32), acc_steps=z(torch.int32),
                           factor=torch.ones(p.shape, dtype=torch.int32, device=p.device),
-                          ones=torch.ones(p.shape, dtype=torch.int32, device=p.device),
                           w_prev=z(torch.float32), dist_w=z(torch.float32), dist_q=z(torch.float32),
-                          codes_prev=u8(rows, cols // 2), scales_prev=u8(rows, cols // 32),
-                          codes=u8(rows, cols // 2), scales=u8(rows, cols // 32))
+                          codes_prev=u8(rows, cols // 2), scales_prev=u8(rows, cols // 32))
         return st
 
     def amplification_factors(self):
@@ -66,7 +64,9 @@ class QRampingAdamW(torch.optim.Optimizer):
     def load_state_dict(self, state_dict):
         """torch's loader converts every state tensor to its parameter's dtype; the integer arrays (update
         and step counts, factors, packed codes) are taken out before and put back unchanged after."""
-        slim = {"state": {k: dict(v) for k, v in state_dict["state"].items()}, "param_groups": state_dict["param_groups"]}
+        dropped = ("ones", "codes", "scales")              # arrays that earlier versions kept and nothing read
+        slim = {"state": {k: {n: t for n, t in v.items() if n not in dropped} for k, v in state_dict["state"].items()},
+                "param_groups": state_dict["param_groups"]}
         held = {k: {n: v.pop(n) for n in list(v) if torch.is_tensor(v[n]) and not v[n].is_floating_point()}
                 for k, v in slim["state"].items()}
         super().load_state_dict(slim)

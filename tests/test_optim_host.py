@@ -38,6 +38,8 @@ def test_state_dict_round_trip_keeps_integer_state():
     opt.state[w]["updates"][0, 0] = (1 << 24) + 1                             # not representable in float32
     opt.param_groups[0]["steps_done"] = 17
     saved = opt.state_dict()
+    unread = {n: torch.zeros(w.shape, dtype=torch.int32) for n in ("ones", "codes", "scales")}
+    saved["state"][0] = dict(saved["state"][0], **unread)                     # as in checkpoints of earlier versions
     new, w2, b2 = _optimizer(lr=0.1)
     new.load_state_dict(saved)
     assert new.param_groups[0]["steps_done"] == 17 and new.param_groups[0]["lr"] == 0.5
