@@ -25,6 +25,7 @@
 // count is not zero (the two are zero together, an element's update clears both), and sum and count are written only
 // where they change, so the weights with factor 1 -- all but a few percent -- cost 44 B instead of 56.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include "mx_device.hpp"
@@ -119,20 +120,22 @@ struct AdamTensor {
     int32_t* acc_steps;           // null iff factor is null
 };
 
+// N: 1 or ADAM_BATCH.  The arguments of 32 tensors are 2.4 KB, which cost a launch of one tensor a microsecond.
+template <int N>
 struct AdamBatch {
     AdamHyper h;
     uint32_t grad_bf16;           // bit i: tensor i's gradient
-    uint32_t end[ADAM_BATCH];     // first workgroup past tensor i
-    int64_t quads[ADAM_BATCH];    // count / 4
-    AdamTensor t[ADAM_BATCH];
+    uint32_t end[N];              // first workgroup past tensor i
+    int64_t quads[N];             // count / 4
+    AdamTensor t[N];
 };
 
-template <bool RAMPING>
-__global__ __launch_bounds__(OPT_THREADS) void ramping_adamw_kernel(AdamBatch b)
+template <bool RAMPING, int N>
+__global__ __launch_bounds__(OPT_THREADS) void ramping_adamw_kernel(AdamBatch<N> b)
 {
     uint32_t i = 0;
 #pragma unroll
-    for (int k = 0; k + 1 < ADAM_BATCH; ++k) i += blockIdx.x >= b.end[k] ? 1u : 0u;
+    for (int k = 0; k + 1 < N; ++k) i += blockIdx.x >= b.end[k] ? 1u : 0u;
     const AdamTensor t = b.t[i];
     const AdamHyper& a = b.h;
     const int64_t q = (int64_t)(blockIdx.x - (i ? b.end[i - 1] : 0u)) * OPT_THREADS + threadIdx.x;
@@ -342,32 +345,39 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch
 
 namespace mxl {
 
+// One launch of up to N tensors.
+template <int N>
+static hipError_t launch_adamw(const RampingAdamwParams* p, int count, hipStream_t st)
+{
+    AdamBatch<N> b{};
+    b.h = hyper_of(p[0].lr, p[0].beta1, p[0].beta2, p[0].eps, p[0].weight_decay);
+    const bool ramping = p[0].factor != nullptr;
+    uint32_t blocks = 0;
+    for (int i = 0; i < N; ++i) {
+        b.end[i] = 0xFFFFFFFFu;
+        if (i >= count) continue;
+        const RampingAdamwParams& q = p[i];
+        if ((q.factor != nullptr) != ramping) return hipErrorInvalidValue;
+        b.t[i] = {q.w, q.grad, q.m, q.v, q.updates, q.g_acc, q.factor, q.acc_steps};
+        b.quads[i] = q.count / 4;
+        if (q.grad_bf16) b.grad_bf16 |= 1u << i;
+        blocks += (uint32_t)((b.quads[i] + OPT_THREADS - 1) / OPT_THREADS);
+        b.end[i] = blocks;
+    }
+    if (blocks == 0) return hipSuccess;
+    if (ramping) hipLaunchKernelGGL((ramping_adamw_kernel<true, N>), dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+    else         hipLaunchKernelGGL((ramping_adamw_kernel<false, N>), dim3(blocks), dim3(OPT_THREADS), 0, st, b);
+    return hipGetLastError();
+}
+
 hipError_t launch_ramping_adamw_batch(const RampingAdamwParams* p, int count, hipStream_t st)
 {
-    for (int at = 0; at < count; at += ADAM_BATCH) {
-        AdamBatch b{};
-        b.h = hyper_of(p[at].lr, p[at].beta1, p[at].beta2, p[at].eps, p[at].weight_decay);
-        const int n = count - at < ADAM_BATCH ? count - at : ADAM_BATCH;
-        const bool ramping = p[at].factor != nullptr;
-        uint32_t blocks = 0;
-        for (int i = 0; i < ADAM_BATCH; ++i) {
-            b.end[i] = 0xFFFFFFFFu;
-            if (i >= n) continue;
-            const RampingAdamwParams& q = p[at + i];
-            if ((q.factor != nullptr) != ramping) return hipErrorInvalidValue;
-            b.t[i] = {q.w, q.grad, q.m, q.v, q.updates, q.g_acc, q.factor, q.acc_steps};
-            b.quads[i] = q.count / 4;
-            if (q.grad_bf16) b.grad_bf16 |= 1u << i;
-            blocks += (uint32_t)((b.quads[i] + OPT_THREADS - 1) / OPT_THREADS);
-            b.end[i] = blocks;
-        }
-        if (blocks == 0) continue;
-        if (ramping) hipLaunchKernelGGL(ramping_adamw_kernel<true>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
-        else         hipLaunchKernelGGL(ramping_adamw_kernel<false>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    for (int at = 0; at < count && e == hipSuccess; at += ADAM_BATCH) {
+        const int n = std::min(count - at, ADAM_BATCH);
+        e = n == 1 ? launch_adamw<1>(p + at, 1, st) : launch_adamw<ADAM_BATCH>(p + at, n, st);
     }
-    return hipSuccess;
+    return e;
 }
 
 hipError_t launch_ramping_window_batch(const RampingWindowParams& p, const WindowTensor* tensors, const int64_t* counts,
