@@ -517,7 +517,8 @@ def main():
                           torch.full((n_par,), 6, dtype=torch.int32, device="cuda"),
                           torch.ones(n_par, dtype=torch.int32, device="cuda"))
     opt = []
-    for label, fac, bytes_per in (("ramping", fac_all, 56), ("plain_adamw", None, 36)):
+    # bytes of an element that holds nothing (one that holds a gradient moves 56)
+    for label, fac, bytes_per in (("ramping", fac_all, 44), ("plain_adamw", None, 36)):
         ost = mx.binding.RampingAdamwState((n_par,), ramping=fac is not None)
         for _ in range(2):
             mx.binding.mx_ramping_adamw_step(w_all, g_all, ost, fac)

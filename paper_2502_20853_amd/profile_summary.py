@@ -137,8 +137,8 @@ def write_step_kernels(out_dir):
                                                                  elements * 1.0625 / 1e6, w_ / (elements * 1.0625)))
     n_par = 12 * (2304 * 768 + 768 * 768 + 3072 * 768 + 768 * 3072)
     opt = []
-    for ok, label in (("ramping_adamw_kernel<float, true>", "with factors (56 B/element algorithmic)"),
-                      ("ramping_adamw_kernel<float, false>", "plain AdamW (36 B/element algorithmic)")):
+    for ok, label in (("ramping_adamw_kernel<true, 1>", "2 % of the factors at 6, the others 1 (44 B/element algorithmic where nothing is held, 56 where something is)"),
+                      ("ramping_adamw_kernel<false, 1>", "plain AdamW (36 B/element algorithmic)")):
         if ok in per["FETCH_SIZE"]:
             f2, w2 = per["FETCH_SIZE"][ok], per["WRITE_SIZE"][ok]
             r2, wr2 = sum(f2) / len(f2) * 1024 * ff, sum(w2) / len(w2) * 1024 * wf
@@ -249,7 +249,7 @@ def write_valu(out_dir):
     path = _find(os.path.join(out_dir, "valu"), "counter_collection.csv")
     if not path:
         return None
-    # grid = workgroups x 512 lanes of 256 x 128 macro tiles (two 256 x 64 halves in the tail)
+    # grid in units of 512 lanes: two workgroups of 256 lanes, each a 128 x 128 macro tile (or a half of one in the tail)
     known = {1340: ("dy_type", 50432, 768, 0), 3546: ("dy_type", 50432, 2304, 0), 4848: ("dy_type", 50432, 3072, 0),
              1376: ("x_type", 50432, 768, 768 * 768), 4992: ("x_type", 50432, 3072, 768 * 3072)}
     detail, per, lines = collections.OrderedDict(), {}, []
