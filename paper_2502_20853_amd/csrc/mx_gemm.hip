@@ -250,7 +250,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, uint8_t* ep, v1
 // erfc keeps its relative accuracy in the negative tail, where 1 + erf would cancel; to keep it through the
 // exponential, z^2 = x^2 / 2 is carried as an FP32 product and its exact remainder, and the exponent of two as
 // a rounded product and its remainder, both folded in as first-order corrections.  Against the FP64 value the
-// result is within 5.5e-7 |GELU(x)| (2^-18 is 3.8e-6) for every x where |GELU(x)| >= 2^-100, and below
+// result is within 4.8e-7 |GELU(x)| (2^-18 is 3.8e-6) for every x where |GELU(x)| >= 2^-100, and below
 // 2^-120 in absolute terms beyond (checked on 6e6 points by the fitting script's FP32 emulation).  |x| is
 // clamped at 17 before squaring: erfc has long underflowed there, and no infinity can arise.
 //

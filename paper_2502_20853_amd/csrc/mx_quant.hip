@@ -140,8 +140,9 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_e3m0_kernel(RowsAr
     }
 }
 
-// Bound by memory: 25216 x 1536 bf16 in 18 us (round_D) and 20 us (round_S), 5.1 TB/s, the rate of a large copy on the
-// card.  With codes taken from the grid sums and packed by shifts it was bound by the vector ALUs, 22.8 and 26.7 us.
+// round_D is bound by memory: 50432 x 3072 bf16 in 60 us, 6.5 TB/s, FP32 in 131, 5.4 TB/s.  round_S of bf16 by the random
+// numbers: 80 to 89 us, 4.4 to 4.9 TB/s; of FP32 by memory, 130 us.  At 25216 x 1536 bf16 16 and 23 us (22.8 and 26.7 with
+// codes taken from the grid sums and packed by shifts).
 template <typename SrcT, bool SR, bool FLOOR>
 __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
 {

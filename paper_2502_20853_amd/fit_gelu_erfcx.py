@@ -1,4 +1,4 @@
-"""Coefficients of the FP32 GELU in the fused output stage (csrc/mx_gemm.hip, gelu_f32), and a check of its error.
+"""Coefficients of the FP32 GELU in the fused output stage (csrc/mx_gemm.hip, gelu4_f32), and a check of its error.
 
 erfc(z) = exp(-z^2) G(z).  G (the scaled complementary error function) is smooth and decays like
 1 / (z sqrt(pi)); with t = 1 / (1 + z / 2) the quotient G / t is close to a low-degree polynomial in t.  The
