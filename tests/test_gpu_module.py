@@ -345,3 +345,52 @@ def test_saved_operands_through_hooks(mx):
             with pytest.raises(mx.MxError) as e:
                 backward()
             assert e.value.code == mx.binding.MX_ERR_SHAPE
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("tokens,D,C,xt,wt", [(1, 32, 32, "f32", "bf16"), (33, 160, 96, "bf16", "f32"), (257, 96, 2080, "bf16", "bf16"),
+                                              # more chunks than one per lane of the row kernel's grid covers
+                                              (8200, 1056, 96, "bf16", "f32"), (2113, 4128, 64, "f32", "f32")])
+def test_forward_without_gradients_equals_the_one_with(mx, mode, tokens, D, C, xt, wt):
+    """Row quantizers alone (both tensors in one launch, one or four chunks per lane) against the fused ones, which the
+    parity tests hold against the oracle; both scale rules, every pair of source types."""
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    torch.manual_seed(tokens)
+    x = torch.randn(tokens, D, device="cuda").mul_(torch.randn(tokens, 1, device="cuda").exp_()).to(tdt[xt])
+    for bias in (True, False):
+        lin = mx.MxLinear(D, C, bias=bias, dtype=tdt[wt], scale_mode=mode, seed=1, layer_id=1)
+        if bias:
+            with torch.no_grad():
+                lin.bias.normal_()
+        y = lin(x).detach()
+        with torch.no_grad():
+            assert torch.equal(lin(x), y)
+        wq, ws = mx.mx_quantize(lin.weight.detach(), scale_mode=mode)
+        xq, xs = mx.mx_quantize(x, scale_mode=mode)
+        args = (xq, xs, wq, ws) + ((lin.bias.detach().float(),) if bias else ())
+        assert torch.equal((mx.mx_linear_fwd_bias if bias else mx.mx_linear_fwd)(*args, out_dtype=x.dtype), y)
+
+
+@pytest.mark.parametrize("flow", ["tetrajet", "microscaling"])
+@pytest.mark.parametrize("xt,wt", [("bf16", "f32"), ("f32", "bf16"), ("f32", "f32")])
+def test_module_with_the_floor_scale_rule(mx, flow, xt, wt):
+    """Eq. 2's scale rule through the native pass, mixed source types in one launch: the separate calls' bits."""
+    tdt, tokens, Np, D, C = {"f32": torch.float32, "bf16": torch.bfloat16}, 70, 96, 160, 96
+    torch.manual_seed(1)
+    x, dy = torch.randn(tokens, D, device="cuda").to(tdt[xt]), (torch.randn(tokens, C, device="cuda") * 1e-3).to(tdt[xt])
+    lin = mx.MxLinear(D, C, dtype=tdt[wt], flow=flow, scale_mode=1, seed=7, layer_id=3)
+    xg = x.clone().requires_grad_(True)
+    y = lin(xg)
+    dx, dw, db = torch.autograd.grad(y, (xg, lin.weight, lin.bias), dy)
+    seed, tetra = ((7 << 16) | 3) << 32, flow == "tetrajet"
+    pad = lambda t: torch.cat([t, t.new_zeros((Np - tokens, t.shape[1]))])
+    rt, pre = (mx.ROUND_SR if tetra else mx.ROUND_RTN), int(tetra)
+    xtq, xts, xq, xs = mx.mx_quantize_transposed(pad(x), rt, 6, pre, True, mx.ROUND_RTN, 1, scale_mode=1, seed=seed)
+    wtq, wts, wq, ws = mx.mx_quantize_transposed(lin.weight.detach(), rt, 4, pre, True, mx.ROUND_RTN, 2, scale_mode=1, seed=seed)
+    dtq, dts, dq, ds = mx.mx_quantize_transposed(pad(dy), rt, 5, 0, True, rt, 3, scale_mode=1, seed=seed)
+    assert torch.equal(y, mx.mx_linear_fwd_bias(xq, xs, wq, ws, lin.bias.detach().float(), out_dtype=x.dtype)[:tokens])
+    assert torch.equal(dx, mx.mx_linear_bwd_dx(dq, ds, wtq, wts, out_dtype=x.dtype)[:tokens])
+    assert torch.equal(dw, mx.mx_linear_bwd_dw(dtq, dts, xtq, xts).to(dw.dtype))
+    # FP32 sums of `tokens` values in some order, then one rounding to the bias's type
+    ref, mag = dy.double().sum(0), dy.double().abs().sum(0)
+    assert bool(((db.double() - ref).abs() <= tokens * 2.0 ** -24 * mag + (ref.abs() * 2.0 ** -8 if wt == "bf16" else 0.0)).all())
