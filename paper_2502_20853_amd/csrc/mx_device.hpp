@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mx_launch.hpp"
 
 namespace mxd {
@@ -129,6 +131,57 @@ __device__ __forceinline__ U4 sr_block(uint64_t blk, uint32_t tensor_id, uint32_
     return philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), tensor_id, 0u, k0, k1);
 }
 
+// The same where every lane of the launch has the block number's upper word in common (`hi`, uniform like the tensor id
+// and the key): of the first two rounds' four products one is then the same for all lanes in each round, and of their
+// values only three depend on the lane and none of these on the tensor id, so the scalar unit does the rest and two
+// streams over the same elements share them.  38 vector instructions with the addition that makes `lo`, 34 for a second
+// stream, against 43 each.
+struct SrCounter32 { uint32_t w3, lo, hi; };
+
+__device__ __forceinline__ SrCounter32 sr_counter(uint32_t lo, uint32_t k1)
+{
+    const uint32_t MUL_A = 0xD2511F53u, MUL_B = 0xCD9E8D57u;
+    const uint64_t pa = (uint64_t)MUL_A * lo;                               // round 1 from (lo, hi, tensor_id, 0)
+    const uint64_t pb = (uint64_t)MUL_B * ((uint32_t)(pa >> 32) ^ k1);      // round 2
+    return {(uint32_t)pa, (uint32_t)pb, (uint32_t)(pb >> 32)};
+}
+
+__device__ __forceinline__ U4 sr_block_uniform_hi(const SrCounter32& c, uint32_t hi, uint32_t tensor_id, uint32_t k0, uint32_t k1)
+{
+    const uint32_t MUL_A = 0xD2511F53u, MUL_B = 0xCD9E8D57u;
+    const uint32_t WEYL_A = 0x9E3779B9u, WEYL_B = 0xBB67AE85u;
+    // round 1: words 0 and 1 are uniform after it
+    const uint32_t u0 = __umulhi(MUL_B, tensor_id) ^ hi ^ k0, u1 = MUL_B * tensor_id;
+    // round 2: word 3 is uniform after it
+    const uint32_t s0 = u1 ^ (k0 + WEYL_A), s2 = __umulhi(MUL_A, u0) ^ (k1 + WEYL_B), u3 = MUL_A * u0;
+    uint32_t c0 = c.hi ^ s0, c1 = c.lo, c2 = c.w3 ^ s2, c3;
+    k0 += 2u * WEYL_A; k1 += 2u * WEYL_B;
+    // round 3
+    {
+        const uint64_t pa = (uint64_t)MUL_A * c0, pb = (uint64_t)MUL_B * c2;
+        const uint32_t s3 = u3 ^ k1;
+        c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pb >> 32), c1, k0, 0x96);
+        c2 = (uint32_t)(pa >> 32) ^ s3;
+        c1 = (uint32_t)pb;
+        c3 = (uint32_t)pa;
+        k0 += WEYL_A; k1 += WEYL_B;
+    }
+#pragma unroll
+    for (int i = 3; i < 10; ++i) {
+        const uint64_t pa = (uint64_t)MUL_A * c0, pb = (uint64_t)MUL_B * c2;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pb >> 32), c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pa >> 32), c3, k1, 0x96);
+        c1 = (uint32_t)pb;
+        c3 = (uint32_t)pa;
+        c0 = n0;
+        c2 = n2;
+        k0 += WEYL_A; k1 += WEYL_B;
+    }
+    U4 r;
+    r.w[0] = c0; r.w[1] = c1; r.w[2] = c2; r.w[3] = c3;
+    return r;
+}
+
 // The eight terms 64 * r16 - (2^22 - 1) of an 8-element block, which sr_grid() subtracts: mag - term carries into bit 22
 // iff p * 2^22 > 64 * r16.  (Subtracting takes r16 as it stands; adding ((65535 - r16) << 6) | 63 instead costs an
 // inversion of each random word, 4 of the 105 instructions a block takes.)
@@ -144,9 +197,8 @@ __device__ __forceinline__ uint32_t sr_term(uint32_t w)
     return r;
 }
 
-__device__ __forceinline__ U8 sr_terms(uint64_t blk, uint32_t tensor_id, uint32_t k0, uint32_t k1)
+__device__ __forceinline__ U8 sr_terms_of(const U4& r)
 {
-    U4 r = sr_block(blk, tensor_id, k0, k1);
     U8 a;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -154,6 +206,19 @@ __device__ __forceinline__ U8 sr_terms(uint64_t blk, uint32_t tensor_id, uint32_
         a.w[2 * i + 1] = sr_term<true>(r.w[i]);
     }
     return a;
+}
+
+// Where block numbers of the launch differ in their upper word (the WIDE kernels): the block number itself.
+struct SrCounter64 { uint64_t blk; };
+__device__ __forceinline__ SrCounter64 sr_counter(uint64_t blk, uint32_t) { return {blk}; }
+
+__device__ __forceinline__ U8 sr_terms(const SrCounter32& c, uint32_t hi, uint32_t tensor_id, uint32_t k0, uint32_t k1)
+{
+    return sr_terms_of(sr_block_uniform_hi(c, hi, tensor_id, k0, k1));
+}
+__device__ __forceinline__ U8 sr_terms(const SrCounter64& c, uint32_t, uint32_t tensor_id, uint32_t k0, uint32_t k1)
+{
+    return sr_terms_of(sr_block(c.blk, tensor_id, k0, k1));
 }
 
 // ---- E3M0 elements (the other 4-bit format of the paper's format ablation, Table 7) -------------
@@ -258,7 +323,9 @@ __device__ __forceinline__ uint32_t ties_to_larger(uint32_t w)
     return bits_as<uint32_t>(__builtin_elementwise_add_sat(v, v >> (short)15)) | 0x00010001u;
 }
 
-// byte SEL of `old` <- codes of the two bf16 values in w (low half first), scale as scale_operand()
+// byte SEL of `old` <- codes of the two bf16 values in w (low half first), scale as scale_operand().  A conversion keeps
+// the other bytes of its destination.  Where they are all written later, or not used, `old` is the source itself, whose
+// register then serves as the destination: a cleared one costs a move.
 template <int SEL>
 __device__ __forceinline__ uint32_t cvt_fp4_bf16(uint32_t old, uint32_t w, float scale)
 {
@@ -326,10 +393,18 @@ __device__ __forceinline__ uint32_t cvt_rtn_f32(uint32_t old, float x0, float x1
     return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, ties_to_larger_f32(x0), ties_to_larger_f32(x1), scale, SEL);
 }
 
+// The same into a fresh register; the other bytes are anything.
+template <int SEL>
+__device__ __forceinline__ uint32_t cvt_rtn_f32(float x0, float x1, float scale)
+{
+    const float t = ties_to_larger_f32(x0);
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(__float_as_uint(t), t, ties_to_larger_f32(x1), scale, SEL);
+}
+
 __device__ __forceinline__ uint32_t rtn_codes8_f32(const float (&x)[8], uint32_t byte)
 {
     const float s = scale_operand(byte);
-    uint32_t p = cvt_rtn_f32<0>(0u, x[0], x[1], s);
+    uint32_t p = cvt_rtn_f32<0>(x[0], x[1], s);
     p = cvt_rtn_f32<1>(p, x[2], x[3], s);
     p = cvt_rtn_f32<2>(p, x[4], x[5], s);
     return cvt_rtn_f32<3>(p, x[6], x[7], s);

@@ -87,7 +87,8 @@ __device__ __forceinline__ uint32_t row_scale_byte(const bf16x8_raw& x)
 __device__ __forceinline__ uint32_t rtn_codes8(const bf16x8_raw& x, uint32_t byte)
 {
     const float s = scale_operand(byte);
-    uint32_t p = cvt_fp4_bf16<0>(0u, ties_to_larger(x[0]), s);
+    const uint32_t first = ties_to_larger(x[0]);
+    uint32_t p = cvt_fp4_bf16<0>(first, first, s);
     p = cvt_fp4_bf16<1>(p, ties_to_larger(x[1]), s);
     p = cvt_fp4_bf16<2>(p, ties_to_larger(x[2]), s);
     return cvt_fp4_bf16<3>(p, ties_to_larger(x[3]), s);
@@ -102,7 +103,7 @@ __device__ __forceinline__ uint32_t sr_codes8(const RAW& x, uint32_t byte, const
     uint32_t g[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) g[t] = sr_grid<FLOOR>(element_of(x, t), e, rnd.w[t]);
-    uint32_t p = pack_grid<0>(0u, g[0], g[1]);
+    uint32_t p = pack_grid<0>(g[0], g[0], g[1]);
     p = pack_grid<1>(p, g[2], g[3]);
     p = pack_grid<2>(p, g[4], g[5]);
     return pack_grid<3>(p, g[6], g[7]);
@@ -143,10 +144,11 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_e3m0_kernel(RowsAr
 // round_D is bound by memory: 50432 x 3072 bf16 in 60 us, 6.5 TB/s, FP32 in 131, 5.4 TB/s.  round_S of bf16 by the random
 // numbers: 80 to 89 us, 4.4 to 4.9 TB/s; of FP32 by memory, 130 us.  At 25216 x 1536 bf16 16 and 23 us (22.8 and 26.7 with
 // codes taken from the grid sums and packed by shifts).
-template <typename SrcT, bool SR, bool FLOOR>
+template <typename SrcT, bool SR, bool FLOOR, bool WIDE>
 __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
 {
     if (SR) f32_round_toward_plus_inf();
+    using Blk = std::conditional_t<WIDE, uint64_t, uint32_t>;
     const SrcT* src = static_cast<const SrcT*>(a.src);
     const uint32_t q0 = blockIdx.x * (ROWS_THREADS * ROWS_UNROLL) + threadIdx.x;
     Raw8<SrcT> x[ROWS_UNROLL];
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
         uint32_t q = q0 + u * ROWS_THREADS;
         const uint32_t byte = row_scale_byte<FLOOR>(x[u]);
         uint32_t packed;
-        if constexpr (SR) packed = sr_codes8<FLOOR>(x[u], byte, sr_terms(a.base_blk + q, a.tensor_id, a.k0, a.k1));
+        if constexpr (SR) packed = sr_codes8<FLOOR>(x[u], byte, sr_terms(sr_counter((Blk)(a.base_blk + q), a.k1), (uint32_t)(a.base_blk >> 32), a.tensor_id, a.k0, a.k1));
         else              packed = rtn_codes8(x[u], byte);
         if (ok[u]) {
             reinterpret_cast<uint32_t*>(a.codes)[q] = packed;
@@ -282,11 +284,17 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 //   - a 32x1 column group is 4 registers x 8 lanes (l/8 = 0..7) of one column.
 // The 32 elements of a lane stay in registers through both quantizers.  Codes and scale
 // bytes are collected in LDS and written out at the end in lines of 64 bytes (8 waves: transposed codes 128), 16 bytes per
-// lane.  Registers allow 16 waves on a compute unit (20 from packed codes, which keep fewer).  Four small workgroups there
-// are seldom all loading or all storing at once, two large ones often are, and a small tensor's waves spread over
-// more units.  8 -> 4 waves: 50432 x 768 bf16 activation 39 -> 37 us, 50432 x 3072 121 -> 112, 25216 x 384 FP32
-// 20 -> 18, from packed codes 25216 x 3072 49 -> 42, 256 x 192 FP32 with its weight 7.0 -> 5.7.  Two waves, 64 columns, or five waves per
-// SIMD (spills) are slower: 39, 40 and 43 us for the first of these.
+// lane.  Several small workgroups on a compute unit are seldom all loading or all storing at once, two large ones often are,
+// and a small tensor's waves spread over more units (4 against 8 waves: 50432 x 768 bf16 activation 37 us / 39, 256 x 192
+// FP32 with its weight 5.7 / 7.0; two waves 39).
+// bf16 sources are bound by the vector ALUs, i.e. by the number of instructions.  In us, a 50432 x 3072 bf16 gradient 138 ->
+// 129 and activation 117 -> 112: the first two Philox rounds on the scalar unit and once for both streams (SrCounter32), the
+// wave's two tiles written out instead of a loop, no cleared destinations for the conversions, one 64-bit address per lane.
+// The loop also held 118 registers, now 93: with one stochastic output five waves share a SIMD instead of four, so that
+// 1280 narrow workgroups run at once (25216 x 384 activation 13.8 -> 12.0; FP32 gradient 17.3 -> 15.2).  A gradient of bf16
+// takes 109 registers for what the streams share; without sharing 95 and 131 us.  FP32 sources are bound by memory
+// (50432 x 3072: 170 us, 4.6 TB/s): fetching a second FP32 tile ahead gains 2 % at four waves a SIMD for an activation, and
+// spills where both outputs are stochastic (210 us).
 // ---------------------------------------------------------------------------
 // What a macro tile of 32 * WAVES rows x 128 columns stages in LDS.
 template <int WAVES, bool ROWS, bool COLSUM>
@@ -314,6 +322,7 @@ struct TileArgs {
     uint32_t rows, cols;
     uint32_t src_rows;     // rows the source has; rows from there up to `rows` are zero
     int pre_quant;
+    int want_row;          // codes_row is set (an integer: the compiler keeps a pointer's test in a vector register)
     int src_bf16;          // instances for both source types: which one this job reads
     // 1-D grid over macro tiles in row-major order: the first n_wide workgroups own tiles of 128 columns
     // (two 32 x 64 tiles per wave), the rest own the two halves of 64 columns of the tiles after those
@@ -422,7 +431,7 @@ __device__ __forceinline__ void widen_bf16(const mxl::WidenJob& j, uint32_t tid,
 // SRC: 0 = FP32 source, 1 = bf16 source, 2 = packed row result given
 // COLSUM: also the column sums of the source (a bias gradient is that of dY), per 256-row block; a
 // separate instance, so that the plain quantizer's code does not change with this feature.
-template <typename S, int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM>
+template <typename S, int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM, bool WIDE>
 __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint32_t block, uint8_t* st)      // a by value: by reference the stochastic
                                                                             // instances take 128 registers and spill
 {
@@ -456,59 +465,74 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
     const bool wave_rows_full = mrow0 + wr * 32 + 32 <= a.src_rows;
     const uint32_t lrow0 = wr * 32 + 4 * rg;              // first of this lane's 4 rows inside the macro tile
     const uint32_t row0 = mrow0 + lrow0;
-    const bool want_row = SRC != 2 && a.codes_row != nullptr;
+    const bool want_row = SRC != 2 && a.want_row;
     const uint32_t half_rows = a.rows >> 1, grp_rows = a.rows >> 5;
     const uint32_t half_cols = a.cols >> 1, grp_cols = a.cols >> 5;
 
     // Element (row0 + j, c + t) has index index_base + (row0 + j) * cols + c + t: one Philox block of 8 per row.
-    const uint64_t blk0 = (a.index_base + (uint64_t)row0 * a.cols + mcol0 + cc * 8) >> 3;
-    const uint32_t blk_row = a.cols >> 3;
+    using Blk = std::conditional_t<WIDE, uint64_t, uint32_t>;
+    const uint32_t blk_row = a.cols >> 3, blk_hi = (uint32_t)(a.index_base >> 35);
+    const Blk blk0 = (Blk)(a.index_base >> 3) + (Blk)row0 * blk_row + (mcol0 >> 3) + cc;
 
     // A lane's four rows of 8 elements, as loaded: bf16 values stay packed in pairs, packed results stay codes.
-    // The next tile's are fetched while the current one is encoded.
+    // The second tile's are fetched while the first one is encoded.
     using Row = Raw8<std::conditional_t<SRC == 0, float, uint16_t>>;
     struct Tile {
         Row x[SRC == 2 ? 1 : 4];
         uint32_t pk[SRC == 2 ? 4 : 1], byte[SRC == 2 ? 4 : 1];
     };
-    auto load_row = [&](Row& r, int j, uint32_t col) {
-        if constexpr (SRC == 0)      r = load8(static_cast<const float*>(a.src) + (int64_t)(row0 + j) * a.ld + col);
-        else if constexpr (SRC == 1) r = load8_raw(static_cast<const uint16_t*>(a.src) + (int64_t)(row0 + j) * a.ld + col);
+    // the lane's first element; the rows and the second tile are uniform offsets from it
+    using SrcT = std::conditional_t<SRC == 0, float, uint16_t>;
+    const SrcT* lane_src = nullptr;
+    const uint8_t *lane_codes = nullptr, *lane_scales = nullptr;
+    if constexpr (SRC == 2) {
+        lane_codes = a.row_codes_in + ((size_t)(mrow0 + wr * 32) * half_cols + (mcol0 >> 1)) + ((uint64_t)(uint32_t)(4 * rg) * half_cols + (uint32_t)(cc * 4));
+        lane_scales = a.row_scales_in + ((size_t)(mrow0 + wr * 32) * grp_cols + (mcol0 >> 5)) + ((uint64_t)(uint32_t)(4 * rg) * grp_cols + (uint32_t)(cc >> 2));
+    } else
+        lane_src = static_cast<const SrcT*>(a.src) + ((int64_t)(mrow0 + wr * 32) * a.ld + mcol0) + ((uint64_t)(uint32_t)(4 * rg) * (uint64_t)a.ld + (uint32_t)(cc * 8));
+    auto load_row = [&](Row& r, int j, int ci) {
+        const SrcT* p = lane_src + j * a.ld + ci * 64;
+        if constexpr (SRC == 0)      r = load8(p);
+        else if constexpr (SRC == 1) r = load8_raw(p);
     };
     auto fetch = [&](Tile& d, int ci) {
         const uint32_t col = mcol0 + ci * 64 + cc * 8;
         if constexpr (SRC == 2) {
+            const uint8_t *pc = lane_codes + ci * 32, *ps = lane_scales + ci * 2;
+            if (mcol0 + ci * 64 + 64 <= a.cols) {                              // uniform: no masking
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                d.pk[j] = 0u; d.byte[j] = 98u;
-                if (col < a.cols) {
-                    d.pk[j] = *reinterpret_cast<const uint32_t*>(a.row_codes_in + (size_t)(row0 + j) * half_cols + (col >> 1));
-                    d.byte[j] = a.row_scales_in[(size_t)(row0 + j) * grp_cols + (col >> 5)];
+                for (int j = 0; j < 4; ++j) {
+                    d.pk[j] = *reinterpret_cast<const uint32_t*>(pc + (size_t)j * half_cols);
+                    d.byte[j] = ps[(size_t)j * grp_cols];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    d.pk[j] = 0u; d.byte[j] = 98u;
+                    if (col < a.cols) {
+                        d.pk[j] = *reinterpret_cast<const uint32_t*>(pc + (size_t)j * half_cols);
+                        d.byte[j] = ps[(size_t)j * grp_cols];
+                    }
                 }
             }
         } else if (wave_rows_full && mcol0 + ci * 64 + 64 <= a.cols) {       // uniform: no masking
 #pragma unroll
-            for (int j = 0; j < 4; ++j) load_row(d.x[j], j, col);
+            for (int j = 0; j < 4; ++j) load_row(d.x[j], j, ci);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if constexpr (SRC == 0) d.x[j] = zero8();
                 else                    d.x[j] = bf16x8_raw{0u, 0u, 0u, 0u};
-                if (col < a.cols && row0 + j < a.src_rows) load_row(d.x[j], j, col);
+                if (col < a.cols && row0 + j < a.src_rows) load_row(d.x[j], j, ci);
             }
         }
     };
     auto element = [](const Row& r, int t) -> float { return element_of(r, t); };
 
-    constexpr bool PREFETCH = SRC != 0;                   // an FP32 tile's 32 registers do not fit twice in 128
-    Tile cur, nxt;
-    if (PREFETCH && wave_has_rows) fetch(cur, 0);
-    for (int ci = 0; ci < tiles_per_wave && wave_has_rows; ++ci) {
-        const uint32_t tcol0 = ci * 64;
-        const uint32_t lcol0 = tcol0 + cc * 8;            // first of this lane's 8 columns inside the macro tile
-        if (mcol0 + tcol0 >= a.cols) break;               // uniform over the wave
-        if (!PREFETCH) fetch(cur, ci);
-        else if (ci + 1 < tiles_per_wave && mcol0 + tcol0 + 64 < a.cols) fetch(nxt, ci + 1);
+    constexpr bool PREFETCH = SRC != 0 || (!ROW_SR && T_SR);   // FP32: 32 registers for the second tile
+    auto encode = [&](const Tile& cur, auto ci_c) {
+        constexpr int ci = decltype(ci_c)::value;
+        const uint32_t lcol0 = ci * 64 + cc * 8;          // first of this lane's 8 columns inside the macro tile
         // ---- column sums of the source over this wave's 32 rows -------------
         if (COLSUM && SRC != 2 && a.col_sum_partials != nullptr) {
             f32_round_to_nearest_even();
@@ -552,6 +576,18 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
             else if (want_row) maxima(std::true_type{}, std::true_type{});
             else               maxima(std::false_type{}, std::true_type{});
         }
+        // ---- random numbers: what both streams have in common is made once ----
+        constexpr bool SHARE = ROW_SR && T_SR && (SRC == 1 || COLSUM);     // FP32 gradients: five waves a SIMD are worth more
+        auto counter = [&](int j) { return sr_counter(blk0 + (Blk)(ci * 8) + (Blk)j * blk_row, k1); };
+        decltype(counter(0)) shared[4];
+        if constexpr (SHARE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) shared[j] = counter(j);
+        }
+        auto counter_of = [&](int j) {
+            if constexpr (SHARE) return shared[j];
+            else                 return counter(j);
+        };
         // ---- 1x32 quantizer: codes of the lane's four rows and their scales ----
         uint32_t pk[4];
         float row_scale[4];
@@ -567,7 +603,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                 else                    byte = (j & 1) ? rbytes[j >> 1] >> 16 : rbytes[j >> 1] & 0xFFFFu;
                 row_scale[j] = scale_operand(byte);
                 if constexpr (ROW_SR)
-                    pk[j] = sr_codes8<FLOOR>(cur.x[j], byte, sr_terms(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_row, k0, k1));
+                    pk[j] = sr_codes8<FLOOR>(cur.x[j], byte, sr_terms(counter_of(j), blk_hi, a.tensor_id_row, k0, k1));
                 else
                     pk[j] = rtn_codes8(cur.x[j], byte);
                 if (want_row) {
@@ -576,6 +612,7 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                 }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
         // ---- 32x1 quantizer: group = this lane's 4 rows x the 8 lanes sharing cc ----
         // Scale bytes of the lane's eight columns, two per register: byte_of(t).
         uint32_t sb[4];
@@ -593,10 +630,8 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
             store_column_bytes(two, 2u * place, 1u);
             spread_row_groups4(two, sb);
         };
-        uint32_t colpk[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) colpk[t] = 0u;
-        auto terms = [&](int j) { return sr_terms(blk0 + (uint64_t)ci * 8u + (uint64_t)j * blk_row, a.tensor_id_t, k0, k1); };
+        uint32_t colpk[8];                                // the lower 16 bits are written and stored
+        auto terms = [&](int j) { return sr_terms(counter_of(j), blk_hi, a.tensor_id_t, k0, k1); };
         if (SRC == 2 || a.pre_quant) {
             uint32_t m[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -635,9 +670,11 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                         for (int t = 0; t < 8; ++t) d[r][t] = __uint_as_float(__float_as_uint(d[r][t]) & ON_GRID);
                 }
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    colpk[t] = T_SR ? pack_grid<jp>(colpk[t], __float_as_uint(d[0][t]), __float_as_uint(d[1][t]))
-                                    : cvt_rtn_f32<jp>(colpk[t], d[0][t], d[1][t], scale_operand(column_byte(t)));
+                for (int t = 0; t < 8; ++t) {
+                    if constexpr (T_SR)         colpk[t] = pack_grid<jp>(jp ? colpk[t] : __float_as_uint(d[0][t]), __float_as_uint(d[0][t]), __float_as_uint(d[1][t]));
+                    else if constexpr (jp == 0) colpk[t] = cvt_rtn_f32<0>(d[0][t], d[1][t], scale_operand(column_byte(t)));
+                    else                        colpk[t] = cvt_rtn_f32<1>(colpk[t], d[0][t], d[1][t], scale_operand(column_byte(t)));
+                }
             });
         } else if constexpr (SRC == 1) {
             column_bytes_bf16(cmax);
@@ -655,14 +692,15 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                         }
                     }
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(jp ? colpk[t] : g[0][t], g[0][t], g[1][t]);
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const uint32_t n0 = ties_to_larger(cur.x[2 * jp][i]), n1 = ties_to_larger(cur.x[2 * jp + 1][i]);
                         // the two rows of one column side by side
-                        colpk[2 * i] = cvt_fp4_bf16<jp>(colpk[2 * i], __builtin_amdgcn_perm(n1, n0, 0x05040100u), scale_operand(sb[i] & 0xFFFFu));
-                        colpk[2 * i + 1] = cvt_fp4_bf16<jp>(colpk[2 * i + 1], __builtin_amdgcn_perm(n1, n0, 0x07060302u), scale_operand(sb[i] >> 16));
+                        const uint32_t lo = __builtin_amdgcn_perm(n1, n0, 0x05040100u), hi = __builtin_amdgcn_perm(n1, n0, 0x07060302u);
+                        colpk[2 * i] = cvt_fp4_bf16<jp>(jp ? colpk[2 * i] : lo, lo, scale_operand(sb[i] & 0xFFFFu));
+                        colpk[2 * i + 1] = cvt_fp4_bf16<jp>(jp ? colpk[2 * i + 1] : hi, hi, scale_operand(sb[i] >> 16));
                     }
                 }
             });
@@ -691,18 +729,32 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
                         for (int t = 0; t < 8; ++t) g[r][t] = sr_grid<FLOOR>(cur.x[2 * jp + r].v[t], 1 - (int)byte_f32(t), rnd.w[t]);
                     }
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(colpk[t], g[0][t], g[1][t]);
+                    for (int t = 0; t < 8; ++t) colpk[t] = pack_grid<jp>(jp ? colpk[t] : g[0][t], g[0][t], g[1][t]);
                 } else {
 #pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        colpk[t] = cvt_rtn_f32<jp>(colpk[t], cur.x[2 * jp].v[t], cur.x[2 * jp + 1].v[t], scale_operand(byte_f32(t)));
+                    for (int t = 0; t < 8; ++t) {
+                        if constexpr (jp == 0) colpk[t] = cvt_rtn_f32<0>(cur.x[0].v[t], cur.x[1].v[t], scale_operand(byte_f32(t)));
+                        else                   colpk[t] = cvt_rtn_f32<1>(colpk[t], cur.x[2].v[t], cur.x[3].v[t], scale_operand(byte_f32(t)));
+                    }
                 }
             });
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t)
             *reinterpret_cast<uint16_t*>(st + S::COL_OFF + (lcol0 + t) * S::COL_PITCH + (lrow0 >> 1)) = (uint16_t)colpk[t];
-        if (PREFETCH) cur = nxt;
+    };
+    // Written out twice and not a loop: handing the fetched registers on costs 14 moves a tile.
+    if (wave_has_rows) {
+        const bool second = wide && mcol0 + 64 < a.cols;  // uniform
+        Tile t0, t1;
+        fetch(t0, 0);
+        if (PREFETCH && second) fetch(t1, 1);
+        encode(t0, std::integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        if (second) {
+            if (!PREFETCH) fetch(t1, 1);
+            encode(t1, std::integral_constant<int, 1>{});
+        }
     }
     __syncthreads();
 
@@ -727,9 +779,20 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
     }
 }
 
+// Waves of a launch that share a SIMD, as the registers of its instance allow (the kernels' launch bounds say so too).
+// src: 0 FP32, 1 bf16, 2 packed codes.
+constexpr int tile_waves_per_simd(int src, bool row_sr, bool t_sr, int waves)
+{
+    if (waves == 8) return 4;
+    if (src == 2) return 8;
+    if (src == 1) return row_sr && t_sr ? 4 : 5;
+    return t_sr && !row_sr ? 4 : 5;
+}
+
 // SRC as above, or 3: FP32 and bf16 jobs in one launch (a bf16 activation and its FP32 master weight).
-template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, SRC == 2 ? 5 : 4) void quantize_tile_kernel(TileBatch batch)
+// WIDE: block numbers of the launch differ in their upper word (SrCounter64).
+template <int SRC, bool ROW_SR, bool T_SR, bool FLOOR, bool COLSUM, int WAVES, bool WIDE>
+__global__ __launch_bounds__(64 * WAVES, tile_waves_per_simd(SRC == 3 ? 0 : SRC, ROW_SR, T_SR, WAVES)) void quantize_tile_kernel(TileBatch batch)
 {
     using S = TileShape<WAVES, SRC != 2, COLSUM>;
     __shared__ __attribute__((aligned(16))) uint8_t st[S::BYTES];
@@ -743,10 +806,10 @@ __global__ __launch_bounds__(64 * WAVES, SRC == 2 ? 5 : 4) void quantize_tile_ke
     const TileArgs a = batch.job[job];
     const uint32_t block = blockIdx.x - batch.first[job];
     if constexpr (SRC == 3) {
-        if (a.src_bf16) quantize_tile_body<S, 1, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
-        else            quantize_tile_body<S, 0, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        if (a.src_bf16) quantize_tile_body<S, 1, ROW_SR, T_SR, FLOOR, COLSUM, WIDE>(a, block, st);
+        else            quantize_tile_body<S, 0, ROW_SR, T_SR, FLOOR, COLSUM, WIDE>(a, block, st);
     } else {
-        quantize_tile_body<S, SRC, ROW_SR, T_SR, FLOOR, COLSUM>(a, block, st);
+        quantize_tile_body<S, SRC, ROW_SR, T_SR, FLOOR, COLSUM, WIDE>(a, block, st);
     }
 }
 
@@ -1049,6 +1112,14 @@ __global__ __launch_bounds__(256) void calibration_copy_kernel(const uint4* __re
 
 namespace mxl {
 
+// Whether the Philox block numbers of elements [index_base, index_base + 8 * blocks) differ in their upper 32 bits.  Those
+// of a tensor of fewer than 2^35 elements without an index base never do; the others run the kernels' WIDE instances.
+static bool spans_counter_words(uint64_t index_base, uint64_t blocks)
+{
+    const uint64_t first = index_base >> 3;
+    return (first >> 32) != ((first + blocks - 1) >> 32);
+}
+
 hipError_t launch_quantize_rows(const QuantRowsParams& p, hipStream_t st)
 {
     RowsArgs a{};
@@ -1059,7 +1130,12 @@ hipError_t launch_quantize_rows(const QuantRowsParams& p, hipStream_t st)
     a.base_blk = p.index_base >> 3;
     const uint32_t per_block = ROWS_THREADS * ROWS_UNROLL;
     dim3 grid((a.total + per_block - 1) / per_block), block(ROWS_THREADS);
-#define MX_ROWS_LAUNCH(T, SR, FL) hipLaunchKernelGGL((quantize_rows_kernel<T, SR, FL>), grid, block, 0, st, a)
+    const bool wide = p.sr && spans_counter_words(p.index_base, a.total);
+#define MX_ROWS_LAUNCH(T, SR, FL) \
+    do { \
+        if (wide) hipLaunchKernelGGL((quantize_rows_kernel<T, SR, FL, SR>), grid, block, 0, st, a); \
+        else      hipLaunchKernelGGL((quantize_rows_kernel<T, SR, FL, false>), grid, block, 0, st, a); \
+    } while (0)
     const int variant = (p.bf16 ? 4 : 0) | (p.sr ? 2 : 0) | (p.floor_mode ? 1 : 0);
     switch (variant) {
         case 0: MX_ROWS_LAUNCH(float, false, false); break;
@@ -1158,29 +1234,36 @@ hipError_t launch_ema_quantize(const QuantRowsParams& p, float* ema, float beta,
     return hipGetLastError();
 }
 
-template <int SRC, bool FL, bool CS, int WAVES>
-static void launch_tile_flags(const TileBatch& a, bool row_sr, bool t_sr, dim3 grid, hipStream_t st)
+template <int SRC, bool FL, bool CS, int WAVES, bool ROW_SR, bool T_SR>
+static void launch_tile_wide(const TileBatch& a, bool wide, dim3 grid, hipStream_t st)
 {
     dim3 block(64 * WAVES);
+    if (wide) hipLaunchKernelGGL((quantize_tile_kernel<SRC, ROW_SR, T_SR, FL, CS, WAVES, ROW_SR || T_SR>), grid, block, 0, st, a);
+    else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, ROW_SR, T_SR, FL, CS, WAVES, false>), grid, block, 0, st, a);
+}
+
+template <int SRC, bool FL, bool CS, int WAVES>
+static void launch_tile_flags(const TileBatch& a, bool row_sr, bool t_sr, bool wide, dim3 grid, hipStream_t st)
+{
     if (row_sr) {
-        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, true, FL, CS, WAVES>), grid, block, 0, st, a);
-        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, true, false, FL, CS, WAVES>), grid, block, 0, st, a);
+        if (t_sr) launch_tile_wide<SRC, FL, CS, WAVES, true, true>(a, wide, grid, st);
+        else      launch_tile_wide<SRC, FL, CS, WAVES, true, false>(a, wide, grid, st);
     } else {
-        if (t_sr) hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, true, FL, CS, WAVES>), grid, block, 0, st, a);
-        else      hipLaunchKernelGGL((quantize_tile_kernel<SRC, false, false, FL, CS, WAVES>), grid, block, 0, st, a);
+        if (t_sr) launch_tile_wide<SRC, FL, CS, WAVES, false, true>(a, wide, grid, st);
+        else      launch_tile_wide<SRC, FL, CS, WAVES, false, false>(a, false, grid, st);
     }
 }
 
 template <int SRC, bool FL>
-static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col_sums, int waves, dim3 grid, hipStream_t st)
+static void launch_tile_src(const TileBatch& a, bool row_sr, bool t_sr, bool col_sums, int waves, bool wide, dim3 grid, hipStream_t st)
 {
     if constexpr (SRC != 2) {
-        if (col_sums) return launch_tile_flags<SRC, FL, true, 8>(a, row_sr, t_sr, grid, st);
+        if (col_sums) return launch_tile_flags<SRC, FL, true, 8>(a, row_sr, t_sr, wide, grid, st);
     }
     if constexpr (SRC == 0) {
-        if (waves == 8) return launch_tile_flags<SRC, FL, false, 8>(a, row_sr, t_sr, grid, st);
+        if (waves == 8) return launch_tile_flags<SRC, FL, false, 8>(a, row_sr, t_sr, wide, grid, st);
     }
-    launch_tile_flags<SRC, FL, false, 4>(a, row_sr, t_sr, grid, st);
+    launch_tile_flags<SRC, FL, false, 4>(a, row_sr, t_sr, wide, grid, st);
 }
 
 // Waves of a macro tile.  Column sums are kept per 256 rows: eight.  Otherwise four (see above), except for FP32 sources so
@@ -1200,29 +1283,34 @@ static int tile_waves(const QuantTileParams* jobs, int count, bool col_sums)
 }
 
 // Fills the kernel arguments of one tensor; returns its number of workgroups.
-static uint32_t make_tile_args(const QuantTileParams& p, int waves, TileArgs& a)
+static uint32_t make_tile_args(const QuantTileParams& p, int waves, int per_simd, TileArgs& a)
 {
     a = TileArgs{};
     a.src = p.src; a.row_codes_in = p.row_codes_in; a.row_scales_in = p.row_scales_in;
     a.codes_t = p.codes_t; a.scales_t = p.scales_t; a.codes_row = p.codes_row; a.scales_row = p.scales_row;
     a.ld = p.ld; a.rows = (uint32_t)p.rows; a.cols = (uint32_t)p.cols;
     a.src_rows = p.src_rows ? (uint32_t)p.src_rows : (uint32_t)p.rows; a.src_bf16 = p.bf16 ? 1 : 0;
-    a.pre_quant = p.pre_quant;
+    a.pre_quant = p.pre_quant; a.want_row = p.codes_row != nullptr;
     a.k0 = (uint32_t)p.seed; a.k1 = (uint32_t)(p.seed >> 32);
     a.seed_dev = reinterpret_cast<const uint32_t*>(p.seed_dev);
     a.col_sum_partials = p.col_sums ? p.col_sum_workspace : nullptr;
     a.tensor_id_t = p.tensor_id_t; a.tensor_id_row = p.tensor_id_row; a.index_base = p.index_base;
-    // Macro tile of a workgroup: 128 columns, 64 for small tensors such as weights, where latency counts.  16 waves run
-    // on a compute unit, so a launch proceeds in rounds of `slots` equal tiles.  When the last round would be less than
-    // half full, its tiles are issued as their halves: twice the workgroups, half the time, and the round ends earlier.
+    // Macro tile of a workgroup: 128 columns, or 64 as long as all of those run at once (a single tile's latency counts
+    // then).  A launch proceeds in rounds of `slots` equal tiles.  When the last round would be at most a quarter full, its
+    // tiles are issued as their halves: twice the workgroups, half the time, and the round ends earlier (bf16 X 32768 x 768,
+    // 0.2 of a round: as halves 21.0, whole 24.4; 38272 x 768, 0.4 of one: 26.7 and 25.0).  Beyond one round
+    // 128 columns are faster even where they leave slots empty, in us for 64 / 128: FP32 X 9856 x 1536 26.1 / 20.2,
+    // 12608 x 768 20.8 / 15.6, FP32 dY 9856 x 1152 20.6 / 17.1, bf16 X 18912 x 576 17.5 / 13.3; except where a round is
+    // short: bf16 with two stochastic outputs 25216 x 384 15.1 / 15.6 (1.15 rounds) but 18912 x 576 18.6 / 16.4 (1.45),
+    // eight waves 9856 x 1152 21.8 / 24.0 (1.37) but 25216 x 512 27.7 / 26.2 (1.55).
     const uint32_t wide_per_row = (uint32_t)((p.cols + 127) / 128);
-    const uint32_t macro_rows = 32u * (uint32_t)waves, slots = 256u * (16u / (uint32_t)waves);
+    const uint32_t macro_rows = 32u * (uint32_t)waves, slots = 256u * 4u * (uint32_t)per_simd / (uint32_t)waves;
     const uint32_t n_tiles = (uint32_t)((p.rows + macro_rows - 1) / macro_rows) * wide_per_row;
-    const int64_t tiles32 = (p.rows / 32) * ((p.cols + 63) / 64);
+    const uint32_t fit = slots + (waves == 8 ? slots / 2u : p.bf16 && p.sr_row && p.sr_t ? slots / 4u : 0u);
     uint32_t n_wide = 0;
-    if (tiles32 >= 8192) {
+    if (n_tiles > fit / 2u) {
         const uint32_t rem = n_tiles % slots;
-        n_wide = (rem > 0u && rem <= slots / 2u) ? n_tiles - rem : n_tiles;
+        n_wide = (rem > 0u && rem <= slots / 4u) ? n_tiles - rem : n_tiles;
     }
     a.n_wide = n_wide; a.wide_per_row = wide_per_row;
     return n_wide + 2u * (n_tiles - n_wide);
@@ -1236,9 +1324,13 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
     const bool row_sr = p.row_codes_in ? false : p.sr_row;
     TileBatch b{};
     uint32_t blocks = 0;
-    bool col_sums = false, mixed = false;
-    for (int j = 0; j < count; ++j) col_sums = col_sums || jobs[j].col_sums != nullptr;
+    bool col_sums = false, mixed = false, wide = false;
+    for (int j = 0; j < count; ++j) {
+        col_sums = col_sums || jobs[j].col_sums != nullptr;
+        mixed = mixed || (!p.row_codes_in && jobs[j].bf16 != p.bf16);
+    }
     const int waves = tile_waves(jobs, count, !p.row_codes_in && col_sums);
+    const int per_simd = tile_waves_per_simd(p.row_codes_in ? 2 : p.bf16 && !mixed ? 1 : 0, row_sr, p.sr_t, waves);
     for (int j = 0; j < TILE_BATCH_MAX; ++j) {
         b.first[j] = 0xFFFFFFFFu;
         if (j >= count) continue;
@@ -1248,8 +1340,8 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
             (q.row_codes_in ? false : q.sr_row) != row_sr || q.floor_mode != p.floor_mode)
             return hipErrorInvalidValue;
         b.first[j] = blocks;
-        blocks += make_tile_args(q, waves, b.job[j]);
-        mixed = mixed || (!p.row_codes_in && q.bf16 != p.bf16);
+        blocks += make_tile_args(q, waves, per_simd, b.job[j]);
+        wide = wide || spans_counter_words(q.index_base, (uint64_t)q.rows * (uint64_t)(q.cols / 8));
     }
     if (mixed && (col_sums || row_sr)) return hipErrorInvalidValue;      // only the forward pass mixes source types
     if (widen && widen->count) {
@@ -1261,12 +1353,12 @@ hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hi
     auto launch = [&](auto fl) {
         constexpr bool FL = decltype(fl)::value;
         switch (src) {
-            case 0: launch_tile_src<0, FL>(b, row_sr, p.sr_t, col_sums, waves, grid, st); break;
-            case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, waves, grid, st); break;
-            case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, waves, grid, st); break;
+            case 0: launch_tile_src<0, FL>(b, row_sr, p.sr_t, col_sums, waves, wide, grid, st); break;
+            case 1: launch_tile_src<1, FL>(b, row_sr, p.sr_t, col_sums, waves, wide, grid, st); break;
+            case 2: launch_tile_src<2, FL>(b, row_sr, p.sr_t, false, waves, wide, grid, st); break;
             default:
-                if (p.sr_t) hipLaunchKernelGGL((quantize_tile_kernel<3, false, true, FL, false, 4>), grid, dim3(256), 0, st, b);
-                else        hipLaunchKernelGGL((quantize_tile_kernel<3, false, false, FL, false, 4>), grid, dim3(256), 0, st, b);
+                if (p.sr_t) launch_tile_wide<3, FL, false, 4, false, true>(b, wide, grid, st);
+                else        launch_tile_wide<3, FL, false, 4, false, false>(b, false, grid, st);
         }
     };
     if (p.floor_mode) launch(std::true_type{});

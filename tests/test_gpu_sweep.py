@@ -147,3 +147,35 @@ def test_fused_quantizer_of_large_f32_sources(mx, orc, rows, cols, rt, pre):
     got, want = mx.mx_quantize_transposed(dev(x), **kw), orc.quantize_transposed(x, **kw)
     for g, w, nm in zip(got, want, ("codes_t", "scales_t", "codes_row", "scales_row")):
         assert_same_bytes(g, w, nm)
+
+
+@pytest.mark.parametrize("before", [0, 1, 40, 700, 10 ** 6])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_block_numbers_across_a_counter_word(mx, orc, dtype, before):
+    """Philox block numbers reach 2^32 `before` blocks into the tensor (0: they start there, 10^6: they stay below)."""
+    rows, cols, base = 160, 224, (1 << 35) - 8 * before
+    x = mixed_matrix(rows, cols, seed=900, dtype=dtype)
+    src, key = dev(x, dtype), dict(seed=(5 << 40) + 9, index_base=base)
+    got, want = mx.mx_quantize(src, 1, 0, tensor_id=3, **key), orc.quantize(x, round=1, scale_mode=0, tensor_id=3, **key)
+    for g, w, nm in zip(got, want, ("codes", "scales")):
+        assert_same_bytes(g, w, "rows " + nm)
+    for pre, round_row in ((0, 1), (1, 0), (1, 1)):
+        kw = dict(round_t=1, tensor_id_t=5, pre_quant=pre, want_row=True, round_row=round_row, tensor_id_row=3, **key)
+        for g, w, nm in zip(mx.mx_quantize_transposed(src, **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):
+            assert_same_bytes(g, w, "pre %d row %d %s" % (pre, round_row, nm))
+    kw = dict(round_t=1, tensor_id_t=6, pre_quant=1, want_row=False, **key)
+    got = mx.mx_quantize_transposed(None, 1, 6, 1, False, row_in=mx.mx_quantize(src), shape=(rows, cols), **key)
+    for g, w, nm in zip(got[:2], orc.quantize_transposed(x, **kw)[:2], ("codes_t", "scales_t")):
+        assert_same_bytes(g, w, "from packed codes " + nm)
+
+
+@pytest.mark.parametrize("rows", [40960, 40992, 82112, 102432])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_transposed_at_the_lines_between_tile_widths(mx, orc, dtype, rows):
+    """192 columns: 64-column tiles in one round, just beyond one, a last round that is a little and more than a quarter full."""
+    x = mixed_matrix(rows, 192, seed=901, dtype=dtype)
+    src = dev(x, dtype)
+    for pre, round_row in ((1, 0), (0, 1)):
+        kw = dict(round_t=1, tensor_id_t=6, pre_quant=pre, want_row=True, round_row=round_row, tensor_id_row=1, seed=77)
+        for g, w, nm in zip(mx.mx_quantize_transposed(src, **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):
+            assert_same_bytes(g, w, "%d rows pre %d row %d %s" % (rows, pre, round_row, nm))
