@@ -101,10 +101,9 @@ __device__ __forceinline__ void store16(void* dst, v4i v)
 // ids go round-robin over the 8 XCDs, each with its own L2, so id % 8 = XCD gets a
 // contiguous range of the logical order (split, m tile, n tile): the workgroups that share
 // an A row panel or a B panel of one K range run on the same XCD at about the same time.
-__device__ __forceinline__ void decode_tile(const GemmArgs& g, uint32_t& zsplit, uint32_t& tm, uint32_t& tn)
+__device__ __forceinline__ void decode_tile(const GemmArgs& g, uint32_t bid, uint32_t& zsplit, uint32_t& tm, uint32_t& tn)
 {
     const uint32_t tiles = g.tiles_m * g.tiles_n, nblk = tiles * (uint32_t)g.split_k;
-    uint32_t bid = blockIdx.x;
     uint32_t per = nblk / 8, rem = nblk % 8;
     uint32_t xcd = bid % 8, idx = bid / 8;
     bid = xcd * per + (xcd < rem ? xcd : rem) + idx;       // bijection on [0, nblk)
@@ -149,8 +148,9 @@ __device__ __forceinline__ uint32_t load_scales4(const uint8_t* row, uint32_t of
 // ---------------------------------------------------------------------------
 constexpr int T_NT = 256;
 
-template <int BM, int BN, int KS>
+template <int BM_, int BN_, int KS_, int OCC_>
 struct TileShape {
+    static constexpr int BM = BM_, BN = BN_, KS = KS_, OCC = OCC_;   // OCC: workgroups per compute unit
     static constexpr int ROWB = KS / 2;                         // code bytes of a row and K step
     static constexpr int PITCH = ROWB;
     static constexpr int SCALEB = KS / 32;
@@ -357,20 +357,19 @@ __device__ __forceinline__ void tile_gelu_quant(const GemmArgs& g, uint8_t* ep, 
     }
 }
 
-template <int BM, int BN, int KS, int OCC, bool GELUQ = false>
-__global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
+template <typename S, bool GELUQ>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t block, uint8_t* lds)
 {
-    using S = TileShape<BM, BN, KS>;
+    constexpr int BM = S::BM, BN = S::BN, KS = S::KS;
     constexpr int CPR = S::ROWB / 16;                              // 16-byte chunks per row and step
     constexpr int A_CHUNKS = BM * CPR / T_NT, B_CHUNKS = BN * CPR / T_NT;
     constexpr int DPR = KS / 128;                                  // scale dwords per row and step
     constexpr int SDW = (BM + BN) * DPR, SC = (SDW + T_NT - 1) / T_NT;
     constexpr int TI = BM / 64, TJ = BN / 64;                      // MFMA tiles of a wave
     static_assert(BM * CPR % T_NT == 0 && BN * CPR % T_NT == 0, "tile/thread mismatch");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[S::LDS];
 
     uint32_t zsplit, tm, tn;
-    decode_tile(g, zsplit, tm, tn);
+    decode_tile(g, block, zsplit, tm, tn);
     const uint32_t m0 = tm * BM, n0 = tn * BN;
     const uint32_t kbeg = zsplit * g.k_per_split;
     const uint32_t kend = min(g.k, kbeg + g.k_per_split);
@@ -500,6 +499,26 @@ __global__ __launch_bounds__(T_NT, OCC) void mx_gemm_tile_kernel(GemmArgs g)
     }
     if (g.split_k == 1) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
     else                tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+}
+
+using Tile128 = TileShape<128, 128, 128, 3>;
+using Tile128x64 = TileShape<128, 64, 256, 3>;
+using Tile64 = TileShape<64, 64, 512, 2>;
+
+template <typename S, bool GELUQ = false>
+__global__ __launch_bounds__(T_NT, S::OCC) void mx_gemm_tile_kernel(GemmArgs g)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[S::LDS];
+    gemm_tile<S, GELUQ>(g, blockIdx.x, lds);
+}
+
+// Two products side by side: see launch_gemm_pair.  Workgroups from blocks0 (a multiple of 8) on work on the second.
+template <typename S0, typename S1>
+__global__ __launch_bounds__(T_NT, S0::OCC < S1::OCC ? S0::OCC : S1::OCC) void mx_gemm_tile_pair_kernel(GemmArgs g0, GemmArgs g1, uint32_t blocks0)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[S0::LDS > S1::LDS ? S0::LDS : S1::LDS];
+    if (blockIdx.x >= blocks0)                                                               gemm_tile<S1, false>(g1, blockIdx.x - blocks0, lds);
+    else if (blockIdx.x < g0.tiles_m * g0.tiles_n * (uint32_t)g0.split_k)                    gemm_tile<S0, false>(g0, blockIdx.x, lds);
 }
 
 // Sum the split-K partials in a fixed order and write the final output.
@@ -1339,14 +1358,14 @@ static GemmKernel plan_fused(int64_t m, int64_t n, int64_t k)
     return k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7 ? GemmKernel::tile128 : GemmKernel::pingpong;
 }
 
-hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail)
+// Kernel arguments of a product and the kernel that it runs on; the tile counts are filled in by tile_grid().
+static GemmKernel make_gemm_args(const GemmParams& p, GemmArgs& g)
 {
-    GemmArgs g{};
+    g = GemmArgs{};
     g.a_codes = p.a_codes; g.a_scales = p.a_scales; g.b_codes = p.b_codes; g.b_scales = p.b_scales;
     g.m = (uint32_t)p.m; g.n = (uint32_t)p.n; g.k = (uint32_t)p.k;
-    g.split_k = p.split_k;
-    uint32_t ksteps = (uint32_t)((p.k + 127) / 128);
-    uint32_t steps_per = (ksteps + p.split_k - 1) / p.split_k;
+    const uint32_t ksteps = (uint32_t)((p.k + 127) / 128);
+    const uint32_t steps_per = (ksteps + p.split_k - 1) / p.split_k;
     g.k_per_split = steps_per * 128;
     g.split_k = (int)((ksteps + steps_per - 1) / steps_per);   // drop empty splits
     g.c = g.split_k > 1 ? p.workspace : p.c;
@@ -1355,45 +1374,23 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
     GemmKernel kernel = p.q_codes ? plan_fused(p.m, p.n, p.k) : plan_gemm(p.m, p.n, p.k).kernel;
     // the main kernel needs four K steps in every split (the last one may be short of that)
     if (kernel == GemmKernel::pingpong && ksteps - (uint32_t)(g.split_k - 1) * steps_per < 4) kernel = GemmKernel::tile128;
-    auto tile_grid = [&](int bm, int bn) -> unsigned {
-        g.tiles_m = (uint32_t)((p.m + bm - 1) / bm);
-        g.tiles_n = (uint32_t)((p.n + bn - 1) / bn);
-        return g.tiles_m * g.tiles_n * (unsigned)g.split_k;
-    };
-    if (p.q_codes) {
-        if (!gemm_takes_fused_quantizer(p.m, p.n, p.k) || !g.bias || g.split_k != 1) return hipErrorInvalidValue;
-        g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
-    }
-    switch (kernel) {
-    case GemmKernel::pingpong: {
-        const unsigned nblk = tile_grid(Q_BM, Q_BN);
-        // measured on the ViT-B products: 2.5 us (3 x 2048 clocks) gains 5-15 % at K = 768 and
-        // 3-5 % at K = 2304, nothing at K = 3072; pointless below two rounds of tiles
-        g.stagger = (g.split_k == 1 && nblk >= 2 * Q_SLOTS && p.k <= 2304) ? 3 : 0;
-        const dim3 pgrid(nblk < Q_SLOTS ? nblk : Q_SLOTS);
-        if (p.q_codes) {
-            hipLaunchKernelGGL((mx_gemm_pingpong_kernel<true, true>), pgrid, dim3(Q_NT), 0, st, g);
-        } else if (g.bias) {
-            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<true>, pgrid, dim3(Q_NT), 0, st, g);
-        } else {
-            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<false>, pgrid, dim3(Q_NT), 0, st, g);
-        }
-        break;
-    }
-    case GemmKernel::tile128:
-        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3, true>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
-        else           hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 128, 128, 3>), dim3(tile_grid(128, 128)), dim3(T_NT), 0, st, g);
-        break;
-    case GemmKernel::tile128x64:
-        hipLaunchKernelGGL((mx_gemm_tile_kernel<128, 64, 256, 3>), dim3(tile_grid(128, 64)), dim3(T_NT), 0, st, g);
-        break;
-    case GemmKernel::tile64:
-        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2, true>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
-        else           hipLaunchKernelGGL((mx_gemm_tile_kernel<64, 64, 512, 2>), dim3(tile_grid(64, 64)), dim3(T_NT), 0, st, g);
-        break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return kernel;
+}
+
+static unsigned tile_grid(GemmArgs& g, uint32_t bm, uint32_t bn)
+{
+    g.tiles_m = (g.m + bm - 1) / bm;
+    g.tiles_n = (g.n + bn - 1) / bn;
+    return g.tiles_m * g.tiles_n * (unsigned)g.split_k;
+}
+
+// Start delay of every other workgroup of the main kernel.  Measured on the ViT-B products: 2.5 us (3 x 2048 clocks) gains
+// 5-15 % at K = 768 and 3-5 % at K = 2304, nothing at K = 3072; pointless below two rounds of tiles.
+static int stagger_of(const GemmArgs& g, unsigned tiles) { return (g.split_k == 1 && tiles >= 2 * Q_SLOTS && g.k <= 2304) ? 3 : 0; }
+
+// What is left of a product after its kernel: the sum over a K split, and the column sums.
+static hipError_t finish_product(const GemmParams& p, const GemmArgs& g, hipStream_t st, const ColumnSumTail* tail)
+{
     if (g.split_k > 1) {
         size_t total = (size_t)p.m * p.n;
         const size_t out_bytes = p.c_bf16 ? 2 : 4;
@@ -1408,11 +1405,83 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
         else
             hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, rblock, 0, st, static_cast<const float*>(p.workspace), g.split_k, g.m, g.n,
                                p.c, p.ldc, (int)p.c_bf16, p.bias, blocks, t);
-        e = hipGetLastError();
-    } else if (tail && tail->cols) {
-        e = launch_column_sum_finish(*tail, st);
+        return hipGetLastError();
     }
-    return e;
+    return tail && tail->cols ? launch_column_sum_finish(*tail, st) : hipSuccess;
+}
+
+hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail)
+{
+    GemmArgs g;
+    const GemmKernel kernel = make_gemm_args(p, g);
+    if (p.q_codes) {
+        if (!gemm_takes_fused_quantizer(p.m, p.n, p.k) || !g.bias || g.split_k != 1) return hipErrorInvalidValue;
+        g.q_codes = p.q_codes; g.q_scales = p.q_scales; g.q_floor = p.q_floor ? 1 : 0;
+    }
+    switch (kernel) {
+    case GemmKernel::pingpong: {
+        const unsigned nblk = tile_grid(g, Q_BM, Q_BN);
+        g.stagger = stagger_of(g, nblk);
+        const dim3 pgrid(nblk < Q_SLOTS ? nblk : Q_SLOTS);
+        if (p.q_codes) {
+            hipLaunchKernelGGL((mx_gemm_pingpong_kernel<true, true>), pgrid, dim3(Q_NT), 0, st, g);
+        } else if (g.bias) {
+            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<true>, pgrid, dim3(Q_NT), 0, st, g);
+        } else {
+            hipLaunchKernelGGL(mx_gemm_pingpong_kernel<false>, pgrid, dim3(Q_NT), 0, st, g);
+        }
+        break;
+    }
+    case GemmKernel::tile128:
+        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<Tile128, true>), dim3(tile_grid(g, 128, 128)), dim3(T_NT), 0, st, g);
+        else           hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile128>, dim3(tile_grid(g, 128, 128)), dim3(T_NT), 0, st, g);
+        break;
+    case GemmKernel::tile128x64:
+        hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile128x64>, dim3(tile_grid(g, 128, 64)), dim3(T_NT), 0, st, g);
+        break;
+    case GemmKernel::tile64:
+        if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<Tile64, true>), dim3(tile_grid(g, 64, 64)), dim3(T_NT), 0, st, g);
+        else           hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile64>, dim3(tile_grid(g, 64, 64)), dim3(T_NT), 0, st, g);
+        break;
+    }
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? finish_product(p, g, st, tail) : e;
+}
+
+// Two independent products of a backward pass, w and x, in one launch where both run on tile kernels and have a workspace
+// each (or need one at most): alone each fills its last round sparsely, or the chip altogether, and waits for the one
+// before.  Faster at every size measured, though both then have the LDS of the larger shape; quantizer, both products and
+// reduction of MxLinearStep.backward in a replayed graph, apart / together in us: 256 x 192 -> 768 FP32 13.1 / 9.9,
+// 1024 x 768 -> 3072 25.1 / 19.7, 6304 x 768 -> 3072 73.5 / 60.3, 12608 x 192 -> 768 35.9 / 33.8, 25216 x 1536 -> 384 FP32
+// 82.0 / 79.1.  Where the main kernel takes one of them they stay apart: a tile kernel in its place costs what is gained
+// (12608 x 768 -> 2304 82 / 90, 6304 x 1024 -> 1024 42 / 37), and two products on the main kernel leave each other
+// nothing (50432 x 2304 x 768 with 768 x 2304 x 50432: 116 apart, 124 together: its units are handed over one by one).
+hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail)
+{
+    GemmArgs gw, gx;
+    const GemmKernel kw = make_gemm_args(w, gw), kx = make_gemm_args(x, gx);
+    const bool own_scratch = gw.split_k == 1 || gx.split_k == 1 || w.workspace != x.workspace;
+    // (w on 128 x 128 tiles: a large weight and few tokens, which fill the chip by themselves)
+    if (!own_scratch || kw == GemmKernel::pingpong || kw == GemmKernel::tile128 || kx == GemmKernel::pingpong || w.q_codes || x.q_codes) {
+        const hipError_t e = launch_gemm(x, st);
+        return e == hipSuccess ? launch_gemm(w, st, tail) : e;
+    }
+    auto launch = [&](auto sw, auto sx) {
+        using SW = decltype(sw);
+        using SX = decltype(sx);
+        const unsigned nw = tile_grid(gw, SW::BM, SW::BN), nx = tile_grid(gx, SX::BM, SX::BN), first = (nw + 7u) / 8u * 8u;
+        hipLaunchKernelGGL((mx_gemm_tile_pair_kernel<SW, SX>), dim3(first + nx), dim3(T_NT), 0, st, gw, gx, first);
+    };
+    auto with_x = [&](auto sw) {
+        if (kx == GemmKernel::tile64)          launch(sw, Tile64{});
+        else if (kx == GemmKernel::tile128x64) launch(sw, Tile128x64{});
+        else                                   launch(sw, Tile128{});
+    };
+    if (kw == GemmKernel::tile64) with_x(Tile64{});
+    else                          with_x(Tile128x64{});
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = finish_product(x, gx, st, nullptr);
+    return e == hipSuccess ? finish_product(w, gw, st, tail) : e;
 }
 
 }  // namespace mxl

@@ -200,5 +200,7 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 int gemm_split_k(int64_t m, int64_t n, int64_t k);
 // tail: column sums to finish as well (in the K split's reduction where there is one, else in a launch of their own).
 hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail = nullptr);
+// Two independent products, in one launch where that pays; the results of launch_gemm(x) and launch_gemm(w, tail), bit for bit.
+hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail = nullptr);
 
 }  // namespace mxl

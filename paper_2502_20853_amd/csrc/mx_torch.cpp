@@ -106,10 +106,9 @@ Seed seed_of(int64_t value, const OptTensor& dev)
     return s;
 }
 
-// One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split.
-void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
-             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr,
-             const mxl::ColumnSumTail* tail = nullptr)
+// One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split; `own` keeps it.
+mxl::GemmParams product_params(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
+                               const Tensor& out, int64_t ldc, const float* bias, const char* fn, const Tensor* workspace, Tensor& own)
 {
     mxl::GemmParams p{};
     p.a_codes = a; p.a_scales = as; p.b_codes = b; p.b_scales = bs;
@@ -118,7 +117,6 @@ void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_
     p.bias = bias;
     check(mxl::check_gemm(p), fn);
     p.split_k = mxl::gemm_split_k(m, n, k);
-    Tensor own;
     if (p.split_k > 1) {
         const int64_t need = (int64_t)p.split_k * m * n * 4;
         if (workspace && workspace->defined() && (int64_t)workspace->nbytes() >= need) {
@@ -129,7 +127,15 @@ void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_
         }
         if ((reinterpret_cast<uintptr_t>(p.workspace) & 255) != 0) throw Status(fn, MX_ERR_ALIGN);
     }
-    check_hip(mxl::launch_gemm(p, st, tail), fn);
+    return p;
+}
+
+void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
+             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr,
+             const mxl::ColumnSumTail* tail = nullptr)
+{
+    Tensor own;
+    check_hip(mxl::launch_gemm(product_params(a, as, b, bs, m, n, k, out, ldc, bias, fn, workspace, own), st, tail), fn);
 }
 
 mxl::QuantRowsParams rows_job(const Tensor& src, int64_t rows, int64_t cols, uint8_t* codes, uint8_t* scales, bool floor_mode)
@@ -335,14 +341,25 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
             q.floor_mode = floor_mode; q.seed_dev = seed.dev;
             launch_tiles(&q, 1, st);
         }
+        const mxl::ColumnSumTail* sums = want_db ? &tail : nullptr;
+        mxl::GemmParams px, pw;
+        Tensor own_x, own_w;
         if (want_dx) {
             dx = at::empty(shape, dy.options());
-            product(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, st, "mx_linear_bwd_dx");
+            px = product_params(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, "mx_linear_bwd_dx", nullptr, own_x);
         }
         if (want_dw) {
             dw = at::empty({C, D}, dy.options().dtype((at::ScalarType)meta[5]));
-            product(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, st, "mx_linear_bwd_dw", nullptr, want_db ? &tail : nullptr);
-        } else if (want_db) {
+            pw = product_params(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, "mx_linear_bwd_dw", nullptr, own_w);
+        }
+        if (want_dx && want_dw) {
+            check_hip(mxl::launch_gemm_pair(pw, px, st, sums), "mx_linear_bwd_dw");
+        } else if (want_dx) {
+            check_hip(mxl::launch_gemm(px, st), "mx_linear_bwd_dx");
+        } else if (want_dw) {
+            check_hip(mxl::launch_gemm(pw, st, sums), "mx_linear_bwd_dw");
+        }
+        if (!want_dw && want_db) {
             check_hip(mxl::launch_column_sum_finish(tail, st), "mx_quantize_transposed_batch");
         }
         if (want_db) db = db.to((at::ScalarType)meta[6]);
@@ -437,8 +454,10 @@ void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t s
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
     launch_tiles(&q, 1, st);
-    product(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, st, "mx_linear_bwd_dx", &workspace);
-    product(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, st, "mx_linear_bwd_dw", &workspace);
+    Tensor own_x, own_w;
+    const mxl::GemmParams px = product_params(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, "mx_linear_bwd_dx", &workspace, own_x);
+    const mxl::GemmParams pw = product_params(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, "mx_linear_bwd_dw", &workspace, own_w);
+    check_hip(mxl::launch_gemm_pair(pw, px, st), "mx_linear_bwd_dw");
 }
 
 // ---- QRampingAdamW: one call per parameter group ----

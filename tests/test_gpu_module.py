@@ -394,3 +394,31 @@ def test_module_with_the_floor_scale_rule(mx, flow, xt, wt):
     # FP32 sums of `tokens` values in some order, then one rounding to the bias's type
     ref, mag = dy.double().sum(0), dy.double().abs().sum(0)
     assert bool(((db.double() - ref).abs() <= tokens * 2.0 ** -24 * mag + (ref.abs() * 2.0 ** -8 if wt == "bf16" else 0.0)).all())
+
+
+@pytest.mark.parametrize("n,d,c", [
+    # tiles of dW / dX: 64 / 64 (with idle workgroups between the two), K split 64 / 128x64, 64 / 128, 128x64 / 64,
+    # 128x64 / 128x64, 128x64 / 128, the smallest, dX split as well (one workspace: apart), dX on the main kernel (apart)
+    (256, 192, 768), (12608, 192, 576), (4064, 2048, 480), (1024, 768, 3072), (2048, 768, 3072), (4064, 2048, 992), (32, 32, 32),
+    (512, 1024, 4096), (25216, 384, 1536)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):
+    """The native backward pass gives what the separate calls give for the same operands, bit for bit."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d + c)
+    x, w, dy = (torch.randn(s, generator=g, device="cuda").to(dtype) for s in ((n, d), (c, d), (n, c)))
+    st = mx.MxLinearStep(n, d, c, out_dtype=dtype)
+    st.forward(x, w, 7)
+    dx, dw = (t.clone() for t in st.backward(dy, 7))
+    assert torch.equal(dx, mx.mx_linear_bwd_dx(st.dyq, st.dys, st.wtq, st.wts, out_dtype=dtype))
+    assert torch.equal(dw, mx.mx_linear_bwd_dw(st.dytq, st.dyts, st.xtq, st.xts, out_dtype=torch.float32))
+    # the module: a workspace each
+    lin = mx.MxLinear(d, c, bias=False, dtype=dtype, seed=7 >> 16, layer_id=0)
+    with torch.no_grad():
+        lin.weight.copy_(w)
+    lin.key_high, lin.calls = 0, 7
+    xg = x.clone().requires_grad_(True)
+    gx, gw = torch.autograd.grad(lin(xg), (xg, lin.weight), dy)
+    assert torch.equal(gx, dx)
+    if n % 128 == 0 or n < 4096:                        # otherwise the module's dW sums over more rows, in another order
+        assert torch.equal(gw, dw.to(dtype))
