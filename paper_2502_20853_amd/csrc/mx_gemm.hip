@@ -135,8 +135,8 @@ __device__ __forceinline__ uint32_t load_scales4(const uint8_t* row, uint32_t of
 //   Operands go global -> registers -> LDS, the next step's loads in flight during the current step's
 //   MFMAs; chunks past the end of K are zero-filled in registers, so K needs no alignment beyond a group.
 //   (No DMA loads: they cannot zero-fill a ragged K tail, and scale rows of K/32 bytes have no alignment.)
-// Three shapes (chosen in plan_gemm, which gives the times):
-//   128 x 128, KS 128: 35 KB of LDS, three workgroups per compute unit, so that one stores its tile or waits for
+// Shapes (chosen in plan_gemm, which gives the times):
+//   128 x 128, KS 128 (384, one step, for K up to that): 35 KB (52) of LDS, three workgroups per compute unit, so that one stores its tile or waits for
 //     its first loads while the others multiply; at four, the 128 registers allowed spill (25216 x 1536 x 384:
 //     41 us against 27).
 //   128 x 64, KS 256: half the tile and twice the K step, for products with fewer tiles, where the latency of a
@@ -154,17 +154,75 @@ struct TileShape {
     static constexpr int ROWB = KS / 2;                         // code bytes of a row and K step
     static constexpr int PITCH = ROWB;
     static constexpr int SCALEB = KS / 32;
-    static constexpr int SPITCH = SCALEB + (KS > 128 ? 4 : 0);  // KS 128: one dword per row, conflict-free as it is
+    static constexpr int SPITCH = SCALEB + (KS % 256 == 0 ? 4 : 0);   // KS 128 and 384: 1 and 3 dwords per row, conflict-free as they are
     static constexpr int STAGE = (BM + BN) * (PITCH + SPITCH);
+    static constexpr int STAGES = KS == 384 ? 1 : 2;            // one: K <= KS, a single step
     static constexpr int EP_PITCH = BN / 2 * 4 + 16;            // output strip: 32 rows of BN/2 FP32 values
-    static constexpr int LDS = 2 * STAGE > 4 * 32 * EP_PITCH ? 2 * STAGE : 4 * 32 * EP_PITCH;
+    static constexpr int LDS = STAGES * STAGE > 4 * 32 * EP_PITCH ? STAGES * STAGE : 4 * 32 * EP_PITCH;
     // 16-byte column of a chunk: XOR-swizzled, so that the 16 lanes of an access phase (16 rows of one chunk, or
     // 4 to 16 chunks of a row) spread over all banks
     static __device__ __forceinline__ uint32_t column(uint32_t row, uint32_t chunk)
     {
+        if (KS == 384) {                                        // 12 chunks: rotated instead
+            const uint32_t p = chunk + ((row >> 2) & 3u);
+            return (p >= 12u ? p - 12u : p) << 4;
+        }
         return (KS == 128 ? chunk ^ ((row >> 2) & 3u) : KS == 256 ? chunk ^ ((row >> 1) & 7u) : chunk ^ (row & 15u)) << 4;
     }
 };
+
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+
+// The output stage of a wave whose TI x TJ tiles of 32 x 32 lie wholly inside the matrix, with rows that can be stored 16
+// bytes at a time: no bounds tests, a store's address is a uniform pointer plus one lane offset, and the strip's
+// accesses need no waits (the LDS executes a wave's instructions in order), so 32 rows are converted and written to the
+// strip while the stores of the 32 before them are issued.  A short-K product is bound by this stage (25216 x 1536 FP32:
+// 155 MB): against the form with tests below, 25216 x 1152 x 384 bf16 21.5 -> 19.4 us, 50432 x 768 x 192 22.2 -> 19.6.
+template <int TI, int TJ, bool STREAM, bool BF16>
+__device__ __forceinline__ void tile_epilogue_interior(const GemmArgs& g, lds_u8* ep, v16f (&acc)[TI][TJ], uint32_t mrow0,
+                                                       uint32_t nbase, uint32_t zsplit, int64_t ldc)
+{
+    typedef __attribute__((address_space(3))) v4i lds_v4i;
+    typedef __attribute__((address_space(3))) v4f lds_v4f;
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) v2i lds_v2i;
+    constexpr int ES = BF16 ? 2 : 4, COLS = 32 * TJ, PITCH = COLS * 4 + 16, LPR = COLS * ES / 16, RPI = 64 / LPR, STORES = 32 / RPI;
+    const uint32_t lane = threadIdx.x & 63, lrow = lane & 31, lhalf = lane >> 5;
+    uint8_t* base = static_cast<uint8_t*>(g.c);
+    if (!BF16 && g.split_k > 1) base += (size_t)zsplit * g.m * g.n * 4;
+    uint8_t* tile = base + ((size_t)mrow0 * ldc + nbase) * ES;                            // uniform
+    const uint32_t voff = (lane / LPR) * (uint32_t)ldc * ES + (lane % LPR) * 16;
+    lds_u8* wr = ep + lrow * PITCH + lhalf * 4 * ES;
+    const lds_u8* rd = ep + (lane / LPR) * PITCH + (lane % LPR) * 16;
+    v4f bias[TJ][4];
+    if (g.bias != nullptr) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bias[j][q] = *reinterpret_cast<const v4f*>(g.bias + nbase + 32 * j + 8 * q + 4 * lhalf);
+    }
+    auto write_rows = [&](int i) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v4f v = v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                if (g.bias != nullptr) v += bias[j][q];
+                if (BF16) *reinterpret_cast<lds_v2i*>(wr + (32 * j + 8 * q) * 2) = v2i{(int)f32x2_to_bf16x2(v.x, v.y), (int)f32x2_to_bf16x2(v.z, v.w)};
+                else      *reinterpret_cast<lds_v4f*>(wr + (32 * j + 8 * q) * 4) = v;
+            }
+    };
+    write_rows(0);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        v4i v[STORES];
+#pragma unroll
+        for (int it = 0; it < STORES; ++it) v[it] = *reinterpret_cast<const lds_v4i*>(rd + it * RPI * PITCH);
+        if (i + 1 < TI) write_rows(i + 1);
+#pragma unroll
+        for (int it = 0; it < STORES; ++it) store16<STREAM>(tile + (size_t)(i * 32 + it * RPI) * ldc * ES + voff, v[it]);
+    }
+}
 
 // Accumulators of one wave (TI x TJ tiles of 32 x 32; first row mrow0, first column nbase) through a per-wave
 // LDS strip of 32 rows, so that a store instruction writes 16 bytes per lane and whole row segments.
@@ -184,6 +242,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, uint8_t* ep, v1
     const bool as_bf16 = g.c_bf16 && g.split_k == 1;
     const bool vec_ok = as_bf16 ? (ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(ch) & 15) == 0
                                 : (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(cf) & 15) == 0;
+    if (mrow0 + 32 * TI <= g.m && nbase + 32 * TJ <= g.n && vec_ok && ldc < (1 << 26)) {       // uniform
+        if (as_bf16) tile_epilogue_interior<TI, TJ, STREAM, true>(g, (lds_u8*)ep, acc, mrow0, nbase, zsplit, ldc);
+        else         tile_epilogue_interior<TI, TJ, STREAM, false>(g, (lds_u8*)ep, acc, mrow0, nbase, zsplit, ldc);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
 #pragma unroll
@@ -374,7 +438,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     const uint32_t kbeg = zsplit * g.k_per_split;
     const uint32_t kend = min(g.k, kbeg + g.k_per_split);
     const uint32_t kbytes = g.k >> 1, kgroups = g.k >> 5;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const uint32_t lrow = lane & 31, lhalf = lane >> 5;
 
@@ -384,12 +448,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     const uint8_t* b_base = g.b_codes + (size_t)n0 * kbytes;
     uint32_t a_off[A_CHUNKS], b_off[B_CHUNKS], s_left[SC];
     const uint8_t* s_src[SC];
-    const uint32_t ch = tid % CPR;                                 // T_NT is a multiple of CPR: the same chunk in every row
+    // chunk u of a thread: 16-byte column and row (where T_NT is a multiple of CPR: the same column in every row)
+    auto ch = [&](int u) -> uint32_t { return (uint32_t)(tid + u * T_NT) % CPR; };
     const uint32_t mlast = g.m - 1 - m0, nlast = g.n - 1 - n0;
 #pragma unroll
-    for (int u = 0; u < A_CHUNKS; ++u) a_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, mlast) * kbytes + ch * 16;
+    for (int u = 0; u < A_CHUNKS; ++u) a_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, mlast) * kbytes + ch(u) * 16;
 #pragma unroll
-    for (int u = 0; u < B_CHUNKS; ++u) b_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, nlast) * kbytes + ch * 16;
+    for (int u = 0; u < B_CHUNKS; ++u) b_off[u] = min((uint32_t)(tid + u * T_NT) / CPR, nlast) * kbytes + ch(u) * 16;
 #pragma unroll
     for (int u = 0; u < SC; ++u) {
         const uint32_t row = min(tid + u * T_NT, SDW - 1) / DPR;
@@ -403,13 +468,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     v4i ra[A_CHUNKS], rb[B_CHUNKS];
     uint32_t rs[SC];
     auto gload = [&](uint32_t k0) {
-        const bool ok = k0 + ch * 32 < kend;
+        auto ok = [&](int u) { return k0 + ch(u) * 32 < kend; };
         const v4i z = v4i{0, 0, 0, 0};
         const uint8_t *pa = a_base + (k0 >> 1), *pb = b_base + (k0 >> 1);
 #pragma unroll
-        for (int u = 0; u < A_CHUNKS; ++u) ra[u] = ok ? *reinterpret_cast<const v4i*>(pa + a_off[u]) : z;
+        for (int u = 0; u < A_CHUNKS; ++u) ra[u] = ok(u) ? *reinterpret_cast<const v4i*>(pa + a_off[u]) : z;
 #pragma unroll
-        for (int u = 0; u < B_CHUNKS; ++u) rb[u] = ok ? *reinterpret_cast<const v4i*>(pb + b_off[u]) : z;
+        for (int u = 0; u < B_CHUNKS; ++u) rb[u] = ok(u) ? *reinterpret_cast<const v4i*>(pb + b_off[u]) : z;
 #pragma unroll
         for (int u = 0; u < SC; ++u) {
             const uint32_t k = k0 + (tid + u * T_NT) % DPR * 128;
@@ -420,12 +485,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
 #pragma unroll
         for (int u = 0; u < A_CHUNKS; ++u) {
             const uint32_t row = (tid + u * T_NT) / CPR;
-            *reinterpret_cast<v4i*>(st + row * S::PITCH + S::column(row, ch)) = ra[u];
+            *reinterpret_cast<v4i*>(st + row * S::PITCH + S::column(row, ch(u))) = ra[u];
         }
 #pragma unroll
         for (int u = 0; u < B_CHUNKS; ++u) {
             const uint32_t row = (tid + u * T_NT) / CPR;
-            *reinterpret_cast<v4i*>(st + (BM + row) * S::PITCH + S::column(row, ch)) = rb[u];
+            *reinterpret_cast<v4i*>(st + (BM + row) * S::PITCH + S::column(row, ch(u))) = rb[u];
         }
 #pragma unroll
         for (int u = 0; u < SC; ++u)
@@ -481,10 +546,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     __syncthreads();
     uint32_t cur = 0;
     for (uint32_t k0 = kbeg; k0 < kend; k0 += KS) {
-        const bool more = k0 + KS < kend;
+        const bool more = S::STAGES > 1 && k0 + KS < kend;
         if (more) gload(k0 + KS);
         compute(lds + cur, k0);
-        cur = cur ? 0u : (uint32_t)S::STAGE;
+        if (S::STAGES > 1) cur = cur ? 0u : (uint32_t)S::STAGE;
         if (more) lstore(lds + cur);
         __syncthreads();
     }
@@ -504,6 +569,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
 using Tile128 = TileShape<128, 128, 128, 3>;
 using Tile128x64 = TileShape<128, 64, 256, 3>;
 using Tile64 = TileShape<64, 64, 512, 2>;
+using Tile128Short = TileShape<128, 128, 384, 3>;
 
 template <typename S, bool GELUQ = false>
 __global__ __launch_bounds__(T_NT, S::OCC) void mx_gemm_tile_kernel(GemmArgs g)
@@ -607,7 +673,6 @@ __device__ __forceinline__ uint32_t fresh_lane_id()
 // Accumulators of one wave (64 rows x 128 columns) -> global through a 32-row LDS strip
 // holding 128 bytes per row: 64 bf16 or 32 fp32 columns at a time.  A store instruction
 // of the wave covers 8 whole 128-byte row segments.
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef int v2i __attribute__((ext_vector_type(2)));
 
 // The same output stage for a wave tile that lies wholly inside the matrix and whose rows can be
@@ -1304,10 +1369,12 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 //     main kernel), with a K split up to two per unit (768 x 192 x 12672: 11 against 13 and 18).
 //   128 x 64 tiles: up to three per unit (9856 x 384 x 1536: 9.4 against 11.3 and 12.3).
 //   128 x 128 tiles: what is left, i.e. long m or n at K < 512 or K % 128 != 0 (25216 x 1536 x 384: 27 against 30
-//     on 256 x 128 tiles with DMA loads, the kernel that ran these sizes before).
+//     on 256 x 128 tiles with DMA loads, the kernel that ran these sizes before); with all of K in one step for 256 < K <=
+//     384 (bf16 25216 x 1536 x 384 22.4 against 24.5, FP32 25216 x 1152 x 384 27.5 against 30.0, 12608 x 1024 x 352 15.7
+//     against 17.1), where steps of 128 wait three times; up to 256 it only takes LDS (12608 x 576 x 192 6.8 against 6.65).
 // K splits (K >= 4096): s partials cost s * m * n * 4 bytes written and read, the K loop is K / s long; the sum is
 // least at s ~ sqrt(K / (m n)) times the constant below, measured per kernel, within the slots of one round.
-enum class GemmKernel { pingpong, tile128, tile128x64, tile64 };
+enum class GemmKernel { pingpong, tile128, tile128_short, tile128x64, tile64 };
 
 struct GemmPlan {
     GemmKernel kernel;
@@ -1330,7 +1397,7 @@ static GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k)
     if (t64 <= (k >= 4096 ? 512 : 256)) return {GemmKernel::tile64, splits(512, t64, 24.0, 1024)};
     if (t12864 <= 768) return {GemmKernel::tile128x64, splits(768, t12864, 35.0, 1024)};
     if (main_ok) return {GemmKernel::pingpong, 1};
-    return {GemmKernel::tile128, 1};
+    return {k > 256 && k <= 384 ? GemmKernel::tile128_short : GemmKernel::tile128, 1};
 }
 
 int gemm_split_k(int64_t m, int64_t n, int64_t k) { return plan_gemm(m, n, k).split_k; }
@@ -1436,6 +1503,9 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
         if (p.q_codes) hipLaunchKernelGGL((mx_gemm_tile_kernel<Tile128, true>), dim3(tile_grid(g, 128, 128)), dim3(T_NT), 0, st, g);
         else           hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile128>, dim3(tile_grid(g, 128, 128)), dim3(T_NT), 0, st, g);
         break;
+    case GemmKernel::tile128_short:
+        hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile128Short>, dim3(tile_grid(g, 128, 128)), dim3(T_NT), 0, st, g);
+        break;
     case GemmKernel::tile128x64:
         hipLaunchKernelGGL(mx_gemm_tile_kernel<Tile128x64>, dim3(tile_grid(g, 128, 64)), dim3(T_NT), 0, st, g);
         break;
@@ -1462,7 +1532,7 @@ hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_
     const GemmKernel kw = make_gemm_args(w, gw), kx = make_gemm_args(x, gx);
     const bool own_scratch = gw.split_k == 1 || gx.split_k == 1 || w.workspace != x.workspace;
     // (w on 128 x 128 tiles: a large weight and few tokens, which fill the chip by themselves)
-    if (!own_scratch || kw == GemmKernel::pingpong || kw == GemmKernel::tile128 || kx == GemmKernel::pingpong || w.q_codes || x.q_codes) {
+    if (!own_scratch || kw == GemmKernel::pingpong || kw == GemmKernel::tile128 || kw == GemmKernel::tile128_short || kx == GemmKernel::pingpong || w.q_codes || x.q_codes) {
         const hipError_t e = launch_gemm(x, st);
         return e == hipSuccess ? launch_gemm(w, st, tail) : e;
     }
@@ -1475,7 +1545,8 @@ hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_
     auto with_x = [&](auto sw) {
         if (kx == GemmKernel::tile64)          launch(sw, Tile64{});
         else if (kx == GemmKernel::tile128x64) launch(sw, Tile128x64{});
-        else                                   launch(sw, Tile128{});
+        else if (kx == GemmKernel::tile128)    launch(sw, Tile128{});
+        else                                   launch(sw, Tile128Short{});
     };
     if (kw == GemmKernel::tile64) with_x(Tile64{});
     else                          with_x(Tile128x64{});

@@ -398,8 +398,8 @@ def test_module_with_the_floor_scale_rule(mx, flow, xt, wt):
 
 @pytest.mark.parametrize("n,d,c", [
     # tiles of dW / dX: 64 / 64 (with idle workgroups between the two), K split 64 / 128x64, 64 / 128, 128x64 / 64,
-    # 128x64 / 128x64, 128x64 / 128, the smallest, dX split as well (one workspace: apart), dX on the main kernel (apart)
-    (256, 192, 768), (12608, 192, 576), (4064, 2048, 480), (1024, 768, 3072), (2048, 768, 3072), (4064, 2048, 992), (32, 32, 32),
+    # 128x64 / 128x64, 128x64 / 128, 64 / 128 with all of K at once, 128x64 / the same, the smallest, dX split as well (one workspace: apart), dX on the main kernel (apart)
+    (256, 192, 768), (12608, 192, 576), (4064, 2048, 480), (1024, 768, 3072), (2048, 768, 3072), (4064, 2048, 992), (25216, 1536, 384), (3968, 4096, 352), (32, 32, 32),
     (512, 1024, 4096), (25216, 384, 1536)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):

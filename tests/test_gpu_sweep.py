@@ -78,6 +78,8 @@ def test_sweep_products(mx, orc):
     (1025, 1024, 96), (1031, 1030, 288), (4096, 1536, 160),
     # one more: 128 x 128 tiles; K % 128 == 0 below and above 512
     (4097, 1536, 160), (12801, 452, 384), (12672, 578, 416),
+    # in steps of 128 up to K = 256, all of K at once above that: ragged K, rows and columns that end inside a wave's tile
+    (12801, 452, 256), (12801, 452, 288), (4163, 1570, 352),
     # the main kernel from 128 tiles of 256 x 256 on (ragged edges, shifted last scale block)
     (32765, 250, 640), (32641, 36, 512), (8200, 1028, 1152),
     # K splits of the 64 x 64 and 128 x 64 tiles (uneven, ragged K), and of the main kernel
