@@ -539,7 +539,16 @@ __device__ __forceinline__ void column_sum_finish(const ColumnSumTail& a, uint32
     float s = 0.f;
     if (c < a.cols) {
         const uint32_t b0 = min(a.blocks, p * per), b1 = min(a.blocks, b0 + per);
-        for (uint32_t b = b0; b < b1; ++b) s += a.partials[(size_t)b * a.cols + c];
+        const float* p0 = a.partials + (size_t)b0 * a.cols + c;
+        uint32_t b = b0;
+        for (; b + 8u <= b1; b += 8u, p0 += (size_t)8 * a.cols) {           // eight loads in flight, added in order
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = p0[(size_t)i * a.cols];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += v[i];
+        }
+        for (; b < b1; ++b, p0 += a.cols) s += *p0;
     }
     part[p][lc] = s;
     __syncthreads();

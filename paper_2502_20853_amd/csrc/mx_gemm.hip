@@ -588,15 +588,18 @@ __global__ __launch_bounds__(T_NT, S0::OCC < S1::OCC ? S0::OCC : S1::OCC) void m
 }
 
 // Sum the split-K partials in a fixed order and write the final output.
-// Workgroups past the reduction's own (`blocks`) finish a column sum, which saves that its own launch.
+// The first `tail_blocks` workgroups finish a column sum, which saves that its own launch: few and each a chain of loads,
+// they run beside the reduction when they start with it.  4096 x 1024, four splits, 197 blocks of column sums: 25.6 us with
+// them as the last workgroups and one load at a time, 15.8 now, 14.4 without column sums.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, int split, uint32_t m, uint32_t n,
-                                     void* c, int64_t ldc, int c_bf16, const float* bias, uint32_t blocks, mxl::ColumnSumTail tail)
+                                     void* c, int64_t ldc, int c_bf16, const float* bias, mxl::ColumnSumTail tail, uint32_t tail_blocks)
 {
-    if (blockIdx.x >= blocks) {
-        mxl::column_sum_finish(tail, blockIdx.x - blocks);
+    if (blockIdx.x < tail_blocks) {
+        mxl::column_sum_finish(tail, blockIdx.x);
         return;
     }
-    size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t block = blockIdx.x - tail_blocks;
+    size_t idx = (size_t)block * blockDim.x + threadIdx.x;
     size_t total = (size_t)m * n;
     if (idx >= total) return;
     float s = 0.f;
@@ -610,13 +613,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, i
 // The same for n % 4 == 0 and 16-byte aligned rows of the output: four columns per thread, the
 // partial loads of a thread issued back to back (same summation order per element).
 __global__ __launch_bounds__(256) void splitk_reduce4_kernel(const float* part, int split, uint32_t m, uint32_t n,
-                                      void* c, int64_t ldc, int c_bf16, const float* bias, uint32_t blocks, mxl::ColumnSumTail tail)
+                                      void* c, int64_t ldc, int c_bf16, const float* bias, mxl::ColumnSumTail tail, uint32_t tail_blocks)
 {
-    if (blockIdx.x >= blocks) {
-        mxl::column_sum_finish(tail, blockIdx.x - blocks);
+    if (blockIdx.x < tail_blocks) {
+        mxl::column_sum_finish(tail, blockIdx.x);
         return;
     }
-    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;       // index of a group of 4 columns
+    const uint32_t block = blockIdx.x - tail_blocks;
+    const size_t q = (size_t)block * blockDim.x + threadIdx.x;            // index of a group of 4 columns
     const size_t total = (size_t)m * n;
     if (q * 4 >= total) return;
     const float4* p4 = reinterpret_cast<const float4*>(part) + q;
@@ -1465,13 +1469,14 @@ static hipError_t finish_product(const GemmParams& p, const GemmArgs& g, hipStre
                          (reinterpret_cast<uintptr_t>(p.c) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.workspace) & 15) == 0;
         const unsigned blocks = (unsigned)(((vec ? total / 4 : total) + 255) / 256);
         const ColumnSumTail t = tail ? *tail : ColumnSumTail{};
-        const dim3 rgrid(blocks + (t.cols + 31) / 32), rblock(256);
+        const unsigned tail_blocks = (t.cols + 31) / 32;
+        const dim3 rgrid(blocks + tail_blocks), rblock(256);
         if (vec)
             hipLaunchKernelGGL(splitk_reduce4_kernel, rgrid, rblock, 0, st, static_cast<const float*>(p.workspace), g.split_k, g.m, g.n,
-                               p.c, p.ldc, (int)p.c_bf16, p.bias, blocks, t);
+                               p.c, p.ldc, (int)p.c_bf16, p.bias, t, tail_blocks);
         else
             hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, rblock, 0, st, static_cast<const float*>(p.workspace), g.split_k, g.m, g.n,
-                               p.c, p.ldc, (int)p.c_bf16, p.bias, blocks, t);
+                               p.c, p.ldc, (int)p.c_bf16, p.bias, t, tail_blocks);
         return hipGetLastError();
     }
     return tail && tail->cols ? launch_column_sum_finish(*tail, st) : hipSuccess;
