@@ -421,6 +421,46 @@ __device__ __forceinline__ void tile_gelu_quant(const GemmArgs& g, uint8_t* ep, 
     }
 }
 
+// One K step of a wave: its TI x TJ tiles from the staged operands at st; `left` K elements are not multiplied yet.
+template <typename S, int TI, int TJ>
+__device__ __forceinline__ void tile_multiply(const uint8_t* st, uint32_t left, v16f (&acc)[TI][TJ], int wm, int wn, uint32_t lrow, uint32_t lhalf)
+{
+    constexpr int BM = S::BM, BN = S::BN;
+    const uint8_t* pa = st + (wm * (BM / 2) + lrow) * S::PITCH;
+    const uint8_t* pb = st + (BM + wn * (BN / 2) + lrow) * S::PITCH;
+    const uint8_t* sa = st + (BM + BN) * S::PITCH + (wm * (BM / 2) + lrow) * S::SPITCH;
+    const uint8_t* sb = st + (BM + BN) * S::PITCH + (BM + wn * (BN / 2) + lrow) * S::SPITCH;
+    static_for<0, S::KS / 128>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        if (d * 128u >= left) return;                              // uniform: whole 128-K blocks past the end are skipped
+        uint32_t ua[TI], ub[TJ];
+#pragma unroll
+        for (int i = 0; i < TI; ++i) ua[i] = *reinterpret_cast<const uint32_t*>(sa + i * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) ub[j] = *reinterpret_cast<const uint32_t*>(sb + j * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
+        static_for<0, 2>([&](auto kc) {
+            constexpr int kk = decltype(kc)::value;
+            v4i fa[TI], fb[TJ];
+            const uint32_t col = S::column(lrow, 4 * d + 2 * kk + lhalf);
+#pragma unroll
+            for (int i = 0; i < TI; ++i) fa[i] = *reinterpret_cast<const v4i*>(pa + i * 32 * S::PITCH + col);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) fb[j] = *reinterpret_cast<const v4i*>(pb + j * 32 * S::PITCH + col);
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const v8i xa = v8i{fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0};
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) {
+                    const v8i xb = v8i{fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0};
+                    // first operand = n side, second = m side: a lane ends up with one m and runs of 4 n
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        xb, xa, acc[i][j], 4, 4, 2 * kk, (int)ub[j], 2 * kk, (int)ua[i]);
+                }
+            }
+        });
+    });
+}
+
 template <typename S, bool GELUQ>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t block, uint8_t* lds)
 {
@@ -505,42 +545,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto compute = [&](const uint8_t* st, uint32_t k0) {
-        const uint8_t* pa = st + (wm * (BM / 2) + lrow) * S::PITCH;
-        const uint8_t* pb = st + (BM + wn * (BN / 2) + lrow) * S::PITCH;
-        const uint8_t* sa = st + (BM + BN) * S::PITCH + (wm * (BM / 2) + lrow) * S::SPITCH;
-        const uint8_t* sb = st + (BM + BN) * S::PITCH + (BM + wn * (BN / 2) + lrow) * S::SPITCH;
-        static_for<0, DPR>([&](auto dc) {
-            constexpr int d = decltype(dc)::value;
-            if (k0 + d * 128 >= kend) return;                      // uniform: whole 128-K blocks past the end are skipped
-            uint32_t ua[TI], ub[TJ];
-#pragma unroll
-            for (int i = 0; i < TI; ++i) ua[i] = *reinterpret_cast<const uint32_t*>(sa + i * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) ub[j] = *reinterpret_cast<const uint32_t*>(sb + j * 32 * S::SPITCH + d * 4) >> 8 * lhalf;
-            static_for<0, 2>([&](auto kc) {
-                constexpr int kk = decltype(kc)::value;
-                v4i fa[TI], fb[TJ];
-                const uint32_t col = S::column(lrow, 4 * d + 2 * kk + lhalf);
-#pragma unroll
-                for (int i = 0; i < TI; ++i) fa[i] = *reinterpret_cast<const v4i*>(pa + i * 32 * S::PITCH + col);
-#pragma unroll
-                for (int j = 0; j < TJ; ++j) fb[j] = *reinterpret_cast<const v4i*>(pb + j * 32 * S::PITCH + col);
-#pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const v8i xa = v8i{fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0};
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j) {
-                        const v8i xb = v8i{fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0};
-                        // first operand = n side, second = m side: a lane ends up with one m and runs of 4 n
-                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            xb, xa, acc[i][j], 4, 4, 2 * kk, (int)ub[j], 2 * kk, (int)ua[i]);
-                    }
-                }
-            });
-        });
-    };
-
     gload(kbeg);
     lstore(lds);
     __syncthreads();
@@ -548,7 +552,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     for (uint32_t k0 = kbeg; k0 < kend; k0 += KS) {
         const bool more = S::STAGES > 1 && k0 + KS < kend;
         if (more) gload(k0 + KS);
-        compute(lds + cur, k0);
+        tile_multiply<S>(lds + cur, kend - k0, acc, wm, wn, lrow, lhalf);
         if (S::STAGES > 1) cur = cur ? 0u : (uint32_t)S::STAGE;
         if (more) lstore(lds + cur);
         __syncthreads();
@@ -585,6 +589,101 @@ __global__ __launch_bounds__(T_NT, S0::OCC < S1::OCC ? S0::OCC : S1::OCC) void m
     __shared__ __attribute__((aligned(16))) uint8_t lds[S0::LDS > S1::LDS ? S0::LDS : S1::LDS];
     if (blockIdx.x >= blocks0)                                                               gemm_tile<S1, false>(g1, blockIdx.x - blocks0, lds);
     else if (blockIdx.x < g0.tiles_m * g0.tiles_n * (uint32_t)g0.split_k)                    gemm_tile<S0, false>(g0, blockIdx.x, lds);
+}
+
+// Y = Q1(X) Q2(W)^T + bias of a small layer where nothing else needs the codes (a forward pass without gradients), in one
+// launch: each workgroup quantizes the 64 rows of X and of W that its tile needs straight into the LDS stages, 256 columns at
+// a time, with the next step's sources in flight.  Rows are quantized once per tile that needs them, which costs less than
+// the launch, the codes' way through memory and the wait between two kernels as long as there are few tiles and K is short
+// (the rule stands at linear_fits_one_launch).  The codes, and the order of every sum, are those of the separate kernels.
+struct QuantizedLinearArgs {
+    const void* x;
+    const void* w;
+    const void* bias;          // n values or null
+    int bias_bf16;
+    GemmArgs g;                // sizes and output
+};
+
+constexpr int QL_NT = 512;     // eight waves quantize, the first four multiply
+
+template <typename XT, typename WT, bool FLOOR>
+__global__ __launch_bounds__(QL_NT, 2) void mx_quantized_linear_kernel(QuantizedLinearArgs a)
+{
+    using S = TileShape<64, 64, 256, 2>;
+    constexpr int CPR = S::KS / 8, RPP = QL_NT / CPR, ROWS = 64 / RPP;      // 8-element chunks per row, rows per pass, passes
+    __shared__ __attribute__((aligned(16))) uint8_t lds[S::LDS];
+    const GemmArgs& g = a.g;
+    uint32_t zsplit, tm, tn;
+    decode_tile(g, blockIdx.x, zsplit, tm, tn);
+    const uint32_t m0 = tm * 64, n0 = tn * 64, k = g.k;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) & 1, wn = wave & 1;
+    const uint32_t lrow = lane & 31, lhalf = lane >> 5;
+    const uint32_t c = tid % CPR, r0 = tid / CPR;
+    const uint32_t mlast = g.m - 1 - m0, nlast = g.n - 1 - n0;
+    const XT* x = static_cast<const XT*>(a.x) + (size_t)m0 * k;
+    const WT* w = static_cast<const WT*>(a.w) + (size_t)n0 * k;
+
+    mxd::Raw8<XT> xr[ROWS];
+    mxd::Raw8<WT> wr[ROWS];
+    auto load = [&](uint32_t k0) {
+        const uint32_t col = k0 + c * 8;                                   // whole groups lie inside or past K
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            xr[u] = mxd::Raw8<XT>{};
+            wr[u] = mxd::Raw8<WT>{};
+            if (col < k) {
+                xr[u] = mxd::load_raw8_shared(x + (size_t)min(r0 + u * RPP, mlast) * k + col);
+                wr[u] = mxd::load_raw8_shared(w + (size_t)min(r0 + u * RPP, nlast) * k + col);
+            }
+        }
+    };
+    auto encode = [&](uint8_t* st) {
+        auto put = [&](const auto& raw, uint32_t row) {
+            const uint32_t byte = mxd::row_scale_byte<FLOOR>(raw);
+            *reinterpret_cast<uint32_t*>(st + row * S::PITCH + S::column(row, c >> 2) + (c & 3) * 4) = mxd::rtn_codes8(raw, byte);
+            if ((c & 3) == 0) st[128 * S::PITCH + row * S::SPITCH + (c >> 2)] = (uint8_t)byte;
+        };
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            put(xr[u], r0 + u * RPP);
+            put(wr[u], 64 + r0 + u * RPP);
+        }
+    };
+
+    v16f acc[1][1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+    load(0);
+    encode(lds);
+    __syncthreads();
+    uint32_t cur = 0;
+    for (uint32_t k0 = 0; k0 < k; k0 += S::KS) {
+        const bool more = k0 + S::KS < k;
+        if (more) load(k0 + S::KS);
+        if (wave < 4) tile_multiply<S>(lds + cur, k - k0, acc, wm, wn, lrow, lhalf);
+        cur = cur ? 0u : (uint32_t)S::STAGE;
+        if (more) encode(lds + cur);
+        __syncthreads();
+    }
+    if (wave >= 4) return;
+    const uint32_t nbase = n0 + wn * 32;
+    if (a.bias != nullptr && nbase < g.n) {                                // n % 32 == 0
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t col = nbase + 8 * q + 4 * lhalf;
+            if (a.bias_bf16) {
+                const uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(a.bias) + col);
+                acc[0][0][4 * q] += __uint_as_float(v.x << 16);     acc[0][0][4 * q + 1] += __uint_as_float(v.x & 0xFFFF0000u);
+                acc[0][0][4 * q + 2] += __uint_as_float(v.y << 16); acc[0][0][4 * q + 3] += __uint_as_float(v.y & 0xFFFF0000u);
+            } else {
+                const v4f v = *reinterpret_cast<const v4f*>(static_cast<const float*>(a.bias) + col);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[0][0][4 * q + r] += v[r];
+            }
+        }
+    }
+    tile_epilogue<1, 1, true>(g, lds + wave * 32 * S::EP_PITCH, acc, m0 + wm * 32, nbase, 0);
 }
 
 // Sum the split-K partials in a fixed order and write the final output.
@@ -1521,6 +1620,42 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? finish_product(p, g, st, tail) : e;
+}
+
+// One tile per compute unit and two K steps at most.  Times of one MxLinear call without gradients, in a replayed graph and
+// called one after the other (host-bound), separate kernels / this one, in us:
+//   197 x 192 -> 768   6.5 / 5.3   10.0 / 6.8     2000 x 256 -> 512 FP32   6.5 / 6.1   10.5 / 6.6
+//   512 x 384 -> 384   6.2 / 7.0   10.0 / 6.8     1576 x 384 -> 384        6.4 / 7.3   10.4 / 7.2
+//   197 x 768 -> 768   7.2 / 9.5   10.3 / 9.2     3152 x 192 -> 576        7.2 / 8.6   10.5 / 8.4 (450 tiles)
+// Beyond 256 columns a step costs 1.8 us (a unit quantizes 128 x 256 values for it), so up to 512 the call is faster by
+// what the host saves only, and not beyond.  Steps of 512 columns take as long.
+bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k)
+{
+    return ((m + 63) / 64) * ((n + 63) / 64) <= 256 && k <= 512;
+}
+
+hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t st)
+{
+    QuantizedLinearArgs a{};
+    a.x = p.x; a.w = p.w; a.bias = p.bias; a.bias_bf16 = p.bias_bf16;
+    a.g.m = (uint32_t)p.m; a.g.n = (uint32_t)p.n; a.g.k = (uint32_t)p.k;
+    a.g.split_k = 1; a.g.k_per_split = a.g.k;
+    a.g.c = p.c; a.g.c_bf16 = p.c_bf16; a.g.ldc = p.n;
+    const dim3 grid(tile_grid(a.g, 64, 64)), block(QL_NT);
+    auto launch = [&](auto x, auto w) {
+        using XT = decltype(x);
+        using WT = decltype(w);
+        if (p.floor_mode) hipLaunchKernelGGL((mx_quantized_linear_kernel<XT, WT, true>), grid, block, 0, st, a);
+        else              hipLaunchKernelGGL((mx_quantized_linear_kernel<XT, WT, false>), grid, block, 0, st, a);
+    };
+    if (p.x_bf16) {
+        if (p.w_bf16) launch(uint16_t{}, uint16_t{});
+        else          launch(uint16_t{}, float{});
+    } else {
+        if (p.w_bf16) launch(float{}, uint16_t{});
+        else          launch(float{}, float{});
+    }
+    return hipGetLastError();
 }
 
 // Two independent products of a backward pass, w and x, in one launch where both run on tile kernels and have a workspace

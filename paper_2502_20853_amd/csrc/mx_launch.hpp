@@ -200,6 +200,19 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 int gemm_split_k(int64_t m, int64_t n, int64_t k);
 // tail: column sums to finish as well (in the K split's reduction where there is one, else in a launch of their own).
 hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail = nullptr);
+// C[m x n] = Q(x[m x k]) . Q(w[n x k])^T + bias with round_D row quantizers, in one launch that keeps no codes; dense rows,
+// 16-byte aligned x, w and bias, n and k multiples of 32.  Worth it, and allowed, where linear_fits_one_launch says so.
+struct QuantizedLinearParams {
+    const void* x;
+    const void* w;
+    const void* bias;          // n values or null
+    bool x_bf16, w_bf16, bias_bf16, floor_mode;
+    int64_t m, n, k;
+    void* c;
+    bool c_bf16;
+};
+bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k);
+hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t st);
 // Two independent products, in one launch where that pays; the results of launch_gemm(x) and launch_gemm(w, tail), bit for bit.
 hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail = nullptr);
 

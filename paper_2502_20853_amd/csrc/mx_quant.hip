@@ -55,47 +55,7 @@ __device__ __forceinline__ void set_round_mode_for()
     else    f32_round_toward_minus_inf();
 }
 
-// Eight source elements of one row, as loaded: bf16 values stay packed in pairs.
-template <typename SrcT> using Raw8 = std::conditional_t<std::is_same_v<SrcT, float>, F8, bf16x8_raw>;
-
-__device__ __forceinline__ F8 load_raw8(const float* p) { return load8(p); }
-__device__ __forceinline__ bf16x8_raw load_raw8(const uint16_t* p) { return load8_raw(p); }
-
-__device__ __forceinline__ float element_of(const F8& r, int t) { return r.v[t]; }
-__device__ __forceinline__ float element_of(const bf16x8_raw& r, int t)
-{
-    return __uint_as_float((t & 1) ? r[t >> 1] & 0xFFFF0000u : r[t >> 1] << 16);
-}
-
-__device__ __forceinline__ uint32_t abs_max_bf16(const bf16x8_raw& x)                 // two partial maxima
-{
-    const uint32_t k = 0x7FFF7FFFu;
-    return pk_max(pk_max(x[0] & k, x[1] & k), pk_max(x[2] & k, x[3] & k));
-}
-
-// Scale byte of a row group from the lane's own eight elements.
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t row_scale_byte(const F8& x) { return scale_byte(quad_max(amax_bits8(x)), FLOOR); }
-template <bool FLOOR>
-__device__ __forceinline__ uint32_t row_scale_byte(const bf16x8_raw& x)
-{
-    const uint32_t m = abs_max_bf16(x);
-    return scale_bytes_bf16<FLOOR>(quad_amax_bf16_rows(m, m)) & 0xFFFFu;
-}
-
-// Codes of eight elements of a row, low nibble first.  SR: with sr_terms() of the block, in the rounding mode of round_S.
-__device__ __forceinline__ uint32_t rtn_codes8(const bf16x8_raw& x, uint32_t byte)
-{
-    const float s = scale_operand(byte);
-    const uint32_t first = ties_to_larger(x[0]);
-    uint32_t p = cvt_fp4_bf16<0>(first, first, s);
-    p = cvt_fp4_bf16<1>(p, ties_to_larger(x[1]), s);
-    p = cvt_fp4_bf16<2>(p, ties_to_larger(x[2]), s);
-    return cvt_fp4_bf16<3>(p, ties_to_larger(x[3]), s);
-}
-
-__device__ __forceinline__ uint32_t rtn_codes8(const F8& x, uint32_t byte) { return rtn_codes8_f32(x.v, byte); }
-
+// round_S codes of eight elements of a row, low nibble first, with sr_terms() of the block, in the rounding mode of round_S.
 template <bool FLOOR, typename RAW>
 __device__ __forceinline__ uint32_t sr_codes8(const RAW& x, uint32_t byte, const U8& rnd)
 {

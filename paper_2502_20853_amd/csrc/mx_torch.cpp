@@ -209,6 +209,15 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
     const int64_t Np = saved ? padded_rows(N) : N;
     hipStream_t st = c10::hip::getCurrentHIPStream(x.get_device()).stream();
 
+    if (!saved && !w_ema && mxl::linear_fits_one_launch(N, C, D)) {
+        Tensor b, y = at::empty(with_last(x_in.sizes(), C), x.options());
+        if (bias) b = dense_source(is_f32_or_bf16(bias->scalar_type()) ? *bias : bias->to(at::kFloat));
+        const mxl::QuantizedLinearParams p{x.data_ptr(), w.data_ptr(), bias ? b.data_ptr() : nullptr, is_bf16(x), is_bf16(w), bias && is_bf16(b), o.floor_mode,
+                                           N, C, D, y.data_ptr(), is_bf16(y)};
+        check_hip(mxl::launch_quantized_linear(p, st), "mx_linear_fwd");
+        return y;
+    }
+
     Carver t;
     const int64_t o_xq = t.codes(Np, D), o_xs = t.scales(Np, D), o_wq = t.codes(C, D), o_ws = t.scales(C, D), o_b = t.take(C * 4);
     Tensor row = bytes_like(x, t.used), keep;

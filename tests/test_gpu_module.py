@@ -349,6 +349,10 @@ def test_saved_operands_through_hooks(mx):
 
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("tokens,D,C,xt,wt", [(1, 32, 32, "f32", "bf16"), (33, 160, 96, "bf16", "f32"), (257, 96, 2080, "bf16", "bf16"),
+                                              # one launch: one K step, two, a ragged second one; the last sizes that it
+                                              # takes, and one more row of tiles, one more group of columns
+                                              (64, 256, 64, "f32", "f32"), (65, 288, 96, "bf16", "f32"), (3, 512, 64, "f32", "bf16"),
+                                              (1000, 512, 1024, "bf16", "bf16"), (1025, 512, 1024, "bf16", "f32"), (130, 544, 64, "bf16", "bf16"),
                                               # more chunks than one per lane of the row kernel's grid covers
                                               (8200, 1056, 96, "bf16", "f32"), (2113, 4128, 64, "f32", "f32")])
 def test_forward_without_gradients_equals_the_one_with(mx, mode, tokens, D, C, xt, wt):
