@@ -1468,6 +1468,8 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 //   main kernel: enough 256 x 256 tiles to occupy half the compute units (12672 x 768 x 768: 10.6 against 11.8 on
 //     128 x 128 tiles, 25216 x 1536 x 3072: 79 against 131), or enough work for a K split of them
 //     (768 x 768 x 50432: 36 against 42 and 46; at 1.5e10 multiply-adds it is even, 768 x 768 x 25216: 29 and 29).
+//     Not where K is short and its second round would be less than a quarter full (25216 x 768 x 512: 16.4 against 15.3 on
+//     128 x 128 tiles, 9856 x 2048 x 512 16.5 / 14.7, 6304 x 3072 x 768 19.7 / 19.0; 25216 x 768 x 1024 22.6 / 22.5).
 //   64 x 64 tiles: up to one tile per compute unit (224 x 192 x 768: 4.1 against 6.6 on 128 x 128 and 8.0 on the
 //     main kernel), with a K split up to two per unit (768 x 192 x 12672: 11 against 13 and 18).
 //   128 x 64 tiles: up to three per unit (9856 x 384 x 1536: 9.4 against 11.3 and 12.3).
@@ -1495,6 +1497,7 @@ static GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k)
     };
     const int64_t t256 = tiles(Q_BM, Q_BN), t12864 = tiles(128, 64), t64 = tiles(64, 64);
     const bool main_ok = (k & 127) == 0 && k >= 512;
+    if (main_ok && k <= 768 && t256 > (int64_t)Q_SLOTS && t256 * 100 < 2 * (int64_t)Q_SLOTS * 62) return {GemmKernel::tile128, 1};
     if (main_ok && (t256 >= 128 || mn * (double)k >= 1.6e10))
         return {GemmKernel::pingpong, t256 * 2 <= 256 ? splits(256, t256, 60.0, 1024) : 1};
     if (t64 <= (k >= 4096 ? 512 : 256)) return {GemmKernel::tile64, splits(512, t64, 24.0, 1024)};
@@ -1517,15 +1520,17 @@ bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k)
 // any number of tiles up to one per compute unit, because both wave groups of a unit go through the stage at once; with
 // 64 x 64 tiles up to two rounds of 512 take 9-13 us, with 128 x 128 tiles waves of three workgroups share a unit and one
 // multiplies while another is in the stage.  Main kernel / 128 x 128 / 64 x 64 tiles in us (m x n x k):
-//   224x3072x768 24 13 9    1312x3072x1024 26 19 15    2048x3072x1024 26 19.9 20.4    6304x3072x1024 52 41 -
-//   33000x1024x1024 71 64   6304x3072x2048 64 57       12608x1024x512 26 30           25216x3072x768 116 123
-//   3136x3072x3072 39 49    25216x3072x3072 216 300
-// 128 x 128 tiles win where the main kernel's rounds of 256 tiles would be filled to less than 70 % and K is not long.
+//   224x3072x768 24 13 9    1312x3072x1024 26 19 15    2048x3072x1024 26 19.9 20.4    6304x3072x1024 53 38 -
+//   25216x2048x640 91 73    12608x3072x768 72 61       25216x3072x768 127 125         50432x3072x768 229 220
+//   40000x1024x896 76 63    25216x3072x1024 126 129    8000x1536x1024 28.6 27.5       25216x3072x2048 162 196
+//   6304x3072x2048 64 57    3136x3072x3072 39 49
+// 128 x 128 tiles win up to K = 896, beyond that where the main kernel's rounds of 256 tiles would be filled to less than
+// 70 % and K is not long.
 static GemmKernel plan_fused(int64_t m, int64_t n, int64_t k)
 {
     if (((m + 63) / 64) * ((n + 63) / 64) <= 1024) return GemmKernel::tile64;
     const int64_t t256 = ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN), rounds = (t256 + Q_SLOTS - 1) / Q_SLOTS;
-    return k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7 ? GemmKernel::tile128 : GemmKernel::pingpong;
+    return k <= 896 || (k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7) ? GemmKernel::tile128 : GemmKernel::pingpong;
 }
 
 // Kernel arguments of a product and the kernel that it runs on; the tile counts are filled in by tile_grid().

@@ -82,6 +82,8 @@ def test_sweep_products(mx, orc):
     (12801, 452, 256), (12801, 452, 288), (4163, 1570, 352),
     # the main kernel from 128 tiles of 256 x 256 on (ragged edges, shifted last scale block)
     (32765, 250, 640), (32641, 36, 512), (8200, 1028, 1152),
+    # short K, a second round of 256 x 256 tiles that is less than a quarter full: 128 x 128 tiles; one more K step
+    (8450, 2044, 768), (8450, 2044, 896),
     # K splits of the 64 x 64 and 128 x 64 tiles (uneven, ragged K), and of the main kernel
     (100, 132, 4128), (192, 768, 12608), (1100, 2080, 8224), (516, 764, 41088)])
 def test_products_at_the_lines_between_kernels(mx, orc, m, n, k):
@@ -100,8 +102,8 @@ def test_products_at_the_lines_between_kernels(mx, orc, m, n, k):
     (1, 32, 512), (33, 544, 640), (1000, 4096, 512),
     # 128 x 128 tiles: one row of tiles more, edges in rows and columns (scale rows of odd length)
     (1025, 4096, 512), (1632, 2720, 512),
-    # the main kernel, edges in rows and columns
-    (4063, 3040, 512), (4100, 1120, 2176)])
+    # the same up to K = 896 whatever their number, then the main kernel, edges in rows and columns
+    (4063, 3040, 512), (4063, 3040, 896), (4063, 3040, 1024), (4100, 1120, 2176)])
 def test_fused_gelu_at_the_lines_between_kernels(mx, orc, m, n, k):
     """The pre-activation is what mx_linear_fwd_bias stores, and the codes are round_D of GELU of it: every kernel of the
     fused stage takes the FP32 sum, so dequantized values differ from the oracle's only next to a threshold
