@@ -19,7 +19,7 @@
 // Work split: one launch serves up to 32 (in a detection window 24) tensors, whose addresses travel in the kernel's
 // arguments; a ViT's step is then 2 to 5 launches instead of one to four per parameter (ViT-Tiny, 144 parameters:
 // 240 launches of 3-5 us each for 5.3 M elements).  A lane owns 4 consecutive elements (16-byte accesses on every
-// array), in a detection window 8, a quarter of a 1x32 group.
+// array), in a detection window two times 4; eight lanes there hold a 1x32 group.
 //
 // Bytes per element: 28 read + 16 written where no gradient is held.  The held sum is read only by lanes whose step
 // count is not zero (the two are zero together, an element's update clears both), and sum and count are written only
@@ -214,42 +214,35 @@ struct WindowBatch {
     uint32_t grad_bf16;
     int opens;
     uint32_t end[WINDOW_BATCH];
-    uint32_t chunks[WINDOW_BATCH];      // count / 8
+    uint32_t quads[WINDOW_BATCH];       // count / 4, a multiple of 8
     mxl::WindowTensor t[WINDOW_BATCH];
 };
 
-// round_D codes of 8 elements of a group and the group's scale byte
+// round_D codes (16 bits) of a lane's 4 elements of a group of 8 lanes, and the group's scale byte
 template <bool FLOOR>
-__device__ __forceinline__ uint32_t rtn_codes8(const float (&x)[8], uint32_t& byte)
+__device__ __forceinline__ uint32_t rtn_codes4(const v4f& x, uint32_t& byte)
 {
     using namespace mxd;
-    F8 f;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) f.v[t] = x[t];
-    byte = scale_byte(quad_max(amax_bits8(f)), FLOOR);
-    return rtn_codes8_f32(x, byte);
+    uint32_t m = quad_max(absmax3_bits(x.x, x.y, absmax3_bits(x.z, x.w, 0u)));
+    const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x141, 0xF, 0xF, true);      // row_half_mirror: the other four lanes
+    m = m > other ? m : other;
+    byte = scale_byte(m, FLOOR);
+    const float s = scale_operand(byte);
+    return cvt_rtn_f32<1>(cvt_rtn_f32<0>(x.x, x.y, s), x.z, x.w, s) & 0xFFFFu;
 }
 
-__device__ __forceinline__ void dequantize8(uint32_t codes, uint32_t byte, float (&x)[8])
+__device__ __forceinline__ v4f dequantize4(uint32_t codes, uint32_t byte)
 {
     using namespace mxd;
     const float s = scale_operand(byte);
-    const f32x2_hw a = cvt_f32_fp4<0>(codes, s), b = cvt_f32_fp4<1>(codes, s), c = cvt_f32_fp4<2>(codes, s), d = cvt_f32_fp4<3>(codes, s);
-    x[0] = a.x; x[1] = a.y; x[2] = b.x; x[3] = b.y; x[4] = c.x; x[5] = c.y; x[6] = d.x; x[7] = d.y;
+    const f32x2_hw a = cvt_f32_fp4<0>(codes, s), b = cvt_f32_fp4<1>(codes, s);
+    return v4f{a.x, a.y, b.x, b.y};
 }
 
-__device__ __forceinline__ void load8f(const float* p, uint32_t q, float (&x)[8])
-{
-    const v4f a = load4(p, 2 * (int64_t)q), b = load4(p, 2 * (int64_t)q + 1);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { x[e] = a[e]; x[4 + e] = b[e]; }
-}
-
-__device__ __forceinline__ void store8f(float* p, uint32_t q, const float (&x)[8])
-{
-    store4(p, 2 * (int64_t)q, v4f{x[0], x[1], x[2], x[3]});
-    store4(p, 2 * (int64_t)q + 1, v4f{x[4], x[5], x[6], x[7]});
-}
+// A lane owns two quads of 4 elements, 64 quads apart, so that every access of a wave is one run of 1 KB (64 bytes to 1 KB
+// for the packed arrays).  With 8 neighbouring elements in a lane instead, each instruction takes every other 16 bytes, and
+// streaming loads and stores do not meet in the cache: 2.65 M elements 52 us, 3.1 TB/s; as two quads 33.7 us, 5.1 TB/s.
+constexpr int WINDOW_QUADS = 2;
 
 template <bool FLOOR>
 __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch b)
@@ -259,51 +252,53 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch
     for (int k = 0; k + 1 < WINDOW_BATCH; ++k) i += blockIdx.x >= b.end[k] ? 1u : 0u;
     const mxl::WindowTensor t = b.t[i];
     const AdamHyper& a = b.h;
-    const uint32_t q = (blockIdx.x - (i ? b.end[i - 1] : 0u)) * OPT_THREADS + threadIdx.x;
-    if (q >= b.chunks[i]) return;       // chunks % 4 == 0: the four lanes of a group stay together
+    const uint32_t quads = b.quads[i];
+    const uint32_t q0 = (blockIdx.x - (i ? b.end[i - 1] : 0u)) * (OPT_THREADS * WINDOW_QUADS) + (threadIdx.x & ~63u) * WINDOW_QUADS + (threadIdx.x & 63u);
     // every load before the first store: the arrays could overlap for all the compiler knows, and a wave that waits
-    // for its stores before it loads again reaches half the memory rate
+    // for its stores before it loads again reaches half the memory rate.  Past the end the last quad is read again and
+    // nothing is stored (quads % 8 == 0: the eight lanes of a group stay together).
     const bool has_grad = t.grad != nullptr;            // a weight without a gradient stands still
-    float w[8], prev[8], dw[8], dq[8], wq_prev[8];
-    v4f g[2], m[2], v[2], acc[2];
-    v4i u[2], c[2];
-    uint32_t byte = 0u, codes_prev = 0u;
-    load8f(t.w, q, w);
-    if (has_grad) {
+    constexpr int H = WINDOW_QUADS;
+    v4f w[H], prev[H], dw[H], dq[H], g[H], m[H], v[H], acc[H];
+    v4i u[H], c[H];
+    uint32_t byte[H], codes_prev[H];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t q4 = 2 * (int64_t)q + h;
-            c[h] = load4(t.acc_steps, q4);
-            u[h] = load4(t.updates, q4);
-            g[h] = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q4);
-            m[h] = load4(t.m, q4);
-            v[h] = load4(t.v, q4);
+    for (int h = 0; h < H; ++h) {
+        const int64_t q = min(q0 + 64u * h, quads - 1u);
+        w[h] = load4(t.w, q);
+        if (has_grad) {
+            c[h] = load4(t.acc_steps, q);
+            u[h] = load4(t.updates, q);
+            g[h] = load_grad4(t.grad, (b.grad_bf16 >> i) & 1u, q);
+            m[h] = load4(t.m, q);
+            v[h] = load4(t.v, q);
+        }
+        if (!b.opens) {
+            prev[h] = load4(t.w_prev, q);
+            dw[h] = load4(t.dist_w, q);
+            dq[h] = load4(t.dist_q, q);
+            codes_prev[h] = reinterpret_cast<const uint16_t*>(t.codes_prev)[q];
+            byte[h] = t.scales_prev[q >> 3];
         }
     }
-    if (!b.opens) {
-        load8f(t.w_prev, q, prev);
-        load8f(t.dist_w, q, dw);
-        load8f(t.dist_q, q, dq);
-        codes_prev = reinterpret_cast<const uint32_t*>(t.codes_prev)[q];
-        byte = t.scales_prev[q >> 2];
-    }
     if (has_grad) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
             acc[h] = v4f{0.f, 0.f, 0.f, 0.f};
-            if ((c[h].x | c[h].y | c[h].z | c[h].w) != 0) acc[h] = load4(t.g_acc, 2 * (int64_t)q + h);
+            if ((c[h].x | c[h].y | c[h].z | c[h].w) != 0) acc[h] = load4(t.g_acc, min(q0 + 64u * h, quads - 1u));
         }
     }
-    if (b.opens) {
-        codes_prev = rtn_codes8<FLOOR>(w, byte);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { prev[e] = w[e]; dw[e] = 0.0f; dq[e] = 0.0f; }
-    }
-    dequantize8(codes_prev, byte, wq_prev);
-    if (has_grad) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t q4 = 2 * (int64_t)q + h;
+    for (int h = 0; h < H; ++h) {
+        const uint32_t q = q0 + 64u * h;
+        const bool ok = q < quads;
+        if (b.opens) {
+            codes_prev[h] = rtn_codes4<FLOOR>(w[h], byte[h]);
+            prev[h] = w[h];
+            dw[h] = dq[h] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        const v4f wq_prev = dequantize4(codes_prev[h], byte[h]);
+        if (has_grad) {
             const bool held = (c[h].x | c[h].y | c[h].z | c[h].w) != 0;
             u[h] += 1;
             const bool uniform = uniform_updates(u[h]);
@@ -312,33 +307,36 @@ __global__ __launch_bounds__(OPT_THREADS) void ramping_window_kernel(WindowBatch
             for (int e = 0; e < 4; ++e) {
                 if (!uniform && e > 0) k = step_scale(a, u[h][e], 1);
                 const float gm = held ? __fdiv_rn(acc[h][e] + g[h][e], (float)(c[h][e] + 1)) : 0.0f + g[h][e];
-                float we = w[4 * h + e], me = m[h][e], ve = v[h][e];
+                float we = w[h][e], me = m[h][e], ve = v[h][e];
                 adamw_update(a, we, me, ve, gm, k);
-                w[4 * h + e] = we; m[h][e] = me; v[h][e] = ve;
+                w[h][e] = we; m[h][e] = me; v[h][e] = ve;
             }
-            store4(t.m, q4, m[h]);
-            store4(t.v, q4, v[h]);
-            store4(t.updates, q4, u[h]);
-            if (held) {
-                store4(t.g_acc, q4, v4f{0.f, 0.f, 0.f, 0.f});
-                store4(t.acc_steps, q4, v4i{0, 0, 0, 0});
+            if (ok) {
+                store4(t.m, q, m[h]);
+                store4(t.v, q, v[h]);
+                store4(t.updates, q, u[h]);
+                store4(t.w, q, w[h]);
+                if (held) {
+                    store4(t.g_acc, q, v4f{0.f, 0.f, 0.f, 0.f});
+                    store4(t.acc_steps, q, v4i{0, 0, 0, 0});
+                }
             }
         }
-        store8f(t.w, q, w);
-    }
-    const uint32_t p = rtn_codes8<FLOOR>(w, byte);
-    float wq[8];
-    dequantize8(p, byte, wq);
+        const uint32_t p = rtn_codes4<FLOOR>(w[h], byte[h]);
+        const v4f wq = dequantize4(p, byte[h]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        dw[e] = __fadd_rn(dw[e], __builtin_fabsf(__fsub_rn(w[e], prev[e])));
-        dq[e] = __fadd_rn(dq[e], __builtin_fabsf(__fsub_rn(wq[e], wq_prev[e])));
+        for (int e = 0; e < 4; ++e) {
+            dw[h][e] = __fadd_rn(dw[h][e], __builtin_fabsf(__fsub_rn(w[h][e], prev[h][e])));
+            dq[h][e] = __fadd_rn(dq[h][e], __builtin_fabsf(__fsub_rn(wq[e], wq_prev[e])));
+        }
+        if (ok) {
+            store4(t.w_prev, q, w[h]);
+            store4(t.dist_w, q, dw[h]);
+            store4(t.dist_q, q, dq[h]);
+            reinterpret_cast<uint16_t*>(t.codes_prev)[q] = (uint16_t)p;
+            if ((threadIdx.x & 7) == 0) t.scales_prev[q >> 3] = (uint8_t)byte[h];
+        }
     }
-    store8f(t.w_prev, q, w);
-    store8f(t.dist_w, q, dw);
-    store8f(t.dist_q, q, dq);
-    reinterpret_cast<uint32_t*>(t.codes_prev)[q] = p;
-    if ((threadIdx.x & 3) == 0) t.scales_prev[q >> 2] = (uint8_t)byte;
 }
 
 }  // namespace
@@ -393,9 +391,9 @@ hipError_t launch_ramping_window_batch(const RampingWindowParams& p, const Windo
             b.end[i] = 0xFFFFFFFFu;
             if (i >= n) continue;
             b.t[i] = tensors[at + i];
-            b.chunks[i] = (uint32_t)(counts[at + i] / 8);
+            b.quads[i] = (uint32_t)(counts[at + i] / 4);
             if (grad_bf16[at + i]) b.grad_bf16 |= 1u << i;
-            blocks += (b.chunks[i] + OPT_THREADS - 1) / OPT_THREADS;
+            blocks += (b.quads[i] + OPT_THREADS * WINDOW_QUADS - 1) / (OPT_THREADS * WINDOW_QUADS);
             b.end[i] = blocks;
         }
         if (p.floor_mode) hipLaunchKernelGGL(ramping_window_kernel<true>, dim3(blocks), dim3(OPT_THREADS), 0, st, b);
