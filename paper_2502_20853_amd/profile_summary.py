@@ -120,7 +120,12 @@ def write_step_kernels(out_dir):
              4848: ("dY-type 50432x3072", 50432 * 3072), 1376: ("X-type 50432x768 + weight", 50432 * 768 + 768 * 768),
              4992: ("X-type 50432x3072 + weight", 50432 * 3072 + 768 * 3072),
              1448: ("X-type 50432x768 + weight 2304x768", 50432 * 768 + 2304 * 768),
-             1484: ("X-type 50432x768 + weight 3072x768", 50432 * 768 + 3072 * 768)}
+             1484: ("X-type 50432x768 + weight 3072x768", 50432 * 768 + 3072 * 768),
+             # the same with a last round in whole tiles
+             1182: ("dY-type 50432x768", 50432 * 768), 1218: ("X-type 50432x768 + weight", 50432 * 768 + 768 * 768),
+             1290: ("X-type 50432x768 + weight 2304x768", 50432 * 768 + 2304 * 768),
+             1326: ("X-type 50432x768 + weight 3072x768", 50432 * 768 + 3072 * 768),
+             4872: ("X-type 50432x3072 + weight", 50432 * 3072 + 768 * 3072)}
     qrows = collections.OrderedDict()
     fd, wd = _dispatches(fetch), _dispatches(write)
     for ef, ew in zip(fd, wd):
@@ -251,7 +256,8 @@ def write_valu(out_dir):
         return None
     # grid in units of 512 lanes: two workgroups of 256 lanes, each a 128 x 128 macro tile (or a half of one in the tail)
     known = {1340: ("dy_type", 50432, 768, 0), 3546: ("dy_type", 50432, 2304, 0), 4848: ("dy_type", 50432, 3072, 0),
-             1376: ("x_type", 50432, 768, 768 * 768), 4992: ("x_type", 50432, 3072, 768 * 3072)}
+             1376: ("x_type", 50432, 768, 768 * 768), 4992: ("x_type", 50432, 3072, 768 * 3072),
+             1182: ("dy_type", 50432, 768, 0), 1218: ("x_type", 50432, 768, 768 * 768), 4872: ("x_type", 50432, 3072, 768 * 3072)}
     detail, per, lines = collections.OrderedDict(), {}, []
     for e in _dispatches(path):
         if "quantize_tile_kernel" not in e["name"] or e["grid"] // 512 not in known:
