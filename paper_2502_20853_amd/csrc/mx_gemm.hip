@@ -1627,16 +1627,20 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail*
     return e == hipSuccess ? finish_product(p, g, st, tail) : e;
 }
 
-// One tile per compute unit and two K steps at most.  Times of one MxLinear call without gradients, in a replayed graph and
-// called one after the other (host-bound), separate kernels / this one, in us:
-//   197 x 192 -> 768   6.5 / 5.3   10.0 / 6.8     2000 x 256 -> 512 FP32   6.5 / 6.1   10.5 / 6.6
-//   512 x 384 -> 384   6.2 / 7.0   10.0 / 6.8     1576 x 384 -> 384        6.4 / 7.3   10.4 / 7.2
-//   197 x 768 -> 768   7.2 / 9.5   10.3 / 9.2     3152 x 192 -> 576        7.2 / 8.6   10.5 / 8.4 (450 tiles)
-// Beyond 256 columns a step costs 1.8 us (a unit quantizes 128 x 256 values for it), so up to 512 the call is faster by
-// what the host saves only, and not beyond.  Steps of 512 columns take as long.
-bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k)
+// One tile per compute unit and two K steps at most.  Device time of one MxLinear call without gradients, separate kernels /
+// this one, in a replayed graph, in us (m x k -> n, X / W):
+//   197 x 192 -> 768    bf16 / FP32 6.3 / 5.1    1000 x 256 -> 1024  FP32 / FP32 6.6 / 5.9    32 x 32 -> 64  bf16 / bf16 5.2 / 4.5
+//   512 x 384 -> 384    bf16 / FP32 6.0 / 7.1    2000 x 512 -> 512   bf16 / FP32 6.5 / 7.7    1 x 288 -> 1024 FP32 / FP32 6.3 / 7.3
+//   8192 x 512 -> 64    FP32 / FP32 8.4 / 7.7    16384 x 384 -> 64   bf16 / FP32 8.3 / 7.6    64 x 512 -> 4096 bf16 / bf16 7.4 / 6.9
+// Up to 256 columns it is faster at every size and type (0.67 to 0.94 of the separate kernels' time).  A second K step costs
+// 1.8 us (a unit quantizes 128 x 256 values for it) and loses that, except where the separate quantizer takes long: an X of
+// about 3.5 M elements and more, and a bf16 bias of 3072 values and more, which one workgroup of that launch widens.
+// A call by itself is bound by the host (512 x 384 -> 384: 10.0 us with two launches, 6.8 with one), which a recorded graph
+// leaves behind: only a call that is being captured goes by the device time.
+bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k, bool bias_bf16, bool captured)
 {
-    return ((m + 63) / 64) * ((n + 63) / 64) <= 256 && k <= 512;
+    if (((m + 63) / 64) * ((n + 63) / 64) > 256 || k > 512) return false;
+    return k <= 256 || !captured || m * k >= (7 << 19) || (bias_bf16 && n >= 3072);
 }
 
 hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t st)

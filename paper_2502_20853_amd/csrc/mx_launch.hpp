@@ -211,7 +211,8 @@ struct QuantizedLinearParams {
     void* c;
     bool c_bf16;
 };
-bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k);
+// captured: the stream is recording a graph.  The codes and sums are those of the separate kernels either way.
+bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k, bool bias_bf16, bool captured);
 hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t st);
 // Two independent products, in one launch where that pays; the results of launch_gemm(x) and launch_gemm(w, tail), bit for bit.
 hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail = nullptr);

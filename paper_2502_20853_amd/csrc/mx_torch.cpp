@@ -199,6 +199,17 @@ std::vector<int64_t> with_last(at::IntArrayRef sizes, int64_t last)
 // so that it runs on the main kernel.  Rows past N are zero: they change no group maximum and add nothing to dW.
 int64_t padded_rows(int64_t N) { return round_up(N, N >= 4096 ? 128 : 32); }
 
+// Whether work on the stream is being recorded into a graph.
+bool is_capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();                             // the launches report what is wrong with the stream
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 // Forward pass.  saved: null where no gradient will be asked for -- only the row codes are made then -- or
 // receives the packed transposed operands [xtq | xts | wtq | wts] of the backward pass.
 Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bias, const OptTensor& w_ema, const Layer& o, const Seed& seed,
@@ -209,7 +220,8 @@ Tensor forward_pass(const Tensor& x_in, const Tensor& w_in, const OptTensor& bia
     const int64_t Np = saved ? padded_rows(N) : N;
     hipStream_t st = c10::hip::getCurrentHIPStream(x.get_device()).stream();
 
-    if (!saved && !w_ema && mxl::linear_fits_one_launch(N, C, D)) {
+    const bool captured = !saved && D > 256 && D <= 512 && is_capturing(st);         // where the rule asks for it
+    if (!saved && !w_ema && mxl::linear_fits_one_launch(N, C, D, bias && bias->scalar_type() == at::kBFloat16, captured)) {
         Tensor b, y = at::empty(with_last(x_in.sizes(), C), x.options());
         if (bias) b = dense_source(is_f32_or_bf16(bias->scalar_type()) ? *bias : bias->to(at::kFloat));
         const mxl::QuantizedLinearParams p{x.data_ptr(), w.data_ptr(), bias ? b.data_ptr() : nullptr, is_bf16(x), is_bf16(w), bias && is_bf16(b), o.floor_mode,
@@ -583,6 +595,7 @@ PYBIND11_MODULE(_mx_torch, m)
         mx_error_class = cls.release().ptr();
     });
     m.def("linear", &linear, py::call_guard<py::gil_scoped_release>());
+    m.def("linear_fits_one_launch", &mxl::linear_fits_one_launch);           // the rule, for tests
     m.def("step_forward", &step_forward, py::call_guard<py::gil_scoped_release>());
     m.def("ramping_step", &ramping_step);
     m.def("step_backward", &step_backward, py::call_guard<py::gil_scoped_release>());

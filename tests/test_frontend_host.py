@@ -152,3 +152,15 @@ def test_forward_mode_tangents_are_refused(mx, which, frozen):
                 lin(x)
         with fwd._set_fwd_grad_enabled(False), pytest.raises(RuntimeError, match="runs on the GPU"):     # tangents switched off
             lin(x)
+
+
+def test_one_launch_where_it_is_not_slower(mx):
+    """A second K step costs device time: a call that is recorded into a graph takes it only where the separate kernels take longer."""
+    fits = mx.binding.host().linear_fits_one_launch
+    for captured in (False, True):
+        assert fits(197, 768, 192, True, captured) and fits(1, 1024, 256, False, captured) and fits(16384, 64, 256, False, captured)
+        assert not fits(197, 768, 544, True, captured) and not fits(16385, 64, 256, False, captured)
+    for m, n, k in ((1, 1024, 288), (512, 384, 384), (1576, 384, 384), (2000, 512, 512), (7168, 64, 480)):
+        assert fits(m, n, k, False, False) and not fits(m, n, k, False, True)
+    assert fits(7168, 64, 512, False, True) and fits(16384, 64, 288, False, True)            # an X of 3.5 M elements
+    assert fits(64, 3072, 512, True, True) and not fits(64, 3072, 512, False, True) and not fits(64, 3040, 512, True, True)

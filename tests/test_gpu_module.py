@@ -426,3 +426,34 @@ def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):
     assert torch.equal(gx, dx)
     if n % 128 == 0 or n < 4096:                        # otherwise the module's dW sums over more rows, in another order
         assert torch.equal(gw, dw.to(dtype))
+
+
+def _kernels_of(graph):
+    """Nodes of a recorded graph, through the HIP library that this process has loaded."""
+    import ctypes
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    count = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("tokens,D,C,nodes", [(197, 256, 96, 1), (197, 288, 96, 2), (1000, 512, 1024, 2), (7168, 512, 64, 1), (33, 384, 3072, 1)])
+def test_forward_recorded_into_a_graph(mx, tokens, D, C, nodes):
+    """Beyond 256 columns a recorded call runs the separate kernels where they take less device time; every replay gives what the
+    eager call gives for the values that the input then holds."""
+    torch.manual_seed(D)
+    lin = mx.MxLinear(D, C, dtype=torch.bfloat16, seed=1, layer_id=1)
+    x = torch.randn(tokens, D, device="cuda").bfloat16()
+    with torch.no_grad():
+        lin.bias.normal_()
+        lin(x)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            y = lin(x)
+        assert _kernels_of(graph) == nodes
+        for _ in range(3):
+            x.copy_(torch.randn(tokens, D, device="cuda").mul_(torch.randn(tokens, 1, device="cuda").exp_()))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, lin(x))
