@@ -1521,16 +1521,34 @@ bool gemm_takes_fused_quantizer(int64_t m, int64_t n, int64_t k)
 // 64 x 64 tiles up to two rounds of 512 take 9-13 us, with 128 x 128 tiles waves of three workgroups share a unit and one
 // multiplies while another is in the stage.  Main kernel / 128 x 128 / 64 x 64 tiles in us (m x n x k):
 //   224x3072x768 24 13 9    1312x3072x1024 26 19 15    2048x3072x1024 26 19.9 20.4    6304x3072x1024 53 38 -
-//   25216x2048x640 91 73    12608x3072x768 72 61       25216x3072x768 127 125         50432x3072x768 229 220
+//   25216x2048x640 93 75    25216x3072x768 120 110     50432x3072x768 229 220         25216x1280x896 57 56
 //   40000x1024x896 76 63    25216x3072x1024 126 129    8000x1536x1024 28.6 27.5       25216x3072x2048 162 196
 //   6304x3072x2048 64 57    3136x3072x3072 39 49
-// 128 x 128 tiles win up to K = 896, beyond that where the main kernel's rounds of 256 tiles would be filled to less than
-// 70 % and K is not long.
+// and where one round of the main kernel holds all tiles and is well filled (medians of 13 such sizes: 1.00 at K = 512, 1.02
+// at 640, 1.04 at 768, 1.06 at 896):
+//   12608x1024x512 25.5 25.1    8192x2048x512 27.1 27.5    4096x4096x640 29.1 29.1    8192x2048x640 28.5 29.3
+//   12608x1024x768 27.1 28.1    6400x2560x768 29.6 31.3    16384x1024x896 30.7 32.7   5120x3072x896 29.9 32.1
+// 128 x 128 tiles win where the main kernel's rounds of 256 tiles would be filled to less than 70 % and K is not long, and
+// up to K = 896 wherever there is more than one round; with one, it is even up to K = 640 and the main kernel wins beyond.
 static GemmKernel plan_fused(int64_t m, int64_t n, int64_t k)
 {
     if (((m + 63) / 64) * ((n + 63) / 64) <= 1024) return GemmKernel::tile64;
     const int64_t t256 = ((m + Q_BM - 1) / Q_BM) * ((n + Q_BN - 1) / Q_BN), rounds = (t256 + Q_SLOTS - 1) / Q_SLOTS;
-    return k <= 896 || (k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7) ? GemmKernel::tile128 : GemmKernel::pingpong;
+    if (k <= 2048 && t256 * 10 < rounds * Q_SLOTS * 7) return GemmKernel::tile128;
+    return k <= (rounds > 1 ? 896 : 640) ? GemmKernel::tile128 : GemmKernel::pingpong;
+}
+
+const char* gemm_kernel_name(int64_t m, int64_t n, int64_t k, bool fused)
+{
+    if (fused && !gemm_takes_fused_quantizer(m, n, k)) return "none";
+    switch (fused ? plan_fused(m, n, k) : plan_gemm(m, n, k).kernel) {
+    case GemmKernel::pingpong: return "main";
+    case GemmKernel::tile128: return "128x128";
+    case GemmKernel::tile128_short: return "128x128 in one step";
+    case GemmKernel::tile128x64: return "128x64";
+    case GemmKernel::tile64: return "64x64";
+    }
+    return "none";
 }
 
 // Kernel arguments of a product and the kernel that it runs on; the tile counts are filled in by tile_grid().

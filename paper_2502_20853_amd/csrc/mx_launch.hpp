@@ -198,6 +198,8 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 
 // Number of K-splits the product will use for these sizes (1 = none).
 int gemm_split_k(int64_t m, int64_t n, int64_t k);
+// Kernel that a product, or one with the fused output quantizer, is planned on (for tests of the rules).
+const char* gemm_kernel_name(int64_t m, int64_t n, int64_t k, bool fused);
 // tail: column sums to finish as well (in the K split's reduction where there is one, else in a launch of their own).
 hipError_t launch_gemm(const GemmParams& p, hipStream_t st, const ColumnSumTail* tail = nullptr);
 // C[m x n] = Q(x[m x k]) . Q(w[n x k])^T + bias with round_D row quantizers, in one launch that keeps no codes; dense rows,

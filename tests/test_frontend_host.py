@@ -164,3 +164,17 @@ def test_one_launch_where_it_is_not_slower(mx):
         assert fits(m, n, k, False, False) and not fits(m, n, k, False, True)
     assert fits(7168, 64, 512, False, True) and fits(16384, 64, 288, False, True)            # an X of 3.5 M elements
     assert fits(64, 3072, 512, True, True) and not fits(64, 3072, 512, False, True) and not fits(64, 3040, 512, True, True)
+
+
+def test_kernel_of_the_fused_gelu_stage(mx):
+    """128 x 128 tiles beyond one round of the main kernel's tiles up to K = 896; where one round holds them all, up to K = 640 and
+    in rounds filled to less than 70 %."""
+    kernel = lambda m, n, k: mx.binding.host().gemm_kernel_name(m, n, k, True)
+    for k in (768, 896):
+        assert kernel(12608, 1024, k) == kernel(8192, 2048, k) == kernel(4096, 4096, k) == "main"
+        assert kernel(11520, 1024, k) == "main" and kernel(11264, 1024, k) == "128x128"          # 180 and 176 of 256
+        assert kernel(16640, 1024, k) == kernel(32768, 1024, k) == kernel(25216, 3072, k) == "128x128"
+    for k in (512, 640):
+        assert kernel(12608, 1024, k) == kernel(8192, 2048, k) == kernel(25216, 3072, k) == "128x128"
+    assert kernel(25216, 3072, 1024) == kernel(25216, 3072, 4096) == "main" and kernel(16640, 1024, 2048) == "128x128"
+    assert kernel(1024, 4096, 896) == "64x64"

@@ -102,8 +102,9 @@ def test_products_at_the_lines_between_kernels(mx, orc, m, n, k):
     (1, 32, 512), (33, 544, 640), (1000, 4096, 512),
     # 128 x 128 tiles: one row of tiles more, edges in rows and columns (scale rows of odd length)
     (1025, 4096, 512), (1632, 2720, 512),
-    # the same up to K = 896 whatever their number, then the main kernel, edges in rows and columns
-    (4063, 3040, 512), (4063, 3040, 896), (4063, 3040, 1024), (4100, 1120, 2176)])
+    # one well-filled round of the main kernel's tiles: 128 x 128 up to K = 640, the main kernel beyond; more than one round:
+    # 128 x 128 up to K = 896.  Edges in rows and columns
+    (4063, 3040, 512), (4063, 3040, 896), (4063, 3040, 1024), (4100, 1120, 2176), (4063, 3040, 768), (5700, 3040, 896)])
 def test_fused_gelu_at_the_lines_between_kernels(mx, orc, m, n, k):
     """The pre-activation is what mx_linear_fwd_bias stores, and the codes are round_D of GELU of it: every kernel of the
     fused stage takes the FP32 sum, so dequantized values differ from the oracle's only next to a threshold
