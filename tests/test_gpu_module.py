@@ -400,14 +400,7 @@ def test_module_with_the_floor_scale_rule(mx, flow, xt, wt):
     assert bool(((db.double() - ref).abs() <= tokens * 2.0 ** -24 * mag + (ref.abs() * 2.0 ** -8 if wt == "bf16" else 0.0)).all())
 
 
-@pytest.mark.parametrize("n,d,c", [
-    # tiles of dW / dX: 64 / 64 (with idle workgroups between the two), K split 64 / 128x64, 64 / 128, 128x64 / 64,
-    # 128x64 / 128x64, 128x64 / 128, 64 / 128 with all of K at once, 128x64 / the same, the smallest, dX split as well (one workspace: apart), dX on the main kernel (apart)
-    (256, 192, 768), (12608, 192, 576), (4064, 2048, 480), (1024, 768, 3072), (2048, 768, 3072), (4064, 2048, 992), (25216, 1536, 384), (3968, 4096, 352), (32, 32, 32),
-    (512, 1024, 4096), (25216, 384, 1536)])
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):
-    """The native backward pass gives what the separate calls give for the same operands, bit for bit."""
+def _check_backward_pass(mx, n, d, c, dtype):
     g = torch.Generator(device="cuda")
     g.manual_seed(n + d + c)
     x, w, dy = (torch.randn(s, generator=g, device="cuda").to(dtype) for s in ((n, d), (c, d), (n, c)))
@@ -426,6 +419,35 @@ def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):
     assert torch.equal(gx, dx)
     if n % 128 == 0 or n < 4096:                        # otherwise the module's dW sums over more rows, in another order
         assert torch.equal(gw, dw.to(dtype))
+
+
+@pytest.mark.parametrize("n,d,c", [
+    # tiles of dW / dX: 64 / 64 (with idle workgroups between the two), K split 64 / 128x64, 64 / 128, 128x64 / 64,
+    # 128x64 / 128x64, 128x64 / 128, 64 / 128 with all of K at once, 128x64 / the same, the smallest, 128x64 / K split 64, dX on the main kernel (apart)
+    (256, 192, 768), (12608, 192, 576), (4064, 2048, 480), (1024, 768, 3072), (2048, 768, 3072), (4064, 2048, 992), (25216, 1536, 384), (3968, 4096, 352), (32, 32, 32),
+    (512, 1024, 4096), (25216, 384, 1536)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_products_of_a_backward_pass_in_one_launch(mx, n, d, c, dtype):
+    """The native backward pass gives what the separate calls give for the same operands, bit for bit."""
+    _check_backward_pass(mx, n, d, c, dtype)
+
+
+def _split_both(mx, n, d, c):
+    """Workspace bytes of dX and dW, each of which splits K."""
+    need = [mx.mx_linear_workspace_bytes(which, n, c, d) for which in (mx.binding.GEMM_BWD_DX, mx.binding.GEMM_BWD_DW)]
+    assert min(need) > 0
+    return need
+
+
+@pytest.mark.parametrize("n,d,c", [
+    (4096, 64, 4096), (4128, 64, 4128), (4096, 96, 5120)])                  # the second: ragged K
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_backward_pass_that_splits_both_products(mx, n, d, c, dtype):
+    """MxLinearStep has one workspace for both, so that they must run one after the other; MxLinear gives each its own."""
+    _split_both(mx, n, d, c)
+    kernel = mx.binding.host().gemm_kernel_name
+    assert kernel(c, d, n, False) == kernel(n, d, c, False) == "64x64"                               # one launch but for the workspace
+    _check_backward_pass(mx, n, d, c, dtype)
 
 
 def _kernels_of(graph):
