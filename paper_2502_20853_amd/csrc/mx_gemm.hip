@@ -1687,19 +1687,33 @@ hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t s
 
 // Two independent products of a backward pass, w and x, in one launch where both run on tile kernels and have a workspace
 // each (or need one at most): alone each fills its last round sparsely, or the chip altogether, and waits for the one
-// before.  Faster at every size measured, though both then have the LDS of the larger shape; quantizer, both products and
-// reduction of MxLinearStep.backward in a replayed graph, apart / together in us: 256 x 192 -> 768 FP32 13.1 / 9.9,
-// 1024 x 768 -> 3072 25.1 / 19.7, 6304 x 768 -> 3072 73.5 / 60.3, 12608 x 192 -> 768 35.9 / 33.8, 25216 x 1536 -> 384 FP32
-// 82.0 / 79.1.  Where the main kernel takes one of them they stay apart: a tile kernel in its place costs what is gained
+// before.  Never slower at 120 pairs timed (32 to 25216 tokens, 128 to 1536 columns, 128 to 4000 outputs, FP32 and bf16: 0.73
+// to 1.00 of the time apart), though both then have the LDS of the larger shape; quantizer, both products and
+// reduction of MxLinearStep.backward in a replayed graph, apart / together in us: 256 x 192 -> 768 FP32 13.0 / 9.9,
+// 1024 x 768 -> 3072 25.5 / 20.4, 6304 x 192 -> 576 24.6 / 20.9, 25216 x 384 -> 384 42.5 / 36.9, 12608 x 192 -> 768
+// 38.8 / 36.4, 25216 x 1536 -> 384 80.7 / 74.7, bf16 3744 x 1504 -> 2208 55.8 / 54.4, 15520 x 1344 -> 672 68.8 / 68.2.
+// Where the main kernel takes one of them they stay apart: a tile kernel in its place costs what is gained
 // (12608 x 768 -> 2304 82 / 90, 6304 x 1024 -> 1024 42 / 37), and two products on the main kernel leave each other
 // nothing (50432 x 2304 x 768 with 768 x 2304 x 50432: 116 apart, 124 together: its units are handed over one by one).
+// (w on 128 x 128 tiles: a large weight and few tokens, which fill the chip by themselves)
+static bool pair_on_tile_kernels(GemmKernel kw, GemmKernel kx)
+{
+    return (kw == GemmKernel::tile64 || kw == GemmKernel::tile128x64) && kx != GemmKernel::pingpong;
+}
+
+bool gemm_pair_fits_one_launch(const GemmParams& w, const GemmParams& x)
+{
+    GemmArgs g;
+    return !w.q_codes && !x.q_codes && pair_on_tile_kernels(make_gemm_args(w, g), make_gemm_args(x, g));
+}
+
 hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail)
 {
     GemmArgs gw, gx;
     const GemmKernel kw = make_gemm_args(w, gw), kx = make_gemm_args(x, gx);
+    // two K splits with one workspace: the partial sums of one must have been added up before the other writes its own
     const bool own_scratch = gw.split_k == 1 || gx.split_k == 1 || w.workspace != x.workspace;
-    // (w on 128 x 128 tiles: a large weight and few tokens, which fill the chip by themselves)
-    if (!own_scratch || kw == GemmKernel::pingpong || kw == GemmKernel::tile128 || kw == GemmKernel::tile128_short || kx == GemmKernel::pingpong || w.q_codes || x.q_codes) {
+    if (!own_scratch || !pair_on_tile_kernels(kw, kx) || w.q_codes || x.q_codes) {
         const hipError_t e = launch_gemm(x, st);
         return e == hipSuccess ? launch_gemm(w, st, tail) : e;
     }

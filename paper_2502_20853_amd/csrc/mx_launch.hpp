@@ -218,5 +218,7 @@ bool linear_fits_one_launch(int64_t m, int64_t n, int64_t k, bool bias_bf16, boo
 hipError_t launch_quantized_linear(const QuantizedLinearParams& p, hipStream_t st);
 // Two independent products, in one launch where that pays; the results of launch_gemm(x) and launch_gemm(w, tail), bit for bit.
 hipError_t launch_gemm_pair(const GemmParams& w, const GemmParams& x, hipStream_t st, const ColumnSumTail* tail = nullptr);
+// Whether it makes one launch of them, given a workspace for each that splits K; otherwise they run x, then w, and may share one.
+bool gemm_pair_fits_one_launch(const GemmParams& w, const GemmParams& x);
 
 }  // namespace mxl

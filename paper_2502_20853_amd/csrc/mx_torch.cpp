@@ -106,9 +106,9 @@ Seed seed_of(int64_t value, const OptTensor& dev)
     return s;
 }
 
-// One product C[m x n] = A . B^T into `out` (row pitch ldc), with a workspace of its own where K is split; `own` keeps it.
+// One product C[m x n] = A . B^T into `out` (row pitch ldc); the workspace of a K split is not set.
 mxl::GemmParams product_params(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
-                               const Tensor& out, int64_t ldc, const float* bias, const char* fn, const Tensor* workspace, Tensor& own)
+                               const Tensor& out, int64_t ldc, const float* bias, const char* fn)
 {
     mxl::GemmParams p{};
     p.a_codes = a; p.a_scales = as; p.b_codes = b; p.b_scales = bs;
@@ -117,25 +117,37 @@ mxl::GemmParams product_params(const uint8_t* a, const uint8_t* as, const uint8_
     p.bias = bias;
     check(mxl::check_gemm(p), fn);
     p.split_k = mxl::gemm_split_k(m, n, k);
-    if (p.split_k > 1) {
-        const int64_t need = (int64_t)p.split_k * m * n * 4;
-        if (workspace && workspace->defined() && (int64_t)workspace->nbytes() >= need) {
-            p.workspace = workspace->data_ptr();
-        } else {
-            own = bytes_like(out, need);                    // returned to the allocator in stream order
-            p.workspace = own.data_ptr();
-        }
-        if ((reinterpret_cast<uintptr_t>(p.workspace) & 255) != 0) throw Status(fn, MX_ERR_ALIGN);
-    }
     return p;
 }
 
+// Workspaces of the K splits of one product or of two that go to launch_gemm_pair: `given` where it is large enough, otherwise
+// pieces of a buffer of the pass's own, returned to the allocator in stream order; `own` keeps it.  Products that run one after
+// the other share a piece, so that a pass holds no more than the larger of the two needs.
+void set_workspaces(mxl::GemmParams* w, mxl::GemmParams* x, const Tensor* given, const Tensor& like, Tensor& own, const char* fn)
+{
+    auto need = [&](mxl::GemmParams* p) -> int64_t {
+        if (p == nullptr || p->split_k <= 1) return 0;
+        const int64_t bytes = round_up((int64_t)p->split_k * p->m * p->n * 4, 256);
+        if (given == nullptr || !given->defined() || (int64_t)given->nbytes() < (int64_t)p->split_k * p->m * p->n * 4) return bytes;
+        p->workspace = given->data_ptr();
+        return 0;
+    };
+    const int64_t nw = need(w), nx = need(x), behind = nw > 0 && nx > 0 && mxl::gemm_pair_fits_one_launch(*w, *x) ? nw : 0;
+    if (nw > 0 || nx > 0) own = bytes_like(like, std::max(nw, behind + nx));
+    if (nw > 0) w->workspace = own.data_ptr<uint8_t>();
+    if (nx > 0) x->workspace = own.data_ptr<uint8_t>() + behind;
+    for (mxl::GemmParams* p : {w, x})
+        if (p != nullptr && p->split_k > 1 && (reinterpret_cast<uintptr_t>(p->workspace) & 255) != 0)
+            throw Status(p == x ? "mx_linear_bwd_dx" : fn, MX_ERR_ALIGN);
+}
+
 void product(const uint8_t* a, const uint8_t* as, const uint8_t* b, const uint8_t* bs, int64_t m, int64_t n, int64_t k,
-             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr,
-             const mxl::ColumnSumTail* tail = nullptr)
+             const Tensor& out, int64_t ldc, const float* bias, hipStream_t st, const char* fn, const Tensor* workspace = nullptr)
 {
     Tensor own;
-    check_hip(mxl::launch_gemm(product_params(a, as, b, bs, m, n, k, out, ldc, bias, fn, workspace, own), st, tail), fn);
+    mxl::GemmParams p = product_params(a, as, b, bs, m, n, k, out, ldc, bias, fn);
+    set_workspaces(&p, nullptr, workspace, out, own, fn);
+    check_hip(mxl::launch_gemm(p, st), fn);
 }
 
 mxl::QuantRowsParams rows_job(const Tensor& src, int64_t rows, int64_t cols, uint8_t* codes, uint8_t* scales, bool floor_mode)
@@ -364,15 +376,16 @@ struct MxLinearFn : torch::autograd::Function<MxLinearFn> {
         }
         const mxl::ColumnSumTail* sums = want_db ? &tail : nullptr;
         mxl::GemmParams px, pw;
-        Tensor own_x, own_w;
+        Tensor own;
         if (want_dx) {
             dx = at::empty(shape, dy.options());
-            px = product_params(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, "mx_linear_bwd_dx", nullptr, own_x);
+            px = product_params(p + o_q, p + o_s, s + o_wtq, s + o_wts, N, D, C, dx, D, nullptr, "mx_linear_bwd_dx");
         }
         if (want_dw) {
             dw = at::empty({C, D}, dy.options().dtype((at::ScalarType)meta[5]));
-            pw = product_params(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, "mx_linear_bwd_dw", nullptr, own_w);
+            pw = product_params(p + o_tq, p + o_ts, s + o_xtq, s + o_xts, C, D, Np, dw, D, nullptr, "mx_linear_bwd_dw");
         }
+        set_workspaces(want_dw ? &pw : nullptr, want_dx ? &px : nullptr, nullptr, dy, own, "mx_linear_bwd_dw");
         if (want_dx && want_dw) {
             check_hip(mxl::launch_gemm_pair(pw, px, st, sums), "mx_linear_bwd_dw");
         } else if (want_dx) {
@@ -475,9 +488,10 @@ void step_backward(const Tensor& dY, int64_t N, int64_t D, int64_t C, uint64_t s
     hipStream_t st = c10::hip::getCurrentHIPStream().stream();
     const mxl::QuantTileParams q = tile_job(dY, N, C, dyb, true, Q5, false, true, Q3, floor_mode, seed_of((int64_t)seed_value, seed_dev));
     launch_tiles(&q, 1, st);
-    Tensor own_x, own_w;
-    const mxl::GemmParams px = product_params(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, "mx_linear_bwd_dx", &workspace, own_x);
-    const mxl::GemmParams pw = product_params(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, "mx_linear_bwd_dw", &workspace, own_w);
+    mxl::GemmParams px = product_params(u8(dyb[0]), u8(dyb[1]), u8(wt[0]), u8(wt[1]), N, D, C, dx, dx.stride(0), nullptr, "mx_linear_bwd_dx");
+    mxl::GemmParams pw = product_params(u8(dyb[2]), u8(dyb[3]), u8(xt[0]), u8(xt[1]), C, D, N, dw, dw.stride(0), nullptr, "mx_linear_bwd_dw");
+    Tensor own;
+    set_workspaces(&pw, &px, &workspace, dY, own, "mx_linear_bwd_dw");
     check_hip(mxl::launch_gemm_pair(pw, px, st), "mx_linear_bwd_dw");
 }
 

@@ -450,6 +450,23 @@ def test_backward_pass_that_splits_both_products(mx, n, d, c, dtype):
     _check_backward_pass(mx, n, d, c, dtype)
 
 
+def test_memory_of_a_backward_pass_that_splits_both_products(mx):
+    """On the main kernel they run one after the other: the pass holds one workspace at a time."""
+    n, d, c = 8192, 768, 8192
+    need = _split_both(mx, n, d, c)
+    assert mx.binding.host().gemm_kernel_name(n, d, c, False) == "main" and min(need) > 40 << 20
+    lin = mx.MxLinear(d, c, bias=False, dtype=torch.bfloat16, seed=1, layer_id=1)
+    x, dy = torch.randn(n, d, device="cuda").bfloat16().requires_grad_(True), torch.randn(n, c, device="cuda").bfloat16()
+    y = lin(x)
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    held = torch.cuda.memory_allocated()
+    torch.autograd.grad(y, (x, lin.weight), dy)
+    torch.cuda.synchronize()
+    results, packed = 2 * (n * d + c * d), 2 * n * c * 17 // 32
+    assert torch.cuda.max_memory_allocated() - held <= results + packed + max(need) + (4 << 20)
+
+
 def _kernels_of(graph):
     """Nodes of a recorded graph, through the HIP library that this process has loaded."""
     import ctypes
