@@ -103,6 +103,8 @@ size_t column_sum_workspace_bytes(int64_t rows, int64_t cols);
 // the column sums' partials itself (column_sum_tail), e.g. in the launch that reduces a K split.
 hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st, const WidenJob* widen = nullptr,
                                       bool finish_col_sums = true);
+// Workgroups (of four waves) that one tensor's launch has (for tests of the rule); src: 0 FP32, 1 bf16, 2 packed codes.
+uint32_t tile_workgroups(int64_t rows, int64_t cols, int src, bool row_sr, bool t_sr);
 ColumnSumTail column_sum_tail(const QuantTileParams& q);
 hipError_t launch_column_sum_finish(const ColumnSumTail& t, hipStream_t st);
 hipError_t launch_dequantize(const uint8_t* codes, const uint8_t* scales, int64_t rows, int64_t cols,

@@ -740,13 +740,15 @@ __device__ __forceinline__ void quantize_tile_body(const TileArgs a, const uint3
 }
 
 // Waves of a launch that share a SIMD, as the registers of its instance allow (the kernels' launch bounds say so too).
-// src: 0 FP32, 1 bf16, 2 packed codes.
+// src: 0 FP32, 1 bf16, 2 packed codes.  Eight-wave workgroups: two on a compute unit (the registers of an instance without
+// stochastic columns would do for three).
 constexpr int tile_waves_per_simd(int src, bool row_sr, bool t_sr, int waves)
 {
     if (waves == 8) return 4;
     if (src == 2) return 8;
-    if (src == 1) return row_sr && t_sr ? 4 : 5;
-    return t_sr && !row_sr ? 4 : 5;
+    if (!t_sr) return src == 1 || row_sr ? 6 : 5;
+    if (src == 1) return row_sr ? 4 : 5;
+    return row_sr ? 5 : 4;
 }
 
 // SRC as above, or 3: FP32 and bf16 jobs in one launch (a bf16 activation and its FP32 master weight).
@@ -1263,17 +1265,31 @@ static uint32_t make_tile_args(const QuantTileParams& p, int waves, int per_simd
     // 12608 x 768 20.8 / 15.6, FP32 dY 9856 x 1152 20.6 / 17.1, bf16 X 18912 x 576 17.5 / 13.3; except where a round is
     // short: bf16 with two stochastic outputs 25216 x 384 15.1 / 15.6 (1.15 rounds) but 18912 x 576 18.6 / 16.4 (1.45),
     // eight waves 9856 x 1152 21.8 / 24.0 (1.37) but 25216 x 512 27.7 / 26.2 (1.55).
+    // Where six waves share a SIMD a round is counted as five: with the sixth, 64 columns for 641 to 768 tiles of 128 take
+    // 11.1-15.1 us against 10.1-10.7 (bf16, both outputs deterministic), and 1296 to 1404 tiles whole 15.5-15.9 against
+    // 14.6-15.4 with a few as halves.  What the sixth changes is the tail of 1409 to 1536 tiles: whole they all run at once, as
+    // halves they do not (1503 tiles: whole 16.1, halves 18.8; FP32 with stochastic rows 28.3 and 31.4).
     const uint32_t wide_per_row = (uint32_t)((p.cols + 127) / 128);
-    const uint32_t macro_rows = 32u * (uint32_t)waves, slots = 256u * 4u * (uint32_t)per_simd / (uint32_t)waves;
+    const uint32_t macro_rows = 32u * (uint32_t)waves, at_once = 256u * 4u * (uint32_t)per_simd / (uint32_t)waves;
+    const uint32_t slots = per_simd == 6 ? at_once / 6u * 5u : at_once;
     const uint32_t n_tiles = (uint32_t)((p.rows + macro_rows - 1) / macro_rows) * wide_per_row;
     const uint32_t fit = slots + (waves == 8 ? slots / 2u : p.bf16 && p.sr_row && p.sr_t ? slots / 4u : 0u);
     uint32_t n_wide = 0;
     if (n_tiles > fit / 2u) {
         const uint32_t rem = n_tiles % slots;
-        n_wide = (rem > 0u && rem <= slots / 4u) ? n_tiles - rem : n_tiles;
+        const bool halves = rem > 0u && rem <= slots / 4u && !(n_tiles <= at_once && n_tiles + rem > at_once);
+        n_wide = halves ? n_tiles - rem : n_tiles;
     }
     a.n_wide = n_wide; a.wide_per_row = wide_per_row;
     return n_wide + 2u * (n_tiles - n_wide);
+}
+
+uint32_t tile_workgroups(int64_t rows, int64_t cols, int src, bool row_sr, bool t_sr)
+{
+    QuantTileParams p{};
+    TileArgs a;
+    p.rows = rows; p.cols = cols; p.bf16 = src == 1; p.sr_row = row_sr; p.sr_t = t_sr;
+    return make_tile_args(p, 4, tile_waves_per_simd(src, row_sr, t_sr, 4), a);
 }
 
 hipError_t launch_quantize_tile_batch(const QuantTileParams* jobs, int count, hipStream_t st, const WidenJob* widen,

@@ -611,6 +611,7 @@ PYBIND11_MODULE(_mx_torch, m)
     m.def("linear", &linear, py::call_guard<py::gil_scoped_release>());
     m.def("linear_fits_one_launch", &mxl::linear_fits_one_launch);           // the rules, for tests
     m.def("gemm_kernel_name", &mxl::gemm_kernel_name);
+    m.def("tile_workgroups", &mxl::tile_workgroups);
     m.def("step_forward", &step_forward, py::call_guard<py::gil_scoped_release>());
     m.def("ramping_step", &ramping_step);
     m.def("step_backward", &step_backward, py::call_guard<py::gil_scoped_release>());

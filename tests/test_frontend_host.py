@@ -178,3 +178,18 @@ def test_kernel_of_the_fused_gelu_stage(mx):
         assert kernel(12608, 1024, k) == kernel(8192, 2048, k) == kernel(25216, 3072, k) == "128x128"
     assert kernel(25216, 3072, 1024) == kernel(25216, 3072, 4096) == "main" and kernel(16640, 1024, 2048) == "128x128"
     assert kernel(1024, 4096, 896) == "64x64"
+
+
+def test_tail_of_a_tile_quantizer_launch(mx):
+    """Tiles of a last round that is at most a quarter full are issued as halves, unless six waves share a SIMD and all tiles run at
+    once as they are."""
+    groups = lambda tiles, src, row_sr, t_sr: mx.binding.host().tile_workgroups(128 * tiles, 128, src, row_sr, t_sr)
+    for src, row_sr, t_sr in ((1, False, False), (1, True, False), (0, True, False), (1, False, True), (0, False, False), (0, True, True)):
+        assert groups(640, src, row_sr, t_sr) == 1280 and groups(641, src, row_sr, t_sr) == 641
+        six = not t_sr and (src == 1 or row_sr)
+        for tiles in (1281, 1408, 1409, 1503, 1536, 1537, 1600):
+            whole = six and 1408 < tiles <= 1536
+            assert groups(tiles, src, row_sr, t_sr) == (tiles if whole else 2 * tiles - 1280), (tiles, src, row_sr, t_sr)
+        assert groups(1601, src, row_sr, t_sr) == 1601 and groups(2600, src, row_sr, t_sr) == 2640
+    assert groups(1024, 2, False, True) == 2048 and groups(1025, 2, False, True) == 1025 and groups(2049, 2, False, True) == 2050
+    assert groups(1025, 1, True, True) == 1026 and groups(1281, 0, False, True) == 1281 and groups(1280, 0, False, True) == 1536

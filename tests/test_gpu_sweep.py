@@ -184,3 +184,12 @@ def test_transposed_at_the_lines_between_tile_widths(mx, orc, dtype, rows):
         kw = dict(round_t=1, tensor_id_t=6, pre_quant=pre, want_row=True, round_row=round_row, tensor_id_row=1, seed=77)
         for g, w, nm in zip(mx.mx_quantize_transposed(src, **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):
             assert_same_bytes(g, w, "%d rows pre %d row %d %s" % (rows, pre, round_row, nm))
+
+
+@pytest.mark.parametrize("rows", [90112, 90240, 98336])
+def test_deterministic_transposed_at_the_lines_between_tile_widths(mx, orc, rows):
+    """192 bf16 columns, both outputs deterministic: 1408, 1410 and 1538 tiles, where the last few are halves, whole, and halves again."""
+    x = mixed_matrix(rows, 192, seed=902, dtype="bf16")
+    kw = dict(round_t=0, tensor_id_t=6, pre_quant=0, want_row=True, round_row=0, tensor_id_row=1, seed=77)
+    for g, w, nm in zip(mx.mx_quantize_transposed(dev(x, "bf16"), **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):
+        assert_same_bytes(g, w, "%d rows %s" % (rows, nm))
