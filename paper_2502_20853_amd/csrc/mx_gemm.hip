@@ -173,6 +173,15 @@ struct TileShape {
 
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
+// Lanes of a wave hand values to each other through its LDS strip: what is written before this call is seen by every lane's
+// reads after it, and what is read before it was not yet overwritten.  It takes no instruction, because the LDS executes a
+// wave's instructions in order; it keeps the compiler from moving the accesses past each other.
+__device__ __forceinline__ void strip_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The output stage of a wave whose TI x TJ tiles of 32 x 32 lie wholly inside the matrix, with rows that can be stored 16
 // bytes at a time: no bounds tests, a store's address is a uniform pointer plus one lane offset, and the strip's
 // accesses need no waits (the LDS executes a wave's instructions in order), so 32 rows are converted and written to the
@@ -216,8 +225,10 @@ __device__ __forceinline__ void tile_epilogue_interior(const GemmArgs& g, lds_u8
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
         v4i v[STORES];
+        strip_order();
 #pragma unroll
         for (int it = 0; it < STORES; ++it) v[it] = *reinterpret_cast<const lds_v4i*>(rd + it * RPI * PITCH);
+        strip_order();
         if (i + 1 < TI) write_rows(i + 1);
 #pragma unroll
         for (int it = 0; it < STORES; ++it) store16<STREAM>(tile + (size_t)(i * 32 + it * RPI) * ldc * ES + voff, v[it]);
@@ -783,6 +794,9 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 // per-store address arithmetic (a store's address is a uniform tile pointer plus one per-lane
 // offset that is computed once), and no waits between the LDS writes and reads of a chunk (the LDS
 // executes a wave's instructions in order; the compiler waits where a register needs its data).
+// The compiler keeps the strip's accesses in program order because writes and reads go through
+// pointers into the same array whose lane offsets it cannot tell apart; strip_order() between them
+// says so, and costs this kernel 1 % at long K (50432 x 768 x 3072 72.6 us, 73.2 with it).
 // BIAS: add the 128 FP32 bias values at LDS address `bias` (column nbase first).
 template <bool STREAM, bool BIAS>
 __device__ __forceinline__ void gemm_epilogue_interior(const GemmArgs& g, lds_u8* ep, v16f (&acc)[2][4],
