@@ -94,6 +94,24 @@ def traffic(fetch_csv, write_csv):
     return per, cal_f, cal_w, ff, wf
 
 
+def tile_launches():
+    """Fused quantizer launches of a step by kind and number of workgroups (of four waves), as the library plans them:
+    {(kind, workgroups): (rows, columns, elements of the weight in the same launch)}."""
+    from . import binding
+    groups = binding.host().tile_workgroups
+    layers = [(n, k) for name, _, n, k in VIT_B_PRODUCTS if name.endswith("fwd")]
+    rows = VIT_B_PRODUCTS[0][1]
+    known = {}
+    for c, d in layers:
+        known["dy_type", groups(rows, c, 1, True, True)] = (rows, c, 0)
+        known["x_type", groups(rows, d, 1, False, True) + groups(c, d, 1, False, True)] = (rows, d, c * d)
+    return known
+
+
+def _kind(dispatch):
+    return "dy_type" if "<1, true, true" in dispatch["name"] else "x_type"
+
+
 def write_step_kernels(out_dir):
     trace = _find(os.path.join(out_dir, "trace"), "kernel_trace.csv")
     fetch = _find(os.path.join(out_dir, "fetch"), "counter_collection.csv")
@@ -116,22 +134,15 @@ def write_step_kernels(out_dir):
               open(os.path.join(PROFILES, "gemm_kernel_only.json"), "w"), indent=1)
     # fused quantizer launches: counter traffic against the algorithmic bytes (bf16 source read once; codes
     # 0.5 B and scale 1/32 B per element, in both layouts)
-    known = {1340: ("dY-type 50432x768", 50432 * 768), 3546: ("dY-type 50432x2304", 50432 * 2304),
-             4848: ("dY-type 50432x3072", 50432 * 3072), 1376: ("X-type 50432x768 + weight", 50432 * 768 + 768 * 768),
-             4992: ("X-type 50432x3072 + weight", 50432 * 3072 + 768 * 3072),
-             1448: ("X-type 50432x768 + weight 2304x768", 50432 * 768 + 2304 * 768),
-             1484: ("X-type 50432x768 + weight 3072x768", 50432 * 768 + 3072 * 768),
-             # the same with a last round in whole tiles
-             1182: ("dY-type 50432x768", 50432 * 768), 1218: ("X-type 50432x768 + weight", 50432 * 768 + 768 * 768),
-             1290: ("X-type 50432x768 + weight 2304x768", 50432 * 768 + 2304 * 768),
-             1326: ("X-type 50432x768 + weight 3072x768", 50432 * 768 + 3072 * 768),
-             4872: ("X-type 50432x3072 + weight", 50432 * 3072 + 768 * 3072)}
+    known = tile_launches()
     qrows = collections.OrderedDict()
     fd, wd = _dispatches(fetch), _dispatches(write)
     for ef, ew in zip(fd, wd):
-        if "quantize_tile_kernel" not in ef["name"] or ef["grid"] // 512 not in known or ef["grid"] != ew["grid"]:
+        if "quantize_tile_kernel" not in ef["name"] or (_kind(ef), ef["grid"] // 256) not in known or ef["grid"] != ew["grid"]:
             continue
-        label, elements = known[ef["grid"] // 512]
+        rows_, cols, extra = known[_kind(ef), ef["grid"] // 256]
+        label = "%s-type %dx%d" % ("dY" if _kind(ef) == "dy_type" else "X", rows_, cols) + (" + weight %dx%d" % (extra // cols, cols) if extra else "")
+        elements = rows_ * cols + extra
         q = qrows.setdefault(label, [elements, [], []])
         q[1].append(ef["FETCH_SIZE"] * 1024 * ff)
         q[2].append(ew["WRITE_SIZE"] * 1024 * wf)
@@ -254,18 +265,14 @@ def write_valu(out_dir):
     path = _find(os.path.join(out_dir, "valu"), "counter_collection.csv")
     if not path:
         return None
-    # grid in units of 512 lanes: two workgroups of 256 lanes, each a 128 x 128 macro tile (or a half of one in the tail)
-    known = {1340: ("dy_type", 50432, 768, 0), 3546: ("dy_type", 50432, 2304, 0), 4848: ("dy_type", 50432, 3072, 0),
-             1376: ("x_type", 50432, 768, 768 * 768), 4992: ("x_type", 50432, 3072, 768 * 3072),
-             1182: ("dy_type", 50432, 768, 0), 1218: ("x_type", 50432, 768, 768 * 768), 4872: ("x_type", 50432, 3072, 768 * 3072)}
+    known = tile_launches()
     detail, per, lines = collections.OrderedDict(), {}, []
     for e in _dispatches(path):
-        if "quantize_tile_kernel" not in e["name"] or e["grid"] // 512 not in known:
+        kind = _kind(e)
+        if "quantize_tile_kernel" not in e["name"] or (kind, e["grid"] // 256) not in known:
             continue
-        kind, rows_, cols, extra = known[e["grid"] // 512]
-        if ("<1, true, true" in e["name"]) != (kind == "dy_type"):
-            continue
-        key = "%s %dx%d%s" % (kind, rows_, cols, " + weight" if extra else "")
+        rows_, cols, extra = known[kind, e["grid"] // 256]
+        key = "%s %dx%d%s" % (kind, rows_, cols, " + weight %dx%d" % (extra // cols, cols) if extra else "")
         if key in detail:
             continue
         elements = rows_ * cols + extra

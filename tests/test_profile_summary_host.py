@@ -57,9 +57,18 @@ def test_valu_summary_counts_lane_operations(tmp_path, monkeypatch):
     dy = "void (anonymous namespace)::quantize_tile_kernel<1, true, true, false, false>(TileBatch)"
     xt = "void (anonymous namespace)::quantize_tile_kernel<1, false, true, false, false>(TileBatch)"
     _write_counter_csv(str(tmp_path / "out" / "valu" / "bench_counter_collection.csv"),
-                       [q(dy, 4848, 50432 * 3072, 33.0), q(xt, 4992, 50432 * 3072 + 768 * 3072, 32.0)])
+                       [q(dy, 4848, 50432 * 3072, 33.0), q(xt, 4872, 50432 * 3072 + 768 * 3072, 32.0)])
     md = ps.write_valu(str(tmp_path / "out"))
     assert md is not None
     j = json.load(open(tmp_path / "quantizer_valu.json"))
     assert abs(j["valu_lane_ops_per_element"]["dy_type"] - 33.0) < 1e-9
     assert abs(j["valu_lane_ops_per_element"]["x_type"] - 32.0) < 1e-9
+
+
+def test_tile_launches_are_those_of_the_library():
+    """Every fused quantizer launch of a ViT-B block step, told apart by kind and number of workgroups."""
+    known = ps.tile_launches()
+    assert sorted(v for (kind, _), v in known.items() if kind == "dy_type") == [(50432, 768, 0), (50432, 2304, 0), (50432, 3072, 0)]
+    assert sorted(v for (kind, _), v in known.items() if kind == "x_type") == sorted(
+        (50432, d, c * d) for c, d in ((2304, 768), (768, 768), (3072, 768), (768, 3072)))
+    assert known["dy_type", 2364] == (50432, 768, 0) and known["x_type", 2436] == (50432, 768, 768 * 768)
