@@ -136,9 +136,9 @@ __device__ __forceinline__ uint32_t load_scales4(const uint8_t* row, uint32_t of
 //   MFMAs; chunks past the end of K are zero-filled in registers, so K needs no alignment beyond a group.
 //   (No DMA loads: they cannot zero-fill a ragged K tail, and scale rows of K/32 bytes have no alignment.)
 // Shapes (chosen in plan_gemm, which gives the times):
-//   128 x 128, KS 128 (384, one step, for K up to that): 35 KB (52) of LDS, three workgroups per compute unit, so that one stores its tile or waits for
-//     its first loads while the others multiply; at four, the 128 registers allowed spill (25216 x 1536 x 384:
-//     41 us against 27).
+//   128 x 128, KS 128 (384, one step, for K up to that): 35 KB (52) of LDS, three workgroups per compute unit, so that one
+//     stores its tile or waits for its first loads while the others multiply; at four, the 128 registers allowed spill,
+//     which took half as long again.
 //   128 x 64, KS 256: half the tile and twice the K step, for products with fewer tiles, where the latency of a
 //     K step counts (12608 x 192 x 768: 6.3 us against 7.4).
 //   64 x 64, KS 512: for products too small to fill the chip otherwise.  What such a launch costs is the chain
@@ -331,8 +331,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, uint8_t* ep, v1
 //
 // The operation sequence of float gelu_f32(float x) as the fitting script emulates it, four values side by side: the stage
 // is bound by the vector ALUs, two waves share a SIMD, and one dependent chain per value (two of its instructions
-// transcendental) leaves it idle.  25216 x 3072 x 768: 150 us value by value with 30 instructions each and codes packed
-// by shifts, 140 us now (the product alone takes 45).
+// transcendental) leaves it idle.  25216 x 3072 x 768 on the main kernel: 150 us value by value with 30 instructions each
+// and codes packed by shifts, 140 in this form; on 128 x 128 tiles 110 to 125 (the product alone takes 45).
 __device__ __forceinline__ void gelu4_f32(const float (&x)[4], float (&y)[4])
 {
     constexpr float T0 = 0.5709219574928284f;
@@ -1487,8 +1487,7 @@ hipError_t launch_calibration_mfma(const uint8_t* operands, int workgroups, int 
 //   64 x 64 tiles: up to one tile per compute unit (224 x 192 x 768: 4.1 against 6.6 on 128 x 128 and 8.0 on the
 //     main kernel), with a K split up to two per unit (768 x 192 x 12672: 11 against 13 and 18).
 //   128 x 64 tiles: up to three per unit (9856 x 384 x 1536: 9.4 against 11.3 and 12.3).
-//   128 x 128 tiles: what is left, i.e. long m or n at K < 512 or K % 128 != 0 (25216 x 1536 x 384: 27 against 30
-//     on 256 x 128 tiles with DMA loads, the kernel that ran these sizes before); with all of K in one step for 256 < K <=
+//   128 x 128 tiles: what is left, i.e. long m or n at K < 512 or K % 128 != 0; with all of K in one step for 256 < K <=
 //     384 (bf16 25216 x 1536 x 384 22.4 against 24.5, FP32 25216 x 1152 x 384 27.5 against 30.0, 12608 x 1024 x 352 15.7
 //     against 17.1), where steps of 128 wait three times; up to 256 it only takes LDS (12608 x 576 x 192 6.8 against 6.65).
 // K splits (K >= 4096): s partials cost s * m * n * 4 bytes written and read, the K loop is K / s long; the sum is

@@ -101,9 +101,9 @@ __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_e3m0_kernel(RowsAr
     }
 }
 
-// round_D is bound by memory: 50432 x 3072 bf16 in 60 us, 6.5 TB/s, FP32 in 131, 5.4 TB/s.  round_S of bf16 by the random
-// numbers: 80 to 89 us, 4.4 to 4.9 TB/s; of FP32 by memory, 130 us.  At 25216 x 1536 bf16 16 and 23 us (22.8 and 26.7 with
-// codes taken from the grid sums and packed by shifts).
+// round_D is bound by memory: 50432 x 3072 bf16 in 60 us, 6.5 TB/s, FP32 in 132, 5.3 TB/s.  round_S of bf16 by the random
+// numbers: 71 to 75 us, 5.2 to 5.5 TB/s (80 to 89 with all rounds of Philox on the vector units); of FP32 by memory, 133 us.  At
+// 25216 x 1536 bf16 16 to 17 and 22 to 23 us.
 template <typename SrcT, bool SR, bool FLOOR, bool WIDE>
 __global__ __launch_bounds__(ROWS_THREADS) void quantize_rows_kernel(RowsArgs a)
 {
