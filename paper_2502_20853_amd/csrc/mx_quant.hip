@@ -1244,6 +1244,23 @@ static int tile_waves(const QuantTileParams* jobs, int count, bool col_sums)
     return largest >= ((int64_t)(jobs[0].sr_t ? 112 : 36) << 20) ? 8 : 4;
 }
 
+// How many of a launch's last tiles of 128 columns are issued as their halves of 64: twice the workgroups, half the time.  What
+// counts is how evenly the 256 compute units are loaded, also where all tiles run at once: the tiles beyond a multiple of 256
+// as halves, up to 128 of them, take 0.87 to 0.97 of the time that they take whole (384 and 768 columns, 264 to 3096 tiles, every
+// kind of source and rounding; FP32 with nothing stochastic, which memory bounds, up to 64 only: beyond, 0.95 to 1.07), and up to
+// 128 tiles altogether 0.73 to 0.97.  In us, whole / halves / all tiles as halves: bf16 X 282 tiles of 768 columns 9.1 / 7.8 / 8.8,
+// 522 12.2 / 10.7 / 12.3, 1068 18.4 / 17.0, 1584 23.5 / 22.0; FP32 X 522 15.1 / 13.7 / 17.2; packed codes 1122 12.7 / 12.0.  With more
+// of them it depends on what a round of `slots` tiles that run at once leaves: up to a quarter of a round as halves is even or
+// better (FP32 gradient 1470 tiles 33.0 / 31.4; bf16 X 2700 tiles 33.3 / 32.2), except where six waves share a SIMD and all tiles run
+// at once whole and not as halves (1409 to 1536 tiles; 1503 of bf16 with both outputs deterministic 16.1 / 18.8).
+static uint32_t tile_tail(uint32_t n_tiles, uint32_t slots, uint32_t at_once, bool plain_f32)
+{
+    const uint32_t over = n_tiles % 256u, rem = n_tiles % slots;
+    if (over <= (plain_f32 && n_tiles > 256u ? 64u : 128u)) return over;
+    if (rem > slots / 4u || (n_tiles <= at_once && n_tiles + rem > at_once)) return 0u;
+    return rem;
+}
+
 // Fills the kernel arguments of one tensor; returns its number of workgroups.
 static uint32_t make_tile_args(const QuantTileParams& p, int waves, int per_simd, TileArgs& a)
 {
@@ -1257,29 +1274,11 @@ static uint32_t make_tile_args(const QuantTileParams& p, int waves, int per_simd
     a.seed_dev = reinterpret_cast<const uint32_t*>(p.seed_dev);
     a.col_sum_partials = p.col_sums ? p.col_sum_workspace : nullptr;
     a.tensor_id_t = p.tensor_id_t; a.tensor_id_row = p.tensor_id_row; a.index_base = p.index_base;
-    // Macro tile of a workgroup: 128 columns, or 64 as long as all of those run at once (a single tile's latency counts
-    // then).  A launch proceeds in rounds of `slots` equal tiles.  When the last round would be at most a quarter full, its
-    // tiles are issued as their halves: twice the workgroups, half the time, and the round ends earlier (bf16 X 32768 x 768,
-    // 0.2 of a round: as halves 21.0, whole 24.4; 38272 x 768, 0.4 of one: 26.7 and 25.0).  Beyond one round
-    // 128 columns are faster even where they leave slots empty, in us for 64 / 128: FP32 X 9856 x 1536 26.1 / 20.2,
-    // 12608 x 768 20.8 / 15.6, FP32 dY 9856 x 1152 20.6 / 17.1, bf16 X 18912 x 576 17.5 / 13.3; except where a round is
-    // short: bf16 with two stochastic outputs 25216 x 384 15.1 / 15.6 (1.15 rounds) but 18912 x 576 18.6 / 16.4 (1.45),
-    // eight waves 9856 x 1152 21.8 / 24.0 (1.37) but 25216 x 512 27.7 / 26.2 (1.55).
-    // Where six waves share a SIMD a round is counted as five: with the sixth, 64 columns for 641 to 768 tiles of 128 take
-    // 11.1-15.1 us against 10.1-10.7 (bf16, both outputs deterministic), and 1296 to 1404 tiles whole 15.5-15.9 against
-    // 14.6-15.4 with a few as halves.  What the sixth changes is the tail of 1409 to 1536 tiles: whole they all run at once, as
-    // halves they do not (1503 tiles: whole 16.1, halves 18.8; FP32 with stochastic rows 28.3 and 31.4).
     const uint32_t wide_per_row = (uint32_t)((p.cols + 127) / 128);
     const uint32_t macro_rows = 32u * (uint32_t)waves, at_once = 256u * 4u * (uint32_t)per_simd / (uint32_t)waves;
-    const uint32_t slots = per_simd == 6 ? at_once / 6u * 5u : at_once;
+    const uint32_t slots = per_simd == 6 ? at_once / 6u * 5u : at_once;         // a sixth wave gains nothing at the quarter of a round
     const uint32_t n_tiles = (uint32_t)((p.rows + macro_rows - 1) / macro_rows) * wide_per_row;
-    const uint32_t fit = slots + (waves == 8 ? slots / 2u : p.bf16 && p.sr_row && p.sr_t ? slots / 4u : 0u);
-    uint32_t n_wide = 0;
-    if (n_tiles > fit / 2u) {
-        const uint32_t rem = n_tiles % slots;
-        const bool halves = rem > 0u && rem <= slots / 4u && !(n_tiles <= at_once && n_tiles + rem > at_once);
-        n_wide = halves ? n_tiles - rem : n_tiles;
-    }
+    const uint32_t n_wide = n_tiles - tile_tail(n_tiles, slots, at_once, !p.bf16 && !p.row_codes_in && !p.sr_t && !p.sr_row);
     a.n_wide = n_wide; a.wide_per_row = wide_per_row;
     return n_wide + 2u * (n_tiles - n_wide);
 }

@@ -181,15 +181,20 @@ def test_kernel_of_the_fused_gelu_stage(mx):
 
 
 def test_tail_of_a_tile_quantizer_launch(mx):
-    """Tiles of a last round that is at most a quarter full are issued as halves, unless six waves share a SIMD and all tiles run at
-    once as they are."""
+    """The tiles beyond a multiple of 256 (one per compute unit) are issued as halves where they are up to 128, or 64 of FP32 with
+    nothing stochastic; with more of them up to a quarter of a round, unless six waves share a SIMD and all run at once as they are."""
     groups = lambda tiles, src, row_sr, t_sr: mx.binding.host().tile_workgroups(128 * tiles, 128, src, row_sr, t_sr)
     for src, row_sr, t_sr in ((1, False, False), (1, True, False), (0, True, False), (1, False, True), (0, False, False), (0, True, True)):
-        assert groups(640, src, row_sr, t_sr) == 1280 and groups(641, src, row_sr, t_sr) == 641
+        tail = lambda tiles: groups(tiles, src, row_sr, t_sr) - tiles
+        few = 64 if (src, row_sr, t_sr) == (0, False, False) else 128
+        assert tail(1) == 1 and tail(128) == 128 and tail(256) == 0 and tail(257) == 1 and tail(512 + few) == few and tail(512 + few + 1) == 0
+        for base in (768, 1024, 1280, 1536, 2304):
+            assert tail(base) == 0 and tail(base + 1) == 1 and tail(base + few) == few
+        assert tail(768 + few + 1) == 0 and tail(1600) == 64 and tail(2304 + few + 1) == 0
         six = not t_sr and (src == 1 or row_sr)
-        for tiles in (1281, 1408, 1409, 1503, 1536, 1537, 1600):
-            whole = six and 1408 < tiles <= 1536
-            assert groups(tiles, src, row_sr, t_sr) == (tiles if whole else 2 * tiles - 1280), (tiles, src, row_sr, t_sr)
-        assert groups(1601, src, row_sr, t_sr) == 1601 and groups(2600, src, row_sr, t_sr) == 2640
-    assert groups(1024, 2, False, True) == 2048 and groups(1025, 2, False, True) == 1025 and groups(2049, 2, False, True) == 2050
-    assert groups(1025, 1, True, True) == 1026 and groups(1281, 0, False, True) == 1281 and groups(1280, 0, False, True) == 1536
+        assert tail(1280 + few + 1) == (0 if six and few == 128 else few + 1)                     # 1409 to 1536 tiles
+        assert tail(1536 - 1) == (0 if six else 255)
+        assert tail(2560 + 255) == 255 and tail(1792 + 129) == 0
+    assert groups(1024, 2, False, True) == 1024 and groups(1025, 2, False, True) == 1026 and groups(2048 + 200, 2, False, True) == 2448
+    assert groups(1280, 1, True, True) == 1280 and groups(1024 + 200, 1, True, True) == 1424 and groups(1280 + 200, 1, True, True) == 1480
+    assert groups(200, 2, False, True) == groups(200, 1, True, True) == 400 and groups(513, 0, False, True) == 514

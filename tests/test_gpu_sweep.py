@@ -177,7 +177,7 @@ def test_block_numbers_across_a_counter_word(mx, orc, dtype, before):
 @pytest.mark.parametrize("rows", [40960, 40992, 82112, 102432])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_transposed_at_the_lines_between_tile_widths(mx, orc, dtype, rows):
-    """192 columns: 64-column tiles in one round, just beyond one, a last round that is a little and more than a quarter full."""
+    """192 columns: 640, 642, 1284 and 1602 tiles of 128 columns, the last 128, 0, 4 and 66 as halves."""
     x = mixed_matrix(rows, 192, seed=901, dtype=dtype)
     src = dev(x, dtype)
     for pre, round_row in ((1, 0), (0, 1)):
@@ -186,9 +186,9 @@ def test_transposed_at_the_lines_between_tile_widths(mx, orc, dtype, rows):
             assert_same_bytes(g, w, "%d rows pre %d row %d %s" % (rows, pre, round_row, nm))
 
 
-@pytest.mark.parametrize("rows", [90112, 90240, 98336])
+@pytest.mark.parametrize("rows", [57472, 90112, 90240, 98336])
 def test_deterministic_transposed_at_the_lines_between_tile_widths(mx, orc, rows):
-    """192 bf16 columns, both outputs deterministic: 1408, 1410 and 1538 tiles, where the last few are halves, whole, and halves again."""
+    """192 bf16 columns, both outputs deterministic: 898, 1408, 1410 and 1538 tiles; the last 0, 128, 0 and 2 are issued as halves."""
     x = mixed_matrix(rows, 192, seed=902, dtype="bf16")
     kw = dict(round_t=0, tensor_id_t=6, pre_quant=0, want_row=True, round_row=0, tensor_id_row=1, seed=77)
     for g, w, nm in zip(mx.mx_quantize_transposed(dev(x, "bf16"), **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):

@@ -71,4 +71,4 @@ def test_tile_launches_are_those_of_the_library():
     assert sorted(v for (kind, _), v in known.items() if kind == "dy_type") == [(50432, 768, 0), (50432, 2304, 0), (50432, 3072, 0)]
     assert sorted(v for (kind, _), v in known.items() if kind == "x_type") == sorted(
         (50432, d, c * d) for c, d in ((2304, 768), (768, 768), (3072, 768), (768, 3072)))
-    assert known["dy_type", 2364] == (50432, 768, 0) and known["x_type", 2436] == (50432, 768, 768 * 768)
+    assert known["dy_type", 2424] == (50432, 768, 0) and known["x_type", 2496] == (50432, 768, 768 * 768)
