@@ -87,8 +87,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// 16-byte store.  A final output is written with the nontemporal hint: it is not read again
-// here, and without the hint an output larger than the last-level cache slows the whole kernel
+// 16-byte store.  A final output is written with the nontemporal hint (by the tile kernels where stream_output says so): it
+// is not read again here, and without the hint an output larger than the last-level cache slows the whole kernel
 // down while it drains (split-K partials keep the default policy, the reduction reads them).
 template <bool STREAM>
 __device__ __forceinline__ void store16(void* dst, v4i v)
@@ -472,6 +472,20 @@ __device__ __forceinline__ void tile_multiply(const uint8_t* st, uint32_t left, 
     });
 }
 
+// Whether the tile kernels store the output with the nontemporal hint: a final one (see store16) whose rows are whole sectors of
+// 64 bytes.  In other rows a wave's piece of a row begins and ends inside a sector that the next tile completes; with the hint
+// both parts go to memory by themselves, and more so the closer the stores follow each other.  Hint / no hint, in us:
+// 25216 x 2808 x 96 bf16 69.8 / 29.6, 12608 x 1000 x 192 bf16 13.9 / 12.6, 36486 x 3180 x 320 FP32 169 / 112, 42568 x 684 x 384
+// FP32 47.7 / 28.9.  Outputs of less than 24 MB, which the L2 caches hold either way, are even (4965 x 472 x 672 FP32 8.9 / 9.2, 5181
+// x 1296 x 352 bf16 9.1 / 9.7), and whole sectors lose without the hint beyond the last-level cache (FP32, 256 MB: 1.07 to 1.2).
+// (Computed from what the output stage needs anyway: one more kernel argument would be one more load that it waits for.)
+__device__ __forceinline__ bool stream_output(const GemmArgs& g)
+{
+    if (g.split_k != 1) return false;
+    const uint64_t pitch = (uint64_t)g.ldc * (g.c_bf16 ? 2u : 4u);
+    return ((reinterpret_cast<uintptr_t>(g.c) | pitch) & 63u) == 0 || pitch * g.m < (24u << 20);
+}
+
 template <typename S, bool GELUQ>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t block, uint8_t* lds)
 {
@@ -572,13 +586,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const uint32_t bloc
     uint8_t* ep = lds + wave * 32 * S::EP_PITCH;
     if constexpr (GELUQ) {                                         // no K split
         static_assert(32 * TI * (16 * TJ + 16) + 32 * TI * TJ <= 32 * S::EP_PITCH, "strip");
-        tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+        if (stream_output(g)) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+        else          tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
         if (g.q_floor) tile_gelu_quant<true, TI, TJ>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2));
         else           tile_gelu_quant<false, TI, TJ>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2));
         return;
     }
-    if (g.split_k == 1) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
-    else                tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+    if (stream_output(g)) tile_epilogue<TI, TJ, true>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
+    else          tile_epilogue<TI, TJ, false>(g, ep, acc, m0 + wm * (BM / 2), n0 + wn * (BN / 2), zsplit);
 }
 
 using Tile128 = TileShape<128, 128, 128, 3>;

@@ -193,3 +193,30 @@ def test_deterministic_transposed_at_the_lines_between_tile_widths(mx, orc, rows
     kw = dict(round_t=0, tensor_id_t=6, pre_quant=0, want_row=True, round_row=0, tensor_id_row=1, seed=77)
     for g, w, nm in zip(mx.mx_quantize_transposed(dev(x, "bf16"), **kw), orc.quantize_transposed(x, **kw), ("codes_t", "scales_t", "codes_row", "scales_row")):
         assert_same_bytes(g, w, "%d rows %s" % (rows, nm))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m,n,k", [(200, 132, 96), (3100, 2056, 96), (6300, 1064, 160), (6400, 1064, 352), (3200, 2080, 512)])
+def test_products_into_padded_and_shifted_rows(mx, dtype, m, n, k):
+    """Rows of whole 64-byte sectors and others, below and above 24 MB: the values do not depend on where they are stored, and nothing
+    outside of the matrix is written.  The last size also through the fused GELU stage."""
+    (ac, as_), (bc, bs) = random_packed(m, k, 31), random_packed(n, k, 32)
+    bs[:] = 127 - 8
+    a, s, b, t = dev(ac), dev(as_), dev(bc), dev(bs)
+    bias = torch.linspace(-2, 2, n, device="cuda")
+    want = mx.mx_linear_fwd_bias(a, s, b, t, bias, out_dtype=dtype)
+    es = want.element_size()
+    for pad, shift in ((0, 0), (16, 0), (16, 16), (64 - n * es % 64, 0), (64 - n * es % 64, 16), (80, 48)):
+        pitch = n + pad // es
+        flat = torch.full((m * pitch + 64,), 7.0, dtype=dtype, device="cuda")
+        out = flat[shift // es: shift // es + m * pitch].view(m, pitch)[:, :n]
+        rest = torch.ones_like(flat, dtype=torch.bool)
+        rest[shift // es: shift // es + m * pitch].view(m, pitch)[:, :n] = False
+        for fused in (False, True) if k >= 512 and n % 32 == 0 else (False,):
+            out.zero_()
+            if fused:
+                mx.mx_linear_fwd_gelu_quant(a, s, b, t, bias, out=out)
+            else:
+                mx.mx_linear_fwd_bias(a, s, b, t, bias, out=out)
+            assert torch.equal(out, want), (pad, shift, fused)
+            assert bool((flat[rest] == 7.0).all()), (pad, shift, fused)
