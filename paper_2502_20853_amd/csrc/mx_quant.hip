@@ -235,8 +235,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 // ---------------------------------------------------------------------------
 // Transposed / fused quantizer.
 //
-// A workgroup of 4 waves owns a 128 x 128 macro tile of the source (128 x 64 for small tensors and for the tiles of a
-// sparsely filled last round); with column sums, and for large FP32 sources (tile_waves), it has 8 waves and 256 rows.
+// A workgroup of 4 waves owns a 128 x 128 macro tile of the source (128 x 64 for small tensors and for the last tiles of
+// others: tile_tail); with column sums, and for large FP32 sources (tile_waves), it has 8 waves and 256 rows.
 // Wave w owns rows [32w, 32w+32) of it and walks over its 32 x 64 tiles.  The grid is one-dimensional over the macro tiles in row-major order.
 // Inside a tile, lane l holds rows 4*(l/8)+j (j = 0..3) x columns 8*(l%8)+t (t = 0..7):
 //   - each load instruction reads 8 full rows of 64 elements,
@@ -246,12 +246,12 @@ __global__ __launch_bounds__(ROWS_THREADS) void ema_quantize_kernel(RowsArgs a)
 // bytes are collected in LDS and written out at the end in lines of 64 bytes (8 waves: transposed codes 128), 16 bytes per
 // lane.  Several small workgroups on a compute unit are seldom all loading or all storing at once, two large ones often are,
 // and a small tensor's waves spread over more units (4 against 8 waves: 50432 x 768 bf16 activation 37 us / 39, 256 x 192
-// FP32 with its weight 5.7 / 7.0; two waves 39).
+// FP32 with its weight 5.7 / 7.0; two waves 39; the activation takes 31 to 35 today).
 // bf16 sources are bound by the vector ALUs, i.e. by the number of instructions.  In us, a 50432 x 3072 bf16 gradient 138 ->
 // 129 and activation 117 -> 112: the first two Philox rounds on the scalar unit and once for both streams (SrCounter32), the
 // wave's two tiles written out instead of a loop, no cleared destinations for the conversions, one 64-bit address per lane.
-// The loop also held 118 registers, now 93: with one stochastic output five waves share a SIMD instead of four, so that
-// 1280 narrow workgroups run at once (25216 x 384 activation 13.8 -> 12.0; FP32 gradient 17.3 -> 15.2).  A gradient of bf16
+// The loop also held 118 registers, now 93: with one stochastic output five waves share a SIMD instead of four (25216 x 384
+// activation 13.8 -> 12.0, FP32 gradient 17.3 -> 14.5).  A gradient of bf16
 // takes 109 registers for what the streams share; without sharing 95 and 131 us.  FP32 sources are bound by memory
 // (50432 x 3072: 170 us, 4.6 TB/s): fetching a second FP32 tile ahead gains 2 % at four waves a SIMD for an activation, and
 // spills where both outputs are stochastic (210 us).
